@@ -9,6 +9,7 @@
 #include <algorithm>
 
 #include "alias_build.hpp"
+#include "alias_regs.hpp"
 
 namespace lda {
 
@@ -100,6 +101,76 @@ struct BetaSink {
     }
 };
 
+// The same sources and sinks for the builder that keeps a lane's entries in registers.
+struct DenseRegs {
+    const int32_t* __restrict__ row;
+    const int32_t* __restrict__ nk;
+    double beta, betabar;
+    uint4* __restrict__ out;
+    struct Raw { int32_t count, nk; };
+    struct Loaded { int32_t other; };
+    __device__ __forceinline__ Raw load(int32_t k) const { return Raw{row[k], nk[k]}; }
+    __device__ __forceinline__ void load2(Raw&) const {}
+    __device__ __forceinline__ uint64_t q0(const Raw& r) const
+    {
+#pragma clang fp contract(off)
+        return quantise40(((double)r.count + beta) / ((double)r.nk + betabar));
+    }
+    __device__ __forceinline__ Loaded load(int32_t, uint32_t al, const Raw&) const { return Loaded{row[al]}; }
+    __device__ __forceinline__ void store(int32_t k, uint32_t split, uint32_t al, const Raw& r,
+                                          const Loaded& v) const
+    {
+        out[k] = make_uint4(split, al, (uint32_t)r.count, (uint32_t)v.other);
+    }
+};
+
+struct MixRegs {
+    const int32_t* __restrict__ topic;
+    const int32_t* __restrict__ count;
+    const int32_t* __restrict__ nk;
+    double betabar;
+    uint4* __restrict__ out;
+    struct Raw { int32_t topic, count, nk; };
+    struct Loaded { int32_t topic, count; };
+    __device__ __forceinline__ Raw load(int32_t i) const { return Raw{topic[i], count[i], 0}; }
+    __device__ __forceinline__ void load2(Raw& r) const { r.nk = nk[r.topic]; }
+    __device__ __forceinline__ uint64_t q0(const Raw& r) const
+    {
+#pragma clang fp contract(off)
+        return quantise40((double)r.count / ((double)r.nk + betabar));
+    }
+    __device__ __forceinline__ Loaded load(int32_t, uint32_t al, const Raw&) const
+    {
+        return Loaded{topic[al], count[al]};
+    }
+    __device__ __forceinline__ void store(int32_t i, uint32_t split, uint32_t, const Raw& r,
+                                          const Loaded& v) const
+    {
+        out[i] = pack_mix_bin(split, r.topic, v.topic, r.count, v.count);
+    }
+};
+
+struct BetaRegs {
+    const int32_t* __restrict__ nk;
+    double beta, betabar;
+    uint2* __restrict__ out;
+    struct Raw { int32_t nk; };
+    struct Loaded {};
+    __device__ __forceinline__ Raw load(int32_t k) const { return Raw{nk[k]}; }
+    __device__ __forceinline__ void load2(Raw&) const {}
+    __device__ __forceinline__ uint64_t q0(const Raw& r) const
+    {
+#pragma clang fp contract(off)
+        return quantise40(beta / ((double)r.nk + betabar));
+    }
+    __device__ __forceinline__ Loaded load(int32_t, uint32_t, const Raw&) const { return Loaded{}; }
+    __device__ __forceinline__ void store(int32_t k, uint32_t split, uint32_t al, const Raw&,
+                                          const Loaded&) const
+    {
+        out[k] = make_uint2(split, al);
+    }
+};
+
 struct DenseArgs {
     const int32_t* words;  // NULL: word = block index
     int32_t n_words;
@@ -110,33 +181,32 @@ struct DenseArgs {
     uint4* alias;
     uint32_t* cap;   // nullable
     uint4* metaA;    // nullable; word w at [2w]
-    int32_t use_cache;
-    unsigned char* ws;  // GLOBAL: list memory, ws_stride bytes per workgroup
+    uint32_t lds_stride;  // bytes of list memory per wave of a workgroup whose waves build a table each
+    unsigned char* ws;  // big tables: list memory, ws_stride bytes per workgroup
     size_t ws_stride;
 };
 
-template <bool GLOBAL>
-__device__ __forceinline__ void dense_table(const DenseArgs& a, int32_t w, unsigned char* lists)
+__device__ __forceinline__ void dense_done(const DenseArgs& a, int32_t w, uint32_t C)
 {
-    const int32_t K = a.K;
-    const int32_t* row = a.nkw + (size_t)w * (size_t)K;
-    DenseSrc src{row, a.nk, a.beta, a.betabar};
-    DenseSink sink{a.alias + (size_t)w * (size_t)K, row};
-    uint64_t Q0;
-    uint32_t C;
-    build_alias_table<GLOBAL>(K, src, sink, lists, a.use_cache != 0, Q0, C);
-    if (threadIdx.x == 0) {
-        if (a.cap) a.cap[w] = C;
-        if (a.metaA) a.metaA[2 * (size_t)w] = make_uint4((uint32_t)K, C, 0u, 0u);
-    }
+    if (a.cap) a.cap[w] = C;
+    if (a.metaA) a.metaA[2 * (size_t)w] = make_uint4((uint32_t)a.K, C, 0u, 0u);
 }
 
-// one workgroup per word, lists in LDS
-__global__ __launch_bounds__(1024) void alias_dense_lds_kernel(DenseArgs a)
+// Tables in LDS: one workgroup per word, or (ONE) one wave per word.
+template <int E, bool ONE, int MAXB>
+__global__ __launch_bounds__(MAXB) void alias_dense_lds_kernel(DenseArgs a)
 {
     extern __shared__ unsigned char smem_raw[];
-    const int32_t w = a.words ? a.words[blockIdx.x] : (int32_t)blockIdx.x;
-    dense_table<false>(a, w, smem_raw);
+    const int wv = ONE ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+    const int32_t i = ONE ? (int32_t)(blockIdx.x * (blockDim.x >> 6)) + wv : (int32_t)blockIdx.x;
+    if (ONE && i >= a.n_words) return;
+    const int32_t w = a.words ? a.words[i] : i;
+    const int32_t* row = a.nkw + (size_t)w * (size_t)a.K;
+    const DenseRegs io{row, a.nk, a.beta, a.betabar, a.alias + (size_t)w * (size_t)a.K};
+    uint64_t Q0;
+    uint32_t C;
+    build_table_regs<E, ONE>(a.K, io, io, smem_raw + (size_t)wv * a.lds_stride, Q0, C);
+    if ((threadIdx.x & (ONE ? kWave - 1 : 1023)) == 0) dense_done(a, w, C);
 }
 
 // persistent workgroups, lists in a global workspace (K too large for LDS)
@@ -145,7 +215,13 @@ __global__ __launch_bounds__(1024) void alias_dense_big_kernel(DenseArgs a)
     unsigned char* lists = a.ws + (size_t)blockIdx.x * a.ws_stride;
     for (int32_t i = blockIdx.x; i < a.n_words; i += gridDim.x) {
         const int32_t w = a.words ? a.words[i] : i;
-        dense_table<true>(a, w, lists);
+        const int32_t* row = a.nkw + (size_t)w * (size_t)a.K;
+        DenseSrc src{row, a.nk, a.beta, a.betabar};
+        DenseSink sink{a.alias + (size_t)w * (size_t)a.K, row};
+        uint64_t Q0;
+        uint32_t C;
+        build_alias_table<true>(a.K, src, sink, lists, true, Q0, C);
+        if (threadIdx.x == 0) dense_done(a, w, C);
         ListMem<true>::barrier();
     }
 }
@@ -161,35 +237,33 @@ struct MixArgs {
     double betabar;
     uint4* ma;
     uint4* metaA;
-    int32_t use_cache;
+    uint32_t lds_stride;
     unsigned char* ws;
     size_t ws_stride;
     int32_t* next;  // big tables: work counter, zero at launch
 };
 
-template <bool GLOBAL>
-__device__ __forceinline__ void mix_table(const MixArgs& a, int32_t w, unsigned char* lists)
+template <int E, bool ONE, int MAXB>
+__global__ __launch_bounds__(MAXB) void alias_mix_lds_kernel(MixArgs a)
 {
+    extern __shared__ unsigned char smem_raw[];
+    const int wv = ONE ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+    const int32_t i = ONE ? (int32_t)(blockIdx.x * (blockDim.x >> 6)) + wv : (int32_t)blockIdx.x;
+    if (ONE && i >= a.n_words) return;
+    const int32_t w = a.words[i];
     const int32_t n = a.sp_nnz[w];
+    const bool first = (threadIdx.x & (ONE ? kWave - 1 : 1023)) == 0;
     if (n <= 0) {  // a word without tokens is never drawn from
-        if (threadIdx.x == 0) a.metaA[2 * (size_t)w] = make_uint4(0u, 0u, 0u, 0u);
+        if (first) a.metaA[2 * (size_t)w] = make_uint4(0u, 0u, 0u, 0u);
         return;
     }
     const size_t off = a.sp_off[w];
-    SparseSrc src{a.sp_topic + off, a.sp_count + off, a.nk, a.betabar};
-    SparseSink sink{a.ma + off, a.sp_topic + off, a.sp_count + off};
+    const MixRegs io{a.sp_topic + off, a.sp_count + off, a.nk, a.betabar, a.ma + off};
     uint64_t QS;
     uint32_t C;
-    build_alias_table<GLOBAL>(n, src, sink, lists, a.use_cache != 0, QS, C);
-    if (threadIdx.x == 0)
+    build_table_regs<E, ONE>(n, io, io, smem_raw + (size_t)wv * a.lds_stride, QS, C);
+    if (first)
         a.metaA[2 * (size_t)w] = make_uint4((uint32_t)n, C, (uint32_t)QS, (uint32_t)(QS >> 32));
-}
-
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void alias_mix_lds_kernel(MixArgs a)
-{
-    extern __shared__ unsigned char smem_raw[];
-    mix_table<false>(a, a.words[blockIdx.x], smem_raw);
 }
 
 __global__ __launch_bounds__(1024) void alias_mix_big_kernel(MixArgs a)
@@ -200,7 +274,18 @@ __global__ __launch_bounds__(1024) void alias_mix_big_kernel(MixArgs a)
     unsigned char* lists = a.ws + (size_t)blockIdx.x * a.ws_stride;
     int32_t i = blockIdx.x;
     while (i < a.n_words) {
-        mix_table<true>(a, a.words[i], lists);
+        const int32_t w = a.words[i];
+        const int32_t n = a.sp_nnz[w];
+        uint64_t QS = 0;
+        uint32_t C = 0;
+        if (n > 0) {  // (a word without tokens is never drawn from)
+            const size_t off = a.sp_off[w];
+            SparseSrc src{a.sp_topic + off, a.sp_count + off, a.nk, a.betabar};
+            SparseSink sink{a.ma + off, a.sp_topic + off, a.sp_count + off};
+            build_alias_table<true>(n, src, sink, lists, true, QS, C);
+        }
+        if (threadIdx.x == 0)
+            a.metaA[2 * (size_t)w] = make_uint4((uint32_t)n, C, (uint32_t)QS, (uint32_t)(QS >> 32));
         ListMem<true>::barrier();
         if (threadIdx.x == 0) s_next = (int32_t)gridDim.x + atomicAdd(a.next, 1);
         __syncthreads();
@@ -211,19 +296,30 @@ __global__ __launch_bounds__(1024) void alias_mix_big_kernel(MixArgs a)
 
 __global__ void set_i32_kernel(int32_t* p, int32_t v) { *p = v; }
 
-template <bool GLOBAL>
-__global__ __launch_bounds__(1024) void alias_beta_kernel(const int32_t* nk, int32_t K, double beta,
-                                                          double betabar, uint2* out,
-                                                          uint64_t* hdr, int32_t use_cache,
-                                                          unsigned char* ws)
+template <int E, bool ONE, int MAXB>
+__global__ __launch_bounds__(MAXB) void alias_beta_lds_kernel(const int32_t* nk, int32_t K, double beta,
+                                                              double betabar, uint2* out, uint64_t* hdr)
 {
     extern __shared__ unsigned char smem_raw[];
-    unsigned char* lists = GLOBAL ? ws : smem_raw;
+    const BetaRegs io{nk, beta, betabar, out};
+    uint64_t QB;
+    uint32_t C;
+    build_table_regs<E, ONE>(K, io, io, smem_raw, QB, C);
+    if (threadIdx.x == 0) {
+        hdr[0] = QB;
+        hdr[1] = C;
+    }
+}
+
+__global__ __launch_bounds__(1024) void alias_beta_big_kernel(const int32_t* nk, int32_t K, double beta,
+                                                              double betabar, uint2* out,
+                                                              uint64_t* hdr, unsigned char* ws)
+{
     BetaSrc src{nk, beta, betabar};
     BetaSink sink{out};
     uint64_t QB;
     uint32_t C;
-    build_alias_table<GLOBAL>(K, src, sink, lists, use_cache != 0, QB, C);
+    build_alias_table<true>(K, src, sink, ws, true, QB, C);
     if (threadIdx.x == 0) {
         hdr[0] = QB;
         hdr[1] = C;
@@ -305,19 +401,55 @@ int set_lds(lda_ctx* c, Kern kern, size_t lds)
     return LDA_OK;
 }
 
-constexpr size_t kLdsLimit = 160 * 1024 - 1024;  // 160 KiB per workgroup, room for statics
+// How a table of at most n entries (n <= kRegsMaxEntries) is built: E entries per thread; up to
+// 256 entries by one wave, four such tables per workgroup, larger ones by a whole workgroup.
+struct TableShape {
+    int e;        // entries per thread: 1, 4 (one wave); 4, 8, 12 (workgroup)
+    bool one;
+    int threads;  // per workgroup
+};
 
-// LDS bytes and cache flag for a table of n entries
-void lds_plan(size_t n, size_t& bytes, int32_t& use_cache)
+TableShape table_shape(int32_t n)
 {
-    use_cache = alias_list_bytes(n, true) <= kLdsLimit ? 1 : 0;
-    bytes = alias_list_bytes(n, use_cache != 0);
+    if (n <= kWave) return {1, true, 256};
+    if (n <= 4 * kWave) return {4, true, 256};
+    if (n <= 1024) return {4, false, (n + 4 * kWave - 1) / (4 * kWave) * kWave};
+    if (n <= 8192) return {8, false, (n + 8 * kWave - 1) / (8 * kWave) * kWave};
+    return {12, false, 1024};
+}
+
+// calls f(E, ONE, MAXB) with the template arguments of a shape
+template <int V>
+struct IntConst { static constexpr int value = V; };
+template <class F>
+int with_shape(const TableShape& s, F&& f)
+{
+    if (s.one) return s.e == 1 ? f(IntConst<1>{}, IntConst<1>{}, IntConst<256>{}) : f(IntConst<4>{}, IntConst<1>{}, IntConst<256>{});
+    if (s.e == 4) return f(IntConst<4>{}, IntConst<0>{}, IntConst<256>{});
+    if (s.e == 8) return f(IntConst<8>{}, IntConst<0>{}, IntConst<1024>{});
+    return f(IntConst<12>{}, IntConst<0>{}, IntConst<1024>{});
+}
+
+int launch_dense_lds(lda_ctx* c, DenseArgs a)
+{
+    const TableShape s = table_shape(a.K);
+    const int per = s.one ? s.threads / kWave : 1;  // tables per workgroup
+    a.lds_stride = (uint32_t)alias_regs_lds_bytes((size_t)a.K);
+    const size_t lds = (size_t)a.lds_stride * (size_t)per;
+    return with_shape(s, [&](auto e, auto one, auto maxb) -> int {
+        auto kern = alias_dense_lds_kernel<decltype(e)::value, decltype(one)::value != 0, decltype(maxb)::value>;
+        const int rc = set_lds(c, kern, lds);
+        if (rc != LDA_OK) return rc;
+        hipLaunchKernelGGL(kern, dim3((a.n_words + per - 1) / per), dim3(s.threads), lds, c->stream, a);
+        LDA_HIP(c, hipGetLastError());
+        return LDA_OK;
+    });
 }
 
 }  // namespace
 
-int max_lds_table_entries() { return 12 * 1024; }
-int max_alias_topics() { return 12 * 1024; }
+int max_lds_table_entries() { return kRegsMaxEntries; }
+int max_alias_topics() { return kRegsMaxEntries; }
 
 // all-dense mode: every word, lists in LDS
 int launch_alias_build(lda_ctx* c)
@@ -326,20 +458,11 @@ int launch_alias_build(lda_ctx* c)
     if (K > max_lds_table_entries())
         return fail(c, LDA_ERR_UNSUPPORTED, "dense alias build in LDS supports K <= %d",
                     max_lds_table_entries());
-    int nw = (K + kWave - 1) / kWave;
-    if (nw > kMaxWaves) nw = kMaxWaves;
-    size_t lds;
-    int32_t use_cache;
-    lds_plan((size_t)K, lds, use_cache);
-    int rc = set_lds(c, alias_dense_lds_kernel, lds);
-    if (rc != LDA_OK) return rc;
     DenseArgs a{};
     a.words = nullptr; a.n_words = c->V; a.nkw = c->d_nkw; a.nk = c->d_nk; a.K = K;
     a.beta = c->beta; a.betabar = c->betabar; a.alias = c->d_alias; a.cap = c->d_cap;
-    a.metaA = nullptr; a.use_cache = use_cache;
-    hipLaunchKernelGGL(alias_dense_lds_kernel, dim3(c->V), dim3(nw * kWave), lds, c->stream, a);
-    LDA_HIP(c, hipGetLastError());
-    return LDA_OK;
+    a.metaA = nullptr;
+    return launch_dense_lds(c, a);
 }
 
 namespace {
@@ -355,34 +478,25 @@ int launch_alias_mix_class(lda_ctx* c, hipStream_t stream, const int32_t* words,
     a.sp_count = c->d_sp_count; a.sp_nnz = c->d_sp_nnz; a.nk = c->d_nk; a.betabar = c->betabar;
     a.ma = c->d_ma; a.metaA = c->d_metaA;
     if (cap_entries > 0) {
-        size_t lds;
-        lds_plan((size_t)cap_entries, lds, a.use_cache);
-        // Tables of a few thousand entries are few per CU (their lists fill the LDS), so each
-        // gets more waves: the time of one table, not the number in flight, bounds such a class.
-        // (c3: 2.95 -> 2.57 ms for all tables, c4: 10.9 -> 10.1)
-        if (cap_entries >= 2048) {
-            int rc = set_lds(c, alias_mix_lds_kernel<1024>, lds);
+        const TableShape s = table_shape(cap_entries);
+        const int per = s.one ? s.threads / kWave : 1;
+        a.lds_stride = (uint32_t)alias_regs_lds_bytes((size_t)cap_entries);
+        const size_t lds = (size_t)a.lds_stride * (size_t)per;
+        return with_shape(s, [&](auto e, auto one, auto maxb) -> int {
+            auto kern = alias_mix_lds_kernel<decltype(e)::value, decltype(one)::value != 0, decltype(maxb)::value>;
+            const int rc = set_lds(c, kern, lds);
             if (rc != LDA_OK) return rc;
-            int threads = cap_entries / 4;
-            threads = threads < 256 ? 256 : (threads > 1024 ? 1024 : threads / kWave * kWave);
-            hipLaunchKernelGGL(alias_mix_lds_kernel<1024>, dim3(n_words), dim3(threads), lds, stream, a);
-        } else {
-            int rc = set_lds(c, alias_mix_lds_kernel<256>, lds);
-            if (rc != LDA_OK) return rc;
-            // small tables: half a wave's worth of entries per lane-round keeps more tables in
-            // flight (two waves per table up to 1024 entries; c2 0.62 -> 0.51 ms, c4 10.0 -> 9.6)
-            int threads = ((cap_entries + kWave - 1) / kWave) * kWave;
-            threads = std::max(64, std::min(threads, 256) / 2 / kWave * kWave);
-            hipLaunchKernelGGL(alias_mix_lds_kernel<256>, dim3(n_words), dim3(threads), lds, stream, a);
-        }
-    } else {
-        a.use_cache = 1; a.ws = c->d_big_ws; a.ws_stride = c->big_ws_stride;
-        a.next = c->d_flag + 1;
-        hipLaunchKernelGGL(set_i32_kernel, dim3(1), dim3(1), 0, stream, a.next, 0);
-        LDA_HIP(c, hipGetLastError());
-        const int grid = n_words < c->n_big_wg ? n_words : c->n_big_wg;
-        hipLaunchKernelGGL(alias_mix_big_kernel, dim3(grid), dim3(1024), 0, stream, a);
+            hipLaunchKernelGGL(kern, dim3((n_words + per - 1) / per), dim3(s.threads), lds, stream, a);
+            LDA_HIP(c, hipGetLastError());
+            return LDA_OK;
+        });
     }
+    a.ws = c->d_big_ws; a.ws_stride = c->big_ws_stride;
+    a.next = c->d_flag + 1;
+    hipLaunchKernelGGL(set_i32_kernel, dim3(1), dim3(1), 0, stream, a.next, 0);
+    LDA_HIP(c, hipGetLastError());
+    const int grid = n_words < c->n_big_wg ? n_words : c->n_big_wg;
+    hipLaunchKernelGGL(alias_mix_big_kernel, dim3(grid), dim3(1024), 0, stream, a);
     LDA_HIP(c, hipGetLastError());
     return LDA_OK;
 }
@@ -394,18 +508,21 @@ int launch_small_mixture_tables(lda_ctx* c, hipStream_t stream)
     const int lds_max = max_lds_table_entries();
     int rc;
     if (K <= lds_max) {
-        size_t lds;
-        int32_t use_cache;
-        lds_plan((size_t)K, lds, use_cache);
-        rc = set_lds(c, alias_beta_kernel<false>, lds);
+        TableShape sh = table_shape(K);
+        if (sh.one) sh.threads = kWave;
+        const size_t lds = alias_regs_lds_bytes((size_t)K);
+        rc = with_shape(sh, [&](auto e, auto one, auto maxb) -> int {
+            auto kern = alias_beta_lds_kernel<decltype(e)::value, decltype(one)::value != 0, decltype(maxb)::value>;
+            const int r = set_lds(c, kern, lds);
+            if (r != LDA_OK) return r;
+            hipLaunchKernelGGL(kern, dim3(1), dim3(sh.threads), lds, stream, c->d_nk, K, c->beta, c->betabar,
+                               c->d_beta_alias, c->d_beta_hdr);
+            return LDA_OK;
+        });
         if (rc != LDA_OK) return rc;
-        int nw = (K + kWave - 1) / kWave;
-        if (nw > kMaxWaves) nw = kMaxWaves;
-        hipLaunchKernelGGL(alias_beta_kernel<false>, dim3(1), dim3(nw * kWave), lds, stream, c->d_nk,
-                           K, c->beta, c->betabar, c->d_beta_alias, c->d_beta_hdr, use_cache, nullptr);
     } else {  // one workgroup, with a slot of list memory of its own
-        hipLaunchKernelGGL(alias_beta_kernel<true>, dim3(1), dim3(1024), 0, stream, c->d_nk, K,
-                           c->beta, c->betabar, c->d_beta_alias, c->d_beta_hdr, 1,
+        hipLaunchKernelGGL(alias_beta_big_kernel, dim3(1), dim3(1024), 0, stream, c->d_nk, K,
+                           c->beta, c->betabar, c->d_beta_alias, c->d_beta_hdr,
                            c->d_big_ws + c->big_ws_stride * (size_t)c->n_big_wg);
     }
     LDA_HIP(c, hipGetLastError());
@@ -452,17 +569,9 @@ int launch_alias_build_hybrid(lda_ctx* c)
         a.nk = c->d_nk; a.K = K; a.beta = c->beta; a.betabar = c->betabar; a.alias = c->d_alias;
         a.cap = c->d_cap; a.metaA = c->d_metaA;
         if (K <= lds_max) {
-            size_t lds;
-            lds_plan((size_t)K, lds, a.use_cache);
-            rc = set_lds(c, alias_dense_lds_kernel, lds);
-            if (rc == LDA_OK) {
-                int nw = (K + kWave - 1) / kWave;
-                if (nw > kMaxWaves) nw = kMaxWaves;
-                hipLaunchKernelGGL(alias_dense_lds_kernel, dim3(c->n_dense_alias), dim3(nw * kWave),
-                                   lds, c->stream, a);
-            }
+            rc = launch_dense_lds(c, a);
         } else {
-            a.use_cache = 1; a.ws = c->d_big_ws; a.ws_stride = c->big_ws_stride;
+            a.ws = c->d_big_ws; a.ws_stride = c->big_ws_stride;
             const int grid = c->n_dense_alias < c->n_big_wg ? c->n_dense_alias : c->n_big_wg;
             hipLaunchKernelGGL(alias_dense_big_kernel, dim3(grid), dim3(1024), 0, c->stream, a);
             rc = LDA_OK;

@@ -1,0 +1,270 @@
+// Alias-table builder for tables of up to kRegsMaxEntries entries (LightLDA Sec. 4.2, Fig. 2).
+// The table is the one alias_build.hpp defines; this form of its construction keeps a lane's
+// entries in registers from the first read of the counts to the stores, and pairs the two
+// lists by merging them instead of by a search per entry.
+//
+//   1  quantise: q0 of the lane's entries, sum over the workgroup
+//   2  C and pad; number of lights, their deficit and the heavies' excess per wave
+//   3  the two ascending lists with their running sums, in LDS (prefix sums within a wave)
+//   4  merge: light a precedes heavy b exactly when Delta_a < X_b.  A thread takes a run of
+//      consecutive positions of the merged order, finds its start by one bisection along the
+//      diagonal and then advances one list or the other per step.  What an entry needs is the
+//      place of the other list at its turn: b(a) for a light, a(b) for a heavy.
+//   5  output, in entry order: coalesced stores
+//
+// LDS: 12 bytes per entry (8 of running sums, 2 for the heavies' entries, 2 for the result of
+// the merge).
+//
+// What bounds it: instruction issue and LDS round trips, not memory (about 200 vector
+// instructions per 64 entries; at K = 10 000 one workgroup per CU keeps the vector units busy
+// for 54 % of the time).  Against the form that searched the partner of every entry and kept
+// the quantised weights in LDS: 10^5 tables of 1000 bins 2.49 -> 0.63 ms (2 GB written and read:
+// 3.2 TB/s), 30 000 of 333 bins 247 -> 84 us, 141 000 of 10 000 bins 20.0 -> 13.9 ms (2 TB/s).
+// Four waves per table of 1000 bins, not sixteen: eight tables per CU overlap their phases.
+#pragma once
+
+#include "alias_build.hpp"
+
+namespace lda {
+
+constexpr int32_t kRegsMaxEntries = 12 * 1024;  // 1024 threads of 12 entries; 144 KB of lists
+
+__host__ __device__ inline size_t alias_regs_lds_bytes(size_t n)
+{
+    return (sizeof(uint64_t) * (n + 1) + sizeof(uint16_t) * 2 * n + 7) / 8 * 8;
+}
+
+// LDS written by some lanes of a wave is read by others after this
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Sum over the wave of values < 2^51
+__device__ __forceinline__ uint64_t wave_total_u64(uint64_t v)
+{
+    return readlane_u64(wave_inclusive_scan_u64(v), kWave - 1);
+}
+
+// Builds one table of n entries, n <= E * (threads that build it).  ONE: the table is built by
+// one wave (n <= 64 E) and no workgroup barrier is used, so the waves of a workgroup can build
+// tables of their own; otherwise all threads of the workgroup build it.  lists:
+// alias_regs_lds_bytes(n) bytes, 8-byte aligned.  Src: Raw load(k), void load2(Raw&) for what
+// is addressed by the first load, uint64_t q0(Raw).  Sink: Loaded load(k, alias, raw),
+// store(k, split, alias, raw, loaded), once per entry.  Returns the pre-shift sum Q0 and the
+// capacity C.
+// A workgroup that builds another table in the same LDS synchronises first.
+template <int E, bool ONE, class Src, class Sink>
+__device__ __forceinline__ void build_table_regs(int32_t n, const Src& src, const Sink& sink,
+                                                 unsigned char* lists, uint64_t& Q0_out,
+                                                 uint32_t& C_out)
+{
+    // dx[0..A]   : Delta_a (exclusive deficit sums of the lights, dx[A] = total)
+    // dx[n-b]    : X_b     (inclusive excess sums of the heavies), b = 0..B-1, A + B = n
+    uint64_t* const dx = reinterpret_cast<uint64_t*>(lists);
+    uint16_t* const hidx = reinterpret_cast<uint16_t*>(dx + (n + 1));  // entry of heavy b
+    uint16_t* const pq = hidx + n;  // [a]: b(a) of light a; [n-1-b]: a(b) of heavy b
+    __shared__ uint64_t w_a[ONE ? 1 : kMaxWaves], w_b[ONE ? 1 : kMaxWaves], w_q[ONE ? 1 : kMaxWaves];
+    __shared__ uint32_t w_c[ONE ? 1 : kMaxWaves];
+
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wv = ONE ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int nw = ONE ? 1 : (int)(blockDim.x >> 6);
+    const int32_t S = (((n + nw - 1) / nw + kWave - 1) / kWave) * kWave;  // entries per wave
+    const int32_t kb = wv * S;
+    const int32_t ke = (kb + S < n) ? kb + S : n;  // may lie below kb: a wave without entries
+    auto sync = [&]() {
+        if constexpr (ONE) wave_lds_order(); else __syncthreads();
+    };
+
+    // 1: the loads of all entries of a lane are in flight together
+    typename Src::Raw raw[E];
+    uint64_t m[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int32_t k = kb + e * kWave + lane;
+        raw[e] = src.load(k < n ? k : n - 1);
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) src.load2(raw[e]);
+    uint64_t p0 = 0, p1 = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        m[e] = src.q0(raw[e]);
+        if (kb + e * kWave + lane < ke) {
+            p0 += m[e];
+            p1 += m[e] < 1 ? 1 : m[e];
+        }
+    }
+    uint64_t Q0 = wave_total_u64(p0), Q = wave_total_u64(p1);
+    if constexpr (!ONE) {
+        if (lane == 0) { w_a[wv] = Q0; w_q[wv] = Q; }
+        __syncthreads();
+        Q0 = Q = 0;
+        for (int i = 0; i < nw; ++i) { Q0 += w_a[i]; Q += w_q[i]; }
+    }
+    int sh = 0;
+    while ((Q0 >> sh) >= ((uint64_t)n << 31)) ++sh;
+    if (sh > 0) {  // uniform
+        p1 = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            m[e] >>= sh;
+            if (kb + e * kWave + lane < ke) p1 += m[e] < 1 ? 1 : m[e];
+        }
+        Q = wave_total_u64(p1);
+        if constexpr (!ONE) {
+            __syncthreads();
+            if (lane == 0) w_q[wv] = Q;
+            __syncthreads();
+            Q = 0;
+            for (int i = 0; i < nw; ++i) Q += w_q[i];
+        }
+    }
+    // ceil(Q / n) through fp64: Q + n < 2^53, and a quotient below 2^32 that is not a whole
+    // number is at least 1/n > 2^-20 away from the next one, more than its rounding error
+    const uint64_t C = (uint64_t)((double)(Q + (uint64_t)n - 1) / (double)n);
+    const uint64_t pad = (uint64_t)n * C - Q;
+
+    // 2: masses and per-wave totals
+    uint32_t lc = 0;
+    uint64_t df = 0, ex = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int32_t k = kb + e * kWave + lane;
+        if (m[e] < 1) m[e] = 1;
+        if ((uint64_t)k < pad) m[e] += 1;
+        const bool valid = k < ke;
+        const bool light = valid && m[e] < C;
+        lc += (uint32_t)__popcll(__ballot(light));
+        if (light) df += C - m[e];
+        else if (valid) ex += m[e] - C;
+    }
+    df = wave_total_u64(df);
+    ex = wave_total_u64(ex);
+    uint32_t a_run = 0, A = lc;
+    uint64_t d_run = 0, x_run = 0, d_tot = df;
+    if constexpr (!ONE) {
+        __syncthreads();  // w_a of step 1 is no longer read
+        if (lane == 0) { w_a[wv] = df; w_b[wv] = ex; w_c[wv] = lc; }
+        __syncthreads();
+        A = 0;
+        d_tot = 0;
+        for (int i = 0; i < nw; ++i) {
+            if (i < wv) { a_run += w_c[i]; d_run += w_a[i]; x_run += w_b[i]; }
+            A += w_c[i];
+            d_tot += w_a[i];
+        }
+    }
+    if (lane == 0 && wv == 0) dx[A] = d_tot;
+    const uint32_t a_wave = a_run;
+
+    // 3: the lists
+    uint32_t b_run = (uint32_t)(kb < n ? kb : n) - a_run;
+    const uint32_t b_wave = b_run;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int32_t k0 = kb + e * kWave;
+        if (k0 < ke) {  // uniform over the wave
+            const bool valid = k0 + lane < ke;
+            const bool light = valid && m[e] < C;
+            const bool heavy = valid && !light;
+            const uint64_t lmask = __ballot(light), hmask = __ballot(heavy);
+            const uint32_t la = rank_below(lmask);
+            if (lmask != 0) {
+                const uint64_t dinc = wave_inclusive_scan_u64(light ? C - m[e] : 0ull);
+                if (light) dx[a_run + la] = d_run + dinc - (C - m[e]);
+                d_run += readlane_u64(dinc, kWave - 1);
+            }
+            if (hmask != 0) {
+                const uint64_t xinc = wave_inclusive_scan_u64(heavy ? m[e] - C : 0ull);
+                if (heavy) {
+                    const uint32_t b = b_run + ((uint32_t)lane - la);
+                    dx[n - b] = x_run + xinc;
+                    hidx[b] = (uint16_t)(k0 + lane);
+                }
+                x_run += readlane_u64(xinc, kWave - 1);
+            }
+            a_run += (uint32_t)__popcll(lmask);
+            b_run += (uint32_t)__popcll(hmask);
+        }
+    }
+    sync();
+
+    // 4: merge.  An odd number of positions per thread spreads the threads' reads over the LDS
+    // banks.  The ends need no test: dx[A] is the total of both lists, so past the lights no
+    // heavy is preceded by "light A", and "heavy B" (also dx[n-B] = dx[A]) precedes no light.
+    {
+        const int32_t T = ONE ? kWave : (int32_t)blockDim.x;
+        const int32_t t = ONE ? lane : (int32_t)threadIdx.x;
+        const int32_t B = n - (int32_t)A;
+        const int32_t Em = ((n + T - 1) / T) | 1;
+        const int32_t q0 = t * Em;
+        const int32_t q1 = q0 + Em < n ? q0 + Em : n;
+        if (q0 < n) {
+            int32_t lo = q0 > B ? q0 - B : 0, hi = q0 < (int32_t)A ? q0 : (int32_t)A;
+            while (lo < hi) {
+                const int32_t mid = (lo + hi) >> 1;
+                if (dx[mid] < dx[n - (q0 - 1 - mid)]) lo = mid + 1; else hi = mid;
+            }
+            int32_t a = lo, b = q0 - lo;
+            uint64_t da = dx[a], xb = dx[n - b];
+            for (int32_t q = q0; q < q1; ++q) {
+                const bool lt = da < xb;
+                pq[lt ? a : n - 1 - b] = (uint16_t)(lt ? b : a);
+                a += lt ? 1 : 0;
+                b += lt ? 0 : 1;
+                const uint64_t v = dx[lt ? a : n - b];
+                da = lt ? v : da;
+                xb = lt ? xb : v;
+            }
+        }
+    }
+    sync();
+
+    // 5: output
+    uint32_t split[E], al[E];
+    a_run = a_wave;
+    b_run = b_wave;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        split[e] = al[e] = 0;
+        const int32_t k0 = kb + e * kWave;
+        if (k0 < ke) {
+            const int32_t k = k0 + lane;
+            const bool valid = k < ke;
+            const bool light = valid && m[e] < C;
+            const uint64_t lmask = __ballot(light);
+            const uint32_t la = rank_below(lmask);
+            if (light) {
+                split[e] = (uint32_t)m[e];
+                al[e] = hidx[pq[a_run + la]];
+            } else if (valid) {
+                const uint32_t b = b_run + ((uint32_t)lane - la);
+                const uint64_t sp = C + dx[n - b] - dx[pq[n - 1 - b]];
+                split[e] = (uint32_t)sp;
+                al[e] = sp < C ? hidx[b + 1] : (uint32_t)k;
+            }
+            const uint32_t nl = (uint32_t)__popcll(lmask);
+            a_run += nl;
+            b_run += (uint32_t)((ke - k0 < kWave) ? ke - k0 : kWave) - nl;
+        }
+    }
+    typename Sink::Loaded got[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int32_t k = kb + e * kWave + lane;
+        if (k < ke) got[e] = sink.load(k, al[e], raw[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int32_t k = kb + e * kWave + lane;
+        if (k < ke) sink.store(k, split[e], al[e], raw[e], got[e]);
+    }
+    Q0_out = Q0;
+    C_out = (uint32_t)C;
+}
+
+}  // namespace lda
