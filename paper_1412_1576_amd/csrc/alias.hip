@@ -4,12 +4,13 @@
 // Mixture form (the paper's sparsified table): per word a table over its non-zero
 // topics only, weights n_kw/(n_k + betabar), plus one table shared by all words over
 // beta/(n_k + betabar); the sweep picks the term by the two integer masses QS_w and QB.
-// Every table is built by one workgroup with the generic builder of alias_build.hpp;
-// tables too large for LDS use a global workspace.
+// Tables whose lists fit LDS are built by a wave or a workgroup each (alias_regs.hpp), larger
+// ones by many workgroups each (alias_split.hpp).
 #include <algorithm>
 
 #include "alias_build.hpp"
 #include "alias_regs.hpp"
+#include "alias_split.hpp"
 
 namespace lda {
 
@@ -20,89 +21,9 @@ __device__ __forceinline__ uint64_t quantise40(double a)
     return (uint64_t)floor(a * 1099511627776.0);
 }
 
-// dense form: entry k is topic k
-struct DenseSrc {
-    const int32_t* __restrict__ row;
-    const int32_t* __restrict__ nk;
-    double beta, betabar;
-    __device__ __forceinline__ uint64_t q0(int32_t k) const
-    {
-#pragma clang fp contract(off)
-        return quantise40(((double)row[k] + beta) / ((double)nk[k] + betabar));
-    }
-};
-
-// A dense bin also carries the word-topic counts of its two outcomes, so the sweep's
-// accept test needs no second gather.
-struct DenseSink {
-    uint4* __restrict__ out;
-    const int32_t* __restrict__ row;
-    struct Loaded { int32_t own, other; };
-    __device__ __forceinline__ Loaded load(int32_t k, uint32_t al) const
-    {
-        return Loaded{row[k], row[al]};
-    }
-    __device__ __forceinline__ void store(int32_t k, uint32_t split, uint32_t al,
-                                          const Loaded& v) const
-    {
-        out[k] = make_uint4(split, al, (uint32_t)v.own, (uint32_t)v.other);
-    }
-};
-
-// sparse term of the mixture: entry i is the word's i-th non-zero topic (ascending)
-struct SparseSrc {
-    const int32_t* __restrict__ topic;
-    const int32_t* __restrict__ count;
-    const int32_t* __restrict__ nk;
-    double betabar;
-    __device__ __forceinline__ uint64_t q0(int32_t i) const
-    {
-#pragma clang fp contract(off)
-        return quantise40((double)count[i] / ((double)nk[topic[i]] + betabar));
-    }
-};
-
-// mixture bin: (split, own topic, alias topic, n_kw[own]) and (n_kw[alias], -, -, -)
-struct SparseSink {
-    uint4* __restrict__ out;
-    const int32_t* __restrict__ topic;
-    const int32_t* __restrict__ count;
-    struct Loaded { int32_t t_own, t_other, n_own, n_other; };
-    __device__ __forceinline__ Loaded load(int32_t i, uint32_t al) const
-    {
-        return Loaded{topic[i], topic[al], count[i], count[al]};
-    }
-    __device__ __forceinline__ void store(int32_t i, uint32_t split, uint32_t,
-                                          const Loaded& v) const
-    {
-        out[i] = pack_mix_bin(split, v.t_own, v.t_other, v.n_own, v.n_other);
-    }
-};
-
-// shared beta term of the mixture: entry k is topic k
-struct BetaSrc {
-    const int32_t* __restrict__ nk;
-    double beta, betabar;
-    __device__ __forceinline__ uint64_t q0(int32_t k) const
-    {
-#pragma clang fp contract(off)
-        return quantise40(beta / ((double)nk[k] + betabar));
-    }
-};
-
-struct BetaSink {
-    uint2* __restrict__ out;
-    struct Loaded {};
-    __device__ __forceinline__ Loaded load(int32_t, uint32_t) const { return Loaded{}; }
-    __device__ __forceinline__ void store(int32_t k, uint32_t split, uint32_t al,
-                                          const Loaded&) const
-    {
-        out[k] = make_uint2(split, al);
-    }
-};
-
-// The same sources and sinks for the builder that keeps a lane's entries in registers.
-struct DenseRegs {
+// dense form: entry k is topic k.  A bin also carries the word-topic counts of its two outcomes,
+// so the sweep's accept test needs no second gather.
+struct DenseIo {
     const int32_t* __restrict__ row;
     const int32_t* __restrict__ nk;
     double beta, betabar;
@@ -124,7 +45,9 @@ struct DenseRegs {
     }
 };
 
-struct MixRegs {
+// sparse term of the mixture: entry i is the word's i-th non-zero topic (ascending); its bin
+// carries the topics and counts of both outcomes
+struct MixIo {
     const int32_t* __restrict__ topic;
     const int32_t* __restrict__ count;
     const int32_t* __restrict__ nk;
@@ -150,7 +73,8 @@ struct MixRegs {
     }
 };
 
-struct BetaRegs {
+// shared beta term of the mixture: entry k is topic k
+struct BetaIo {
     const int32_t* __restrict__ nk;
     double beta, betabar;
     uint2* __restrict__ out;
@@ -182,8 +106,6 @@ struct DenseArgs {
     uint32_t* cap;   // nullable
     uint4* metaA;    // nullable; word w at [2w]
     uint32_t lds_stride;  // bytes of list memory per wave of a workgroup whose waves build a table each
-    unsigned char* ws;  // big tables: list memory, ws_stride bytes per workgroup
-    size_t ws_stride;
 };
 
 __device__ __forceinline__ void dense_done(const DenseArgs& a, int32_t w, uint32_t C)
@@ -202,29 +124,25 @@ __global__ __launch_bounds__(MAXB) void alias_dense_lds_kernel(DenseArgs a)
     if (ONE && i >= a.n_words) return;
     const int32_t w = a.words ? a.words[i] : i;
     const int32_t* row = a.nkw + (size_t)w * (size_t)a.K;
-    const DenseRegs io{row, a.nk, a.beta, a.betabar, a.alias + (size_t)w * (size_t)a.K};
+    const DenseIo io{row, a.nk, a.beta, a.betabar, a.alias + (size_t)w * (size_t)a.K};
     uint64_t Q0;
     uint32_t C;
     build_table_regs<E, ONE>(a.K, io, io, smem_raw + (size_t)wv * a.lds_stride, Q0, C);
     if ((threadIdx.x & (ONE ? kWave - 1 : 1023)) == 0) dense_done(a, w, C);
 }
 
-// persistent workgroups, lists in a global workspace (K too large for LDS)
-__global__ __launch_bounds__(1024) void alias_dense_big_kernel(DenseArgs a)
-{
-    unsigned char* lists = a.ws + (size_t)blockIdx.x * a.ws_stride;
-    for (int32_t i = blockIdx.x; i < a.n_words; i += gridDim.x) {
-        const int32_t w = a.words ? a.words[i] : i;
-        const int32_t* row = a.nkw + (size_t)w * (size_t)a.K;
-        DenseSrc src{row, a.nk, a.beta, a.betabar};
-        DenseSink sink{a.alias + (size_t)w * (size_t)a.K, row};
-        uint64_t Q0;
-        uint32_t C;
-        build_alias_table<true>(a.K, src, sink, lists, true, Q0, C);
-        if (threadIdx.x == 0) dense_done(a, w, C);
-        ListMem<true>::barrier();
+// the same tables for the builder of alias_split.hpp
+struct DenseTables {
+    DenseArgs a;
+    __device__ __forceinline__ int32_t word(int32_t i) const { return a.words ? a.words[i] : i; }
+    __device__ __forceinline__ int32_t entries(int32_t) const { return a.K; }
+    __device__ __forceinline__ DenseIo io(int32_t i) const
+    {
+        const size_t wk = (size_t)word(i) * (size_t)a.K;
+        return DenseIo{a.nkw + wk, a.nk, a.beta, a.betabar, a.alias + wk};
     }
-}
+    __device__ __forceinline__ void done(int32_t i, int32_t, uint64_t, uint32_t C) const { dense_done(a, word(i), C); }
+};
 
 struct MixArgs {
     const int32_t* words;
@@ -238,9 +156,6 @@ struct MixArgs {
     uint4* ma;
     uint4* metaA;
     uint32_t lds_stride;
-    unsigned char* ws;
-    size_t ws_stride;
-    int32_t* next;  // big tables: work counter, zero at launch
 };
 
 template <int E, bool ONE, int MAXB>
@@ -258,7 +173,7 @@ __global__ __launch_bounds__(MAXB) void alias_mix_lds_kernel(MixArgs a)
         return;
     }
     const size_t off = a.sp_off[w];
-    const MixRegs io{a.sp_topic + off, a.sp_count + off, a.nk, a.betabar, a.ma + off};
+    const MixIo io{a.sp_topic + off, a.sp_count + off, a.nk, a.betabar, a.ma + off};
     uint64_t QS;
     uint32_t C;
     build_table_regs<E, ONE>(n, io, io, smem_raw + (size_t)wv * a.lds_stride, QS, C);
@@ -266,42 +181,26 @@ __global__ __launch_bounds__(MAXB) void alias_mix_lds_kernel(MixArgs a)
         a.metaA[2 * (size_t)w] = make_uint4((uint32_t)n, C, (uint32_t)QS, (uint32_t)(QS >> 32));
 }
 
-__global__ __launch_bounds__(1024) void alias_mix_big_kernel(MixArgs a)
-{
-    // The tables differ in size by orders of magnitude and are listed largest first: a
-    // workgroup takes its first table by its index and every further one from a counter.
-    __shared__ int32_t s_next;
-    unsigned char* lists = a.ws + (size_t)blockIdx.x * a.ws_stride;
-    int32_t i = blockIdx.x;
-    while (i < a.n_words) {
-        const int32_t w = a.words[i];
-        const int32_t n = a.sp_nnz[w];
-        uint64_t QS = 0;
-        uint32_t C = 0;
-        if (n > 0) {  // (a word without tokens is never drawn from)
-            const size_t off = a.sp_off[w];
-            SparseSrc src{a.sp_topic + off, a.sp_count + off, a.nk, a.betabar};
-            SparseSink sink{a.ma + off, a.sp_topic + off, a.sp_count + off};
-            build_alias_table<true>(n, src, sink, lists, true, QS, C);
-        }
-        if (threadIdx.x == 0)
-            a.metaA[2 * (size_t)w] = make_uint4((uint32_t)n, C, (uint32_t)QS, (uint32_t)(QS >> 32));
-        ListMem<true>::barrier();
-        if (threadIdx.x == 0) s_next = (int32_t)gridDim.x + atomicAdd(a.next, 1);
-        __syncthreads();
-        i = s_next;
-        __syncthreads();
+struct MixTables {
+    MixArgs a;
+    __device__ __forceinline__ int32_t entries(int32_t i) const { return a.sp_nnz[a.words[i]]; }
+    __device__ __forceinline__ MixIo io(int32_t i) const
+    {
+        const size_t off = a.sp_off[a.words[i]];
+        return MixIo{a.sp_topic + off, a.sp_count + off, a.nk, a.betabar, a.ma + off};
     }
-}
-
-__global__ void set_i32_kernel(int32_t* p, int32_t v) { *p = v; }
+    __device__ __forceinline__ void done(int32_t i, int32_t n, uint64_t Q0, uint32_t C) const
+    {
+        a.metaA[2 * (size_t)a.words[i]] = make_uint4((uint32_t)n, C, (uint32_t)Q0, (uint32_t)(Q0 >> 32));
+    }
+};
 
 template <int E, bool ONE, int MAXB>
 __global__ __launch_bounds__(MAXB) void alias_beta_lds_kernel(const int32_t* nk, int32_t K, double beta,
                                                               double betabar, uint2* out, uint64_t* hdr)
 {
     extern __shared__ unsigned char smem_raw[];
-    const BetaRegs io{nk, beta, betabar, out};
+    const BetaIo io{nk, beta, betabar, out};
     uint64_t QB;
     uint32_t C;
     build_table_regs<E, ONE>(K, io, io, smem_raw, QB, C);
@@ -311,20 +210,20 @@ __global__ __launch_bounds__(MAXB) void alias_beta_lds_kernel(const int32_t* nk,
     }
 }
 
-__global__ __launch_bounds__(1024) void alias_beta_big_kernel(const int32_t* nk, int32_t K, double beta,
-                                                              double betabar, uint2* out,
-                                                              uint64_t* hdr, unsigned char* ws)
-{
-    BetaSrc src{nk, beta, betabar};
-    BetaSink sink{out};
-    uint64_t QB;
-    uint32_t C;
-    build_alias_table<true>(K, src, sink, ws, true, QB, C);
-    if (threadIdx.x == 0) {
-        hdr[0] = QB;
+struct BetaTables {
+    const int32_t* nk;
+    int32_t K;
+    double beta, betabar;
+    uint2* out;
+    uint64_t* hdr;
+    __device__ __forceinline__ int32_t entries(int32_t) const { return K; }
+    __device__ __forceinline__ BetaIo io(int32_t) const { return BetaIo{nk, beta, betabar, out}; }
+    __device__ __forceinline__ void done(int32_t, int32_t, uint64_t Q0, uint32_t C) const
+    {
+        hdr[0] = Q0;
         hdr[1] = C;
     }
-}
+};
 
 // Non-zero topics of a dense row, ascending, into the word's list (a mixture word
 // that keeps a dense row).  One workgroup per word; every wave owns a contiguous run of
@@ -446,7 +345,117 @@ int launch_dense_lds(lda_ctx* c, DenseArgs a)
     });
 }
 
+// the five launches of alias_split.hpp for every batch of the set
+template <class Tables>
+int launch_big_tables(lda_ctx* c, hipStream_t stream, const BigSet& set, const Tables& tab)
+{
+    BigWork W{};
+    W.chunks = set.d_chunks; W.first = set.d_first; W.list = set.d_list; W.sums = set.d_sums;
+    W.state = set.d_state; W.dx = set.dx; W.hidx = set.hidx;
+    for (size_t b = 0; b + 1 < set.batch_chunk.size(); ++b) {
+        W.c0 = set.batch_chunk[b];
+        const dim3 grid(set.batch_chunk[b + 1] - W.c0), block(kBigThreads);
+        hipLaunchKernelGGL(big_mass_kernel<Tables>, grid, block, 0, stream, tab, W);
+        hipLaunchKernelGGL(big_shift_kernel<Tables>, grid, block, 0, stream, tab, W);
+        hipLaunchKernelGGL(big_counts_kernel<Tables>, grid, block, 0, stream, tab, W);
+        hipLaunchKernelGGL(big_lists_kernel<Tables>, grid, block, 0, stream, tab, W);
+        hipLaunchKernelGGL(big_pairs_kernel<Tables>, grid, block, 0, stream, tab, W);
+        LDA_HIP(c, hipGetLastError());
+    }
+    return LDA_OK;
+}
+
+// Chunks and batches of the tables with the given largest numbers of entries: a batch's lists
+// fit `room` list entries (a single table always does).  Returns the list entries needed.
+template <class Entries>
+int setup_big_set(lda_ctx* c, BigSet* set, size_t n_tables, Entries entries, uint64_t room, uint64_t* need)
+{
+    *need = 0;
+    if (n_tables == 0) return LDA_OK;
+    std::vector<int2> chunks;
+    std::vector<uint32_t> first;
+    std::vector<uint64_t> list;
+    uint64_t used = 0;
+    set->batch_chunk.assign(1, 0u);
+    for (size_t t = 0; t < n_tables; ++t) {
+        const int32_t n = entries(t);
+        if (used > 0 && used + (uint64_t)n + 1 > room) {
+            set->batch_chunk.push_back((uint32_t)chunks.size());
+            used = 0;
+        }
+        list.push_back(used);
+        used += (uint64_t)n + 1;
+        *need = std::max(*need, used);
+        first.push_back((uint32_t)chunks.size());
+        for (int32_t k = 0; k < n; k += kBigChunk) chunks.push_back(make_int2((int32_t)t, k));
+    }
+    set->batch_chunk.push_back((uint32_t)chunks.size());
+    LDA_ALLOC(c, &set->d_chunks, chunks.size(), "table chunks");
+    LDA_ALLOC(c, &set->d_first, first.size(), "table chunks");
+    LDA_ALLOC(c, &set->d_list, list.size(), "table chunks");
+    LDA_ALLOC(c, &set->d_sums, chunks.size(), "table chunks");
+    LDA_ALLOC(c, &set->d_state, n_tables, "table chunks");
+    LDA_HIP(c, hipMemcpy(set->d_chunks, chunks.data(), sizeof(int2) * chunks.size(), hipMemcpyHostToDevice));
+    LDA_HIP(c, hipMemcpy(set->d_first, first.data(), sizeof(uint32_t) * first.size(), hipMemcpyHostToDevice));
+    LDA_HIP(c, hipMemcpy(set->d_list, list.data(), sizeof(uint64_t) * list.size(), hipMemcpyHostToDevice));
+    return LDA_OK;
+}
+
+void free_big_set(lda_ctx* c, BigSet& s)
+{
+    device_free(c, s.d_chunks);
+    device_free(c, s.d_first);
+    device_free(c, s.d_list);
+    device_free(c, s.d_sums);
+    device_free(c, s.d_state);
+    s = BigSet{};
+}
+
 }  // namespace
+
+// Work lists and list memory of the tables built by many workgroups each: the dense tables and
+// the shared beta table when K exceeds one workgroup's LDS, and the mixture words of `big_mix`.
+// Dense and mixture tables follow each other on one stream and share their list memory; the
+// beta table is built beside them and has its own.
+int setup_big_tables(lda_ctx* c, const std::vector<int32_t>& big_mix)
+{
+    const int32_t K = c->K;
+    const bool big_k = K > kRegsMaxEntries;
+    // Room of a batch: 340 tables of K entries (4 KB K bytes) fill the chip many times over --
+    // at the smallest K it is 2000 chunks -- and keep the lists small beside the tables.
+    const uint64_t room = std::min<uint64_t>(340ull * (uint64_t)K, 1000000000ull);
+    uint64_t need_dense = 0, need_mix = 0, need_beta = 0;
+    int rc = setup_big_set(c, &c->big_dense, big_k ? (size_t)c->n_dense_alias : 0,
+                           [&](size_t) { return K; }, room, &need_dense);
+    if (rc != LDA_OK) return rc;
+    rc = setup_big_set(c, &c->big_mix, big_mix.size(), [&](size_t i) {
+        const int32_t w = big_mix[i];
+        return (int32_t)(c->h_sp_off[w + 1] - c->h_sp_off[w]);
+    }, room, &need_mix);
+    if (rc != LDA_OK) return rc;
+    rc = setup_big_set(c, &c->big_beta, big_k && c->n_mix > 0 ? 1 : 0, [&](size_t) { return K; }, room, &need_beta);
+    if (rc != LDA_OK) return rc;
+    const uint64_t main = std::max(need_dense, need_mix);
+    if (main + need_beta == 0) return LDA_OK;
+    LDA_ALLOC(c, &c->d_big_dx, main + need_beta, "table workspace");
+    LDA_ALLOC(c, &c->d_big_hidx, main + need_beta, "table workspace");
+    c->big_dense.dx = c->big_mix.dx = c->d_big_dx;
+    c->big_dense.hidx = c->big_mix.hidx = c->d_big_hidx;
+    c->big_beta.dx = c->d_big_dx + main;
+    c->big_beta.hidx = c->d_big_hidx + main;
+    return LDA_OK;
+}
+
+void free_big_tables(lda_ctx* c)
+{
+    free_big_set(c, c->big_dense);
+    free_big_set(c, c->big_mix);
+    free_big_set(c, c->big_beta);
+    device_free(c, c->d_big_dx);
+    device_free(c, c->d_big_hidx);
+    c->d_big_dx = nullptr;
+    c->d_big_hidx = nullptr;
+}
 
 int max_lds_table_entries() { return kRegsMaxEntries; }
 int max_alias_topics() { return kRegsMaxEntries; }
@@ -468,7 +477,7 @@ int launch_alias_build(lda_ctx* c)
 namespace {
 
 // Mixture tables of the words in `words` whose list capacity is at most cap_entries
-// (cap_entries = 0: any size, built in the global workspace).
+// (cap_entries = 0: any size, many workgroups each).
 int launch_alias_mix_class(lda_ctx* c, hipStream_t stream, const int32_t* words, int32_t n_words,
                            int32_t cap_entries)
 {
@@ -491,14 +500,7 @@ int launch_alias_mix_class(lda_ctx* c, hipStream_t stream, const int32_t* words,
             return LDA_OK;
         });
     }
-    a.ws = c->d_big_ws; a.ws_stride = c->big_ws_stride;
-    a.next = c->d_flag + 1;
-    hipLaunchKernelGGL(set_i32_kernel, dim3(1), dim3(1), 0, stream, a.next, 0);
-    LDA_HIP(c, hipGetLastError());
-    const int grid = n_words < c->n_big_wg ? n_words : c->n_big_wg;
-    hipLaunchKernelGGL(alias_mix_big_kernel, dim3(grid), dim3(1024), 0, stream, a);
-    LDA_HIP(c, hipGetLastError());
-    return LDA_OK;
+    return launch_big_tables(c, stream, c->big_mix, MixTables{a});
 }
 
 // the shared beta table and the mixture tables that are built in LDS, in this order on `stream`
@@ -520,15 +522,15 @@ int launch_small_mixture_tables(lda_ctx* c, hipStream_t stream)
             return LDA_OK;
         });
         if (rc != LDA_OK) return rc;
-    } else {  // one workgroup, with a slot of list memory of its own
-        hipLaunchKernelGGL(alias_beta_big_kernel, dim3(1), dim3(1024), 0, stream, c->d_nk, K,
-                           c->beta, c->betabar, c->d_beta_alias, c->d_beta_hdr,
-                           c->d_big_ws + c->big_ws_stride * (size_t)c->n_big_wg);
+        LDA_HIP(c, hipGetLastError());
+    } else {
+        rc = launch_big_tables(c, stream, c->big_beta,
+                               BetaTables{c->d_nk, K, c->beta, c->betabar, c->d_beta_alias, c->d_beta_hdr});
+        if (rc != LDA_OK) return rc;
     }
-    LDA_HIP(c, hipGetLastError());
     for (int cl = 0; cl < kMixClasses; ++cl) {
         const int32_t cap = kMixClassCap[cl];
-        if (cap < 0) continue;  // the class of the global workspace
+        if (cap < 0) continue;  // the class of any size
         rc = launch_alias_mix_class(c, stream, c->d_mix_class[cl], c->n_mix_class[cl],
                                     cap ? cap : lds_max);
         if (rc != LDA_OK) return rc;
@@ -540,8 +542,8 @@ int launch_small_mixture_tables(lda_ctx* c, hipStream_t stream)
 
 // Hybrid mode: the shared beta table, dense tables of the head words, mixture tables of the
 // rest.  Two chains of kernels run side by side: on a second stream of the library's own the
-// beta table (one workgroup, milliseconds when K is large) and the many small tables built in
-// LDS; on the caller's stream the dense tables and the tables built in the global workspace.
+// beta table and the many small tables built in LDS; on the caller's stream the dense tables
+// and the large mixture tables.
 // The second stream is forked from the caller's by an event and joined at the end.
 int launch_alias_build_hybrid(lda_ctx* c)
 {
@@ -571,13 +573,8 @@ int launch_alias_build_hybrid(lda_ctx* c)
         if (K <= lds_max) {
             rc = launch_dense_lds(c, a);
         } else {
-            a.ws = c->d_big_ws; a.ws_stride = c->big_ws_stride;
-            const int grid = c->n_dense_alias < c->n_big_wg ? c->n_dense_alias : c->n_big_wg;
-            hipLaunchKernelGGL(alias_dense_big_kernel, dim3(grid), dim3(1024), 0, c->stream, a);
-            rc = LDA_OK;
+            rc = launch_big_tables(c, c->stream, c->big_dense, DenseTables{a});
         }
-        if (rc == LDA_OK && hipGetLastError() != hipSuccess)
-            rc = fail(c, LDA_ERR_HIP, "launch of the dense table build failed");
     } else {
         rc = LDA_OK;
     }

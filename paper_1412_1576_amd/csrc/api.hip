@@ -54,9 +54,6 @@ void device_free(lda_ctx* c, void* p)
 
 namespace {
 
-// bytes of list memory of the alias builder for n entries with the mass cache
-size_t alias_list_bytes_host(size_t n) { return 8 * (n + 1) + 4 * n + 4 * n; }
-
 int setup_hybrid(lda_ctx* c, const std::vector<int32_t>& woff);
 
 template <class T>
@@ -102,7 +99,8 @@ void free_all(lda_ctx* c)
     dev_free(c, c->d_sparse_words); dev_free(c, c->d_compact_words); dev_free(c, c->d_sp_off);
     dev_free(c, c->d_sp_topic); dev_free(c, c->d_sp_count); dev_free(c, c->d_sp_nnz); dev_free(c, c->d_hs_off);
     dev_free(c, c->d_hs); dev_free(c, c->d_ma); dev_free(c, c->d_metaA); c->d_metaB = nullptr;
-    dev_free(c, c->d_beta_alias); dev_free(c, c->d_beta_hdr); dev_free(c, c->d_big_ws);
+    dev_free(c, c->d_beta_alias); dev_free(c, c->d_beta_hdr);
+    free_big_tables(c);
 }
 
 }  // namespace
@@ -268,12 +266,6 @@ int setup_hybrid(lda_ctx* c, const std::vector<int32_t>& woff)
     UP(d_dense_alias_words, dense_alias, "dense-table words");
     UP(d_sparse_words, sparse, "sparse-row words");
     UP(d_compact_words, compact, "compaction words");
-    {  // the tables built in the global workspace: largest list first (see alias_mix_big_kernel)
-        std::vector<int32_t>& big = mixc[kMixClasses - 1];
-        std::stable_sort(big.begin(), big.end(), [&](int32_t a, int32_t b) {
-            return c->h_sp_off[a + 1] - c->h_sp_off[a] > c->h_sp_off[b + 1] - c->h_sp_off[b];
-        });
-    }
     for (int i = 0; i < kMixClasses; ++i) {
         c->n_mix_class[i] = (int32_t)mixc[i].size();
         UP(d_mix_class[i], mixc[i], "mixture class");
@@ -292,16 +284,7 @@ int setup_hybrid(lda_ctx* c, const std::vector<int32_t>& woff)
     AL(d_beta_alias, (size_t)K + 2, "beta table");  // read in aligned pairs
     AL(d_beta_hdr, 2, "beta table");
     LDA_HIP(c, hipMemsetAsync(c->d_sp_nnz, 0, sizeof(int32_t) * (size_t)V, c->stream));
-    // global list memory for tables too large for LDS
-    const bool need_big = (K > lds_max && (c->n_dense_alias > 0 || c->n_mix > 0)) ||
-                          c->n_mix_class[kMixClasses - 1] > 0;
-    if (need_big) {
-        c->big_ws_stride = (alias_list_bytes_host((size_t)K) + 255) / 256 * 256;
-        // one workgroup per compute unit when 12 GB allow it (K = 10^6: 256 x 40 MB)
-        int64_t wg = (int64_t)(12.0e9 / (double)c->big_ws_stride);
-        c->n_big_wg = (int32_t)std::max<int64_t>(1, std::min<int64_t>(256, wg));
-        AL(d_big_ws, c->big_ws_stride * ((size_t)c->n_big_wg + 1), "table workspace");
-    }
+    if ((rc = setup_big_tables(c, mixc[kMixClasses - 1])) != LDA_OK) return rc;
 #undef AL
     return setup_sparse_rows(c, woff);
 }

@@ -20,8 +20,7 @@ enum State { COUNTS_VALID = 1, ALIAS_VALID = 2, SWEPT = 3 };
 
 // One rebuild work item: a slice [p0, p1) of word w's word-major segment.
 // Mixture tables are launched by size class so that a small table does not reserve a large
-// table's LDS: list capacity of each class, 0 = the largest that fits LDS, -1 = any size (built
-// in the global workspace).
+// table's LDS: list capacity of each class, 0 = the largest that fits LDS, -1 = any size.
 constexpr int kMixClasses = 8;
 constexpr int32_t kMixClassCap[kMixClasses] = {64, 256, 1024, 2048, 4096, 8192, 0, -1};
 
@@ -39,6 +38,30 @@ struct RebuildTile {
 struct PartTile {
     int32_t seg;
     int32_t p0, p1;
+};
+
+// Alias tables built by many workgroups each (alias_split.hpp).  Per chunk of a table:
+struct BigSums {
+    uint64_t q0, q;        // sums of the quantised weights, of the shifted ones
+    uint64_t df, ex;       // deficit of the lights, excess of the heavies
+    uint32_t lights;
+    uint32_t a_before;     // lights of the table's chunks before this one
+};
+// per table:
+struct BigState {
+    uint64_t Q0, C, pad;
+    uint32_t sh;
+    uint32_t A;            // lights
+};
+struct BigSet {
+    int2* d_chunks = nullptr;
+    uint32_t* d_first = nullptr;
+    uint64_t* d_list = nullptr;
+    BigSums* d_sums = nullptr;
+    BigState* d_state = nullptr;
+    uint64_t* dx = nullptr;    // not owned
+    uint32_t* hidx = nullptr;
+    std::vector<uint32_t> batch_chunk;  // first chunk of every batch, and the end
 };
 
 // Streamed data blocks (stream_blocks.hip): tiles [c0, c1) = tokens [g0, g1) of the corpus
@@ -152,8 +175,8 @@ struct lda_ctx {
     int32_t* d_dense_alias_words = nullptr;  // words that draw from a dense K-bin table
     int32_t n_dense_alias = 0;
     int32_t n_mix = 0;                   // words that draw from the mixture
-    // the mixture words by list capacity (kMixClassCap; the last class is built in the global
-    // workspace)
+    // the mixture words by list capacity (kMixClassCap; the tables of the last class are built by
+    // many workgroups each)
     int32_t* d_mix_class[lda::kMixClasses] = {};
     int32_t n_mix_class[lda::kMixClasses] = {};
     int32_t* d_sparse_words = nullptr;   // words whose n_kw row lives as a list: sparse rows and
@@ -175,10 +198,11 @@ struct lda_ctx {
     uint4* d_metaB = nullptr;            // = d_metaA + 1 (not owned)
     uint2* d_beta_alias = nullptr;       // [K] shared table of the beta term (split, alias)
     uint64_t* d_beta_hdr = nullptr;      // [2] QB, capacity
-    unsigned char* d_big_ws = nullptr;   // list memory of the workgroups that build big tables
-    size_t big_ws_stride = 0;
-    int32_t n_big_wg = 0;                // the shared beta table has one more slot of its own
-    // the one-workgroup build of a large beta table runs beside the other table kernels
+    // tables built by many workgroups each (alias_split.hpp): work lists, and the list memory
+    lda::BigSet big_dense, big_mix, big_beta;
+    uint64_t* d_big_dx = nullptr;
+    uint32_t* d_big_hidx = nullptr;
+    // the build of the beta table and of the small tables runs beside the other table kernels
     hipStream_t side_stream = nullptr;
     hipEvent_t side_fork = nullptr, side_join = nullptr;
     bool side_pending = false;           // side_join recorded, not yet waited for
@@ -275,6 +299,8 @@ int fork_side_stream(lda_ctx* c);
 int side_stream_done(lda_ctx* c);
 int join_side_stream(lda_ctx* c);
 int max_lds_table_entries();  // largest alias table built in LDS
+int setup_big_tables(lda_ctx* c, const std::vector<int32_t>& big_mix);
+void free_big_tables(lda_ctx* c);
 
 // Up to this many topics the doc pass keeps a copy of n_k in every workgroup's LDS.
 constexpr int32_t kNkLdsTopics = 16384;
