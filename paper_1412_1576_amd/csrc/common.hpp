@@ -357,8 +357,9 @@ int launch_sparse_rows(lda_ctx* c);   // lists, list lengths and hash rows of th
 int launch_nk_by_ranges(lda_ctx* c);  // n_k when K is too large for a few LDS histograms over z
 int launch_loglik(lda_ctx* c, double* doc_part, double* word_part);
 int launch_loglik_doc_tiles(lda_ctx* c, double* d_partial);  // partial[tile] of the bound tiles
-// zw[wpos[i]] = z[i], i < n: topics into the word-major copy
-int launch_scatter_word_major(lda_ctx* c, const int32_t* z, const int32_t* wpos, int64_t n);
+// zw[wpos[i]] = z[i], i < n: topics into the word-major copy (go: only if *go is not zero)
+int launch_scatter_word_major(lda_ctx* c, const int32_t* z, const int32_t* wpos, int64_t n,
+                              const int32_t* go = nullptr);
 // streamed data blocks (stream_blocks.hip)
 int enter_streamed_mode(lda_ctx* c, const std::vector<int32_t>& chunk_doc);
 void leave_streamed_mode(lda_ctx* c);
