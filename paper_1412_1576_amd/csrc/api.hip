@@ -420,6 +420,12 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
     c->sweep_block = std::max(c->sweep_block, ((c->chunk_tokens + 7) / 8 + 63) / 64 * 64);
     const int32_t tile_tokens = o.rebuild_tile_tokens > 0 ? o.rebuild_tile_tokens : 262144;
     c->rebuild_tile_tokens = tile_tokens;
+    // Words of the dense form are cut finer where a tile would hold more than a CU's share of the
+    // corpus (the longest would be the time of the rebuild: 1.9 * 10^6 tokens, K = 500, 77 us),
+    // but not below four tokens per topic that a tile adds to the row.  A mixture word keeps one
+    // tile, which writes its list of non-zeros too.
+    const int32_t dense_tile = o.rebuild_tile_tokens > 0 ? tile_tokens
+        : (int32_t)std::min<int64_t>(tile_tokens, std::max<int64_t>(std::max<int64_t>(1024, 4 * (int64_t)K), N / 256));
 
     int rc = LDA_OK;
     auto bail = [&](int code) {
@@ -556,13 +562,14 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
     tiles.reserve((size_t)H + 1024);
     for (int32_t w = 0; w < H; ++w) {
         const int32_t b = woff[w], e = woff[w + 1];
-        if (e - b <= tile_tokens) {
+        const int32_t limit = hybrid && (c->h_wkind[w] & 2) == 0 ? tile_tokens : dense_tile;
+        if (e - b <= limit) {
             const int32_t form = !list_from_rebuild(c, w) ? 0 : ((c->h_wkind[w] & kKindListOnly) ? 3 : 2);
             tiles.push_back(RebuildTile{w, b, e, form});
         } else {
             multi.push_back(w);
-            for (int32_t p = b; p < e; p += tile_tokens)
-                tiles.push_back(RebuildTile{w, p, std::min(e, p + tile_tokens), 1});
+            for (int32_t p = b; p < e; p += limit)
+                tiles.push_back(RebuildTile{w, p, std::min(e, p + limit), 1});
         }
     }
     c->n_tiles = (int32_t)tiles.size();

@@ -54,10 +54,10 @@ __global__ __launch_bounds__(1024) void scatter_wm_kernel(const int32_t* __restr
 }
 
 // blockIdx.x: tile; blockIdx.y: range of `span` topics (one range when the row fits LDS)
-constexpr int32_t kTileRun = 32;
+constexpr int32_t kTileRun = 32;  // consecutive tiles of an XCD, at most
 
 __global__ __launch_bounds__(1024) void nkw_tiles_kernel(const RebuildTile* __restrict__ tiles,
-                                                         int32_t n_tiles,
+                                                         int32_t n_tiles, int32_t run,
                                                          const int32_t* __restrict__ zw,
                                                          int32_t sh, uint32_t zmask, int32_t K,
                                                          int32_t span,
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(1024) void nkw_tiles_kernel(const RebuildTile* __re
     if (unwanted(go)) return;
     // runs of consecutive tiles (neighbouring words) share an XCD and with it the lines of
     // the records they read
-    const int32_t ti = xcd_runs(kTileRun);
+    const int32_t ti = xcd_runs(run);
     if (ti >= n_tiles) return;
     const RebuildTile t = tiles[ti];
     const int32_t k0 = (int32_t)blockIdx.y * span;
@@ -264,6 +264,16 @@ __global__ __launch_bounds__(1024) void update_counts_kernel(const int32_t* __re
     }
 }
 
+// Workgroups of a pass over all tokens with K counters of its own each: 65536 tokens per
+// workgroup, fewer for a small corpus (down to one 16-byte load per thread) as long as they are
+// four times the counters that every workgroup adds to the result.
+int64_t hist_blocks(const lda_ctx* c)
+{
+    const int64_t least = std::max<int64_t>(4096, 4 * (int64_t)c->K);
+    const int64_t per = std::min<int64_t>(65536, std::max(least, c->N / 256));
+    return (c->N + per - 1) / per;
+}
+
 // *recount = 1 if more than `most` of the kMovedSample tokens spread evenly over z have moved
 constexpr int32_t kMovedSample = 16384;
 
@@ -318,9 +328,10 @@ int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
                            c->d_multi_words, K, c->d_nkw, go);
         LDA_HIP(c, hipGetLastError());
     }
-    hipLaunchKernelGGL(nkw_tiles_kernel, dim3(xcd_runs_grid(c->n_tiles, kTileRun), (K + span - 1) / span),
+    const int32_t run = xcd_run_length(c->n_tiles, kTileRun);
+    hipLaunchKernelGGL(nkw_tiles_kernel, dim3(xcd_runs_grid(c->n_tiles, run), (K + span - 1) / span),
                        dim3(span <= 512 ? 256 : (span <= 16384 ? 512 : 1024)), lds, c->stream, c->d_tiles,
-                       c->n_tiles, c->d_zt,
+                       c->n_tiles, run, c->d_zt,
                        c->zt_shift, c->zt_mask, K, span,
                        c->d_nkw, c->d_sp_off, c->d_sp_topic, c->d_sp_count, c->d_sp_nnz, c->d_xmap, go);
     LDA_HIP(c, hipGetLastError());
@@ -336,10 +347,7 @@ int launch_nk_hist(lda_ctx* c, const int32_t* go = nullptr)
     LDA_HIP(c, hipGetLastError());
     const int32_t nr = (K + kNkRangeTopics - 1) / kNkRangeTopics;
     const int32_t span = (K + nr - 1) / nr;
-    int64_t blocks = (c->N + 65535) / 65536;
-    const int64_t most = nr > 1 ? 512 : 2048;
-    if (blocks > most) blocks = most;
-    if (blocks < 1) blocks = 1;
+    const int64_t blocks = std::min<int64_t>(hist_blocks(c), nr > 1 ? 512 : 2048);
     const size_t lds = sizeof(int32_t) * (size_t)span;
     if (lds > 48 * 1024)
         LDA_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(nk_hist_ranges_kernel),
@@ -388,8 +396,7 @@ int launch_update_counts(lda_ctx* c)
                            (int32_t)(break_even * kMovedSample), recount);
         LDA_HIP(c, hipGetLastError());
     }
-    int64_t blocks = (c->N + 65535) / 65536;
-    blocks = std::max<int64_t>(1, std::min<int64_t>(blocks, 2048));
+    const int64_t blocks = std::min<int64_t>(hist_blocks(c), 2048);
     const size_t lds = sizeof(int32_t) * (size_t)c->K;
     if (lds > 48 * 1024)
         LDA_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(update_counts_kernel),

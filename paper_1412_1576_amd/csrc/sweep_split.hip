@@ -34,7 +34,11 @@ namespace lda {
 
 namespace {
 
-constexpr int32_t kRowItemTokens = 65536;  // tokens a workgroup serves from one staging of the rows
+// Tokens a workgroup serves from one staging of the rows: at most 65536, fewer where that would
+// leave less than two items per CU, but not so few that staging K entries outweighs them.
+// (1.9 * 10^6 tokens, K = 500, the largest word one item: 52 us, split 20 us.)
+constexpr int32_t kRowItemTokens = 65536, kRowItemLeast = 1024;
+constexpr int64_t kRowItemsWanted = 512;
 constexpr int32_t kRowMinTokens = 2048;    // words with fewer tokens are gathered
 // Tokens of a gather piece.  Small on purpose: a piece is one workgroup, some 200 of them are
 // in flight on an XCD, and what they gather from -- the hash rows and tables of their words --
@@ -135,6 +139,7 @@ struct SplitArgs {
     const int4* row_items;
     const int4* pieces;
     int32_t n_chunks, n_row_items, n_pieces;
+    int32_t row_run, mix_run, piece_run;  // consecutive items of an XCD (xcd_runs)
     int32_t K, cap_tokens;
     int32_t max_doc_tokens;  // a longer document is a tile of its own, left to the long-document kernel
     int32_t doc_block;       // threads per workgroup of the doc pass
@@ -259,7 +264,7 @@ __device__ __forceinline__ void with_record_layout(const SplitArgs& A, F&& f)
     }
 }
 
-constexpr int32_t kRowItemRun = 8, kMixItemRun = 16, kPieceRun = 256;
+constexpr int32_t kRowItemRun = 8, kMixItemRun = 16, kPieceRun = 256;  // at most
 
 // Eq. (9), (12): the topic of a random token of the document, or a uniform topic.
 // zat(j) is the snapshot topic of the document's j-th token.
@@ -314,7 +319,7 @@ __global__ __launch_bounds__(1024) void word_pass_rows_kernel(SplitArgs A)
     extern __shared__ int32_t smem[];
     uint2* __restrict__ tab = reinterpret_cast<uint2*>(smem);  // [K] (split, alias)
     int32_t* __restrict__ row = smem + 2 * (size_t)A.K;        // [K] n_kw
-    const int32_t it_i = xcd_runs(kRowItemRun);
+    const int32_t it_i = xcd_runs(A.row_run);
     if (it_i >= A.n_row_items) return;
     const int4 it = A.row_items[it_i];  // (w, p0, n, 0)
     const int32_t K = A.K;
@@ -406,7 +411,7 @@ __global__ __launch_bounds__(256) void word_pass_gather_kernel(SplitArgs A)
 {
     using C = Chain<NW, ND>;
     __shared__ int32_t soff[kPieceWords + 1];
-    const int32_t pc_i = xcd_runs(kPieceRun);
+    const int32_t pc_i = xcd_runs(A.piece_run);
     if (pc_i >= A.n_pieces) return;
     const int4 pc = A.pieces[pc_i];  // (w0, w1, p0, n)
     const int32_t nwords = pc.y - pc.x;
@@ -596,7 +601,7 @@ __global__ __launch_bounds__(512) void word_pass_mix_rows_kernel(SplitArgs A)
     using C = Chain<NW, ND>;
     extern __shared__ int32_t smem[];
     int32_t* __restrict__ row = smem;  // [K] n_kw
-    const int32_t it_i = xcd_runs(kMixItemRun);
+    const int32_t it_i = xcd_runs(A.mix_run);
     if (it_i >= A.n_mix_items) return;
     const int4 it = A.mix_items[it_i];  // (w, p0, n, 0)
     const int32_t K = A.K, w = it.x;
@@ -1109,18 +1114,18 @@ int launch_chain(lda_ctx* c, const SplitArgs& A, bool need_proposals)
         auto kern = word_pass_rows_kernel<NW, ND>;
         const size_t lds = sizeof(int32_t) * 3 * (size_t)c->K;
         if ((rc = raise_lds_limit(c, kern, lds)) != LDA_OK) return rc;
-        hipLaunchKernelGGL(kern, dim3(xcd_runs_grid(c->n_row_items, kRowItemRun)), dim3(1024), lds, c->stream, A);
+        hipLaunchKernelGGL(kern, dim3(xcd_runs_grid(c->n_row_items, A.row_run)), dim3(1024), lds, c->stream, A);
         LDA_HIP(c, hipGetLastError());
     }
     if (c->n_mix_items > 0) {
         auto kern = word_pass_mix_rows_kernel<NW, ND>;
         const size_t lds = sizeof(int32_t) * (size_t)c->K;
         if ((rc = raise_lds_limit(c, kern, lds)) != LDA_OK) return rc;
-        hipLaunchKernelGGL(kern, dim3(xcd_runs_grid(c->n_mix_items, kMixItemRun)), dim3(512), lds, c->stream, A);
+        hipLaunchKernelGGL(kern, dim3(xcd_runs_grid(c->n_mix_items, A.mix_run)), dim3(512), lds, c->stream, A);
         LDA_HIP(c, hipGetLastError());
     }
     if (c->n_gather_pieces > 0) {
-        const dim3 grid(xcd_runs_grid(c->n_gather_pieces, kPieceRun));
+        const dim3 grid(xcd_runs_grid(c->n_gather_pieces, A.piece_run));
         if (!c->hybrid)
             hipLaunchKernelGGL((word_pass_gather_kernel<NW, ND, 0>), grid, dim3(256), 0, c->stream, A);
         else if (c->H == c->V)
@@ -1196,13 +1201,21 @@ int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
     // rows are staged for frequent words with a dense row and a dense table of at most
     // max_alias_topics() bins (12 bytes of LDS per topic)
     const bool rows_fit = c->K <= max_alias_topics();
+    auto dense_form = [&](int32_t w) { return !c->hybrid || (c->h_wkind[w] & 3) == 3; };
+    int64_t row_tokens = 0;
+    for (int32_t w = 0; w < V; ++w) {
+        const int32_t n = woff[w + 1] - woff[w];
+        if (n >= kRowMinTokens && rows_fit && dense_form(w)) row_tokens += n;
+    }
+    const int32_t row_item = (int32_t)std::min<int64_t>(
+        kRowItemTokens, std::max<int64_t>(std::max(kRowItemLeast, c->K), row_tokens / kRowItemsWanted));
     for (int32_t w = 0; w < V; ++w) {
         const int32_t b = woff[w], n = woff[w + 1] - b;
-        const bool dense_dense = !c->hybrid || (c->h_wkind[w] & 3) == 3;
+        const bool dense_dense = dense_form(w);
         if (n >= kRowMinTokens && rows_fit && dense_dense) {
             close_piece(w);
-            for (int32_t p = b; p < b + n; p += kRowItemTokens)
-                items.push_back(make_int4(w, p, std::min(kRowItemTokens, b + n - p), 0));
+            for (int32_t p = b; p < b + n; p += row_item)
+                items.push_back(make_int4(w, p, std::min(row_item, b + n - p), 0));
             continue;
         }
         // a mixture word with a dense row of at most kMixRowTopics topics and enough
@@ -1269,6 +1282,9 @@ int launch_sweep_split(lda_ctx* c, int32_t mh_steps)
     A.nkw = c->d_nkw; A.nk = c->d_nk; A.alias = c->d_alias; A.cap = c->d_cap;
     A.zt = c->d_zt; A.zt_pack16 = c->zt_pack16 ? 1 : 0; A.rec = c->d_rec; A.row_items = c->d_row_items; A.pieces = c->d_gather_pieces;
     A.n_chunks = c->n_chunks; A.n_row_items = c->n_row_items; A.n_pieces = c->n_gather_pieces;
+    A.row_run = xcd_run_length(c->n_row_items, kRowItemRun);
+    A.mix_run = xcd_run_length(c->n_mix_items, kMixItemRun);
+    A.piece_run = xcd_run_length(c->n_gather_pieces, kPieceRun);
     A.K = c->K; A.cap_tokens = c->chunk_tokens; A.max_doc_tokens = c->chunk_tokens;
     A.doc_block = c->sweep_block;
     // (rounded up to 16 bytes: the copy of n_k behind the tile is moved as int4)

@@ -31,6 +31,14 @@ __device__ __forceinline__ int32_t xcd_runs(int32_t run)
     return ((seq / run) * kXcds + xcd) * run + seq % run;
 }
 
+// Length of the runs: `most`, or less where the list is so short that runs of that length would
+// leave XCDs without work.
+inline int32_t xcd_run_length(int32_t n_items, int32_t most)
+{
+    const int32_t even = (n_items + kXcds - 1) / kXcds;
+    return even < 1 ? 1 : (even < most ? even : most);
+}
+
 inline unsigned xcd_runs_grid(int32_t n_items, int32_t run)
 {
     const int32_t runs = (n_items + run - 1) / run;
