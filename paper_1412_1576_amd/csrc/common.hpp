@@ -249,6 +249,7 @@ struct lda_ctx {
     // scratch
     double* d_partial = nullptr;       // per-block partial sums (log-likelihood)
     int32_t n_partial = 0;
+    double* d_lg_terms = nullptr;      // log-likelihood terms by count: of alpha, then of beta
     int32_t* d_row = nullptr;          // [max(K,1)] row staging for accessors
     int32_t* d_flag = nullptr;         // [4] validation flags
     // host copies of small layouts
@@ -355,6 +356,8 @@ int launch_update_counts(lda_ctx* c);  // n_kw, n_k by +-1 for the tokens the la
 int setup_sparse_rows(lda_ctx* c, const std::vector<int32_t>& woff);
 int launch_sparse_rows(lda_ctx* c);   // lists, list lengths and hash rows of the sparse-row words
 int launch_nk_by_ranges(lda_ctx* c);  // n_k when K is too large for a few LDS histograms over z
+size_t loglik_partials(const lda_ctx* c);
+int setup_loglik(lda_ctx* c);
 int launch_loglik(lda_ctx* c, double* doc_part, double* word_part);
 int launch_loglik_doc_tiles(lda_ctx* c, double* d_partial);  // partial[tile] of the bound tiles
 // zw[wpos[i]] = z[i], i < n: topics into the word-major copy (go: only if *go is not zero)

@@ -32,12 +32,30 @@ __device__ __forceinline__ double block_sum_f64(double v, double* wtot)
     return s;
 }
 
+// The terms of counts below kTermTable, by count: lgG(v + a) - lgG(a).  They depend on the
+// context's alpha and beta alone and are made once, by the same fp64 expression that larger
+// counts are computed with, so a sum does not depend on where a term comes from.  Nearly every
+// count is small, and lgamma is some 200 fp64 instructions that a wave runs if any of its lanes
+// needs it.
+constexpr int32_t kTermTable = 4096;
+
+__device__ __forceinline__ double count_term(int32_t v, double a, double lg_a, const double* __restrict__ table)
+{
+    return v < kTermTable ? table[v] : lgamma((double)v + a) - lg_a;
+}
+
+__global__ __launch_bounds__(256) void term_table_kernel(double a, double lg_a, double* __restrict__ table)
+{
+    const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
+    if (v < kTermTable) table[v] = lgamma((double)v + a) - lg_a;
+}
+
 // doc part over LDS document tiles: one partial per tile
 __global__ __launch_bounds__(1024) void loglik_doc_tiles_kernel(
     const int32_t* __restrict__ z, const int32_t* __restrict__ doff,
     const int32_t* __restrict__ chunk_doc, const uint8_t* __restrict__ tokdoc, int32_t cap_tokens,
     int32_t cap_docs, double alpha, double alphabar, double lg_alpha, double lg_alphabar,
-    double* __restrict__ partial)
+    const double* __restrict__ terms, double* __restrict__ partial)
 {
     extern __shared__ int32_t smem[];
     __shared__ double wtot[16];
@@ -60,7 +78,7 @@ __global__ __launch_bounds__(1024) void loglik_doc_tiles_kernel(
             acc += lg_alphabar - lgamma((double)(T.sdoff[i + 1] - T.sdoff[i]) + alphabar);
         for (int32_t i = threadIdx.x; i < T.ntok; i += blockDim.x) {
             const int32_t s = slot_of(i);
-            if (first[s] == i) acc += lgamma((double)(T.tab[s] >> kTopicBits) + alpha) - lg_alpha;
+            if (first[s] == i) acc += count_term((int32_t)(T.tab[s] >> kTopicBits), alpha, lg_alpha, terms);
         }
     }
     const double s = block_sum_f64(acc, wtot);
@@ -71,7 +89,7 @@ __global__ __launch_bounds__(1024) void loglik_long_docs_kernel(
     const int32_t* __restrict__ z, const int32_t* __restrict__ doff,
     const int32_t* __restrict__ long_doc, const int64_t* __restrict__ long_slot, int32_t* keys,
     int32_t* cnts, int32_t* first_all, double alpha, double alphabar, double lg_alpha,
-    double lg_alphabar, double* __restrict__ partial)
+    double lg_alphabar, const double* __restrict__ terms, double* __restrict__ partial)
 {
     __shared__ double wtot[16];
     const int32_t d = long_doc[blockIdx.x];
@@ -91,24 +109,37 @@ __global__ __launch_bounds__(1024) void loglik_long_docs_kernel(
     for (int32_t i = threadIdx.x; i < L; i += blockDim.x) {
         const uint32_t s = tab.slot_of(z[tok0 + i]);
         if (GlobalDocTable::ld(&first[s]) == i)
-            acc += lgamma((double)GlobalDocTable::ld(&tab.cnts[s]) + alpha) - lg_alpha;
+            acc += count_term(GlobalDocTable::ld(&tab.cnts[s]), alpha, lg_alpha, terms);
     }
     const double s = block_sum_f64(acc, wtot);
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
-// word part: grid-stride over the dense table, one partial per block
+// word part: grid-stride over the dense table, one partial per block; a thread adds its terms in
+// the order of their places, four counts in flight.  Bound by reading the rows: 2.7 * 10^7 counts
+// (108 MB) took 97 us with an lgamma per non-zero.  With the table, and one copy and one wait for
+// all partial sums instead of four, a likelihood of 1.9 * 10^6 tokens at K = 500 costs 0.12 ms less.
 __global__ __launch_bounds__(256) void loglik_word_kernel(const int32_t* __restrict__ nkw,
                                                           int64_t total, double beta,
                                                           double lg_beta,
+                                                          const double* __restrict__ terms,
                                                           double* __restrict__ partial)
 {
     __shared__ double wtot[4];
     double acc = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-         i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (; i + 3 * step < total; i += 4 * step) {
+        int32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = nkw[i + u * step];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (v[u] > 0) acc += count_term(v[u], beta, lg_beta, terms);
+    }
+    for (; i < total; i += step) {
         const int32_t v = nkw[i];
-        if (v > 0) acc += lgamma((double)v + beta) - lg_beta;
+        if (v > 0) acc += count_term(v, beta, lg_beta, terms);
     }
     const double s = block_sum_f64(acc, wtot);
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
@@ -133,6 +164,7 @@ __global__ __launch_bounds__(256) void loglik_sparse_kernel(const int32_t* __res
                                                             const int32_t* __restrict__ sp_count,
                                                             const int32_t* __restrict__ sp_nnz,
                                                             double beta, double lg_beta,
+                                                            const double* __restrict__ terms,
                                                             double* __restrict__ partial)
 {
     __shared__ double wtot[4];
@@ -144,7 +176,7 @@ __global__ __launch_bounds__(256) void loglik_sparse_kernel(const int32_t* __res
         const int32_t w = words[i];
         const int32_t nnz = sp_nnz[w];
         const int32_t* __restrict__ cnt = sp_count + sp_off[w];
-        for (int32_t e = lane; e < nnz; e += kWave) acc += lgamma((double)cnt[e] + beta) - lg_beta;
+        for (int32_t e = lane; e < nnz; e += kWave) acc += count_term(cnt[e], beta, lg_beta, terms);
     }
     const double s = block_sum_f64(acc, wtot);
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
@@ -161,24 +193,6 @@ struct CompensatedSum {
     }
     double value() const { return s + comp; }
 };
-
-// Sum of the n partials at d_partial in index order.  Staged through `host` (a buffer of
-// host_cap doubles owned by the caller) a piece at a time, so the result does not depend on
-// host_cap.  Waits for the stream.
-int sum_partials(lda_ctx* c, const double* d_partial, size_t n, double* host, size_t host_cap,
-                 double* out)
-{
-    CompensatedSum acc;
-    for (size_t i0 = 0; i0 < n; i0 += host_cap) {
-        const size_t m = (n - i0 < host_cap) ? n - i0 : host_cap;
-        LDA_HIP(c, hipMemcpyAsync(host, d_partial + i0, sizeof(double) * m, hipMemcpyDeviceToHost,
-                                  c->stream));
-        LDA_HIP(c, hipStreamSynchronize(c->stream));
-        for (size_t i = 0; i < m; ++i) acc.add(host[i]);
-    }
-    *out = acc.value();
-    return LDA_OK;
-}
 
 // Scratch of lda_loglik_noalloc: the per-block partial sums of the kernels above.  One copy
 // of the array per GPU, at an address that hipGetSymbolAddress reports for the current
@@ -208,61 +222,126 @@ int static_partials(lda_ctx* c, double** out)
     return LDA_OK;
 }
 
-// The log-likelihood with the partial sums in d_partial (device memory of at least
-// max(n_chunks, n_long, 4096) doubles) and host staging in `h` (h_cap doubles).
-int run_loglik(lda_ctx* c, double* d_partial, double* h, size_t h_cap, double* doc_part,
+// Partial sums of several kernels side by side in one device buffer: one copy to the host and
+// one wait for all of them, as far as the buffer holds them.
+class Parts {
+public:
+    Parts(lda_ctx* c, double* d, size_t cap, double* h, size_t h_cap) : c_(c), d_(d), cap_(cap), h_(h), h_cap_(h_cap) {}
+    // room for n partials (n <= cap) whose sum will be added to *into; NULL on an error (rc)
+    double* take(size_t n, double* into, int* rc)
+    {
+        *rc = LDA_OK;
+        if (used_ + n > cap_ && (*rc = finish()) != LDA_OK) return nullptr;
+        part_[n_parts_++] = Part{used_, n, into};
+        used_ += n;
+        return d_ + used_ - n;
+    }
+    // waits for the stream and adds every part's sum, parts and terms in the order they were taken
+    int finish()
+    {
+        size_t i = 0, at = 0;
+        CompensatedSum acc;
+        for (size_t i0 = 0; i0 < used_; i0 += h_cap_) {
+            const size_t m = (used_ - i0 < h_cap_) ? used_ - i0 : h_cap_;
+            LDA_HIP(c_, hipMemcpyAsync(h_, d_ + i0, sizeof(double) * m, hipMemcpyDeviceToHost, c_->stream));
+            LDA_HIP(c_, hipStreamSynchronize(c_->stream));
+            for (size_t j = 0; j < m; ++j) {
+                acc.add(h_[j]);
+                if (++at == part_[i].n) {
+                    *part_[i].into += acc.value();
+                    acc = CompensatedSum();
+                    at = 0;
+                    ++i;
+                }
+            }
+        }
+        used_ = 0;
+        n_parts_ = 0;
+        return LDA_OK;
+    }
+
+private:
+    struct Part { size_t first, n; double* into; };
+    lda_ctx* c_;
+    double* d_;
+    size_t cap_;
+    double* h_;
+    size_t h_cap_;
+    size_t used_ = 0;
+    int n_parts_ = 0;
+    Part part_[8];
+};
+
+constexpr int kWordBlocks = 4096, kNkBlocks = 64;
+
+// The log-likelihood with the partial sums in d_partial (device memory of cap doubles, at least
+// max(n_chunks, n_long, kWordBlocks)) and host staging in `h` (h_cap doubles).
+int run_loglik(lda_ctx* c, double* d_partial, size_t cap, double* h, size_t h_cap, double* doc_part,
                double* word_part)
 {
     const double lga = lgamma(c->alpha), lgab = lgamma(c->alphabar);
     const double lgb = lgamma(c->beta), lgbb = lgamma(c->betabar);
-    double doc = 0.0, word = 0.0, part = 0.0;
+    double doc = 0.0, word = 0.0;
+    double* p;
     int rc;
-
+    Parts parts(c, d_partial, cap, h, h_cap);
     if (c->n_chunks > 0) {
-        rc = c->streamed ? launch_loglik_doc_streamed(c, d_partial) : launch_loglik_doc_tiles(c, d_partial);
+        if (!(p = parts.take((size_t)c->n_chunks, &doc, &rc))) return rc;
+        rc = c->streamed ? launch_loglik_doc_streamed(c, p) : launch_loglik_doc_tiles(c, p);
         if (rc != LDA_OK) return rc;
-        if ((rc = sum_partials(c, d_partial, (size_t)c->n_chunks, h, h_cap, &part)) != LDA_OK) return rc;
-        doc += part;
     }
     if (c->n_long > 0) {
+        if (!(p = parts.take((size_t)c->n_long, &doc, &rc))) return rc;
         hipLaunchKernelGGL(loglik_long_docs_kernel, dim3(c->n_long), dim3(1024), 0, c->stream,
                            c->d_z, c->d_doff, c->d_long_doc, c->d_long_slot, c->d_long_keys,
-                           c->d_long_cnts, c->d_long_first, c->alpha, c->alphabar, lga, lgab, d_partial);
+                           c->d_long_cnts, c->d_long_first, c->alpha, c->alphabar, lga, lgab, c->d_lg_terms, p);
         LDA_HIP(c, hipGetLastError());
-        if ((rc = sum_partials(c, d_partial, (size_t)c->n_long, h, h_cap, &part)) != LDA_OK) return rc;
-        doc += part;
     }
-    {
-        const int blocks = 4096;
-        const int64_t dense_rows = c->hybrid ? c->H : c->V;
-        if (dense_rows > 0) {
-            hipLaunchKernelGGL(loglik_word_kernel, dim3(blocks), dim3(256), 0, c->stream, c->d_nkw,
-                               dense_rows * (int64_t)c->K, c->beta, lgb, d_partial);
-            LDA_HIP(c, hipGetLastError());
-            if ((rc = sum_partials(c, d_partial, blocks, h, h_cap, &part)) != LDA_OK) return rc;
-            word += part;
-        }
-        if (c->hybrid && c->n_sparse > 0) {
-            hipLaunchKernelGGL(loglik_sparse_kernel, dim3(blocks), dim3(256), 0, c->stream,
-                               c->d_sparse_words, c->n_sparse, c->d_sp_off, c->d_sp_count,
-                               c->d_sp_nnz, c->beta, lgb, d_partial);
-            LDA_HIP(c, hipGetLastError());
-            if ((rc = sum_partials(c, d_partial, blocks, h, h_cap, &part)) != LDA_OK) return rc;
-            word += part;
-        }
-        const int kb = 64;
-        hipLaunchKernelGGL(loglik_nk_kernel, dim3(kb), dim3(256), 0, c->stream, c->d_nk, c->K,
-                           c->betabar, lgbb, d_partial);
+    const double* beta_terms = c->d_lg_terms + kTermTable;
+    const int64_t dense_rows = c->hybrid ? c->H : c->V;
+    if (dense_rows > 0) {
+        if (!(p = parts.take(kWordBlocks, &word, &rc))) return rc;
+        hipLaunchKernelGGL(loglik_word_kernel, dim3(kWordBlocks), dim3(256), 0, c->stream, c->d_nkw,
+                           dense_rows * (int64_t)c->K, c->beta, lgb, beta_terms, p);
         LDA_HIP(c, hipGetLastError());
-        if ((rc = sum_partials(c, d_partial, kb, h, h_cap, &part)) != LDA_OK) return rc;
-        word += part;
     }
+    if (c->hybrid && c->n_sparse > 0) {
+        if (!(p = parts.take(kWordBlocks, &word, &rc))) return rc;
+        hipLaunchKernelGGL(loglik_sparse_kernel, dim3(kWordBlocks), dim3(256), 0, c->stream,
+                           c->d_sparse_words, c->n_sparse, c->d_sp_off, c->d_sp_count,
+                           c->d_sp_nnz, c->beta, lgb, beta_terms, p);
+        LDA_HIP(c, hipGetLastError());
+    }
+    if (!(p = parts.take(kNkBlocks, &word, &rc))) return rc;
+    hipLaunchKernelGGL(loglik_nk_kernel, dim3(kNkBlocks), dim3(256), 0, c->stream, c->d_nk, c->K,
+                       c->betabar, lgbb, p);
+    LDA_HIP(c, hipGetLastError());
+    if ((rc = parts.finish()) != LDA_OK) return rc;
     *doc_part = doc;
     *word_part = word;
     return LDA_OK;
 }
 
 }  // namespace
+
+// largest number of partial sums one log-likelihood has
+size_t loglik_partials(const lda_ctx* c)
+{
+    return (size_t)c->n_chunks + (size_t)c->n_long + 2 * kWordBlocks + kNkBlocks;
+}
+
+// the term tables of alpha and beta
+int setup_loglik(lda_ctx* c)
+{
+    LDA_ALLOC(c, &c->d_lg_terms, 2 * kTermTable, "log-likelihood terms");
+    const double a[2] = {c->alpha, c->beta};
+    for (int i = 0; i < 2; ++i) {
+        hipLaunchKernelGGL(term_table_kernel, dim3(kTermTable / 256), dim3(256), 0, c->stream, a[i],
+                           lgamma(a[i]), c->d_lg_terms + i * kTermTable);
+        LDA_HIP(c, hipGetLastError());
+    }
+    return LDA_OK;
+}
 
 // doc part of the tiles the context's token arrays are bound to: partial[tile]
 int launch_loglik_doc_tiles(lda_ctx* c, double* d_partial)
@@ -275,7 +354,7 @@ int launch_loglik_doc_tiles(lda_ctx* c, double* d_partial)
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     hipLaunchKernelGGL(loglik_doc_tiles_kernel, dim3(c->n_chunks), dim3(c->sweep_block), lds, c->stream,
                        c->d_z, c->d_doff, c->d_chunk_doc, c->d_tokdoc, c->chunk_tokens, c->chunk_docs,
-                       c->alpha, c->alphabar, lga, lgab, d_partial);
+                       c->alpha, c->alphabar, lga, lgab, c->d_lg_terms, d_partial);
     LDA_HIP(c, hipGetLastError());
     return LDA_OK;
 }
@@ -283,7 +362,7 @@ int launch_loglik_doc_tiles(lda_ctx* c, double* d_partial)
 int launch_loglik(lda_ctx* c, double* doc_part, double* word_part)
 {
     std::vector<double> h((size_t)c->n_partial);
-    return run_loglik(c, c->d_partial, h.data(), h.size(), doc_part, word_part);
+    return run_loglik(c, c->d_partial, (size_t)c->n_partial, h.data(), h.size(), doc_part, word_part);
 }
 
 }  // namespace lda
@@ -306,7 +385,7 @@ extern "C" int lda_loglik_noalloc(lda_ctx* c, double* total, double* doc_part, d
     if (rc != LDA_OK) return rc;
     double staging[2048];  // host side: on the stack
     double d = 0.0, w = 0.0;
-    rc = run_loglik(c, scratch, staging, sizeof(staging) / sizeof(staging[0]), &d, &w);
+    rc = run_loglik(c, scratch, kStaticPartials, staging, sizeof(staging) / sizeof(staging[0]), &d, &w);
     if (rc != LDA_OK) return rc;
     if (doc_part) *doc_part = d;
     if (word_part) *word_part = w;
