@@ -51,6 +51,22 @@ def test_ragged_documents_modes_and_K(lda_mod, oracle_mod):
             run(lda_mod, oracle_mod, doff, words, V, K, 0.1, 0.01, [2, 3, 1, 4], mode=mode, seed=V + mode)
 
 
+# lanes to a document: 8 up to K = 1200 or so at these lengths, then 16, 32, 64; beyond 256
+# counters per token of a mean document (24 tokens) no counters; fewer documents take more lanes
+@pytest.mark.parametrize("K,D", [(1, 4200), (7, 4200), (1000, 4200), (1001, 2100), (1300, 4200),
+                                 (3000, 4200), (6001, 4200), (6300, 4200), (33, 100)])
+def test_every_number_of_lanes(lda_mod, oracle_mod, K, D):
+    rng = np.random.default_rng(K)
+    lens = rng.integers(0, 49, D)
+    lens[:12] = (0, 7, 8, 9, 15, 16, 17, 31, 32, 33, 64, 65)
+    doff = np.zeros(D + 1, np.int64)
+    doff[1:] = np.cumsum(lens)
+    V = 61
+    words = rng.integers(0, V, doff[-1]).astype(np.int32)
+    run(lda_mod, oracle_mod, doff, words, V, K, 0.1, 0.01, [2, 4])
+    run(lda_mod, oracle_mod, doff, words, V, K, 0.1, 0.01, [3], mode=2)
+
+
 def test_what_the_mode_refuses(lda_mod):
     cfg = corpus.scaled(corpus.CONFIGS["c1"], D=50)
     doff, words = corpus.make_corpus(cfg)
