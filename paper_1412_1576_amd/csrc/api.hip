@@ -516,6 +516,7 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
     TRY(setup_loglik(c));
     TRY(dev_alloc(c, &c->d_row, (size_t)K, "row staging"));
     TRY(dev_alloc(c, &c->d_flag, 4, "flags"));
+    TRY_HIP(hipMemsetAsync(c->d_flag, 0, sizeof(int32_t) * 4, c->stream));
 
     TRY_HIP(hipMemcpyAsync(c->d_word, word_ids, sizeof(int32_t) * (size_t)N, hipMemcpyHostToDevice,
                            c->stream));

@@ -251,7 +251,7 @@ struct lda_ctx {
     int32_t n_partial = 0;
     double* d_lg_terms = nullptr;      // log-likelihood terms by count: of alpha, then of beta
     int32_t* d_row = nullptr;          // [max(K,1)] row staging for accessors
-    int32_t* d_flag = nullptr;         // [4] validation flags
+    int32_t* d_flag = nullptr;         // [4] validation; recount wanted; sum of a sample (zero between uses)
     // host copies of small layouts
     std::vector<int32_t> h_doff;
 };
