@@ -347,7 +347,7 @@ int launch_sweep(lda_ctx* c, int32_t mh_steps);
 int refresh_sweep_max_doc();
 int launch_sweep_doc_refresh(lda_ctx* c, int32_t mh_steps, int32_t longest_doc);
 // Two-pass sweep (word pass over word-major tokens, doc pass over document tiles)
-bool split_sweep_supported(const lda_ctx* c, int32_t mh_steps);
+bool split_sweep_supported(lda_ctx* c, int32_t mh_steps);
 int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff);
 int launch_sweep_split(lda_ctx* c, int32_t mh_steps);
 int launch_tokdoc(lda_ctx* c);                               // per-token document index in its tile

@@ -349,7 +349,7 @@ __global__ __launch_bounds__(1024) void word_pass_rows_kernel(SplitArgs A)
     const uint32_t capw = A.cap[it.x];
     with_record_layout(A, [&](auto xm, auto p16) {
         // U tokens per thread and round, their loads issued together stage by stage
-        constexpr int U = 4;
+        constexpr int U = C::M <= 4 ? 4 : 2;
         for (int32_t i0 = 0; i0 < it.z; i0 += U * nt) {
             int32_t p[U];
             bool live[U];
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(256) void word_pass_gather_kernel(SplitArgs A)
     __syncthreads();
     if constexpr (STORE == 0) {
         with_record_layout(A, [&](auto xm, auto p16) {
-            constexpr int U = 4;
+            constexpr int U = C::M <= 4 ? 4 : 2;
             for (int32_t i0 = 0; i0 < pc.w; i0 += U * nt) {
                 int32_t p[U], zt[U][1 + ND], out[U][C::R];
                 size_t wk[U];
@@ -487,7 +487,7 @@ __global__ __launch_bounds__(256) void word_pass_gather_kernel(SplitArgs A)
         BetaTable bt{};
         if constexpr (NW > 0) bt = load_beta_table(A);
         with_record_layout(A, [&](auto xm, auto p16) {
-            constexpr int U = 2;
+            constexpr int U = C::M <= 4 ? 2 : 1;
             for (int32_t i0 = 0; i0 < pc.w; i0 += U * nt) {
                 int32_t p[U], w[U], zt[U][1 + ND], out[U][C::R];
                 bool live[U];
@@ -734,84 +734,92 @@ __device__ __forceinline__ void doc_pass_chains(const SplitArgs& A, const DocVie
     // Proposals do not depend on the chain's state, so every step's proposal, its n_kd probe
     // and its n_k gather are issued before the first accept test: one round trip to L2
     // for all of them instead of one per step.
-    uint32_t x2[C::M][T];
-    int32_t t[C::M][T], ndt[C::M][T], nwt[C::M][T], nkt[C::M][T];
+    // Four steps at a time: more would take the registers of a second workgroup per CU.
+    constexpr int B = C::M < 4 ? C::M : 4;
 #pragma unroll
-    for (int j = 0; j < C::M; ++j) {
-        const bool word_step = C::is_word(j);
-        const int i = C::index(j);
+    for (int j0 = 0; j0 < C::M; j0 += B) {
+        uint32_t x2[B][T];
+        int32_t t[B][T], ndt[B][T], nwt[B][T], nkt[B][T];
 #pragma unroll
-        for (int u = 0; u < T; ++u) {
-            if (word_step) {
-                // the record's topic int: the topic, and above it the top bits of x2
-                x2[j][u] = (uint32_t)r[u][C::rec_topic(i)] & ~kHintSpan;
-                t[j][u] = (int32_t)((uint32_t)r[u][C::rec_topic(i)] & kHintSpan);
-                nwt[j][u] = r[u][C::rec_topic(i) + 1];
-                ndt[j][u] = doc[u].count(t[j][u]);
-            } else {
-                uint32_t x[4];
-                philox4x32_10(g[u], 0u, A.sweep, (uint32_t)j, A.seed_lo, A.seed_hi, x);
-                x2[j][u] = x[2];
-                const double u0 = unit_open(x[0]);
-                const double Ld = (double)doc[u].L;
-                if (u0 * (Ld + A.alphabar) < Ld) {
-                    doc[u].token(mulhi32(x[1], (uint32_t)doc[u].L), t[j][u], ndt[j][u]);
+        for (int q = 0; q < B; ++q) {
+            const int j = j0 + q;
+            if (j >= C::M) break;
+            const bool word_step = C::is_word(j);
+            const int i = C::index(j);
+#pragma unroll
+            for (int u = 0; u < T; ++u) {
+                if (word_step) {
+                    // the record's topic int: the topic, and above it the top bits of x2
+                    x2[q][u] = (uint32_t)r[u][C::rec_topic(i)] & ~kHintSpan;
+                    t[q][u] = (int32_t)((uint32_t)r[u][C::rec_topic(i)] & kHintSpan);
+                    nwt[q][u] = r[u][C::rec_topic(i) + 1];
+                    ndt[q][u] = doc[u].count(t[q][u]);
                 } else {
-                    t[j][u] = (int32_t)mulhi32(x[1], (uint32_t)A.K);
-                    ndt[j][u] = doc[u].count(t[j][u]);
-                }
-                nwt[j][u] = r[u][C::rec_doc(i)];
-            }
-            nkt[j][u] = nk[t[j][u]];
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < C::M; ++j) {
-        const bool word_step = C::is_word(j);
-#pragma unroll
-        for (int u = 0; u < T; ++u) {
-            const int32_t tt = t[j][u], nd_t = ndt[j][u], nw_t = nwt[j][u], nk_t = nkt[j][u];
-            const int32_t ms = (s[u] == z0[u]) ? 1 : 0;
-            const int32_t mt = (tt == z0[u]) ? 1 : 0;
-            // Eq. (4) ratio p(t)/p(s), the token removed at its snapshot topic
-            double num = (double)(nd_t - mt) + A.alpha;
-            num = num * ((double)(nw_t - mt) + A.beta);
-            num = num * ((double)(nks[u] - ms) + A.betabar);
-            double den = (double)(nds[u] - ms) + A.alpha;
-            den = den * ((double)(nws[u] - ms) + A.beta);
-            den = den * ((double)(nk_t - mt) + A.betabar);
-            if (word_step) {  // Eq. (8): times p_w(s)/p_w(t)
-                num = num * ((double)nws[u] + A.beta);
-                num = num * ((double)nk_t + A.betabar);
-                den = den * ((double)nw_t + A.beta);
-                den = den * ((double)nks[u] + A.betabar);
-            } else {          // Eq. (11): times p_d(s)/p_d(t)
-                num = num * ((double)nds[u] + A.alpha);
-                den = den * ((double)nd_t + A.alpha);
-            }
-            bool accept;
-            if (word_step) {
-                // x2 is known up to its low bits.  The test is monotone in x2 (a rounded product
-                // of a positive number is monotone), so if both ends of the interval agree the
-                // test is decided; if they differ in any lane, the wave draws the number itself.
-                const bool at_low = unit_open(x2[j][u]) * den < num;
-                const bool at_high = unit_open(x2[j][u] | kHintSpan) * den < num;
-                accept = at_high;
-                if (__any((at_low != at_high) && (tt != s[u]))) {
                     uint32_t x[4];
                     philox4x32_10(g[u], 0u, A.sweep, (uint32_t)j, A.seed_lo, A.seed_hi, x);
-                    accept = unit_open(x[2]) * den < num;
+                    x2[q][u] = x[2];
+                    const double u0 = unit_open(x[0]);
+                    const double Ld = (double)doc[u].L;
+                    if (u0 * (Ld + A.alphabar) < Ld) {
+                        doc[u].token(mulhi32(x[1], (uint32_t)doc[u].L), t[q][u], ndt[q][u]);
+                    } else {
+                        t[q][u] = (int32_t)mulhi32(x[1], (uint32_t)A.K);
+                        ndt[q][u] = doc[u].count(t[q][u]);
+                    }
+                    nwt[q][u] = r[u][C::rec_doc(i)];
                 }
-            } else {
-                accept = unit_open(x2[j][u]) * den < num;
+                nkt[q][u] = nk[t[q][u]];
             }
-            accept = accept && (tt != s[u]);
-            s[u] = accept ? tt : s[u];
-            nds[u] = accept ? nd_t : nds[u];
-            nws[u] = accept ? nw_t : nws[u];
-            nks[u] = accept ? nk_t : nks[u];
         }
-    }
+#pragma unroll
+        for (int q = 0; q < B; ++q) {
+            const int j = j0 + q;
+            if (j >= C::M) break;
+            const bool word_step = C::is_word(j);
+#pragma unroll
+            for (int u = 0; u < T; ++u) {
+                const int32_t tt = t[q][u], nd_t = ndt[q][u], nw_t = nwt[q][u], nk_t = nkt[q][u];
+                const int32_t ms = (s[u] == z0[u]) ? 1 : 0;
+                const int32_t mt = (tt == z0[u]) ? 1 : 0;
+                // Eq. (4) ratio p(t)/p(s), the token removed at its snapshot topic
+                double num = (double)(nd_t - mt) + A.alpha;
+                num = num * ((double)(nw_t - mt) + A.beta);
+                num = num * ((double)(nks[u] - ms) + A.betabar);
+                double den = (double)(nds[u] - ms) + A.alpha;
+                den = den * ((double)(nws[u] - ms) + A.beta);
+                den = den * ((double)(nk_t - mt) + A.betabar);
+                if (word_step) {  // Eq. (8): times p_w(s)/p_w(t)
+                    num = num * ((double)nws[u] + A.beta);
+                    num = num * ((double)nk_t + A.betabar);
+                    den = den * ((double)nw_t + A.beta);
+                    den = den * ((double)nks[u] + A.betabar);
+                } else {          // Eq. (11): times p_d(s)/p_d(t)
+                    num = num * ((double)nds[u] + A.alpha);
+                    den = den * ((double)nd_t + A.alpha);
+                }
+                bool accept;
+                if (word_step) {
+                    // x2 is known up to its low bits.  The test is monotone in x2 (a rounded product
+                    // of a positive number is monotone), so if both ends of the interval agree the
+                    // test is decided; if they differ in any lane, the wave draws the number itself.
+                    const bool at_low = unit_open(x2[q][u]) * den < num;
+                    const bool at_high = unit_open(x2[q][u] | kHintSpan) * den < num;
+                    accept = at_high;
+                    if (__any((at_low != at_high) && (tt != s[u]))) {
+                        uint32_t x[4];
+                        philox4x32_10(g[u], 0u, A.sweep, (uint32_t)j, A.seed_lo, A.seed_hi, x);
+                        accept = unit_open(x[2]) * den < num;
+                    }
+                } else {
+                    accept = unit_open(x2[q][u]) * den < num;
+                }
+                accept = accept && (tt != s[u]);
+                s[u] = accept ? tt : s[u];
+                nds[u] = accept ? nd_t : nds[u];
+                nws[u] = accept ? nw_t : nws[u];
+                nks[u] = accept ? nk_t : nks[u];
+            }
+        }    }
 }
 
 // What a thread holds of its T tokens of one tile before the tile is staged.
@@ -1099,7 +1107,9 @@ template <int NW, int ND>
 int launch_chain(lda_ctx* c, const SplitArgs& A, bool need_proposals)
 {
     int rc;
-    const bool timed = c->opt.time_sweep_passes != 0;
+    // lda_sweep_pass_ms answers for chains of up to four steps
+    const bool timed = c->opt.time_sweep_passes != 0 && NW + ND <= 4;
+    if (!timed) c->pass_ev_recorded = false;
     if (timed) {
         for (hipEvent_t& e : c->pass_ev)
             if (!e) LDA_HIP(c, hipEventCreate(&e));
@@ -1137,10 +1147,16 @@ int launch_chain(lda_ctx* c, const SplitArgs& A, bool need_proposals)
     if (timed) LDA_HIP(c, hipEventRecord(c->pass_ev[1], c->stream));
     if (A.n_chunks > 0) {
         const size_t lds = sizeof(int32_t) * (size_t)A.tile_lds_ints;
-        const int tpt = tokens_per_thread(A);
-        rc = tpt <= 1 ? launch_doc_tiles<NW, ND, 1>(c, A, lds)
-           : tpt <= 2 ? launch_doc_tiles<NW, ND, 2>(c, A, lds)
-                      : launch_doc_tiles<NW, ND, 4>(c, A, lds);
+        if constexpr (NW + ND > 4) {  // one token per thread (split_sweep_supported)
+            rc = c->K <= kNkLdsTopics
+                ? launch_doc_tiles_as<NW, ND, 1, 1024, true>(c, A, lds + sizeof(int32_t) * (size_t)((c->K + 3) / 4 * 4))
+                : launch_doc_tiles_as<NW, ND, 1, 1024, false>(c, A, lds);
+        } else {
+            const int tpt = tokens_per_thread(A);
+            rc = tpt <= 1 ? launch_doc_tiles<NW, ND, 1>(c, A, lds)
+               : tpt <= 2 ? launch_doc_tiles<NW, ND, 2>(c, A, lds)
+                          : launch_doc_tiles<NW, ND, 4>(c, A, lds);
+        }
         if (rc != LDA_OK) return rc;
     }
     if (timed) {
@@ -1176,13 +1192,55 @@ int grow(lda_ctx* c, T** p, size_t* have, size_t need, const char* what)
     return LDA_OK;
 }
 
+// The records of a chain that can also run without them: allocated beside the old ones, which
+// stay as they are if there is no room.
+bool have_split_records(lda_ctx* c, int32_t mh_steps)
+{
+    int32_t nw, nd;
+    chain_shape(c->opt.proposal_mode, mh_steps, nw, nd);
+    const size_t zt = (size_t)c->N << zt_record_shift(nd, c->zt_pack16);
+    const size_t rec = (size_t)c->N << pow2_shift(1 + 2 * nw + nd);
+    if (c->zt_ints >= zt && c->rec_ints >= rec) return true;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return false;  // no allocation into a graph
+    }
+    int32_t *new_zt = nullptr, *new_rec = nullptr;
+    const bool ok = (c->zt_ints >= zt || device_malloc(c, &new_zt, zt, "word-major records") == LDA_OK) &&
+                    (c->rec_ints >= rec || device_malloc(c, &new_rec, rec, "word-pass records") == LDA_OK);
+    if (!ok) {
+        (void)hipGetLastError();
+        if (new_zt) device_free(c, new_zt);
+        return false;
+    }
+    if (new_zt) {
+        device_free(c, c->d_zt);
+        c->d_zt = new_zt;
+        c->zt_ints = zt;
+        c->zt_current = false;
+        c->td_valid = false;
+    }
+    if (new_rec) {
+        device_free(c, c->d_rec);
+        c->d_rec = new_rec;
+        c->rec_ints = rec;
+    }
+    return true;
+}
+
 }  // namespace
 
 // Chains of 1..4 steps in the cycle mode (and the one-step word chain), tiles of at most
-// 4 tokens per thread; everything else runs the fused kernel.
-bool split_sweep_supported(const lda_ctx* c, int32_t mh_steps)
+// 4 tokens per thread; chains of 5..8 steps with the default tiles, one token per thread, if their
+// records (32 or 64 bytes per token) can be had; everything else runs the fused kernel.
+// Sweep of 8 steps, 2 * 10^7 tokens, K = 1000: 3.55 ms fused, 2.17 ms in two passes.
+bool split_sweep_supported(lda_ctx* c, int32_t mh_steps)
 {
-    if (mh_steps < 1 || mh_steps > 4) return false;
+    if (mh_steps < 1 || mh_steps > 8) return false;
+    if (mh_steps > 4)
+        return c->opt.proposal_mode == 0 && c->n_chunks2 > 0 && c->chunk_tokens <= 1024 &&
+               have_split_records(c, mh_steps);
     if (c->opt.proposal_mode == 2 || (c->opt.proposal_mode == 1 && mh_steps != 1)) return false;
     return (c->chunk_tokens + c->sweep_block - 1) / c->sweep_block <= 4;
 }
@@ -1317,6 +1375,10 @@ int launch_sweep_split(lda_ctx* c, int32_t mh_steps)
     else if (nw == 1 && nd == 1) rc = launch_chain<1, 1>(c, A, !have);
     else if (nw == 2 && nd == 1) rc = launch_chain<2, 1>(c, A, !have);
     else if (nw == 2 && nd == 2) rc = launch_chain<2, 2>(c, A, !have);
+    else if (nw == 3 && nd == 2) rc = launch_chain<3, 2>(c, A, !have);
+    else if (nw == 3 && nd == 3) rc = launch_chain<3, 3>(c, A, !have);
+    else if (nw == 4 && nd == 3) rc = launch_chain<4, 3>(c, A, !have);
+    else if (nw == 4 && nd == 4) rc = launch_chain<4, 4>(c, A, !have);
     else rc = fail(c, LDA_ERR_UNSUPPORTED, "two-pass sweep: chain of %d word and %d doc steps", nw, nd);
     if (rc != LDA_OK) return rc;
     // the doc pass left (new z, doc proposals of the next sweep) in the records

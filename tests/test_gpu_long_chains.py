@@ -1,0 +1,97 @@
+"""Chains of 5 to 8 steps: in two passes where their records can be had, otherwise (and beyond 8
+steps) in one; against the oracle, bit for bit, in every store and in turn with other chains."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lda_mod():
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_1412_1576_amd import lda
+    lda.load_library()
+    return lda
+
+
+def make(V, seed, docs=150):
+    rng = np.random.default_rng(seed)
+    # around a tile, longer than one (a document of its own workgroup), empty ones
+    lens = [0, 1024, 3, 1025, 1, 0, 1023, 2500, 512, 63] + list(rng.integers(0, 130, docs)) + [0]
+    doff = np.zeros(len(lens) + 1, np.int64)
+    doff[1:] = np.cumsum(lens)
+    p = 1.0 / np.arange(1, V + 1)
+    return doff, rng.choice(V, int(doff[-1]), p=p / p.sum()).astype(np.int32)
+
+
+def pair(lda_mod, oracle_mod, doff, words, V, K, **opt):
+    g = lda_mod.Lda(doff, words, V, K, 0.1, 0.01, seed=5, **opt)
+    o = oracle_mod.Oracle(doff, words, V, K, 0.1, 0.01, seed=5,
+                          dense_alias_min_count=opt.get("dense_alias_min_count", 0))
+    return g, o
+
+
+def sweep_both(g, o, m):
+    g.build_alias(); o.build_alias()
+    g.sweep(m); o.sweep(m)
+    g.rebuild_counts(); o.rebuild_counts()
+    assert np.array_equal(g.get_z(), o.get_z()), m
+    assert np.array_equal(g.get_nk(), o.get_nk()), m
+
+
+# rows staged in LDS and gathered (dense), staged and gathered mixture rows, rows beyond LDS, no
+# dense rows, n_k gathered (K > 16384), topics of more than 16 bits
+@pytest.mark.parametrize("V,K,dense_rows", [(90, 33, 0), (300, 1000, 300), (40, 13000, 25),
+                                            (90, 17001, -1), (40, 66000, 3)])
+@pytest.mark.parametrize("m", [5, 6, 7, 8])
+def test_steps_and_stores(lda_mod, oracle_mod, V, K, dense_rows, m):
+    doff, words = make(V, 10 * m + V)
+    cnt = np.bincount(words, minlength=V)
+    opt = {}
+    if dense_rows:
+        tail = cnt[max(dense_rows, 0):]
+        opt = {"dense_rows": dense_rows, "dense_alias_min_count": int(tail.max()) + 1 if len(tail) else 400}
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K, **opt)
+    for steps in (m, m, 2, m, 9, m):
+        sweep_both(g, o, steps)
+    g.close(); o.close()
+
+
+def test_record_buckets(lda_mod, oracle_mod):
+    doff, words = make(50, 3)
+    g, o = pair(lda_mod, oracle_mod, doff, words, 50, 70, record_bucket_tokens=512)
+    for steps in (8, 7, 8, 5, 6):
+        sweep_both(g, o, steps)
+    g.close(); o.close()
+
+
+def test_no_room_for_the_records(lda_mod, oracle_mod):
+    """An allocator that refuses the records of a long chain, the first or the second of them: the
+    sweep runs without them, and what was there before stays usable."""
+    doff, words = make(50, 4, docs=600)
+    left, live = [1 << 60], set()
+
+    def alloc(nbytes):
+        if nbytes > left[0]:
+            return 0
+        p = torch.cuda.caching_allocator_alloc(nbytes, 0)
+        live.add(p)
+        return p
+
+    def free(p):
+        live.remove(p)
+        torch.cuda.synchronize()
+        torch.cuda.caching_allocator_delete(p)
+
+    g, o = pair(lda_mod, oracle_mod, doff, words, 50, 64, dev_alloc=alloc, dev_free=free)
+    N = int(doff[-1])
+    sweep_both(g, o, 2)
+    for limit in (N, 20 * N, 1 << 60):
+        left[0] = limit
+        n = len(live)
+        for steps in (8, 2, 6):
+            sweep_both(g, o, steps)
+        assert len(live) == n
+    g.close(); o.close()
+    assert not live
