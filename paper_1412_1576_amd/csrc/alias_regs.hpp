@@ -3,9 +3,9 @@
 // entries in registers from the first read of the counts to the stores, and pairs the two
 // lists by merging them instead of by a search per entry.
 //
-//   1  quantise: q0 of the lane's entries, sum over the workgroup
-//   2  C and pad; number of lights, their deficit and the heavies' excess per wave
-//   3  the two ascending lists with their running sums, in LDS (prefix sums within a wave)
+//   1  quantise: q0 of the thread's entries, sum over the workgroup
+//   2  C and pad; the masses, number of lights, their deficit and the heavies' excess
+//   3  the two ascending lists with their running sums, in LDS (prefix sums)
 //   4  merge: light a precedes heavy b exactly when Delta_a < X_b.  A thread takes a run of
 //      consecutive positions of the merged order, finds its start by one bisection along the
 //      diagonal and then advances one list or the other per step.  What an entry needs is the
@@ -15,11 +15,12 @@
 // LDS: 12 bytes per entry (8 of running sums, 2 for the heavies' entries, 2 for the result of
 // the merge).
 //
-// What bounds it: instruction issue and LDS round trips, not memory (about 200 vector
-// instructions per 64 entries; at K = 10 000 one workgroup per CU keeps the vector units busy
-// for 54 % of the time).  Against the form that searched the partner of every entry and kept
-// the quantised weights in LDS: 10^5 tables of 1000 bins 2.49 -> 0.63 ms (2 GB written and read:
-// 3.2 TB/s), 30 000 of 333 bins 247 -> 84 us, 141 000 of 10 000 bins 20.0 -> 13.9 ms (2 TB/s).
+// What bounds it: instruction issue and LDS round trips, not memory.  Tables of K = 10 000, one
+// workgroup per CU, 141 000 of them: 20.0 ms when the partner of every entry was searched and the
+// weights were kept in LDS, 13.9 ms with the merge and a scan for every 64 entries in steps 2 to 5
+// (vector units busy for 54 % of the time), 11.2 ms with a run of entries per thread there (2.5
+// TB/s).  30 000 tables of 333 bins: 247, 84, 71 us; the lists of a K = 1000 corpus (257 to 1024
+// entries) 83 -> 68 us for the last change.
 // Four waves per table of 1000 bins, not sixteen: eight tables per CU overlap their phases.
 #pragma once
 
@@ -48,16 +49,210 @@ __device__ __forceinline__ uint64_t wave_total_u64(uint64_t v)
     return readlane_u64(wave_inclusive_scan_u64(v), kWave - 1);
 }
 
-// Builds one table of n entries, n <= E * (threads that build it).  ONE: the table is built by
-// one wave (n <= 64 E) and no workgroup barrier is used, so the waves of a workgroup can build
-// tables of their own; otherwise all threads of the workgroup build it.  lists:
-// alias_regs_lds_bytes(n) bytes, 8-byte aligned.  Src: Raw load(k), void load2(Raw&) for what
-// is addressed by the first load, uint64_t q0(Raw).  Sink: Loaded load(k, alias, raw),
-// store(k, split, alias, raw, loaded), once per entry.  Returns the pre-shift sum Q0 and the
-// capacity C.
-// A workgroup that builds another table in the same LDS synchronises first.
-template <int E, bool ONE, class Src, class Sink>
-__device__ __forceinline__ void build_table_regs(int32_t n, const Src& src, const Sink& sink,
+// The workgroup's form: all its threads build one table of n <= E * threads entries.  Entries are
+// read and written in lane order (coalesced), but steps 2, 3 and 5 work on a run of consecutive
+// entries per thread: the prefix sums are then additions in a thread and one scan over the wave
+// instead of a scan for every 64 entries.  The masses and the results change between the two
+// orders through the LDS that holds the running sums before and after.
+template <int E, class Src, class Sink>
+__device__ __forceinline__ void build_table_workgroup(int32_t n, const Src& src, const Sink& sink,
+                                                      unsigned char* lists, uint64_t& Q0_out,
+                                                      uint32_t& C_out)
+{
+    // dx[0..A]   : Delta_a (exclusive deficit sums of the lights, dx[A] = total)
+    // dx[n-b]    : X_b     (inclusive excess sums of the heavies), b = 0..B-1, A + B = n
+    uint64_t* const dx = reinterpret_cast<uint64_t*>(lists);
+    uint16_t* const hidx = reinterpret_cast<uint16_t*>(dx + (n + 1));  // entry of heavy b
+    uint16_t* const pq = hidx + n;  // [a]: b(a) of light a; [n-1-b]: a(b) of heavy b
+    __shared__ uint64_t w_a[kMaxWaves], w_b[kMaxWaves], w_q[kMaxWaves], w_q2[kMaxWaves];
+    __shared__ uint32_t w_c[kMaxWaves];
+
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int nw = (int)(blockDim.x >> 6);
+    const int32_t T = (int32_t)blockDim.x, t = (int32_t)threadIdx.x;
+    // entries of a thread: an odd number where it fits, which spreads the threads' accesses over
+    // the LDS banks
+    const int32_t per = (n + T - 1) / T;
+    const int32_t R = (per | 1) <= E ? (per | 1) : per;
+    const int32_t r0 = t * R;
+    const int32_t rn = r0 >= n ? 0 : (n - r0 < R ? n - r0 : R);
+
+    // 1: the loads of all entries of a thread are in flight together
+    typename Src::Raw raw[E];
+    uint64_t m[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int32_t k = e * T + t;
+        raw[e] = src.load(k < n ? k : n - 1);
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) src.load2(raw[e]);
+    uint64_t p0 = 0, p1 = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int32_t k = e * T + t;
+        if (k < n) {
+            const uint64_t q = src.q0(raw[e]);
+            dx[k] = q;
+            p0 += q;
+            p1 += q < 1 ? 1 : q;
+        }
+    }
+    uint64_t Q0 = wave_total_u64(p0), Q = wave_total_u64(p1);
+    if (lane == 0) { w_a[wv] = Q0; w_q[wv] = Q; }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e) m[e] = e < rn ? dx[r0 + e] : 0ull;
+    Q0 = Q = 0;
+    for (int i = 0; i < nw; ++i) { Q0 += w_a[i]; Q += w_q[i]; }
+    int sh = 0;
+    while ((Q0 >> sh) >= ((uint64_t)n << 31)) ++sh;
+    if (sh > 0) {  // uniform
+        p1 = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            m[e] >>= sh;
+            if (e < rn) p1 += m[e] < 1 ? 1 : m[e];
+        }
+        Q = wave_total_u64(p1);
+        if (lane == 0) w_q2[wv] = Q;
+        __syncthreads();
+        Q = 0;
+        for (int i = 0; i < nw; ++i) Q += w_q2[i];
+    }
+    // ceil(Q / n) through fp64: Q + n < 2^53, and a quotient below 2^32 that is not a whole
+    // number is at least 1/n > 2^-20 away from the next one, more than its rounding error
+    const uint64_t C = (uint64_t)((double)(Q + (uint64_t)n - 1) / (double)n);
+    const uint64_t pad = (uint64_t)n * C - Q;
+
+    // 2: masses; lights, deficit and excess of the thread's run, and of all runs before it
+    uint32_t lc = 0;
+    uint64_t df = 0, ex = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        if (e < rn) {
+            if (m[e] < 1) m[e] = 1;
+            if ((uint64_t)(r0 + e) < pad) m[e] += 1;
+            const bool light = m[e] < C;
+            lc += light ? 1u : 0u;
+            df += light ? C - m[e] : 0ull;
+            ex += light ? 0ull : m[e] - C;
+        }
+    }
+    const uint32_t lc_inc = wave_inclusive_scan_u32(lc);
+    const uint64_t df_inc = wave_inclusive_scan_u64(df), ex_inc = wave_inclusive_scan_u64(ex);
+    __syncthreads();  // w_a of step 1 is no longer read, and neither are the weights in dx
+    if (lane == kWave - 1) { w_a[wv] = df_inc; w_b[wv] = ex_inc; w_c[wv] = lc_inc; }
+    __syncthreads();
+    uint32_t a0 = lc_inc - lc, A = 0;
+    uint64_t d0 = df_inc - df, x0 = ex_inc - ex, d_tot = 0;
+    for (int i = 0; i < nw; ++i) {
+        if (i < wv) { a0 += w_c[i]; d0 += w_a[i]; x0 += w_b[i]; }
+        A += w_c[i];
+        d_tot += w_a[i];
+    }
+    if (t == 0) dx[A] = d_tot;
+
+    // 3: the lists
+    uint32_t a_run = a0, b_run = (uint32_t)(r0 < n ? r0 : n) - a0;
+    const uint32_t b0 = b_run;
+    uint64_t d_run = d0, x_run = x0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        if (e < rn) {
+            const bool light = m[e] < C;
+            const uint64_t x_inc = x_run + (m[e] - C);
+            dx[light ? a_run : (uint32_t)n - b_run] = light ? d_run : x_inc;
+            if (!light) hidx[b_run] = (uint16_t)(r0 + e);
+            d_run += light ? C - m[e] : 0ull;
+            x_run = light ? x_run : x_inc;
+            a_run += light ? 1u : 0u;
+            b_run += light ? 0u : 1u;
+        }
+    }
+    __syncthreads();
+
+    // 4: merge.  An odd number of positions per thread, as above.  The ends need no test: dx[A] is
+    // the total of both lists, so past the lights no heavy is preceded by "light A", and
+    // "heavy B" (also dx[n-B] = dx[A]) precedes no light.
+    {
+        const int32_t B = n - (int32_t)A;
+        const int32_t Em = per | 1;
+        const int32_t q0 = t * Em;
+        const int32_t q1 = q0 + Em < n ? q0 + Em : n;
+        if (q0 < n) {
+            int32_t lo = q0 > B ? q0 - B : 0, hi = q0 < (int32_t)A ? q0 : (int32_t)A;
+            while (lo < hi) {
+                const int32_t mid = (lo + hi) >> 1;
+                if (dx[mid] < dx[n - (q0 - 1 - mid)]) lo = mid + 1; else hi = mid;
+            }
+            int32_t a = lo, b = q0 - lo;
+            uint64_t da = dx[a], xb = dx[n - b];
+            for (int32_t q = q0; q < q1; ++q) {
+                const bool lt = da < xb;
+                pq[lt ? a : n - 1 - b] = (uint16_t)(lt ? b : a);
+                a += lt ? 1 : 0;
+                b += lt ? 0 : 1;
+                const uint64_t v = dx[lt ? a : n - b];
+                da = lt ? v : da;
+                xb = lt ? xb : v;
+            }
+        }
+    }
+    __syncthreads();
+
+    // 5: output, brought back into lane order
+    a_run = a0;
+    b_run = b0;
+    x_run = x0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        if (e < rn) {
+            const bool light = m[e] < C;
+            x_run += light ? 0ull : m[e] - C;
+            const uint32_t other = pq[light ? a_run : (uint32_t)n - 1 - b_run];
+            uint32_t split, al;
+            if (light) {
+                split = (uint32_t)m[e];
+                al = hidx[other];
+            } else {
+                const uint64_t sp = C + x_run - dx[other];
+                split = (uint32_t)sp;
+                al = sp < C ? hidx[b_run + 1] : (uint32_t)(r0 + e);
+            }
+            a_run += light ? 1u : 0u;
+            b_run += light ? 0u : 1u;
+            m[e] = ((uint64_t)al << 32) | split;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (e < rn) dx[r0 + e] = m[e];
+    __syncthreads();
+    typename Sink::Loaded got[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int32_t k = e * T + t;
+        if (k < n) {
+            m[e] = dx[k];
+            got[e] = sink.load(k, (uint32_t)(m[e] >> 32), raw[e]);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int32_t k = e * T + t;
+        if (k < n) sink.store(k, (uint32_t)m[e], (uint32_t)(m[e] >> 32), raw[e], got[e]);
+    }
+    Q0_out = Q0;
+    C_out = (uint32_t)C;
+}
+
+// One wave's form: entry e * 64 + lane is in the lane's registers throughout, so lists and results
+// need no change of order; the prefix sums are scans over the wave, 64 entries at a time.
+template <int E, class Src, class Sink>
+__device__ __forceinline__ void build_table_wave(int32_t n, const Src& src, const Sink& sink,
                                                  unsigned char* lists, uint64_t& Q0_out,
                                                  uint32_t& C_out)
 {
@@ -66,25 +261,15 @@ __device__ __forceinline__ void build_table_regs(int32_t n, const Src& src, cons
     uint64_t* const dx = reinterpret_cast<uint64_t*>(lists);
     uint16_t* const hidx = reinterpret_cast<uint16_t*>(dx + (n + 1));  // entry of heavy b
     uint16_t* const pq = hidx + n;  // [a]: b(a) of light a; [n-1-b]: a(b) of heavy b
-    __shared__ uint64_t w_a[ONE ? 1 : kMaxWaves], w_b[ONE ? 1 : kMaxWaves], w_q[ONE ? 1 : kMaxWaves];
-    __shared__ uint32_t w_c[ONE ? 1 : kMaxWaves];
 
     const int lane = threadIdx.x & (kWave - 1);
-    const int wv = ONE ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int nw = ONE ? 1 : (int)(blockDim.x >> 6);
-    const int32_t S = (((n + nw - 1) / nw + kWave - 1) / kWave) * kWave;  // entries per wave
-    const int32_t kb = wv * S;
-    const int32_t ke = (kb + S < n) ? kb + S : n;  // may lie below kb: a wave without entries
-    auto sync = [&]() {
-        if constexpr (ONE) wave_lds_order(); else __syncthreads();
-    };
 
     // 1: the loads of all entries of a lane are in flight together
     typename Src::Raw raw[E];
     uint64_t m[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const int32_t k = kb + e * kWave + lane;
+        const int32_t k = e * kWave + lane;
         raw[e] = src.load(k < n ? k : n - 1);
     }
 #pragma unroll
@@ -93,18 +278,12 @@ __device__ __forceinline__ void build_table_regs(int32_t n, const Src& src, cons
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         m[e] = src.q0(raw[e]);
-        if (kb + e * kWave + lane < ke) {
+        if (e * kWave + lane < n) {
             p0 += m[e];
             p1 += m[e] < 1 ? 1 : m[e];
         }
     }
     uint64_t Q0 = wave_total_u64(p0), Q = wave_total_u64(p1);
-    if constexpr (!ONE) {
-        if (lane == 0) { w_a[wv] = Q0; w_q[wv] = Q; }
-        __syncthreads();
-        Q0 = Q = 0;
-        for (int i = 0; i < nw; ++i) { Q0 += w_a[i]; Q += w_q[i]; }
-    }
     int sh = 0;
     while ((Q0 >> sh) >= ((uint64_t)n << 31)) ++sh;
     if (sh > 0) {  // uniform
@@ -112,63 +291,41 @@ __device__ __forceinline__ void build_table_regs(int32_t n, const Src& src, cons
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             m[e] >>= sh;
-            if (kb + e * kWave + lane < ke) p1 += m[e] < 1 ? 1 : m[e];
+            if (e * kWave + lane < n) p1 += m[e] < 1 ? 1 : m[e];
         }
         Q = wave_total_u64(p1);
-        if constexpr (!ONE) {
-            __syncthreads();
-            if (lane == 0) w_q[wv] = Q;
-            __syncthreads();
-            Q = 0;
-            for (int i = 0; i < nw; ++i) Q += w_q[i];
-        }
     }
     // ceil(Q / n) through fp64: Q + n < 2^53, and a quotient below 2^32 that is not a whole
     // number is at least 1/n > 2^-20 away from the next one, more than its rounding error
     const uint64_t C = (uint64_t)((double)(Q + (uint64_t)n - 1) / (double)n);
     const uint64_t pad = (uint64_t)n * C - Q;
 
-    // 2: masses and per-wave totals
+    // 2: masses, the lights and their deficit
     uint32_t lc = 0;
-    uint64_t df = 0, ex = 0;
+    uint64_t df = 0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const int32_t k = kb + e * kWave + lane;
+        const int32_t k = e * kWave + lane;
         if (m[e] < 1) m[e] = 1;
         if ((uint64_t)k < pad) m[e] += 1;
-        const bool valid = k < ke;
+        const bool valid = k < n;
         const bool light = valid && m[e] < C;
         lc += (uint32_t)__popcll(__ballot(light));
         if (light) df += C - m[e];
-        else if (valid) ex += m[e] - C;
     }
     df = wave_total_u64(df);
-    ex = wave_total_u64(ex);
-    uint32_t a_run = 0, A = lc;
-    uint64_t d_run = 0, x_run = 0, d_tot = df;
-    if constexpr (!ONE) {
-        __syncthreads();  // w_a of step 1 is no longer read
-        if (lane == 0) { w_a[wv] = df; w_b[wv] = ex; w_c[wv] = lc; }
-        __syncthreads();
-        A = 0;
-        d_tot = 0;
-        for (int i = 0; i < nw; ++i) {
-            if (i < wv) { a_run += w_c[i]; d_run += w_a[i]; x_run += w_b[i]; }
-            A += w_c[i];
-            d_tot += w_a[i];
-        }
-    }
-    if (lane == 0 && wv == 0) dx[A] = d_tot;
-    const uint32_t a_wave = a_run;
+    const uint32_t A = lc;
+    uint32_t a_run = 0;
+    uint64_t d_run = 0, x_run = 0;
+    if (lane == 0) dx[A] = df;
 
     // 3: the lists
-    uint32_t b_run = (uint32_t)(kb < n ? kb : n) - a_run;
-    const uint32_t b_wave = b_run;
+    uint32_t b_run = 0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const int32_t k0 = kb + e * kWave;
-        if (k0 < ke) {  // uniform over the wave
-            const bool valid = k0 + lane < ke;
+        const int32_t k0 = e * kWave;
+        if (k0 < n) {  // uniform over the wave
+            const bool valid = k0 + lane < n;
             const bool light = valid && m[e] < C;
             const bool heavy = valid && !light;
             const uint64_t lmask = __ballot(light), hmask = __ballot(heavy);
@@ -191,17 +348,15 @@ __device__ __forceinline__ void build_table_regs(int32_t n, const Src& src, cons
             b_run += (uint32_t)__popcll(hmask);
         }
     }
-    sync();
+    wave_lds_order();
 
     // 4: merge.  An odd number of positions per thread spreads the threads' reads over the LDS
     // banks.  The ends need no test: dx[A] is the total of both lists, so past the lights no
     // heavy is preceded by "light A", and "heavy B" (also dx[n-B] = dx[A]) precedes no light.
     {
-        const int32_t T = ONE ? kWave : (int32_t)blockDim.x;
-        const int32_t t = ONE ? lane : (int32_t)threadIdx.x;
         const int32_t B = n - (int32_t)A;
-        const int32_t Em = ((n + T - 1) / T) | 1;
-        const int32_t q0 = t * Em;
+        const int32_t Em = ((n + kWave - 1) / kWave) | 1;
+        const int32_t q0 = lane * Em;
         const int32_t q1 = q0 + Em < n ? q0 + Em : n;
         if (q0 < n) {
             int32_t lo = q0 > B ? q0 - B : 0, hi = q0 < (int32_t)A ? q0 : (int32_t)A;
@@ -222,19 +377,19 @@ __device__ __forceinline__ void build_table_regs(int32_t n, const Src& src, cons
             }
         }
     }
-    sync();
+    wave_lds_order();
 
     // 5: output
     uint32_t split[E], al[E];
-    a_run = a_wave;
-    b_run = b_wave;
+    a_run = 0;
+    b_run = 0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         split[e] = al[e] = 0;
-        const int32_t k0 = kb + e * kWave;
-        if (k0 < ke) {
+        const int32_t k0 = e * kWave;
+        if (k0 < n) {
             const int32_t k = k0 + lane;
-            const bool valid = k < ke;
+            const bool valid = k < n;
             const bool light = valid && m[e] < C;
             const uint64_t lmask = __ballot(light);
             const uint32_t la = rank_below(lmask);
@@ -249,22 +404,38 @@ __device__ __forceinline__ void build_table_regs(int32_t n, const Src& src, cons
             }
             const uint32_t nl = (uint32_t)__popcll(lmask);
             a_run += nl;
-            b_run += (uint32_t)((ke - k0 < kWave) ? ke - k0 : kWave) - nl;
+            b_run += (uint32_t)((n - k0 < kWave) ? n - k0 : kWave) - nl;
         }
     }
     typename Sink::Loaded got[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const int32_t k = kb + e * kWave + lane;
-        if (k < ke) got[e] = sink.load(k, al[e], raw[e]);
+        const int32_t k = e * kWave + lane;
+        if (k < n) got[e] = sink.load(k, al[e], raw[e]);
     }
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const int32_t k = kb + e * kWave + lane;
-        if (k < ke) sink.store(k, split[e], al[e], raw[e], got[e]);
+        const int32_t k = e * kWave + lane;
+        if (k < n) sink.store(k, split[e], al[e], raw[e], got[e]);
     }
     Q0_out = Q0;
     C_out = (uint32_t)C;
+}
+
+// Builds one table of n entries, n <= E * (threads that build it): one wave (ONE, n <= 64 E; no
+// workgroup barrier, so the waves of a workgroup can build tables of their own) or the whole
+// workgroup.  lists: alias_regs_lds_bytes(n) bytes, 8-byte aligned.  Src: Raw load(k), void
+// load2(Raw&) for what is addressed by the first load, uint64_t q0(Raw).  Sink: Loaded
+// load(k, alias, raw), store(k, split, alias, raw, loaded), once per entry.  Returns the
+// pre-shift sum Q0 and the capacity C.
+// A workgroup that builds another table in the same LDS synchronises first.
+template <int E, bool ONE, class Src, class Sink>
+__device__ __forceinline__ void build_table_regs(int32_t n, const Src& src, const Sink& sink,
+                                                 unsigned char* lists, uint64_t& Q0_out,
+                                                 uint32_t& C_out)
+{
+    if constexpr (ONE) build_table_wave<E>(n, src, sink, lists, Q0_out, C_out);
+    else build_table_workgroup<E>(n, src, sink, lists, Q0_out, C_out);
 }
 
 }  // namespace lda
