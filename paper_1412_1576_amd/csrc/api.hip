@@ -575,6 +575,11 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
         }
     }
     c->n_tiles = (int32_t)tiles.size();
+    c->n_wide_tiles = (int32_t)(std::stable_partition(tiles.begin(), tiles.end(), [K](const RebuildTile& t) {
+        return !is_wave_tile(K, t);
+    }) - tiles.begin());
+    // one launch where both would not fill the chip (10^5 tokens of 1000 words: 6.6 us in one, 8 in two)
+    if (c->n_tiles - c->n_wide_tiles < kWaveTilesLeast) c->n_wide_tiles = c->n_tiles;
     c->n_multi_words = (int32_t)multi.size();
     TRY(dev_alloc(c, &c->d_tiles, tiles.size(), "rebuild tiles"));
     TRY(dev_alloc(c, &c->d_multi_words, multi.size(), "multi-tile words"));

@@ -166,6 +166,7 @@ struct lda_ctx {
     // rebuild tiling
     lda::RebuildTile* d_tiles = nullptr;
     int32_t n_tiles = 0;
+    int32_t n_wide_tiles = 0;  // a workgroup's each; the short ones after them are a wave's
     int32_t rebuild_tile_tokens = 0;
     int32_t* d_multi_words = nullptr;  // words that own several tiles
     int32_t n_multi_words = 0;
@@ -376,6 +377,8 @@ int launch_ndk_row(lda_ctx* c, int64_t d);                  // dense n_dk row in
 int launch_check_range(lda_ctx* c, const int32_t* d_vals, int64_t n, int32_t lo, int32_t hi,
                        bool* ok);
 int max_alias_topics();    // largest K the dense alias kernel handles
+constexpr int32_t kWaveTilesLeast = 4096;
+bool is_wave_tile(int32_t K, const RebuildTile& t);
 int max_rebuild_topics();  // largest K the count-rebuild tiles handle
 
 // ------------------------------------------------------------------------------------

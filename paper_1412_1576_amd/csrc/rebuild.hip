@@ -53,10 +53,23 @@ __global__ __launch_bounds__(1024) void scatter_wm_kernel(const int32_t* __restr
     }
 }
 
-// blockIdx.x: tile; blockIdx.y: range of `span` topics (one range when the row fits LDS)
-constexpr int32_t kTileRun = 32;  // consecutive tiles of an XCD, at most
+// LDS written by some lanes of a wave is read by others after this
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
-__global__ __launch_bounds__(1024) void nkw_tiles_kernel(const RebuildTile* __restrict__ tiles,
+// blockIdx.x: tile; blockIdx.y: range of `span` topics (one range when the row fits LDS).
+// ONE: four short tiles to a workgroup, each a wave's, which meets no barrier (one range).  With
+// a workgroup to each of 53 975 words of 35 tokens the launches of the workgroups bounded the
+// pass: 76 us.
+constexpr int32_t kTileRun = 32;  // consecutive tiles of an XCD, at most
+constexpr int32_t kWaveTileTokens = 512, kWaveTileTopics = 2048;
+
+template <bool ONE>
+__global__ __launch_bounds__(ONE ? 256 : 1024) void nkw_tiles_kernel(const RebuildTile* __restrict__ tiles,
                                                          int32_t n_tiles, int32_t run,
                                                          const int32_t* __restrict__ zw,
                                                          int32_t sh, uint32_t zmask, int32_t K,
@@ -69,17 +82,22 @@ __global__ __launch_bounds__(1024) void nkw_tiles_kernel(const RebuildTile* __re
                                                          const int32_t* __restrict__ xmap,
                                                          const int32_t* __restrict__ go)
 {
-    extern __shared__ int32_t hist[];
+    extern __shared__ int32_t hist_all[];
     __shared__ uint32_t wcnt[16];
     if (unwanted(go)) return;
     // runs of consecutive tiles (neighbouring words) share an XCD and with it the lines of
     // the records they read
-    const int32_t ti = xcd_runs(run);
-    if (ti >= n_tiles) return;
+    const int wave = ONE ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+    const int32_t ti = ONE ? 4 * xcd_runs(run) + wave : xcd_runs(run);
+    if (ti >= n_tiles) return;  // (ONE: a whole wave leaves, no barrier follows)
+    int32_t* const hist = hist_all + wave * span;
+    auto sync = [&]() {
+        if constexpr (ONE) wave_lds_order(); else __syncthreads();
+    };
     const RebuildTile t = tiles[ti];
     const int32_t k0 = (int32_t)blockIdx.y * span;
     const int32_t nk_r = ((k0 + span < K) ? k0 + span : K) - k0;
-    const int tid = threadIdx.x, nt = blockDim.x;
+    const int tid = ONE ? (int)threadIdx.x & 63 : (int)threadIdx.x, nt = ONE ? 64 : (int)blockDim.x;
     auto count = [&](int32_t rec) {
         const uint32_t r = ((uint32_t)rec & zmask) - (uint32_t)k0;
         if (r < (uint32_t)nk_r) atomicAdd(&hist[r], 1);
@@ -98,7 +116,7 @@ __global__ __launch_bounds__(1024) void nkw_tiles_kernel(const RebuildTile* __re
         for (int u = 0; u < 2; ++u) first[u] = __builtin_nontemporal_load(&zw[q[u] << sh]);
     }
     for (int32_t k = tid; k < nk_r; k += nt) hist[k] = 0;
-    __syncthreads();
+    sync();
 #pragma unroll
     for (int u = 0; u < 2; ++u)
         if (p + u * nt < t.p1) count(first[u]);
@@ -114,7 +132,7 @@ __global__ __launch_bounds__(1024) void nkw_tiles_kernel(const RebuildTile* __re
         for (int u = 0; u < 4; ++u) count(rec[u]);
     }
     for (; p < t.p1; p += nt) count(zw[at(p) << sh]);
-    __syncthreads();
+    sync();
     int32_t* __restrict__ row = nkw + (size_t)t.w * (size_t)K + (size_t)k0;
     if (t.multi == 1) {
         for (int32_t k = tid; k < nk_r; k += nt) {
@@ -137,12 +155,15 @@ __global__ __launch_bounds__(1024) void nkw_tiles_kernel(const RebuildTile* __re
             if (k < kb1 && t.multi == 2) row[k] = v;  // 3: the row is not kept
             cnt += (uint32_t)__popcll(__ballot(v > 0));
         }
-        if (lane == 0) wcnt[wv] = cnt;
-        __syncthreads();
-        uint32_t base = 0, pos = 0;
-        for (int i = 0; i < nw; ++i) {
-            if (i < wv) pos += wcnt[i];
-            base += wcnt[i];
+        uint32_t base = cnt, pos = 0;
+        if constexpr (!ONE) {
+            if (lane == 0) wcnt[wv] = cnt;
+            __syncthreads();
+            base = 0;
+            for (int i = 0; i < nw; ++i) {
+                if (i < wv) pos += wcnt[i];
+                base += wcnt[i];
+            }
         }
         for (int32_t kb = kb0; kb < kb1; kb += 64) {
             const int32_t k = kb + lane;
@@ -304,6 +325,13 @@ __global__ __launch_bounds__(1024) void sample_moved_kernel(const int32_t* __res
 
 int max_rebuild_topics() { return 36 * 1024; }
 
+// Tiles that a wave counts by itself: a single tile of its word with at most kWaveTileTokens
+// tokens, in a row that 64 lanes clear and write in few steps.
+bool is_wave_tile(int32_t K, const RebuildTile& t)
+{
+    return t.multi != 1 && K <= kWaveTileTopics && t.p1 - t.p0 <= kWaveTileTokens;
+}
+
 namespace {
 
 // word-major copy of z, then the dense rows by LDS histograms over topic ranges
@@ -321,19 +349,28 @@ int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
     const int32_t span = (((K + nr - 1) / nr) + 63) / 64 * 64;
     const size_t lds = sizeof(int32_t) * (size_t)span;
     if (lds > 48 * 1024)
-        LDA_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(nkw_tiles_kernel),
+        LDA_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(nkw_tiles_kernel<false>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     if (c->n_multi_words > 0) {
         hipLaunchKernelGGL(zero_rows_kernel, dim3(c->n_multi_words), dim3(256), 0, c->stream,
                            c->d_multi_words, K, c->d_nkw, go);
         LDA_HIP(c, hipGetLastError());
     }
-    const int32_t run = xcd_run_length(c->n_tiles, kTileRun);
-    hipLaunchKernelGGL(nkw_tiles_kernel, dim3(xcd_runs_grid(c->n_tiles, run), (K + span - 1) / span),
-                       dim3(span <= 512 ? 256 : (span <= 16384 ? 512 : 1024)), lds, c->stream, c->d_tiles,
-                       c->n_tiles, run, c->d_zt,
-                       c->zt_shift, c->zt_mask, K, span,
-                       c->d_nkw, c->d_sp_off, c->d_sp_topic, c->d_sp_count, c->d_sp_nnz, c->d_xmap, go);
+    if (c->n_wide_tiles > 0) {
+        const int32_t run = xcd_run_length(c->n_wide_tiles, kTileRun);
+        hipLaunchKernelGGL(nkw_tiles_kernel<false>, dim3(xcd_runs_grid(c->n_wide_tiles, run), nr),
+                           dim3(span <= 512 ? 256 : (span <= 16384 ? 512 : 1024)), lds, c->stream, c->d_tiles,
+                           c->n_wide_tiles, run, c->d_zt, c->zt_shift, c->zt_mask, K, span,
+                           c->d_nkw, c->d_sp_off, c->d_sp_topic, c->d_sp_count, c->d_sp_nnz, c->d_xmap, go);
+    }
+    const int32_t n_short = c->n_tiles - c->n_wide_tiles;
+    if (n_short > 0) {  // (K <= kWaveTileTopics: one range, less than 48 KB for four histograms)
+        const int32_t blocks = (n_short + 3) / 4, run = xcd_run_length(blocks, kTileRun / 4);
+        hipLaunchKernelGGL(nkw_tiles_kernel<true>, dim3(xcd_runs_grid(blocks, run)), dim3(256), 4 * lds,
+                           c->stream, c->d_tiles + c->n_wide_tiles, n_short, run, c->d_zt, c->zt_shift,
+                           c->zt_mask, K, span, c->d_nkw, c->d_sp_off, c->d_sp_topic, c->d_sp_count,
+                           c->d_sp_nnz, c->d_xmap, go);
+    }
     LDA_HIP(c, hipGetLastError());
     return LDA_OK;
 }
