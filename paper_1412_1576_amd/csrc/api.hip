@@ -92,7 +92,7 @@ void free_all(lda_ctx* c)
     dev_free(c, c->d_woff); dev_free(c, c->d_nkw); dev_free(c, c->d_nk);
     dev_free(c, c->d_alias); dev_free(c, c->d_cap); dev_free(c, c->d_chunk_doc); dev_free(c, c->d_chunk_tok); dev_free(c, c->d_tokdoc); dev_free(c, c->d_chunk_doc2); dev_free(c, c->d_chunk_tok2); dev_free(c, c->d_tokdoc2); dev_free(c, c->d_long_doc);
     dev_free(c, c->d_long_slot); dev_free(c, c->d_long_keys); dev_free(c, c->d_long_cnts); dev_free(c, c->d_long_first);
-    dev_free(c, c->d_tiles); dev_free(c, c->d_multi_words); dev_free(c, c->d_partial); dev_free(c, c->d_lg_terms); dev_free(c, c->d_row);
+    dev_free(c, c->d_tiles); dev_free(c, c->d_list_tiles); dev_free(c, c->d_multi_words); dev_free(c, c->d_partial); dev_free(c, c->d_lg_terms); dev_free(c, c->d_row);
     dev_free(c, c->d_flag);
     dev_free(c, c->d_dense_alias_words);
     for (int i = 0; i < kMixClasses; ++i) dev_free(c, c->d_mix_class[i]);
@@ -183,8 +183,7 @@ int upload(lda_ctx* c, T** dst, const std::vector<T>& v, const char* what)
 // pass over the row (needs h_wcount, h_wkind).
 bool list_from_rebuild(const lda_ctx* c, int32_t w)
 {
-    return c->hybrid && (c->h_wkind[w] & 3) == 1 && c->h_wcount[w] <= c->rebuild_tile_tokens &&
-           c->K <= max_rebuild_topics();
+    return c->hybrid && (c->h_wkind[w] & 3) == 1 && c->h_wcount[w] <= c->rebuild_tile_tokens;
 }
 
 // Word classes, list / hash-row offsets, work lists and buffers of the hybrid store.
@@ -559,7 +558,7 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
     }
     TRY(setup_split_sweep(c, woff));
     TRY(dev_alloc(c, &c->d_alias, any_dense_alias ? VK : 1, "alias tables"));
-    std::vector<RebuildTile> tiles;
+    std::vector<RebuildTile> tiles, list_tiles;
     std::vector<int32_t> multi;
     tiles.reserve((size_t)H + 1024);
     for (int32_t w = 0; w < H; ++w) {
@@ -567,7 +566,11 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
         const int32_t limit = hybrid && (c->h_wkind[w] & 2) == 0 ? tile_tokens : dense_tile;
         if (e - b <= limit) {
             const int32_t form = !list_from_rebuild(c, w) ? 0 : ((c->h_wkind[w] & kKindListOnly) ? 3 : 2);
-            tiles.push_back(RebuildTile{w, b, e, form});
+            // rows of several topic ranges that also give a list have a kernel of their own
+            if (form == 2 && K > max_rebuild_topics())
+                list_tiles.push_back(RebuildTile{w, b, e, form});
+            else
+                tiles.push_back(RebuildTile{w, b, e, form});
         } else {
             multi.push_back(w);
             for (int32_t p = b; p < e; p += limit)
@@ -580,6 +583,8 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
     }) - tiles.begin());
     // one launch where both would not fill the chip (10^5 tokens of 1000 words: 6.6 us in one, 8 in two)
     if (c->n_tiles - c->n_wide_tiles < kWaveTilesLeast) c->n_wide_tiles = c->n_tiles;
+    c->n_list_tiles = (int32_t)list_tiles.size();
+    TRY(upload(c, &c->d_list_tiles, list_tiles, "rebuild tiles"));
     c->n_multi_words = (int32_t)multi.size();
     TRY(dev_alloc(c, &c->d_tiles, tiles.size(), "rebuild tiles"));
     TRY(dev_alloc(c, &c->d_multi_words, multi.size(), "multi-tile words"));

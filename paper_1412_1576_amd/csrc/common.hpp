@@ -167,6 +167,8 @@ struct lda_ctx {
     lda::RebuildTile* d_tiles = nullptr;
     int32_t n_tiles = 0;
     int32_t n_wide_tiles = 0;  // a workgroup's each; the short ones after them are a wave's
+    lda::RebuildTile* d_list_tiles = nullptr;  // form 2, of rows of several topic ranges
+    int32_t n_list_tiles = 0;
     int32_t rebuild_tile_tokens = 0;
     int32_t* d_multi_words = nullptr;  // words that own several tiles
     int32_t n_multi_words = 0;

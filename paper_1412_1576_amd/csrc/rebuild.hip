@@ -182,6 +182,130 @@ __global__ __launch_bounds__(ONE ? 256 : 1024) void nkw_tiles_kernel(const Rebui
     }
 }
 
+// Rows of more topics than one LDS histogram, of mixture words of one tile: a workgroup takes the
+// topic ranges of its word one after the other, so that the list of non-zeros comes out of the
+// histograms with the row and no second pass reads the row back.  The topics of a short word are
+// read once and kept in registers.  A histogram takes at most half of the LDS: two workgroups
+// share a CU, and one's barriers are hidden by the other's work.
+//
+// 20 000 rows of 10^5 topics, 10^8 tokens: 2.3 ms for the rows and 2.7 ms for the lists before,
+// 2.5 ms for both.  (Writing only the topics of the previous and the new list, for words with
+// few tokens, gained nothing.)
+constexpr int32_t kListRowSpan = 18432;
+constexpr int kListRowKept = 8;  // topics of a thread kept in registers
+
+__global__ __launch_bounds__(1024, 8) void nkw_list_rows_kernel(
+    const RebuildTile* __restrict__ tiles, int32_t n_tiles, int32_t run, const int32_t* __restrict__ zw,
+    int32_t sh, uint32_t zmask, int32_t K, int32_t span, int32_t* __restrict__ nkw,
+    const uint32_t* __restrict__ sp_off, int32_t* __restrict__ sp_topic, int32_t* __restrict__ sp_count,
+    int32_t* __restrict__ sp_nnz, const int32_t* __restrict__ xmap)
+{
+    extern __shared__ int32_t hist[];  // span counters, a multiple of 64
+    __shared__ uint32_t wcnt[2][16];
+    const int32_t ti = xcd_runs(run);
+    if (ti >= n_tiles) return;
+    const RebuildTile t = tiles[ti];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const size_t off = sp_off[t.w];
+    int32_t* __restrict__ row = nkw + (size_t)t.w * (size_t)K;
+    auto topic_at = [&](int32_t p) {
+        const size_t q = xmap ? (size_t)xmap[p] : (size_t)p;
+        return (uint32_t)__builtin_nontemporal_load(&zw[q << sh]) & zmask;
+    };
+    const bool kept = t.p1 - t.p0 <= 1024 * kListRowKept;
+    uint32_t mine[kListRowKept];
+    if (kept) {
+#pragma unroll
+        for (int e = 0; e < kListRowKept; ++e) {
+            const int32_t p = t.p0 + e * 1024 + tid;
+            mine[e] = p < t.p1 ? topic_at(p) : 0xFFFFFFFFu;  // (beyond every range)
+        }
+    }
+    for (int32_t k = 4 * tid; k < span; k += 4096) *reinterpret_cast<int4*>(&hist[k]) = make_int4(0, 0, 0, 0);
+    const bool aligned = (K & 3) == 0;
+    // every wave owns a contiguous run of a range's topics, four to a lane
+    const int32_t chunk = (((span + 15) / 16) + 255) & ~255;
+    const uint64_t below = (1ull << lane) - 1ull;
+    uint32_t total = 0;  // entries of the ranges done
+    int parity = 0;
+    for (int32_t k0 = 0; k0 < K; k0 += span, parity ^= 1) {
+        const uint32_t nk_r = (uint32_t)((k0 + span < K) ? span : K - k0);
+        __syncthreads();
+        if (kept) {
+#pragma unroll
+            for (int e = 0; e < kListRowKept; ++e) {
+                const uint32_t r = mine[e] - (uint32_t)k0;
+                if (r < nk_r) atomicAdd(&hist[r], 1);
+            }
+        } else {
+            int32_t p = t.p0 + tid;
+            for (; p + 3 * 1024 < t.p1; p += 4 * 1024) {
+                uint32_t z[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) z[u] = topic_at(p + u * 1024) - (uint32_t)k0;
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (z[u] < nk_r) atomicAdd(&hist[z[u]], 1);
+            }
+            for (; p < t.p1; p += 1024) {
+                const uint32_t r = topic_at(p) - (uint32_t)k0;
+                if (r < nk_r) atomicAdd(&hist[r], 1);
+            }
+        }
+        __syncthreads();
+        const int32_t kb0 = wv * chunk, kb1 = (kb0 + chunk < span) ? kb0 + chunk : span;
+        uint32_t cnt = 0;
+        for (int32_t kb = kb0; kb < kb1; kb += 256) {
+            const int32_t k = kb + 4 * lane;
+            int4 v = make_int4(0, 0, 0, 0);
+            if (k < kb1) v = *reinterpret_cast<const int4*>(&hist[k]);
+            if (k < (int32_t)nk_r) {
+                if (aligned) {
+                    *reinterpret_cast<int4*>(&row[k0 + k]) = v;
+                } else {
+                    row[k0 + k] = v.x;
+                    if (k + 1 < (int32_t)nk_r) row[k0 + k + 1] = v.y;
+                    if (k + 2 < (int32_t)nk_r) row[k0 + k + 2] = v.z;
+                    if (k + 3 < (int32_t)nk_r) row[k0 + k + 3] = v.w;
+                }
+            }
+            cnt += (uint32_t)(__popcll(__ballot(v.x > 0)) + __popcll(__ballot(v.y > 0)) +
+                              __popcll(__ballot(v.z > 0)) + __popcll(__ballot(v.w > 0)));
+        }
+        if (lane == 0) wcnt[parity][wv] = cnt;
+        __syncthreads();
+        size_t pos = off + total;
+        for (int i = 0; i < 16; ++i) {
+            const uint32_t n = wcnt[parity][i];
+            if (i < wv) pos += n;
+            total += n;
+        }
+        for (int32_t kb = kb0; kb < kb1; kb += 256) {  // places, and clears for the next range
+            const int32_t k = kb + 4 * lane;
+            int4 v = make_int4(0, 0, 0, 0);
+            if (k < kb1) {
+                v = *reinterpret_cast<const int4*>(&hist[k]);
+                *reinterpret_cast<int4*>(&hist[k]) = make_int4(0, 0, 0, 0);
+            }
+            const uint64_t m0 = __ballot(v.x > 0), m1 = __ballot(v.y > 0),
+                           m2 = __ballot(v.z > 0), m3 = __ballot(v.w > 0);
+            if ((m0 | m1 | m2 | m3) == 0) continue;  // uniform over the wave
+            size_t p = pos + (uint32_t)(__popcll(m0 & below) + __popcll(m1 & below) + __popcll(m2 & below) +
+                                        __popcll(m3 & below));
+            const int32_t c[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (c[u] <= 0) continue;
+                sp_topic[p] = k0 + k + u;
+                sp_count[p] = c[u];
+                ++p;
+            }
+            pos += (uint32_t)(__popcll(m0) + __popcll(m1) + __popcll(m2) + __popcll(m3));
+        }
+    }
+    if (tid == 0) sp_nnz[t.w] = (int32_t)total;
+}
+
 __global__ __launch_bounds__(256) void zero_rows_kernel(const int32_t* __restrict__ words,
                                                         int32_t K, int32_t* __restrict__ nkw,
                                                         const int32_t* __restrict__ go)
@@ -343,6 +467,19 @@ int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
         if (rc != LDA_OK) return rc;
         c->zt_current = !go;  // (the host does not know whether a conditional scatter ran)
         c->td_valid = false;  // any stored doc proposals belong to another assignment
+    }
+    if (c->n_list_tiles > 0) {
+        const int32_t ranges = (K + kListRowSpan - 1) / kListRowSpan;
+        const int32_t part = (((K + ranges - 1) / ranges) + 63) / 64 * 64;
+        const size_t part_lds = sizeof(int32_t) * (size_t)part;
+        LDA_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(nkw_list_rows_kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)part_lds));
+        const int32_t lrun = xcd_run_length(c->n_list_tiles, kTileRun);
+        hipLaunchKernelGGL(nkw_list_rows_kernel, dim3(xcd_runs_grid(c->n_list_tiles, lrun)), dim3(1024),
+                           part_lds, c->stream, c->d_list_tiles, c->n_list_tiles, lrun, c->d_zt, c->zt_shift,
+                           c->zt_mask, K, part, c->d_nkw, c->d_sp_off, c->d_sp_topic, c->d_sp_count,
+                           c->d_sp_nnz, c->d_xmap);
+        LDA_HIP(c, hipGetLastError());
     }
     if (c->n_tiles == 0) return LDA_OK;
     const int32_t nr = (K + max_rebuild_topics() - 1) / max_rebuild_topics();
