@@ -157,7 +157,7 @@ int lda_sweep(lda_ctx* ctx, int32_t mh_steps);
  * kernel that evaluates the word side of the chains, Eq. 6-8, in word-major order),
  * *doc_pass_ms the one kernel that runs the accept tests over the document tiles.
  * Waits for the events.  LDA_ERR_STATE if the option is off, no sweep has run, or the
- * last sweep ran as one fused kernel (more than 4 steps, word-only or doc-only chains of
+ * last sweep had more than 4 steps or ran as one fused kernel (word-only or doc-only chains of
  * several steps, tiles of more than 4 tokens per thread).
  */
 int lda_sweep_pass_ms(lda_ctx* ctx, float* word_pass_ms, float* doc_pass_ms);
