@@ -306,22 +306,25 @@ __global__ __launch_bounds__(1024, 8) void nkw_list_rows_kernel(
     if (tid == 0) sp_nnz[t.w] = (int32_t)total;
 }
 
-__global__ __launch_bounds__(256) void zero_rows_kernel(const int32_t* __restrict__ words,
-                                                        int32_t K, int32_t* __restrict__ nkw,
-                                                        const int32_t* __restrict__ go)
-{
-    if (unwanted(go)) return;
-    int32_t* __restrict__ row = nkw + (size_t)words[blockIdx.x] * (size_t)K;
-    for (int32_t k = threadIdx.x; k < K; k += blockDim.x) row[k] = 0;
-}
+// What the counts below add to: the rows of the words of several tiles, a workgroup each, and
+// after them n_k, kZeroNk topics to a workgroup.  One launch for both: in a corpus of 10^5 tokens
+// a launch is 4 of the 56 us of an iteration.
+constexpr int32_t kZeroNk = 4096;
 
-__global__ __launch_bounds__(256) void fill_i32_kernel(int32_t* __restrict__ p, int64_t n,
-                                                       int32_t v, const int32_t* __restrict__ go)
+__global__ __launch_bounds__(256) void zero_counts_kernel(const int32_t* __restrict__ words, int32_t n_words,
+                                                          int32_t K, int32_t* __restrict__ nkw,
+                                                          int32_t* __restrict__ nk,
+                                                          const int32_t* __restrict__ go)
 {
     if (unwanted(go)) return;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
+    const int32_t i = (int32_t)blockIdx.x;
+    if (i < n_words) {
+        int32_t* __restrict__ row = nkw + (size_t)words[i] * (size_t)K;
+        for (int32_t k = threadIdx.x; k < K; k += blockDim.x) row[k] = 0;
+    } else {
+        const int32_t k0 = (i - n_words) * kZeroNk, k1 = (K - k0 > kZeroNk) ? k0 + kZeroNk : K;
+        for (int32_t k = k0 + threadIdx.x; k < k1; k += blockDim.x) nk[k] = 0;
+    }
 }
 
 constexpr int32_t kNkRangeTopics = 36864;  // 144 KB of LDS counters per workgroup
@@ -458,7 +461,8 @@ bool is_wave_tile(int32_t K, const RebuildTile& t)
 
 namespace {
 
-// word-major copy of z, then the dense rows by LDS histograms over topic ranges
+// word-major copy of z, then the dense rows by LDS histograms over topic ranges; n_k is zeroed for
+// launch_nk_hist
 int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
 {
     const int32_t K = c->K;
@@ -467,6 +471,14 @@ int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
         if (rc != LDA_OK) return rc;
         c->zt_current = !go;  // (the host does not know whether a conditional scatter ran)
         c->td_valid = false;  // any stored doc proposals belong to another assignment
+    }
+    {
+        const int32_t n_nk = K <= 8 * kNkRangeTopics ? (K + kZeroNk - 1) / kZeroNk : 0;
+        const int32_t n_rows = c->n_tiles > 0 ? c->n_multi_words : 0;
+        if (n_rows + n_nk > 0)
+            hipLaunchKernelGGL(zero_counts_kernel, dim3(n_rows + n_nk), dim3(256), 0, c->stream,
+                               c->d_multi_words, n_rows, K, c->d_nkw, c->d_nk, go);
+        LDA_HIP(c, hipGetLastError());
     }
     if (c->n_list_tiles > 0) {
         const int32_t ranges = (K + kListRowSpan - 1) / kListRowSpan;
@@ -488,11 +500,6 @@ int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
     if (lds > 48 * 1024)
         LDA_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(nkw_tiles_kernel<false>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    if (c->n_multi_words > 0) {
-        hipLaunchKernelGGL(zero_rows_kernel, dim3(c->n_multi_words), dim3(256), 0, c->stream,
-                           c->d_multi_words, K, c->d_nkw, go);
-        LDA_HIP(c, hipGetLastError());
-    }
     if (c->n_wide_tiles > 0) {
         const int32_t run = xcd_run_length(c->n_wide_tiles, kTileRun);
         hipLaunchKernelGGL(nkw_tiles_kernel<false>, dim3(xcd_runs_grid(c->n_wide_tiles, run), nr),
@@ -513,12 +520,10 @@ int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
 }
 
 
-// n_k by LDS histograms (K <= 8 * kNkRangeTopics)
+// n_k, zero since launch_dense_rows, by LDS histograms (K <= 8 * kNkRangeTopics)
 int launch_nk_hist(lda_ctx* c, const int32_t* go = nullptr)
 {
     const int32_t K = c->K;
-    hipLaunchKernelGGL(fill_i32_kernel, dim3(64), dim3(256), 0, c->stream, c->d_nk, (int64_t)K, 0, go);
-    LDA_HIP(c, hipGetLastError());
     const int32_t nr = (K + kNkRangeTopics - 1) / kNkRangeTopics;
     const int32_t span = (K + nr - 1) / nr;
     const int64_t blocks = std::min<int64_t>(hist_blocks(c), nr > 1 ? 512 : 2048);
