@@ -178,12 +178,15 @@ int upload(lda_ctx* c, T** dst, const std::vector<T>& v, const char* what)
     return LDA_OK;
 }
 
-// A mixture word with a dense row whose tokens fit one rebuild tile gets its list of
-// non-zeros from the workgroup that histograms the row; the others from a compaction
-// pass over the row (needs h_wcount, h_wkind).
+// A mixture word with a dense row gets its list of non-zeros from the workgroup that
+// histograms the row, if its tokens fit one rebuild tile and, in a row of several topic ranges,
+// one workgroup's registers; the others from a compaction pass over the row (needs h_wcount,
+// h_wkind).
 bool list_from_rebuild(const lda_ctx* c, int32_t w)
 {
-    return c->hybrid && (c->h_wkind[w] & 3) == 1 && c->h_wcount[w] <= c->rebuild_tile_tokens;
+    const int32_t most = c->K <= max_rebuild_topics() ? c->rebuild_tile_tokens
+                                                      : std::min(c->rebuild_tile_tokens, kListRowTokens);
+    return c->hybrid && (c->h_wkind[w] & 3) == 1 && c->h_wcount[w] <= most;
 }
 
 // Word classes, list / hash-row offsets, work lists and buffers of the hybrid store.

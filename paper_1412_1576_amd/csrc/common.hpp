@@ -382,6 +382,8 @@ int max_alias_topics();    // largest K the dense alias kernel handles
 constexpr int32_t kWaveTilesLeast = 4096;
 bool is_wave_tile(int32_t K, const RebuildTile& t);
 int max_rebuild_topics();  // largest K the count-rebuild tiles handle
+// Tokens of a word whose row of several topic ranges gives its list too (nkw_list_rows_kernel)
+constexpr int32_t kListRowTokens = 8192;
 
 // ------------------------------------------------------------------------------------
 // device helpers

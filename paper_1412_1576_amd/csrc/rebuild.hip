@@ -182,17 +182,20 @@ __global__ __launch_bounds__(ONE ? 256 : 1024) void nkw_tiles_kernel(const Rebui
     }
 }
 
-// Rows of more topics than one LDS histogram, of mixture words of one tile: a workgroup takes the
-// topic ranges of its word one after the other, so that the list of non-zeros comes out of the
-// histograms with the row and no second pass reads the row back.  The topics of a short word are
-// read once and kept in registers.  A histogram takes at most half of the LDS: two workgroups
-// share a CU, and one's barriers are hidden by the other's work.
+// Rows of more topics than one LDS histogram, of mixture words of at most kListRowTokens tokens: a
+// workgroup takes the topic ranges of its word one after the other, so that the list of non-zeros
+// comes out of the histograms with the row and no second pass reads the row back.  The word's
+// topics are read once and kept in registers.  A histogram takes at most half of the LDS: two
+// workgroups share a CU, and one's barriers are hidden by the other's work.
 //
-// 20 000 rows of 10^5 topics, 10^8 tokens: 2.3 ms for the rows and 2.7 ms for the lists before,
-// 2.5 ms for both.  (Writing only the topics of the previous and the new list, for words with
-// few tokens, gained nothing.)
+// Rows and tables of an iteration, ranges and lists in two passes before / in one here, ms: 6000
+// words of 4000 tokens, K = 10^5, 1.96 / 1.18; 600 of them at K = 10^6 1.90 / 0.87.  (Writing only
+// the topics of the previous and the new list, for words with few tokens, gained nothing.)
+// Longer words would be read again for every range, one range after the other, where
+// nkw_tiles_kernel has a workgroup to each range: 40 words of 250 000 tokens, K = 10^6, 1.11
+// there and 7.02 in this form; of 16 000 tokens 0.46 and 0.76, 600 of them 2.55 and 2.26.
 constexpr int32_t kListRowSpan = 18432;
-constexpr int kListRowKept = 8;  // topics of a thread kept in registers
+constexpr int kListRowKept = kListRowTokens / 1024;  // topics of a thread, kept in registers
 
 __global__ __launch_bounds__(1024, 8) void nkw_list_rows_kernel(
     const RebuildTile* __restrict__ tiles, int32_t n_tiles, int32_t run, const int32_t* __restrict__ zw,
@@ -212,14 +215,11 @@ __global__ __launch_bounds__(1024, 8) void nkw_list_rows_kernel(
         const size_t q = xmap ? (size_t)xmap[p] : (size_t)p;
         return (uint32_t)__builtin_nontemporal_load(&zw[q << sh]) & zmask;
     };
-    const bool kept = t.p1 - t.p0 <= 1024 * kListRowKept;
     uint32_t mine[kListRowKept];
-    if (kept) {
 #pragma unroll
-        for (int e = 0; e < kListRowKept; ++e) {
-            const int32_t p = t.p0 + e * 1024 + tid;
-            mine[e] = p < t.p1 ? topic_at(p) : 0xFFFFFFFFu;  // (beyond every range)
-        }
+    for (int e = 0; e < kListRowKept; ++e) {
+        const int32_t p = t.p0 + e * 1024 + tid;
+        mine[e] = p < t.p1 ? topic_at(p) : 0xFFFFFFFFu;  // (beyond every range)
     }
     for (int32_t k = 4 * tid; k < span; k += 4096) *reinterpret_cast<int4*>(&hist[k]) = make_int4(0, 0, 0, 0);
     const bool aligned = (K & 3) == 0;
@@ -231,26 +231,10 @@ __global__ __launch_bounds__(1024, 8) void nkw_list_rows_kernel(
     for (int32_t k0 = 0; k0 < K; k0 += span, parity ^= 1) {
         const uint32_t nk_r = (uint32_t)((k0 + span < K) ? span : K - k0);
         __syncthreads();
-        if (kept) {
 #pragma unroll
-            for (int e = 0; e < kListRowKept; ++e) {
-                const uint32_t r = mine[e] - (uint32_t)k0;
-                if (r < nk_r) atomicAdd(&hist[r], 1);
-            }
-        } else {
-            int32_t p = t.p0 + tid;
-            for (; p + 3 * 1024 < t.p1; p += 4 * 1024) {
-                uint32_t z[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) z[u] = topic_at(p + u * 1024) - (uint32_t)k0;
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (z[u] < nk_r) atomicAdd(&hist[z[u]], 1);
-            }
-            for (; p < t.p1; p += 1024) {
-                const uint32_t r = topic_at(p) - (uint32_t)k0;
-                if (r < nk_r) atomicAdd(&hist[r], 1);
-            }
+        for (int e = 0; e < kListRowKept; ++e) {
+            const uint32_t r = mine[e] - (uint32_t)k0;
+            if (r < nk_r) atomicAdd(&hist[r], 1);
         }
         __syncthreads();
         const int32_t kb0 = wv * chunk, kb1 = (kb0 + chunk < span) ? kb0 + chunk : span;

@@ -130,9 +130,10 @@ def test_large_K_hybrid(lda_mod, oracle_mod):
 
 
 # one topic more than an LDS histogram of all topics holds; three to five ranges of the list
-# kernel, K not a multiple of four, words of more tokens than registers keep, and than a tile
-@pytest.mark.parametrize("K", [36865, 40001, 80000])
-def test_dense_rows_of_several_ranges_with_lists(lda_mod, oracle_mod, K):
+# kernel, K not a multiple of four; words of more tokens than its registers keep, whose lists are
+# made by compaction of a row of one tile, and words of several tiles
+@pytest.mark.parametrize("K,tile", [(36865, 8600), (40001, 8600), (80000, 8600), (40001, 0), (100_000, 0)])
+def test_dense_rows_of_several_ranges_with_lists(lda_mod, oracle_mod, K, tile):
     counts = [20000, 9000, 8601, 8600, 8500, 8193, 8192, 2500, 2501, 1252, 1251, 1250, 1153, 1152, 64, 2, 1, 0,
               9000, 70, 0]
     rng = np.random.default_rng(K)
@@ -140,7 +141,7 @@ def test_dense_rows_of_several_ranges_with_lists(lda_mod, oracle_mod, K):
     rng.shuffle(words)
     doff = np.append(np.arange(0, len(words), 211), len(words)).astype(np.int64)
     run_hybrid(lda_mod, oracle_mod, doff, words, len(counts), K, 0.01, 0.01, 4, 3, 2, dense_rows=18,
-               table_words=range(1, 21), rebuild_tile_tokens=8600)
+               table_words=range(1, 21), rebuild_tile_tokens=tile)
 
 
 @pytest.mark.timeout(600)
