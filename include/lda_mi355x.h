@@ -66,8 +66,9 @@ typedef struct lda_options {
        and hipFree.  When set, every device buffer of the context -- at lda_init and the ones
        that later calls grow or create on first use -- comes from dev_alloc(bytes, alloc_user),
        which returns device memory aligned to 256 bytes or NULL (reported as LDA_ERR_OOM), and
-       goes back through dev_free(ptr, alloc_user), at lda_destroy at the latest.  The
-       callbacks run on the thread that calls the library; setting only one is LDA_ERR_ARG.
+       goes back through dev_free(ptr, alloc_user), at lda_destroy at the latest, and only when
+       no work queued on the context's stream uses it any more.  The callbacks run on the thread
+       that calls the library; setting only one is LDA_ERR_ARG.
        rocprim's temporary storage is requested through them as well. */
     void* (*dev_alloc)(size_t bytes, void* alloc_user);
     void (*dev_free)(void* ptr, void* alloc_user);

@@ -52,6 +52,22 @@ void device_free(lda_ctx* c, void* p)
     else (void)hipFree(p);
 }
 
+void device_release(lda_ctx* c, void* p)
+{
+    if (!p) return;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        try {
+            c->kept.push_back(p);
+        } catch (...) {  // no room to remember it: not given back at all
+        }
+        return;
+    }
+    (void)hipStreamSynchronize(c->stream);
+    device_free(c, p);
+}
+
 namespace {
 
 int setup_hybrid(lda_ctx* c, const std::vector<int32_t>& woff);
@@ -101,6 +117,8 @@ void free_all(lda_ctx* c)
     dev_free(c, c->d_hs); dev_free(c, c->d_ma); dev_free(c, c->d_metaA); c->d_metaB = nullptr;
     dev_free(c, c->d_beta_alias); dev_free(c, c->d_beta_hdr);
     free_big_tables(c);
+    for (void* p : c->kept) device_free(c, p);
+    c->kept.clear();
 }
 
 }  // namespace

@@ -255,6 +255,7 @@ struct lda_ctx {
     double* d_lg_terms = nullptr;      // log-likelihood terms by count: of alpha, then of beta
     int32_t* d_row = nullptr;          // [max(K,1)] row staging for accessors
     int32_t* d_flag = nullptr;         // [4] validation; recount wanted; sum of a sample (zero between uses)
+    std::vector<void*> kept;           // replaced while the stream was being captured; freed at the end
     // host copies of small layouts
     std::vector<int32_t> h_doff;
 };
@@ -267,6 +268,10 @@ int fail(lda_ctx* c, int code, const char* fmt, ...);
 // device_malloc returns LDA_OK or records LDA_ERR_OOM; *p is NULL on failure.
 int device_malloc(lda_ctx* c, void** p, size_t bytes, const char* what);
 void device_free(lda_ctx* c, void* p);
+// Gives back memory that work queued on the context's stream may still use: waits for the stream
+// first (a caller's allocator may hand the block to other work at once), or, while the stream is
+// being captured and cannot be waited for, keeps the block until lda_destroy.
+void device_release(lda_ctx* c, void* p);
 
 template <class T>
 int device_malloc(lda_ctx* c, T** p, size_t count, const char* what)

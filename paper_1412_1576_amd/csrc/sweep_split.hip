@@ -1183,7 +1183,7 @@ template <class T>
 int grow(lda_ctx* c, T** p, size_t* have, size_t need, const char* what)
 {
     if (*have >= need) return LDA_OK;
-    device_free(c, *p);
+    device_release(c, *p);
     *p = nullptr;
     *have = 0;
     const int rc = device_malloc(c, p, need, what);
@@ -1215,14 +1215,14 @@ bool have_split_records(lda_ctx* c, int32_t mh_steps)
         return false;
     }
     if (new_zt) {
-        device_free(c, c->d_zt);
+        device_release(c, c->d_zt);
         c->d_zt = new_zt;
         c->zt_ints = zt;
         c->zt_current = false;
         c->td_valid = false;
     }
     if (new_rec) {
-        device_free(c, c->d_rec);
+        device_release(c, c->d_rec);
         c->d_rec = new_rec;
         c->rec_ints = rec;
     }
