@@ -449,6 +449,7 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
 
     int rc = LDA_OK;
     auto bail = [&](int code) {
+        (void)hipStreamSynchronize(c->stream);  // the arrays may be in use by what is queued so far
         free_all(c);
         delete c;
         return code;

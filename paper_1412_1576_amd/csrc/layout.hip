@@ -130,6 +130,7 @@ int build_record_order(lda_ctx* c)
     int32_t *keys = nullptr, *keys_sorted = nullptr, *pos = nullptr, *pos_sorted = nullptr;
     void* tmp = nullptr;
     auto release = [&]() {
+        (void)hipStreamSynchronize(c->stream);  // on an error the kernels so far may still use them
         device_free(c, keys);
         device_free(c, keys_sorted);
         device_free(c, pos);
@@ -183,6 +184,7 @@ int launch_layout(lda_ctx* c, const int32_t* /*h_word*/)
     int32_t *keys_out = nullptr, *vals_in = nullptr;
     void* tmp = nullptr;
     auto release = [&]() {
+        (void)hipStreamSynchronize(c->stream);  // on an error the kernels so far may still use them
         device_free(c, tmp);
         device_free(c, keys_out);
         device_free(c, vals_in);

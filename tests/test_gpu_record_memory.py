@@ -40,3 +40,47 @@ def test_given_back_when_no_longer_used(lda_mod, oracle_mod, steps):
         assert np.array_equal(g.get_z(), o.get_z()), m
     assert given_back and all(given_back), (steps, given_back)
     g.close(); o.close()
+
+
+@pytest.mark.parametrize("opt", [{}, {"dense_rows": 12, "dense_alias_min_count": 1 << 20},
+                                 {"record_bucket_tokens": 512}, {"stream_block_tokens": 3000}])
+def test_a_failed_init_gives_back_idle_memory(lda_mod, opt):
+    """lda_init behind other work on its stream, with an allocator that fails at the first, the
+    second, ... request: every block comes back, and only when the stream is idle."""
+    rng = np.random.default_rng(2)
+    doff = np.arange(0, 10_001, 100, dtype=np.int64)
+    words = rng.integers(0, 30, 10_000).astype(np.int32)
+    stream = torch.cuda.Stream()
+    busy = torch.zeros(1 << 26, device="cuda")
+    torch.cuda.synchronize()
+    live, idle, left = {}, [], [0]
+
+    def alloc(nbytes):
+        if left[0] == 0:
+            return 0
+        left[0] -= 1
+        t = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        live[t.data_ptr()] = t
+        return t.data_ptr()
+
+    def free(p):
+        idle.append(stream.query())
+        assert p in live
+        back.append(live.pop(p))  # held until the next attempt
+
+    for budget in range(1, 200):
+        left[0], back = budget, []
+        with torch.cuda.stream(stream):
+            for _ in range(10):
+                busy.add_(1.0)
+        try:
+            g = lda_mod.Lda(doff, words, 30, 20, 0.1, 0.01, dev_alloc=alloc, dev_free=free,
+                            stream=stream.cuda_stream, **opt)
+        except lda_mod.LdaError as e:
+            assert e.code == lda_mod.LDA_ERR_OOM
+            assert not live and len(back) == budget
+        else:
+            g.close()
+            break
+        torch.cuda.synchronize()
+    assert 20 < budget < 199 and not live and all(idle)
