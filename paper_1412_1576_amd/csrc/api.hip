@@ -24,25 +24,24 @@ int fail(lda_ctx* c, int code, const char* fmt, ...)
     return code;
 }
 
+void* try_device_malloc(lda_ctx* c, size_t bytes)
+{
+    if (bytes == 0) bytes = 1;
+    if (c->opt.dev_alloc) return c->opt.dev_alloc(bytes, c->opt.alloc_user);
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return p;
+}
+
 int device_malloc(lda_ctx* c, void** p, size_t bytes, const char* what)
 {
-    *p = nullptr;
-    if (bytes == 0) bytes = 1;
-    if (c->opt.dev_alloc) {
-        *p = c->opt.dev_alloc(bytes, c->opt.alloc_user);
-        if (!*p)
-            return fail(c, LDA_ERR_OOM, "the caller's allocator returned NULL for %zu bytes (%s)",
-                        bytes, what);
-        return LDA_OK;
-    }
-    const hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess) {
-        *p = nullptr;
-        (void)hipGetLastError();
-        return fail(c, LDA_ERR_OOM, "device allocation of %zu bytes for %s failed: %s", bytes, what,
-                    hipGetErrorString(e));
-    }
-    return LDA_OK;
+    *p = try_device_malloc(c, bytes);
+    if (*p) return LDA_OK;
+    return fail(c, LDA_ERR_OOM, "%s no %zu bytes for %s",
+                c->opt.dev_alloc ? "the caller's allocator has" : "the device has", bytes, what);
 }
 
 void device_free(lda_ctx* c, void* p)

@@ -265,7 +265,9 @@ namespace lda {
 int fail(lda_ctx* c, int code, const char* fmt, ...);
 
 // Device memory of a context: the caller's allocator (lda_options) or hipMalloc / hipFree.
-// device_malloc returns LDA_OK or records LDA_ERR_OOM; *p is NULL on failure.
+// device_malloc returns LDA_OK or records LDA_ERR_OOM; *p is NULL on failure.  try_device_malloc
+// records nothing and returns NULL.
+void* try_device_malloc(lda_ctx* c, size_t bytes);
 int device_malloc(lda_ctx* c, void** p, size_t bytes, const char* what);
 void device_free(lda_ctx* c, void* p);
 // Gives back memory that work queued on the context's stream may still use: waits for the stream

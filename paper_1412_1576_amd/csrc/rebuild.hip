@@ -526,6 +526,8 @@ int launch_nk_hist(lda_ctx* c, const int32_t* go = nullptr)
 int launch_scatter_word_major(lda_ctx* c, const int32_t* z, const int32_t* wpos, int64_t n, const int32_t* go)
 {
     if (n <= 0) return LDA_OK;
+    if (!c->d_zt)  // a sweep ran out of memory, and what it had given back was gone
+        return fail(c, LDA_ERR_OOM, "no memory for the word-major copy of the assignment");
     const int64_t per_xcd = (n + kXcds - 1) / kXcds;
     const int64_t per_block = kScatterBlock * kScatterPerThread;
     const int64_t blocks = ((per_xcd + per_block - 1) / per_block) * kXcds;

@@ -1183,13 +1183,24 @@ template <class T>
 int grow(lda_ctx* c, T** p, size_t* have, size_t need, const char* what)
 {
     if (*have >= need) return LDA_OK;
-    device_release(c, *p);
+    T* const old = *p;
+    const size_t before = *have;
+    device_release(c, old);
     *p = nullptr;
     *have = 0;
     const int rc = device_malloc(c, p, need, what);
-    if (rc != LDA_OK) return rc;
-    *have = need;
-    return LDA_OK;
+    if (rc == LDA_OK) {
+        *have = need;
+    } else if (before > 0) {  // what shorter chains and the count rebuild go on with
+        if (!c->kept.empty() && c->kept.back() == old) {
+            c->kept.pop_back();
+            *p = old;
+        } else {
+            *p = static_cast<T*>(try_device_malloc(c, sizeof(T) * before));
+        }
+        if (*p) *have = before;
+    }
+    return rc;
 }
 
 // The records of a chain that can also run without them: allocated beside the old ones, which

@@ -84,3 +84,41 @@ def test_a_failed_init_gives_back_idle_memory(lda_mod, opt):
             break
         torch.cuda.synchronize()
     assert 20 < budget < 199 and not live and all(idle)
+
+
+# bytes per token that the allocator grants: two steps use 4 for the word-major records and 16 for
+# the others, four steps 8 and 32; 0: not even what was given back
+@pytest.mark.parametrize("grant", [0, 6, 10, 20])
+def test_out_of_memory_leaves_a_usable_context(lda_mod, oracle_mod, grant):
+    doff, words = make(50, 7, docs=300)
+    N = int(doff[-1])
+    limit, live = [1 << 60], {}
+
+    def alloc(nbytes):
+        if nbytes > limit[0]:
+            return 0
+        t = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        live[t.data_ptr()] = t
+        return t.data_ptr()
+
+    g, o = pair(lda_mod, oracle_mod, doff, words, 50, 64, dev_alloc=alloc, dev_free=lambda p: live.pop(p))
+    sweep_both(g, o, 2)
+    g.build_alias()
+    limit[0] = grant * N
+    with pytest.raises(lda_mod.LdaError) as e:
+        g.sweep(4)
+    assert e.value.code == lda_mod.LDA_ERR_OOM
+    if grant:  # the word-major records are there again
+        g.rebuild_counts()
+        assert np.array_equal(g.get_nk(), o.get_nk())
+    else:
+        with pytest.raises(lda_mod.LdaError) as e:
+            g.rebuild_counts()
+        assert e.value.code == lda_mod.LDA_ERR_OOM
+    if grant in (6, 20):
+        sweep_both(g, o, 2)
+    limit[0] = 1 << 60
+    for m in (2, 4, 1):
+        sweep_both(g, o, m)
+    g.close(); o.close()
+    assert not live
