@@ -124,6 +124,7 @@ struct lda_ctx {
     // Word-pass output, word-major, 2^rec_shift ints per token (sweep_split.hip)
     int32_t* d_rec = nullptr;
     size_t rec_ints = 0;
+    size_t refused_ints = SIZE_MAX;  // of records of chains of 5 to 8 steps: not asked for again
     // Work lists of the word pass: items (w, p0, n, 0) whose rows are staged in LDS, and
     // pieces (w0, w1, p0, n) of several short words whose rows are gathered
     int4* d_row_items = nullptr;

@@ -1204,25 +1204,30 @@ int grow(lda_ctx* c, T** p, size_t* have, size_t need, const char* what)
 }
 
 // The records of a chain that can also run without them: allocated beside the old ones, which
-// stay as they are if there is no room.
+// stay as they are if there is no room.  A refusal is no error, and is remembered: asking on every
+// sweep could make the host wait for the device each time.  Only a smaller wish is tried again.
 bool have_split_records(lda_ctx* c, int32_t mh_steps)
 {
     int32_t nw, nd;
     chain_shape(c->opt.proposal_mode, mh_steps, nw, nd);
     const size_t zt = (size_t)c->N << zt_record_shift(nd, c->zt_pack16);
     const size_t rec = (size_t)c->N << pow2_shift(1 + 2 * nw + nd);
-    if (c->zt_ints >= zt && c->rec_ints >= rec) return true;
+    const size_t more_zt = c->zt_ints >= zt ? 0 : zt, more_rec = c->rec_ints >= rec ? 0 : rec;
+    if (more_zt + more_rec == 0) return true;
+    if (more_zt + more_rec >= c->refused_ints) return false;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
         return false;  // no allocation into a graph
     }
-    int32_t *new_zt = nullptr, *new_rec = nullptr;
-    const bool ok = (c->zt_ints >= zt || device_malloc(c, &new_zt, zt, "word-major records") == LDA_OK) &&
-                    (c->rec_ints >= rec || device_malloc(c, &new_rec, rec, "word-pass records") == LDA_OK);
-    if (!ok) {
-        (void)hipGetLastError();
-        if (new_zt) device_free(c, new_zt);
+    auto ask = [&](size_t ints) {
+        return ints ? static_cast<int32_t*>(try_device_malloc(c, sizeof(int32_t) * ints)) : nullptr;
+    };
+    int32_t* const new_rec = ask(more_rec);  // the larger one first
+    int32_t* const new_zt = more_rec && !new_rec ? nullptr : ask(more_zt);
+    if ((more_rec && !new_rec) || (more_zt && !new_zt)) {
+        device_free(c, new_rec);
+        c->refused_ints = more_zt + more_rec;
         return false;
     }
     if (new_zt) {
@@ -1244,7 +1249,8 @@ bool have_split_records(lda_ctx* c, int32_t mh_steps)
 
 // Chains of 1..4 steps in the cycle mode (and the one-step word chain), tiles of at most
 // 4 tokens per thread; chains of 5..8 steps with the default tiles, one token per thread, if their
-// records (32 or 64 bytes per token) can be had; everything else runs the fused kernel.
+// records can be had (64 bytes per token, and 8 to 32 for the proposals); everything else runs the
+// fused kernel.
 // Sweep of 8 steps, 2 * 10^7 tokens, K = 1000: 3.55 ms fused, 2.17 ms in two passes.
 bool split_sweep_supported(lda_ctx* c, int32_t mh_steps)
 {

@@ -84,14 +84,47 @@ def test_no_room_for_the_records(lda_mod, oracle_mod):
         torch.cuda.synchronize()
         torch.cuda.caching_allocator_delete(p)
 
-    g, o = pair(lda_mod, oracle_mod, doff, words, 50, 64, dev_alloc=alloc, dev_free=free)
     N = int(doff[-1])
-    sweep_both(g, o, 2)
     for limit in (N, 20 * N, 1 << 60):
+        left[0] = 1 << 60
+        g, o = pair(lda_mod, oracle_mod, doff, words, 50, 64, dev_alloc=alloc, dev_free=free)
+        sweep_both(g, o, 2)
         left[0] = limit
         n = len(live)
         for steps in (8, 2, 6):
             sweep_both(g, o, steps)
         assert len(live) == n
+        g.close(); o.close()
+        assert not live
+
+
+def test_a_refusal_is_remembered(lda_mod, oracle_mod):
+    """Refused records are no error, are asked for once, and again only if a chain needs less."""
+    doff, words = make(50, 8, docs=600)
+    N = int(doff[-1])
+    left, live, asked = [1 << 60], {}, []
+
+    def alloc(nbytes):
+        asked.append(nbytes)
+        if nbytes > left[0]:
+            return 0
+        left[0] -= nbytes
+        t = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        live[t.data_ptr()] = t
+        return t.data_ptr()
+
+    def free(p):
+        left[0] += len(live.pop(p))
+
+    g, o = pair(lda_mod, oracle_mod, doff, words, 50, 64, dev_alloc=alloc, dev_free=free)
+    sweep_both(g, o, 2)
+    left[0] = 75 * N  # 8 steps take 64 and 16 bytes per token, 5 steps 64 and 8
+    seen = []
+    for steps in (8, 8, 7, 2, 8, 5, 6, 8, 8):
+        del asked[:]
+        sweep_both(g, o, steps)
+        seen.append([n // N for n in asked])
+        assert not lda_mod.load_library().lda_last_error(g._h), steps
+    assert seen == [[64, 16], [], [64, 8], [], [16], [], [], [], []], seen
     g.close(); o.close()
     assert not live
