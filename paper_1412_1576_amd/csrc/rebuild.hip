@@ -68,33 +68,32 @@ __device__ __forceinline__ void wave_lds_order()
 constexpr int32_t kTileRun = 32;  // consecutive tiles of an XCD, at most
 constexpr int32_t kWaveTileTokens = 512, kWaveTileTopics = 2048;
 
+struct TilesArgs {
+    const RebuildTile* __restrict__ tiles;
+    int32_t n_tiles, run;
+    uint32_t n_blocks;  // that have a tile (ONE: four)
+    const int32_t* __restrict__ zw;
+    int32_t sh;
+    uint32_t zmask;
+    int32_t K, span;
+    int32_t* __restrict__ nkw;
+    const uint32_t* __restrict__ sp_off;
+    int32_t *__restrict__ sp_topic, *__restrict__ sp_count, *__restrict__ sp_nnz;
+    const int32_t* __restrict__ xmap;
+    const int32_t* __restrict__ go;
+};
+
 template <bool ONE>
-__global__ __launch_bounds__(ONE ? 256 : 1024) void nkw_tiles_kernel(const RebuildTile* __restrict__ tiles,
-                                                         int32_t n_tiles, int32_t run,
-                                                         const int32_t* __restrict__ zw,
-                                                         int32_t sh, uint32_t zmask, int32_t K,
-                                                         int32_t span,
-                                                         int32_t* __restrict__ nkw,
-                                                         const uint32_t* __restrict__ sp_off,
-                                                         int32_t* __restrict__ sp_topic,
-                                                         int32_t* __restrict__ sp_count,
-                                                         int32_t* __restrict__ sp_nnz,
-                                                         const int32_t* __restrict__ xmap,
-                                                         const int32_t* __restrict__ go)
+__device__ __forceinline__ void nkw_tile(const TilesArgs& A, const RebuildTile t, int32_t* hist, uint32_t* wcnt)
 {
-    extern __shared__ int32_t hist_all[];
-    __shared__ uint32_t wcnt[16];
-    if (unwanted(go)) return;
-    // runs of consecutive tiles (neighbouring words) share an XCD and with it the lines of
-    // the records they read
-    const int wave = ONE ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
-    const int32_t ti = ONE ? 4 * xcd_runs(run) + wave : xcd_runs(run);
-    if (ti >= n_tiles) return;  // (ONE: a whole wave leaves, no barrier follows)
-    int32_t* const hist = hist_all + wave * span;
+    const int32_t* __restrict__ zw = A.zw;
+    int32_t* __restrict__ nkw = A.nkw;
+    const int32_t* __restrict__ xmap = A.xmap;
+    const int32_t K = A.K, span = A.span, sh = A.sh;
+    const uint32_t zmask = A.zmask;
     auto sync = [&]() {
         if constexpr (ONE) wave_lds_order(); else __syncthreads();
     };
-    const RebuildTile t = tiles[ti];
     const int32_t k0 = (int32_t)blockIdx.y * span;
     const int32_t nk_r = ((k0 + span < K) ? k0 + span : K) - k0;
     const int tid = ONE ? (int)threadIdx.x & 63 : (int)threadIdx.x, nt = ONE ? 64 : (int)blockDim.x;
@@ -142,7 +141,7 @@ __global__ __launch_bounds__(ONE ? 256 : 1024) void nkw_tiles_kernel(const Rebui
     } else if (t.multi >= 2) {
         // the whole row is here (one tile, one topic range): write it and the list of its
         // non-zero topics, ascending
-        const size_t off = sp_off[t.w];
+        const size_t off = A.sp_off[t.w];
         const int lane = tid & 63, wv = tid >> 6, nw = nt >> 6;
         // every wave owns a contiguous run of topics: count its non-zeros, then place them
         const int32_t chunk = (((nk_r + nw - 1) / nw) + 63) & ~63;
@@ -171,14 +170,41 @@ __global__ __launch_bounds__(ONE ? 256 : 1024) void nkw_tiles_kernel(const Rebui
             const uint64_t mask = __ballot(v > 0);
             if (v > 0) {
                 const size_t p = off + pos + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
-                sp_topic[p] = k;
-                sp_count[p] = v;
+                A.sp_topic[p] = k;
+                A.sp_count[p] = v;
             }
             pos += (uint32_t)__popcll(mask);
         }
-        if (tid == 0) sp_nnz[t.w] = (int32_t)base;
+        if (tid == 0) A.sp_nnz[t.w] = (int32_t)base;
     } else {
         for (int32_t k = tid; k < nk_r; k += nt) row[k] = hist[k];
+    }
+}
+
+// MAYBE: at most kMaybeBlocks workgroups loop over the tiles, and only if *go is set.  A workgroup
+// that finds it is not wanted still costs its launch, 1.2 ns of the whole chip's time.  lda_update_counts
+// with nothing moved, 2 * 10^7 tokens, us, one workgroup per tile (four) / so / the +-1 form alone: 10^5
+// words, K = 2500 113 / 68 / 53; 4 * 10^5 words, K = 300 90 / 69 / 57.  A wanted recount of 5 * 10^6
+// tokens, 6 * 10^4 words, K = 2500, takes 210 instead of 190, the others as long as before.  (The
+// scatter of the assignment keeps a workgroup to 1024 tokens: four rounds each, or looping
+// workgroups, widen the window of partial lines; 2 * 10^7 tokens of 10^5 words 285 -> 410 to 490.)
+constexpr unsigned kMaybeBlocks = 4096;  // a multiple of the XCDs
+
+template <bool ONE, bool MAYBE>
+__global__ __launch_bounds__(ONE ? 256 : 1024) void nkw_tiles_kernel(TilesArgs A)
+{
+    extern __shared__ int32_t hist_all[];
+    __shared__ uint32_t wcnt[16];
+    if (MAYBE && unwanted(A.go)) return;
+    // runs of consecutive tiles (neighbouring words) share an XCD and with it the lines of
+    // the records they read
+    const int wave = ONE ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+    int32_t* const hist = hist_all + wave * A.span;
+    for (uint32_t b = blockIdx.x; b < A.n_blocks; b += gridDim.x) {
+        const int32_t ti = ONE ? 4 * xcd_runs(A.run, b) + wave : xcd_runs(A.run, b);
+        if (ti < A.n_tiles) nkw_tile<ONE>(A, A.tiles[ti], hist, wcnt);  // (ONE: uniform over the wave)
+        if constexpr (!MAYBE) return;
+        if constexpr (ONE) wave_lds_order(); else __syncthreads();  // before the histogram is cleared
     }
 }
 
@@ -482,22 +508,30 @@ int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
     const int32_t span = (((K + nr - 1) / nr) + 63) / 64 * 64;
     const size_t lds = sizeof(int32_t) * (size_t)span;
     if (lds > 48 * 1024)
-        LDA_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(nkw_tiles_kernel<false>),
+        LDA_HIP(c, hipFuncSetAttribute(go ? reinterpret_cast<const void*>(nkw_tiles_kernel<false, true>)
+                                          : reinterpret_cast<const void*>(nkw_tiles_kernel<false, false>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    TilesArgs A{};
+    A.zw = c->d_zt; A.sh = c->zt_shift; A.zmask = c->zt_mask; A.K = K; A.span = span; A.nkw = c->d_nkw;
+    A.sp_off = c->d_sp_off; A.sp_topic = c->d_sp_topic; A.sp_count = c->d_sp_count; A.sp_nnz = c->d_sp_nnz;
+    A.xmap = c->d_xmap; A.go = go;
     if (c->n_wide_tiles > 0) {
-        const int32_t run = xcd_run_length(c->n_wide_tiles, kTileRun);
-        hipLaunchKernelGGL(nkw_tiles_kernel<false>, dim3(xcd_runs_grid(c->n_wide_tiles, run), nr),
-                           dim3(span <= 512 ? 256 : (span <= 16384 ? 512 : 1024)), lds, c->stream, c->d_tiles,
-                           c->n_wide_tiles, run, c->d_zt, c->zt_shift, c->zt_mask, K, span,
-                           c->d_nkw, c->d_sp_off, c->d_sp_topic, c->d_sp_count, c->d_sp_nnz, c->d_xmap, go);
+        A.tiles = c->d_tiles; A.n_tiles = c->n_wide_tiles;
+        A.run = xcd_run_length(A.n_tiles, kTileRun);
+        A.n_blocks = xcd_runs_grid(A.n_tiles, A.run);
+        const dim3 grid(go ? std::min(A.n_blocks, kMaybeBlocks) : A.n_blocks, nr), block(span <= 512 ? 256 : (span <= 16384 ? 512 : 1024));
+        if (go) hipLaunchKernelGGL((nkw_tiles_kernel<false, true>), grid, block, lds, c->stream, A);
+        else hipLaunchKernelGGL((nkw_tiles_kernel<false, false>), grid, block, lds, c->stream, A);
     }
     const int32_t n_short = c->n_tiles - c->n_wide_tiles;
     if (n_short > 0) {  // (K <= kWaveTileTopics: one range, less than 48 KB for four histograms)
-        const int32_t blocks = (n_short + 3) / 4, run = xcd_run_length(blocks, kTileRun / 4);
-        hipLaunchKernelGGL(nkw_tiles_kernel<true>, dim3(xcd_runs_grid(blocks, run)), dim3(256), 4 * lds,
-                           c->stream, c->d_tiles + c->n_wide_tiles, n_short, run, c->d_zt, c->zt_shift,
-                           c->zt_mask, K, span, c->d_nkw, c->d_sp_off, c->d_sp_topic, c->d_sp_count,
-                           c->d_sp_nnz, c->d_xmap, go);
+        const int32_t blocks = (n_short + 3) / 4;
+        A.tiles = c->d_tiles + c->n_wide_tiles; A.n_tiles = n_short;
+        A.run = xcd_run_length(blocks, kTileRun / 4);
+        A.n_blocks = xcd_runs_grid(blocks, A.run);
+        const dim3 grid(go ? std::min(A.n_blocks, kMaybeBlocks) : A.n_blocks), block(256);
+        if (go) hipLaunchKernelGGL((nkw_tiles_kernel<true, true>), grid, block, 4 * lds, c->stream, A);
+        else hipLaunchKernelGGL((nkw_tiles_kernel<true, false>), grid, block, 4 * lds, c->stream, A);
     }
     LDA_HIP(c, hipGetLastError());
     return LDA_OK;

@@ -25,11 +25,13 @@ inline unsigned xcd_grid(int32_t n_items) { return (unsigned)((n_items + kXcds -
 // word's class (frequent words are served from LDS or L2, rare ones miss), so contiguous
 // eighths would leave the XCDs unevenly loaded.  Runs of `run` consecutive items are dealt
 // to the XCDs in turn instead: neighbours still share an L2, every XCD sees every class.
-__device__ __forceinline__ int32_t xcd_runs(int32_t run)
+__device__ __forceinline__ int32_t xcd_runs(int32_t run, uint32_t block)
 {
-    const int32_t xcd = (int32_t)(blockIdx.x % kXcds), seq = (int32_t)(blockIdx.x / kXcds);
+    const int32_t xcd = (int32_t)(block % kXcds), seq = (int32_t)(block / kXcds);
     return ((seq / run) * kXcds + xcd) * run + seq % run;
 }
+
+__device__ __forceinline__ int32_t xcd_runs(int32_t run) { return xcd_runs(run, blockIdx.x); }
 
 // Length of the runs: `most`, or less where the list is so short that runs of that length would
 // leave XCDs without work.
