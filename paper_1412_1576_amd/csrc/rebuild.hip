@@ -181,21 +181,22 @@ __device__ __forceinline__ void nkw_tile(const TilesArgs& A, const RebuildTile t
     }
 }
 
-// MAYBE: at most kMaybeBlocks workgroups loop over the tiles, and only if *go is set.  A workgroup
-// that finds it is not wanted still costs its launch, 1.2 ns of the whole chip's time.  lda_update_counts
-// with nothing moved, 2 * 10^7 tokens, us, one workgroup per tile (four) / so / the +-1 form alone: 10^5
-// words, K = 2500 113 / 68 / 53; 4 * 10^5 words, K = 300 90 / 69 / 57.  A wanted recount of 5 * 10^6
-// tokens, 6 * 10^4 words, K = 2500, takes 210 instead of 190, the others as long as before.  (The
-// scatter of the assignment keeps a workgroup to 1024 tokens: four rounds each, or looping
-// workgroups, widen the window of partial lines; 2 * 10^7 tokens of 10^5 words 285 -> 410 to 490.)
-constexpr unsigned kMaybeBlocks = 4096;  // a multiple of the XCDs
+// With `go`, where more than twice kLoopBlocks workgroups may be launched for nothing, that many
+// loop over the tiles (LOOP): a workgroup that finds it is not wanted still costs its launch, 1.2 ns of
+// the whole chip's time.  lda_update_counts with nothing moved, 2 * 10^7 tokens, us, one workgroup
+// per tile (four) / so / the +-1 form alone: 10^5 words, K = 2500 113 / 69 / 53; 4 * 10^5 words,
+// K = 300 90 / 69 / 57.  A wanted recount of 5 * 10^6 tokens, 6 * 10^4 words, K = 2500, takes 210
+// instead of 190, the others as long as before.  (The scatter of the assignment keeps a workgroup to
+// 1024 tokens: four rounds each, or looping workgroups, widen the window of partial lines; 2 * 10^7
+// tokens of 10^5 words 285 -> 410 to 490.)
+constexpr unsigned kLoopBlocks = 4096;  // a multiple of the XCDs
 
-template <bool ONE, bool MAYBE>
+template <bool ONE, bool LOOP>
 __global__ __launch_bounds__(ONE ? 256 : 1024) void nkw_tiles_kernel(TilesArgs A)
 {
     extern __shared__ int32_t hist_all[];
     __shared__ uint32_t wcnt[16];
-    if (MAYBE && unwanted(A.go)) return;
+    if (unwanted(A.go)) return;
     // runs of consecutive tiles (neighbouring words) share an XCD and with it the lines of
     // the records they read
     const int wave = ONE ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(ONE ? 256 : 1024) void nkw_tiles_kernel(TilesArgs A
     for (uint32_t b = blockIdx.x; b < A.n_blocks; b += gridDim.x) {
         const int32_t ti = ONE ? 4 * xcd_runs(A.run, b) + wave : xcd_runs(A.run, b);
         if (ti < A.n_tiles) nkw_tile<ONE>(A, A.tiles[ti], hist, wcnt);  // (ONE: uniform over the wave)
-        if constexpr (!MAYBE) return;
+        if constexpr (!LOOP) return;
         if constexpr (ONE) wave_lds_order(); else __syncthreads();  // before the histogram is cleared
     }
 }
@@ -507,9 +508,8 @@ int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
     const int32_t nr = (K + max_rebuild_topics() - 1) / max_rebuild_topics();
     const int32_t span = (((K + nr - 1) / nr) + 63) / 64 * 64;
     const size_t lds = sizeof(int32_t) * (size_t)span;
-    if (lds > 48 * 1024)
-        LDA_HIP(c, hipFuncSetAttribute(go ? reinterpret_cast<const void*>(nkw_tiles_kernel<false, true>)
-                                          : reinterpret_cast<const void*>(nkw_tiles_kernel<false, false>),
+    if (lds > 48 * 1024)  // (looping workgroups: the all-dense store, K <= 12 288)
+        LDA_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(nkw_tiles_kernel<false, false>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     TilesArgs A{};
     A.zw = c->d_zt; A.sh = c->zt_shift; A.zmask = c->zt_mask; A.K = K; A.span = span; A.nkw = c->d_nkw;
@@ -519,8 +519,9 @@ int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
         A.tiles = c->d_tiles; A.n_tiles = c->n_wide_tiles;
         A.run = xcd_run_length(A.n_tiles, kTileRun);
         A.n_blocks = xcd_runs_grid(A.n_tiles, A.run);
-        const dim3 grid(go ? std::min(A.n_blocks, kMaybeBlocks) : A.n_blocks, nr), block(span <= 512 ? 256 : (span <= 16384 ? 512 : 1024));
-        if (go) hipLaunchKernelGGL((nkw_tiles_kernel<false, true>), grid, block, lds, c->stream, A);
+        const bool loop = go && A.n_blocks > 2 * kLoopBlocks;
+        const dim3 grid(loop ? kLoopBlocks : A.n_blocks, nr), block(span <= 512 ? 256 : (span <= 16384 ? 512 : 1024));
+        if (loop) hipLaunchKernelGGL((nkw_tiles_kernel<false, true>), grid, block, lds, c->stream, A);
         else hipLaunchKernelGGL((nkw_tiles_kernel<false, false>), grid, block, lds, c->stream, A);
     }
     const int32_t n_short = c->n_tiles - c->n_wide_tiles;
@@ -529,8 +530,9 @@ int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
         A.tiles = c->d_tiles + c->n_wide_tiles; A.n_tiles = n_short;
         A.run = xcd_run_length(blocks, kTileRun / 4);
         A.n_blocks = xcd_runs_grid(blocks, A.run);
-        const dim3 grid(go ? std::min(A.n_blocks, kMaybeBlocks) : A.n_blocks), block(256);
-        if (go) hipLaunchKernelGGL((nkw_tiles_kernel<true, true>), grid, block, 4 * lds, c->stream, A);
+        const bool loop = go && A.n_blocks > 2 * kLoopBlocks;
+        const dim3 grid(loop ? kLoopBlocks : A.n_blocks), block(256);
+        if (loop) hipLaunchKernelGGL((nkw_tiles_kernel<true, true>), grid, block, 4 * lds, c->stream, A);
         else hipLaunchKernelGGL((nkw_tiles_kernel<true, false>), grid, block, 4 * lds, c->stream, A);
     }
     LDA_HIP(c, hipGetLastError());
@@ -581,6 +583,13 @@ int launch_scatter_word_major(lda_ctx* c, const int32_t* z, const int32_t* wpos,
 // traffic of rows and tokens at about 4 TB/s (2.8 ms for the former corpus at K = 10 000, 0.1 ms
 // for the latter at K = 333).  First sweeps move nearly every token: 1.8 * 10^6 tokens in short
 // documents, K = 333: 350 us by +-1, 190 us as decided here.
+// Neither is known better beforehand: moved tokens that share counters cost up to 2.5 ns (K = 2), a
+// recount where one topic holds most of a word's tokens 6.5 ps per token instead of 2, and after a
+// sweep of one pass (the refreshed doc side, chains without records) it first copies the assignment
+// into word-major order, 5 to 6.5 ps per token.  Both at their dearest for the form chosen: 2 * 10^7
+// tokens, 5000 words, K = 2000, 5 % moved after a refreshed sweep, 111 us by +-1 and 229 by the recount.
+// With the two in the model, a like corpus with 7 % moved among counters that are shared went from
+// 241 to 558 us, so they are left out.
 int launch_update_counts(lda_ctx* c)
 {
     if (c->K > kNkRangeTopics)
