@@ -128,3 +128,44 @@ def test_a_refusal_is_remembered(lda_mod, oracle_mod):
     assert seen == [[64, 16], [], [64, 8], [], [16], [], [], [], []], seen
     g.close(); o.close()
     assert not live
+
+
+def test_first_long_chain_in_a_graph(lda_mod, oracle_mod):
+    """While its stream is captured a sweep allocates nothing: it runs without records, and the
+    graph gives the oracle's assignment at every replay.  The next sweep asks for the records."""
+    doff, words = make(50, 9, docs=600)
+    N = int(doff[-1])
+    live, asked = {}, []
+
+    def alloc(nbytes):
+        asked.append(nbytes // N)
+        t = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        live[t.data_ptr()] = t
+        return t.data_ptr()
+
+    stream = torch.cuda.Stream()
+    g, o = pair(lda_mod, oracle_mod, doff, words, 50, 64, dev_alloc=alloc, dev_free=lambda p: live.pop(p),
+                stream=stream.cuda_stream)
+    sweep_both(g, o, 2)
+    g.build_alias(); o.build_alias()
+    g.sync()
+    other = torch.ones(1 << 20, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    del asked[:]
+    with torch.cuda.graph(graph, stream=stream):
+        g.sweep(8)
+    assert not asked
+    o.sweep(8)
+    for i in range(3):
+        with torch.cuda.stream(stream):
+            graph.replay()
+            other.mul_(2.0)
+        assert np.array_equal(g.get_z(), o.get_z()), i
+        torch.cuda.synchronize()
+    g.rebuild_counts(); o.rebuild_counts()
+    assert np.array_equal(g.get_nk(), o.get_nk())
+    assert not asked
+    sweep_both(g, o, 8)
+    assert asked == [64, 16]
+    sweep_both(g, o, 2)
+    g.close(); o.close()

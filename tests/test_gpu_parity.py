@@ -294,7 +294,7 @@ def test_caller_allocator(lda_mod, oracle_mod, hybrid):
 def test_chain_shape_changes_between_sweeps(lda_mod, oracle_mod):
     """The two-pass sweep keeps the next sweep's doc proposals from the previous doc pass;
     they must be redrawn when the number of steps changes, after lda_set_z (other
-    assignment, other sweep index), and after a sweep that ran the fused kernel (5 steps).
+    assignment, other sweep index), and after a sweep that ran the fused kernel (9 steps).
     Hybrid store too.  Every sweep is compared with the oracle."""
     cfg = corpus.scaled(corpus.CONFIGS["c1"], D=400, K=64)
     doff, words = corpus.make_corpus(cfg)
@@ -304,7 +304,7 @@ def test_chain_shape_changes_between_sweeps(lda_mod, oracle_mod):
         g = lda_mod.Lda(doff, words, cfg.V, cfg.K, cfg.alpha, cfg.beta, seed=7, **opt)
         o = oracle_mod.Oracle(doff, words, cfg.V, cfg.K, cfg.alpha, cfg.beta, seed=7,
                               dense_alias_min_count=opt.get("dense_alias_min_count", 0))
-        for it, m in enumerate((2, 2, 4, 1, 3, 5, 2, 2, 1, 4)):
+        for it, m in enumerate((2, 2, 4, 1, 3, 9, 2, 2, 1, 5, 4)):
             if it == 4:  # jump to another assignment and sweep index
                 z = rng.integers(0, cfg.K, g.N).astype(np.int32)
                 for x in (g, o):
@@ -332,7 +332,7 @@ def test_incremental_count_update(lda_mod, oracle_mod):
         g = lda_mod.Lda(doff, words, cfg.V, cfg.K, cfg.alpha, cfg.beta, seed=5)
         h = lda_mod.Lda(doff, words, cfg.V, cfg.K, cfg.alpha, cfg.beta, seed=5)
         o = oracle_mod.Oracle(doff, words, cfg.V, cfg.K, cfg.alpha, cfg.beta, seed=5)
-        for it, m in enumerate((2, 4, 1, 5, 2)):
+        for it, m in enumerate((2, 4, 1, 5, 9, 2)):
             for x in (g, h, o):
                 x.build_alias()
                 x.sweep(m)
@@ -378,10 +378,11 @@ def test_sweep_pass_times(lda_mod):
     g.build_alias(); g.sweep(2)
     word_ms, doc_ms = g.sweep_pass_ms()
     assert 0.0 < word_ms < 1e3 and 0.0 < doc_ms < 1e3
-    g.rebuild_counts(); g.build_alias(); g.sweep(5)   # five steps run as one fused kernel
-    with pytest.raises(lda_mod.LdaError) as e:
-        g.sweep_pass_ms()
-    assert e.value.code == lda_mod.LDA_ERR_STATE
+    for m in (5, 9):                           # more than four steps: not timed, in two passes or one
+        g.rebuild_counts(); g.build_alias(); g.sweep(m)
+        with pytest.raises(lda_mod.LdaError) as e:
+            g.sweep_pass_ms()
+        assert e.value.code == lda_mod.LDA_ERR_STATE
     g.close()
     h = lda_mod.Lda(doff, words, cfg.V, cfg.K, cfg.alpha, cfg.beta)
     h.build_alias(); h.sweep(2)

@@ -95,3 +95,41 @@ def test_dense_tables_beyond_one_workgroup(lda_mod, oracle_mod, pattern):
         check_alias(g, o, range(len(counts)), tag="K = %d" % K)
         g.close()
         o.close()
+
+
+def two_builds(g, o, sweep_check):
+    for it in range(2):
+        for m in (g, o):
+            m.build_alias()
+        sweep_check("build %d" % it)
+        for m in (g, o):
+            m.sweep(2)
+            m.rebuild_counts()
+        assert np.array_equal(g.get_z(), o.get_z()), it
+    g.close()
+    o.close()
+
+
+# 340 K list entries hold 339 tables of K entries: the first and the last table of every batch
+def test_dense_tables_in_several_batches(lda_mod, oracle_mod):
+    K, V = 12_290, 700
+    doff, words = word_corpus(np.random.default_rng(3).integers(1, 12, V))
+    g = lda_mod.Lda(doff, words, V, K, 0.1, 0.01, seed=6)
+    o = oracle_mod.Oracle(doff, words, V, K, 0.1, 0.01, seed=6)
+    two_builds(g, o, lambda tag: check_alias(g, o, [0, 1, 337, 338, 339, 340, 677, 678, 679, 698, 699], tag=tag))
+
+
+def test_mixture_tables_in_several_batches(lda_mod, oracle_mod):
+    """Behind dense tables, which use the same list memory."""
+    K, V = 12_290, 350
+    counts = [20_000, 12_500, 20_001] + [12_300] * (V - 4) + [5]
+    doff, words = word_corpus(counts)
+    opt = dict(seed=7, dense_alias_min_count=20_000)
+    g = lda_mod.Lda(doff, words, V, K, 0.1, 0.01, dense_rows=V, **opt)
+    o = oracle_mod.Oracle(doff, words, V, K, 0.1, 0.01, **opt)
+
+    def check(tag):
+        check_alias(g, o, [0, 2], tag=tag)
+        check_mixture_tables(g, o, [1, 3, 4, 338, 339, 340, 341, 342, 347, 348, 349], tag=tag)
+
+    two_builds(g, o, check)

@@ -71,3 +71,28 @@ def test_many_tiles_wanted_or_not(lda_mod, oracle_mod, V, K, steps):
         g.rebuild_counts()  # and every row, by the recount
         assert np.array_equal(g.get_nk(), nk)
     g.close()
+
+
+# the refreshed sweep leaves no word-major copy either: nearly all tokens move, then about half
+@pytest.mark.parametrize("V,K", [(50, 300), (50, 2), (9_000, 65)])
+def test_after_refreshed_sweeps(lda_mod, oracle_mod, V, K):
+    rng = np.random.default_rng(V + K)
+    N = 400_001
+    words = (V * rng.random(N) ** 3).astype(np.int32)
+    doff = np.append(np.arange(0, N, 90), N).astype(np.int64)
+    g = lda_mod.Lda(doff, words, V, K, 0.1, 0.01, seed=4, doc_refresh=1)
+    o = oracle_mod.Oracle(doff, words, V, K, 0.1, 0.01, seed=4)
+    for i, (mh, update) in enumerate([(2, True), (2, True), (3, False), (1, True)]):
+        g.build_alias(); o.build_alias()
+        g.sweep(mh); o.sweep_doc_refresh(mh)
+        if update:
+            g.update_counts()
+        else:
+            g.rebuild_counts()
+        o.rebuild_counts()
+        assert np.array_equal(g.get_z(), o.get_z()), i
+        assert np.array_equal(g.get_nk(), o.get_nk()), i
+        for w in range(0, V, max(1, V // 150)):
+            assert np.array_equal(g.get_nkw_row(w), o.get_nkw_row(w)), (i, w)
+    g.close()
+    o.close()
