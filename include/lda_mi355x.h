@@ -150,10 +150,11 @@ int lda_build_alias(lda_ctx* ctx);
  * Uses the context's sweep index as Philox counter word 2 and increments it.
  * The longest chain asked for decides how much the context holds for the records its passes
  * exchange, from the first such sweep until lda_destroy: 20 bytes per token for 2 steps, 40 for 4,
- * 72 or 80 for 5 to 8 (K > 65536: 24, 48, and 80 or 96); LDA_ERR_OOM if there is no room.  A chain
- * of 5 to 8 steps that finds no room, or would have to allocate while the stream is being captured,
- * runs without records instead, more slowly, as longer chains always do; a context that was
- * refused the memory once does not ask for as much again.
+ * 72 or 80 for 5 to 8 (K > 65536: 24, 48, and 80 or 96); LDA_ERR_OOM if there is no room.  Chains
+ * of 5 to 8 steps use records only where they gain (many tokens of the mixture form, or of long
+ * documents) and run as one kernel without them otherwise, as longer chains always do; so they do,
+ * more slowly, where there is no room or the records would have to be allocated while the stream is
+ * being captured.  A context that was refused the memory once does not ask for as much again.
  * ALIAS_VALID -> SWEPT (the counts no longer match z).
  */
 int lda_sweep(lda_ctx* ctx, int32_t mh_steps);

@@ -244,6 +244,7 @@ int setup_hybrid(lda_ctx* c, const std::vector<int32_t>& woff)
             const int32_t cap = std::min(cw, K);
             list_total += (uint64_t)cap;
             mix.push_back(w);
+            c->mix_tokens += cw;
             int cl = 0;
             while (kMixClassCap[cl] >= 0 && cap > (kMixClassCap[cl] ? kMixClassCap[cl] : lds_max)) ++cl;
             mixc[cl].push_back(w);
@@ -491,6 +492,7 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
         long_slot[i + 1] = long_slot[i] + 2 * (int64_t)(c->h_doff[d + 1] - c->h_doff[d]);
     }
     c->long_slots = long_slot[c->n_long];
+    c->long_tokens = c->long_slots / 2;
 
     const size_t VK = (size_t)H * (size_t)K;  // dense rows (all V of them in the all-dense mode)
     bool any_dense_alias = true;  // refined below in the hybrid mode

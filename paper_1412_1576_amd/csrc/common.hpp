@@ -163,6 +163,7 @@ struct lda_ctx {
     int32_t* d_long_first = nullptr;   // [total slots] log-likelihood: first token of every topic
     int32_t n_long = 0;
     int64_t long_slots = 0;
+    int64_t long_tokens = 0;           // tokens of these documents
     std::vector<int32_t> h_long_doc;
     // rebuild tiling
     lda::RebuildTile* d_tiles = nullptr;
@@ -179,6 +180,7 @@ struct lda_ctx {
     int32_t* d_dense_alias_words = nullptr;  // words that draw from a dense K-bin table
     int32_t n_dense_alias = 0;
     int32_t n_mix = 0;                   // words that draw from the mixture
+    int64_t mix_tokens = 0;              // and their tokens
     // the mixture words by list capacity (kMixClassCap; the tables of the last class are built by
     // many workgroups each)
     int32_t* d_mix_class[lda::kMixClasses] = {};

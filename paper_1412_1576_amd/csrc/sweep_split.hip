@@ -1245,19 +1245,45 @@ bool have_split_records(lda_ctx* c, int32_t mh_steps)
     return true;
 }
 
+// Whether a chain of 5 to 8 steps is worth its records.  Two passes write and read 64 bytes per token
+// for them; what they save is the fused kernel's look-ups of the word side, which are cheap in
+// dense tables and dear where a word draws from the mixture (a hash row, or a search of its list:
+// one such token in a wave of 64 is enough), and the long-document kernel's, one after the
+// other.  A word's rows are staged for its tokens, so a small corpus gains nothing.
+// Sweep of 5 / of 8 steps, two passes over fused; after the fused form the rebuild also copies the
+// assignment into word-major order, 5 to 6 ps per token, 3 to 6 % of such a sweep:
+//   dense tables   5 * 10^6 tokens, 10^5 words, K = 300 1.69 / 1.48, K = 10 000 1.45 / 1.30;
+//                  4 * 10^7, K = 10 000 1.22 / 1.05; 2 * 10^7, 2000 words, K = 50 2.71 / 2.47
+//   mixture        2 * 10^7 tokens, 10^5 words, K = 100 1.79 / 1.61, 400 1.02 / 0.92, 1000 0.85 / 0.75,
+//   below K        6000 0.65 / 0.57; 3 * 10^4 words, K = 300 1.07 / 0.89, with 3 * 10^6 tokens 1.24 /
+//                  1.10; 10^5 words, 5 * 10^6 tokens, K = 1000 0.95 / 0.88; 10^6, K = 1000 1.15 / 1.13, 6000
+//                  1.09 / 1.00; 10^5, K = 1000 1.05 / 0.95, 6000 1.43 / 1.21
+//     of few tokens  2 * 10^7 tokens, 3000 words, K = 1000 (4.6 % mixture) 1.01 / 0.89, 400 (none) 1.78 / 1.60
+//   sparse rows    K = 10^6: 5 * 10^6 tokens 0.78 / 0.75, 10^6 0.69 / 0.71, 3 * 10^5 0.97 / 0.96; K = 20 000
+//                  1.04 / 1.01, 1.18 / 1.24, 1.24 / 1.26
+//   6 to 10 % in long documents   10^5 tokens, K = 1000 mixture 0.73 / 0.69, K = 100 0.97 / 0.94; dense
+//                  tables 3 * 10^5, K = 1500 0.82 / 0.77, K = 300 1.05 / 1.13; 3 * 10^6, K = 1500 1.38 / 1.25
+bool long_chain_in_two_passes(const lda_ctx* c, int32_t mh_steps)
+{
+    const bool mixture = c->mix_tokens * 25 >= c->N, longs = c->long_tokens * 33 >= c->N;
+    const int64_t topic_steps = (int64_t)c->K * mh_steps;
+    if (longs && c->N < 1000000) return topic_steps >= (mixture ? 1500 : 7500);
+    return mixture && topic_steps >= (c->N >= 10000000 ? 2000 : 3000) && (longs || c->N >= 3000000);
+}
+
 }  // namespace
 
 // Chains of 1..4 steps in the cycle mode (and the one-step word chain), tiles of at most
-// 4 tokens per thread; chains of 5..8 steps with the default tiles, one token per thread, if their
-// records can be had (64 bytes per token, and 8 to 32 for the proposals); everything else runs the
-// fused kernel.
-// Sweep of 8 steps, 2 * 10^7 tokens, K = 1000: 3.55 ms fused, 2.17 ms in two passes.
+// 4 tokens per thread; chains of 5..8 steps with the default tiles, one token per thread, where they
+// gain and their records can be had (64 bytes per token, and 8 to 32 for the proposals); everything
+// else runs the fused kernel.  Sweep of 8 steps, 2 * 10^7 tokens, K = 1000, mixture below K tokens:
+// 3.55 ms fused, 2.17 ms in two passes.
 bool split_sweep_supported(lda_ctx* c, int32_t mh_steps)
 {
     if (mh_steps < 1 || mh_steps > 8) return false;
     if (mh_steps > 4)
         return c->opt.proposal_mode == 0 && c->n_chunks2 > 0 && c->chunk_tokens <= 1024 &&
-               have_split_records(c, mh_steps);
+               long_chain_in_two_passes(c, mh_steps) && have_split_records(c, mh_steps);
     if (c->opt.proposal_mode == 2 || (c->opt.proposal_mode == 1 && mh_steps != 1)) return false;
     return (c->chunk_tokens + c->sweep_block - 1) / c->sweep_block <= 4;
 }

@@ -1,5 +1,7 @@
-"""Chains of 5 to 8 steps: in two passes where their records can be had, otherwise (and beyond 8
-steps) in one; against the oracle, bit for bit, in every store and in turn with other chains."""
+"""Chains of 5 to 8 steps: in two passes where that gains and their records can be had, otherwise
+(and beyond 8 steps) in one; against the oracle, bit for bit, in every store and in turn with other
+chains.  The corpora of make() have long documents, so they take two passes from K * steps = 7500 on
+(1500 with words of the mixture)."""
 import numpy as np
 import pytest
 import torch
@@ -42,7 +44,7 @@ def sweep_both(g, o, m):
 
 # rows staged in LDS and gathered (dense), staged and gathered mixture rows, rows beyond LDS, no
 # dense rows, n_k gathered (K > 16384), topics of more than 16 bits
-@pytest.mark.parametrize("V,K,dense_rows", [(90, 33, 0), (300, 1000, 300), (40, 13000, 25),
+@pytest.mark.parametrize("V,K,dense_rows", [(90, 33, 0), (90, 1510, 0), (300, 1000, 300), (40, 13000, 25),
                                             (90, 17001, -1), (40, 66000, 3)])
 @pytest.mark.parametrize("m", [5, 6, 7, 8])
 def test_steps_and_stores(lda_mod, oracle_mod, V, K, dense_rows, m):
@@ -60,7 +62,7 @@ def test_steps_and_stores(lda_mod, oracle_mod, V, K, dense_rows, m):
 
 def test_record_buckets(lda_mod, oracle_mod):
     doff, words = make(50, 3)
-    g, o = pair(lda_mod, oracle_mod, doff, words, 50, 70, record_bucket_tokens=512)
+    g, o = pair(lda_mod, oracle_mod, doff, words, 50, 1570, record_bucket_tokens=512)
     for steps in (8, 7, 8, 5, 6):
         sweep_both(g, o, steps)
     g.close(); o.close()
@@ -87,7 +89,7 @@ def test_no_room_for_the_records(lda_mod, oracle_mod):
     N = int(doff[-1])
     for limit in (N, 20 * N, 1 << 60):
         left[0] = 1 << 60
-        g, o = pair(lda_mod, oracle_mod, doff, words, 50, 64, dev_alloc=alloc, dev_free=free)
+        g, o = pair(lda_mod, oracle_mod, doff, words, 50, 1564, dev_alloc=alloc, dev_free=free)
         sweep_both(g, o, 2)
         left[0] = limit
         n = len(live)
@@ -116,7 +118,7 @@ def test_a_refusal_is_remembered(lda_mod, oracle_mod):
     def free(p):
         left[0] += len(live.pop(p))
 
-    g, o = pair(lda_mod, oracle_mod, doff, words, 50, 64, dev_alloc=alloc, dev_free=free)
+    g, o = pair(lda_mod, oracle_mod, doff, words, 50, 1564, dev_alloc=alloc, dev_free=free)
     sweep_both(g, o, 2)
     left[0] = 75 * N  # 8 steps take 64 and 16 bytes per token, 5 steps 64 and 8
     seen = []
@@ -144,7 +146,7 @@ def test_first_long_chain_in_a_graph(lda_mod, oracle_mod):
         return t.data_ptr()
 
     stream = torch.cuda.Stream()
-    g, o = pair(lda_mod, oracle_mod, doff, words, 50, 64, dev_alloc=alloc, dev_free=lambda p: live.pop(p),
+    g, o = pair(lda_mod, oracle_mod, doff, words, 50, 1564, dev_alloc=alloc, dev_free=lambda p: live.pop(p),
                 stream=stream.cuda_stream)
     sweep_both(g, o, 2)
     g.build_alias(); o.build_alias()
@@ -169,3 +171,37 @@ def test_first_long_chain_in_a_graph(lda_mod, oracle_mod):
     assert asked == [64, 16]
     sweep_both(g, o, 2)
     g.close(); o.close()
+
+
+# corpora on both sides of the rule: tokens, length of most documents, tokens of one long document,
+# words, K, dense_alias_min_count, steps, whether the records are asked for
+@pytest.mark.parametrize("N,L,long,V,K,below,m,two", [
+    (100_000, 90, 0, 50, 64, 0, 5, False), (100_000, 90, 0, 900, 2000, 0, 8, False),
+    (100_000, 90, 0, 900, 2000, 2000, 8, False),
+    (100_000, 90, 4000, 50, 937, 0, 8, False), (100_000, 90, 4000, 50, 938, 0, 8, True),
+    (100_000, 90, 4000, 900, 299, 900, 5, False), (100_000, 90, 4000, 900, 300, 900, 5, True),
+    (100_000, 90, 3000, 900, 300, 900, 5, False), (1_200_000, 90, 40_000, 50, 2000, 0, 8, False),
+    (1_200_000, 90, 40_000, 9000, 600, 600, 5, True), (1_200_000, 90, 0, 9000, 600, 600, 5, False),
+    (3_000_000, 90, 0, 9000, 600, 600, 5, True), (3_000_000, 90, 0, 9000, 599, 599, 5, False),
+    (3_000_000, 90, 0, 9000, 600, 2, 5, False), (3_000_000, 90, 0, 9000, 600, 0, 8, False)])
+def test_which_form(lda_mod, N, L, long, V, K, below, m, two):
+    rng = np.random.default_rng(N + K)
+    words = (V * rng.random(N) ** 4).astype(np.int32)
+    doff = np.append(np.arange(0, N - long, L), [N - long, N] if long else [N]).astype(np.int64)
+    live, asked = {}, []
+
+    def alloc(nbytes):
+        asked.append(nbytes)
+        t = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        live[t.data_ptr()] = t
+        return t.data_ptr()
+
+    g = lda_mod.Lda(doff, words, V, K, 0.1, 0.01, seed=1, dev_alloc=alloc, dev_free=lambda p: live.pop(p),
+                    dense_alias_min_count=below)
+    g.build_alias()
+    del asked[:]
+    g.sweep(m)
+    assert (64 * N in asked) == two, asked
+    g.rebuild_counts()
+    assert np.array_equal(g.get_nk(), np.bincount(g.get_z(), minlength=K))
+    g.close()

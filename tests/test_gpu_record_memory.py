@@ -24,7 +24,7 @@ def test_given_back_when_no_longer_used(lda_mod, oracle_mod, steps):
     def free(p):
         idle.append(stream.query())
 
-    g, o = pair(lda_mod, oracle_mod, doff, words, 50, 64, dev_alloc=alloc, dev_free=free,
+    g, o = pair(lda_mod, oracle_mod, doff, words, 50, 1564, dev_alloc=alloc, dev_free=free,
                 stream=stream.cuda_stream)
     busy = torch.zeros(1 << 28, device="cuda")
     torch.cuda.synchronize()
