@@ -421,9 +421,10 @@ int setup_big_tables(lda_ctx* c, const std::vector<int32_t>& big_mix)
 {
     const int32_t K = c->K;
     const bool big_k = K > kRegsMaxEntries;
-    // Room of a batch: 340 tables of K entries (4 KB K bytes) fill the chip many times over --
-    // at the smallest K it is 2000 chunks -- and keep the lists small beside the tables.
-    const uint64_t room = std::min<uint64_t>(340ull * (uint64_t)K, 1000000000ull);
+    // Room of a batch: 340 tables of K entries (4 KB K bytes, 4.3 GB for the largest K) fill the chip
+    // many times over -- at the smallest K it is 2000 chunks -- and keep the lists small beside
+    // the tables.
+    const uint64_t room = 340ull * (uint64_t)K;
     uint64_t need_dense = 0, need_mix = 0, need_beta = 0;
     int rc = setup_big_set(c, &c->big_dense, big_k ? (size_t)c->n_dense_alias : 0,
                            [&](size_t) { return K; }, room, &need_dense);

@@ -38,6 +38,7 @@ __device__ __forceinline__ double block_sum_f64(double v, double* wtot)
 // count is small, and lgamma is some 200 fp64 instructions that a wave runs if any of its lanes
 // needs it.
 constexpr int32_t kTermTable = 4096;
+static_assert(kMaxTileTokens < kTermTable, "a count of a document tile is in the table");
 
 __device__ __forceinline__ double count_term(int32_t v, double a, double lg_a, const double* __restrict__ table)
 {
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(1024) void loglik_doc_tiles_kernel(
             acc += lg_alphabar - lgamma((double)(T.sdoff[i + 1] - T.sdoff[i]) + alphabar);
         for (int32_t i = threadIdx.x; i < T.ntok; i += blockDim.x) {
             const int32_t s = slot_of(i);
-            if (first[s] == i) acc += count_term((int32_t)(T.tab[s] >> kTopicBits), alpha, lg_alpha, terms);
+            if (first[s] == i) acc += terms[T.tab[s] >> kTopicBits];  // (at most kMaxTileTokens)
         }
     }
     const double s = block_sum_f64(acc, wtot);

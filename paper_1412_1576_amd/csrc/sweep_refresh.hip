@@ -313,10 +313,10 @@ int32_t counts_doc_ints(int32_t K, int32_t longest_doc) { return counter_ints(K)
 // counters per token of a mean document.
 int refresh_lanes(const lda_ctx* c, int32_t longest_doc)
 {
-    if (c->K > 65536 || (double)c->K * (double)c->D > 256.0 * (double)c->N) return 0;
+    if ((double)c->K * (double)c->D > 256.0 * (double)c->N) return 0;
+    // (at most 32 KB: the all-dense store has K <= 12 288, and a document 4096 tokens)
     const size_t bytes = sizeof(int32_t) * (size_t)counts_doc_ints(c->K, longest_doc);
     const size_t lds = 160 * 1024;
-    if (bytes > lds) return 0;
     int g = 8;
     while (g < 64 && (lds / (bytes * (size_t)(64 / g)) < 8 || c->D * g / 64 < 512)) g *= 2;
     return g;
@@ -326,10 +326,7 @@ template <int M, int G>
 int launch_refresh_counts_as(lda_ctx* c, const RefreshArgs& A)
 {
     const auto kern = sweep_doc_refresh_counts_kernel<M, G>;
-    const size_t lds = sizeof(int32_t) * (size_t)(64 / G) * (size_t)A.lds_doc;
-    if (lds > 48 * 1024)
-        LDA_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    const size_t lds = sizeof(int32_t) * (size_t)(64 / G) * (size_t)A.lds_doc;  // (less than 48 KB)
     hipLaunchKernelGGL(kern, dim3((unsigned)((c->D + 64 / G - 1) / (64 / G))), dim3(64), lds, c->stream, A);
     LDA_HIP(c, hipGetLastError());
     return LDA_OK;
