@@ -35,18 +35,39 @@ __host__ __device__ inline size_t alias_regs_lds_bytes(size_t n)
     return (sizeof(uint64_t) * (n + 1) + sizeof(uint16_t) * 2 * n + 7) / 8 * 8;
 }
 
-// LDS written by some lanes of a wave is read by others after this
-__device__ __forceinline__ void wave_lds_order()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Sum over the wave of values < 2^51
 __device__ __forceinline__ uint64_t wave_total_u64(uint64_t v)
 {
     return readlane_u64(wave_inclusive_scan_u64(v), kWave - 1);
+}
+
+// Step 4: thread t's run of Em positions of the merged order, an odd number, which spreads the
+// threads' reads over the LDS banks.  pq[a]: b(a) of light a; pq[n-1-b]: a(b) of heavy b.  The ends
+// need no test: dx[A] is the total of both lists, so past the lights no heavy is preceded by
+// "light A", and "heavy B" (also dx[n-B] = dx[A]) precedes no light.
+__device__ __forceinline__ void merge_run(const uint64_t* dx, uint16_t* pq, int32_t n, int32_t A, int32_t t,
+                                          int32_t Em)
+{
+    const int32_t B = n - A;
+    const int32_t q0 = t * Em;
+    const int32_t q1 = q0 + Em < n ? q0 + Em : n;
+    if (q0 >= n) return;
+    int32_t lo = q0 > B ? q0 - B : 0, hi = q0 < A ? q0 : A;
+    while (lo < hi) {
+        const int32_t mid = (lo + hi) >> 1;
+        if (dx[mid] < dx[n - (q0 - 1 - mid)]) lo = mid + 1; else hi = mid;
+    }
+    int32_t a = lo, b = q0 - lo;
+    uint64_t da = dx[a], xb = dx[n - b];
+    for (int32_t q = q0; q < q1; ++q) {
+        const bool lt = da < xb;
+        pq[lt ? a : n - 1 - b] = (uint16_t)(lt ? b : a);
+        a += lt ? 1 : 0;
+        b += lt ? 0 : 1;
+        const uint64_t v = dx[lt ? a : n - b];
+        da = lt ? v : da;
+        xb = lt ? xb : v;
+    }
 }
 
 // The workgroup's form: all its threads build one table of n <= E * threads entries.  Entries are
@@ -173,33 +194,8 @@ __device__ __forceinline__ void build_table_workgroup(int32_t n, const Src& src,
     }
     __syncthreads();
 
-    // 4: merge.  An odd number of positions per thread, as above.  The ends need no test: dx[A] is
-    // the total of both lists, so past the lights no heavy is preceded by "light A", and
-    // "heavy B" (also dx[n-B] = dx[A]) precedes no light.
-    {
-        const int32_t B = n - (int32_t)A;
-        const int32_t Em = per | 1;
-        const int32_t q0 = t * Em;
-        const int32_t q1 = q0 + Em < n ? q0 + Em : n;
-        if (q0 < n) {
-            int32_t lo = q0 > B ? q0 - B : 0, hi = q0 < (int32_t)A ? q0 : (int32_t)A;
-            while (lo < hi) {
-                const int32_t mid = (lo + hi) >> 1;
-                if (dx[mid] < dx[n - (q0 - 1 - mid)]) lo = mid + 1; else hi = mid;
-            }
-            int32_t a = lo, b = q0 - lo;
-            uint64_t da = dx[a], xb = dx[n - b];
-            for (int32_t q = q0; q < q1; ++q) {
-                const bool lt = da < xb;
-                pq[lt ? a : n - 1 - b] = (uint16_t)(lt ? b : a);
-                a += lt ? 1 : 0;
-                b += lt ? 0 : 1;
-                const uint64_t v = dx[lt ? a : n - b];
-                da = lt ? v : da;
-                xb = lt ? xb : v;
-            }
-        }
-    }
+    // 4: merge
+    merge_run(dx, pq, n, (int32_t)A, t, per | 1);
     __syncthreads();
 
     // 5: output, brought back into lane order
@@ -350,33 +346,8 @@ __device__ __forceinline__ void build_table_wave(int32_t n, const Src& src, cons
     }
     wave_lds_order();
 
-    // 4: merge.  An odd number of positions per thread spreads the threads' reads over the LDS
-    // banks.  The ends need no test: dx[A] is the total of both lists, so past the lights no
-    // heavy is preceded by "light A", and "heavy B" (also dx[n-B] = dx[A]) precedes no light.
-    {
-        const int32_t B = n - (int32_t)A;
-        const int32_t Em = ((n + kWave - 1) / kWave) | 1;
-        const int32_t q0 = lane * Em;
-        const int32_t q1 = q0 + Em < n ? q0 + Em : n;
-        if (q0 < n) {
-            int32_t lo = q0 > B ? q0 - B : 0, hi = q0 < (int32_t)A ? q0 : (int32_t)A;
-            while (lo < hi) {
-                const int32_t mid = (lo + hi) >> 1;
-                if (dx[mid] < dx[n - (q0 - 1 - mid)]) lo = mid + 1; else hi = mid;
-            }
-            int32_t a = lo, b = q0 - lo;
-            uint64_t da = dx[a], xb = dx[n - b];
-            for (int32_t q = q0; q < q1; ++q) {
-                const bool lt = da < xb;
-                pq[lt ? a : n - 1 - b] = (uint16_t)(lt ? b : a);
-                a += lt ? 1 : 0;
-                b += lt ? 0 : 1;
-                const uint64_t v = dx[lt ? a : n - b];
-                da = lt ? v : da;
-                xb = lt ? xb : v;
-            }
-        }
-    }
+    // 4: merge
+    merge_run(dx, pq, n, (int32_t)A, lane, ((n + kWave - 1) / kWave) | 1);
     wave_lds_order();
 
     // 5: output

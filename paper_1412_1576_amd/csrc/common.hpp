@@ -398,6 +398,14 @@ constexpr int32_t kListRowTokens = 8192;
 // ------------------------------------------------------------------------------------
 // device helpers
 // ------------------------------------------------------------------------------------
+// LDS written by some lanes of a wave is read by others after this
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 __device__ __forceinline__ uint32_t mulhi32(uint32_t a, uint32_t b) { return __umulhi(a, b); }
 
 // Philox4x32-10 (Salmon et al., SC'11): ten rounds of two 32x32->64 multiplies,

@@ -53,14 +53,6 @@ __global__ __launch_bounds__(1024) void scatter_wm_kernel(const int32_t* __restr
     }
 }
 
-// LDS written by some lanes of a wave is read by others after this
-__device__ __forceinline__ void wave_lds_order()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // blockIdx.x: tile; blockIdx.y: range of `span` topics (one range when the row fits LDS).
 // ONE: four short tiles to a workgroup, each a wave's, which meets no barrier (one range).  With
 // a workgroup to each of 53 975 words of 35 tokens the launches of the workgroups bounded the

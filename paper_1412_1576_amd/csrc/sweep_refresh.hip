@@ -36,13 +36,6 @@ struct RefreshArgs {
     uint32_t seed_lo, seed_hi, sweep;
 };
 
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // n_kd of topic k in the document whose current assignment is zs[0..L): every lane gets it
 __device__ __forceinline__ int32_t doc_count(const int32_t* zs, int32_t L, int lane, int32_t k)
 {
@@ -67,7 +60,7 @@ __global__ __launch_bounds__(64 * kRefreshWaves) void sweep_doc_refresh_kernel(R
     if (L == 0) return;
     int32_t* __restrict__ zs = smem + (size_t)wave * A.lds_doc;
     for (int32_t i = lane; i < L; i += 64) zs[i] = A.z[b + i];
-    wave_lds_sync();
+    wave_lds_order();
     const int32_t K = A.K;
     const double Ld = (double)L;
     for (int32_t base = 0; base < L; base += 64) {
@@ -154,7 +147,7 @@ __global__ __launch_bounds__(64 * kRefreshWaves) void sweep_doc_refresh_kernel(R
                 zs[base + q] = s;  // the rest of the document sees the move
                 A.znew[b + base + q] = s;
             }
-            wave_lds_sync();
+            wave_lds_order();
         }
     }
 }
@@ -183,13 +176,13 @@ __global__ __launch_bounds__(64) void sweep_doc_refresh_counts_kernel(RefreshArg
         for (int32_t i = sub; i < A.lds_counts / 4; i += G)
             reinterpret_cast<int4*>(mine)[i] = make_int4(0, 0, 0, 0);
     }
-    wave_lds_sync();
+    wave_lds_order();
     for (int32_t i = sub; i < L; i += G) {
         const uint32_t k = (uint32_t)A.z[b + i];
         zs[i] = (uint16_t)k;
         atomicAdd(reinterpret_cast<uint32_t*>(mine) + (k >> 1), 1u << (16 * (k & 1)));
     }
-    wave_lds_sync();
+    wave_lds_order();
     const int32_t K = A.K;
     const double Ld = (double)L;
     int32_t w_next = L > 0 ? A.word[b + (sub < L ? sub : L - 1)] : 0;
@@ -288,7 +281,7 @@ __global__ __launch_bounds__(64) void sweep_doc_refresh_counts_kernel(RefreshArg
                     zs[i] = (uint16_t)s;
                 }
             }
-            wave_lds_sync();
+            wave_lds_order();
         }
         if (base + sub < L) A.znew[g] = s;
     }
