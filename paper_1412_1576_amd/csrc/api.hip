@@ -390,7 +390,7 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
     if ((o.dev_alloc == nullptr) != (o.dev_free == nullptr))
         return fail(nullptr, LDA_ERR_ARG, "lda_init: dev_alloc and dev_free must be set together");
     // The kernels of the all-dense case keep a whole row or table in LDS; beyond their K the
-    // general ones (topic ranges, tables in a global workspace) take over, with every row dense.
+    // general ones (topic ranges, tables of many workgroups each) take over, with every row dense.
     const bool hybrid = (o.dense_rows != 0) || (o.dense_alias_min_count != 0) ||
                         K > max_alias_topics() || K > max_rebuild_topics();
     const int32_t H = o.dense_rows < 0 ? 0 : (o.dense_rows == 0 ? V : std::min(o.dense_rows, V));

@@ -734,7 +734,9 @@ __device__ __forceinline__ void doc_pass_chains(const SplitArgs& A, const DocVie
     // Proposals do not depend on the chain's state, so every step's proposal, its n_kd probe
     // and its n_k gather are issued before the first accept test: one round trip to L2
     // for all of them instead of one per step.
-    // Four steps at a time: more would take the registers of a second workgroup per CU.
+    // Four steps at a time: 66, 70, 72, 72 VGPRs for 5 to 8 steps with one token per thread, where all
+    // at once take 66, 78, 80, 92.  Above 64 one 1024-thread workgroup is resident on a CU; chains of
+    // up to four steps have two.
     constexpr int B = C::M < 4 ? C::M : 4;
 #pragma unroll
     for (int j0 = 0; j0 < C::M; j0 += B) {
@@ -819,7 +821,8 @@ __device__ __forceinline__ void doc_pass_chains(const SplitArgs& A, const DocVie
                 nws[u] = accept ? nw_t : nws[u];
                 nks[u] = accept ? nk_t : nks[u];
             }
-        }    }
+        }
+    }
 }
 
 // What a thread holds of its T tokens of one tile before the tile is staged.
@@ -1399,8 +1402,9 @@ int launch_sweep_split(lda_ctx* c, int32_t mh_steps)
         A.cap_tokens = c->chunk_tokens2; A.doc_block = c->sweep_block2;
         A.tile_lds_ints = tile_ints(c->chunk_tokens2, c->chunk_docs2);
     } else if (c->n_chunks2 > 0) {
-        // longer chains (default tiles): one token per thread keeps the chain's registers low
-        // enough for two 1024-thread workgroups per CU (4 steps: 28.9 instead of 33.4 ms)
+        // longer chains (default tiles): one token per thread.  Up to 4 steps take 64 VGPRs, which
+        // leaves two 1024-thread workgroups per CU (4 steps: 28.9 instead of 33.4 ms); 5 to 8 steps
+        // take 66 to 72, and one workgroup is resident
         A.doc_block = std::min(1024, (c->chunk_tokens + 63) / 64 * 64);
     }
     A.alpha = c->alpha; A.beta = c->beta; A.alphabar = c->alphabar; A.betabar = c->betabar;
