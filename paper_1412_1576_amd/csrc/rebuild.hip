@@ -427,7 +427,7 @@ int64_t hist_blocks(const lda_ctx* c)
 
 // *recount = 1 if more than `most` of the kMovedSample tokens spread evenly over z have moved.
 // Every sampled token is two cache lines of its own: one workgroup alone took 78 us for them,
-// sixteen, a token to a thread, 8 us.  *sum collects the workgroups' counts with one count of
+// sixteen, a token to a thread, 7.4 us.  *sum collects the workgroups' counts with one count of
 // arrivals above them, in one atomic; the last workgroup decides and leaves it zero.
 constexpr int32_t kMovedSample = 16384;
 constexpr int kArrivalShift = 20;
