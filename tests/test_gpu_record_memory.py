@@ -122,3 +122,47 @@ def test_out_of_memory_leaves_a_usable_context(lda_mod, oracle_mod, grant):
         sweep_both(g, o, m)
     g.close(); o.close()
     assert not live
+
+
+def test_records_that_grow_in_a_graph(lda_mod, oracle_mod):
+    """While its stream is captured a sweep may take larger records from the caller's allocator; the
+    old ones, which earlier work may still use, stay until lda_destroy."""
+    doff, words = make(50, 11, docs=300)
+    pool = torch.empty(1 << 26, dtype=torch.uint8, device="cuda")  # handed out piece by piece
+    used, live, freed = [0], set(), []
+
+    def alloc(nbytes):
+        at = used[0]
+        used[0] += (nbytes + 255) // 256 * 256
+        assert used[0] <= len(pool)
+        live.add(pool.data_ptr() + at)
+        return pool.data_ptr() + at
+
+    def free(p):
+        live.remove(p)
+        freed.append(p)
+
+    stream = torch.cuda.Stream()
+    g, o = pair(lda_mod, oracle_mod, doff, words, 50, 64, dev_alloc=alloc, dev_free=free,
+                stream=stream.cuda_stream)
+    sweep_both(g, o, 2)
+    g.build_alias(); o.build_alias()
+    g.sync()
+    before, taken = len(freed), used[0]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        g.sweep(4)
+    assert len(freed) == before and used[0] > taken
+    o.sweep(4)
+    for i in range(3):
+        with torch.cuda.stream(stream):
+            graph.replay()
+        assert np.array_equal(g.get_z(), o.get_z()), i
+        torch.cuda.synchronize()
+    g.rebuild_counts(); o.rebuild_counts()
+    assert np.array_equal(g.get_nk(), o.get_nk())
+    for m in (4, 2, 3):
+        sweep_both(g, o, m)
+    assert len(freed) == before
+    g.close(); o.close()
+    assert not live
