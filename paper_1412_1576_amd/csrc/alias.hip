@@ -105,6 +105,7 @@ struct DenseArgs {
     uint4* alias;
     uint32_t* cap;   // nullable
     uint4* metaA;    // nullable; word w at [2w]
+    const int32_t* n_dev;  // nullable: the number of words, of which n_words is the most there can be
     uint32_t lds_stride;  // bytes of list memory per wave of a workgroup whose waves build a table each
 };
 
@@ -114,21 +115,26 @@ __device__ __forceinline__ void dense_done(const DenseArgs& a, int32_t w, uint32
     if (a.metaA) a.metaA[2 * (size_t)w] = make_uint4((uint32_t)a.K, C, 0u, 0u);
 }
 
-// Tables in LDS: one workgroup per word, or (ONE) one wave per word.
-template <int E, bool ONE, int MAXB>
+// Tables in LDS: one workgroup per word, or (ONE) one wave per word.  With n_dev, whose value the
+// host does not know, the workgroups loop (LOOP; the loop costs the others 1 % where it is not needed).
+template <int E, bool ONE, int MAXB, bool LOOP>
 __global__ __launch_bounds__(MAXB) void alias_dense_lds_kernel(DenseArgs a)
 {
     extern __shared__ unsigned char smem_raw[];
     const int wv = ONE ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
-    const int32_t i = ONE ? (int32_t)(blockIdx.x * (blockDim.x >> 6)) + wv : (int32_t)blockIdx.x;
-    if (ONE && i >= a.n_words) return;
-    const int32_t w = a.words ? a.words[i] : i;
-    const int32_t* row = a.nkw + (size_t)w * (size_t)a.K;
-    const DenseIo io{row, a.nk, a.beta, a.betabar, a.alias + (size_t)w * (size_t)a.K};
-    uint64_t Q0;
-    uint32_t C;
-    build_table_regs<E, ONE>(a.K, io, io, smem_raw + (size_t)wv * a.lds_stride, Q0, C);
-    if ((threadIdx.x & (ONE ? kWave - 1 : 1023)) == 0) dense_done(a, w, C);
+    const int32_t step = ONE ? (int32_t)(gridDim.x * (blockDim.x >> 6)) : (int32_t)gridDim.x;
+    const int32_t n = LOOP ? *a.n_dev : a.n_words;
+    for (int32_t i = ONE ? (int32_t)(blockIdx.x * (blockDim.x >> 6)) + wv : (int32_t)blockIdx.x; i < n; i += step) {
+        const int32_t w = a.words ? a.words[i] : i;
+        const int32_t* row = a.nkw + (size_t)w * (size_t)a.K;
+        const DenseIo io{row, a.nk, a.beta, a.betabar, a.alias + (size_t)w * (size_t)a.K};
+        uint64_t Q0;
+        uint32_t C;
+        build_table_regs<E, ONE>(a.K, io, io, smem_raw + (size_t)wv * a.lds_stride, Q0, C);
+        if ((threadIdx.x & (ONE ? kWave - 1 : 1023)) == 0) dense_done(a, w, C);
+        if constexpr (!LOOP) return;  // a table each
+        if constexpr (ONE) wave_lds_order(); else __syncthreads();  // before the lists are written again
+    }
 }
 
 // the same tables for the builder of alias_split.hpp
@@ -329,17 +335,23 @@ int with_shape(const TableShape& s, F&& f)
     return f(IntConst<12>{}, IntConst<0>{}, IntConst<1024>{});
 }
 
-int launch_dense_lds(lda_ctx* c, DenseArgs a)
+constexpr int32_t kDenseLoopBlocks = 1024;  // beyond the tables the host knows of
+
+int launch_dense_lds(lda_ctx* c, DenseArgs a, int32_t n_known)
 {
     const TableShape s = table_shape(a.K);
     const int per = s.one ? s.threads / kWave : 1;  // tables per workgroup
     a.lds_stride = (uint32_t)alias_regs_lds_bytes((size_t)a.K);
     const size_t lds = (size_t)a.lds_stride * (size_t)per;
     return with_shape(s, [&](auto e, auto one, auto maxb) -> int {
-        auto kern = alias_dense_lds_kernel<decltype(e)::value, decltype(one)::value != 0, decltype(maxb)::value>;
+        constexpr int E = decltype(e)::value, MAXB = decltype(maxb)::value;
+        constexpr bool ONE = decltype(one)::value != 0;
+        auto kern = a.n_dev ? alias_dense_lds_kernel<E, ONE, MAXB, true> : alias_dense_lds_kernel<E, ONE, MAXB, false>;
         const int rc = set_lds(c, kern, lds);
         if (rc != LDA_OK) return rc;
-        hipLaunchKernelGGL(kern, dim3((a.n_words + per - 1) / per), dim3(s.threads), lds, c->stream, a);
+        const int32_t blocks = (n_known + per - 1) / per +
+                               std::min((a.n_words - n_known + per - 1) / per, kDenseLoopBlocks);
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(s.threads), lds, c->stream, a);
         LDA_HIP(c, hipGetLastError());
         return LDA_OK;
     });
@@ -472,7 +484,44 @@ int launch_alias_build(lda_ctx* c)
     a.words = nullptr; a.n_words = c->V; a.nkw = c->d_nkw; a.nk = c->d_nk; a.K = K;
     a.beta = c->beta; a.betabar = c->betabar; a.alias = c->d_alias; a.cap = c->d_cap;
     a.metaA = nullptr;
-    return launch_dense_lds(c, a);
+    return launch_dense_lds(c, a, a.n_words);
+}
+
+int launch_dense_listed(lda_ctx* c)
+{
+    DenseArgs a{};
+    a.words = c->d_dense_words; a.n_words = c->n_dense_fixed + c->n_implied; a.n_dev = c->d_n_dense;
+    a.nkw = c->d_nkw; a.nk = c->d_nk; a.K = c->K; a.beta = c->beta; a.betabar = c->betabar;
+    a.alias = c->d_alias; a.cap = c->d_cap;
+    return launch_dense_lds(c, a, c->n_dense_fixed);
+}
+
+int launch_dense_table(lda_ctx* c, int32_t w)
+{
+    DenseArgs a{};
+    const size_t wk = (size_t)w * (size_t)c->K;
+    a.n_words = 1; a.nkw = c->d_nkw + wk; a.nk = c->d_nk; a.K = c->K; a.beta = c->beta; a.betabar = c->betabar;
+    a.alias = c->d_alias + wk; a.cap = c->d_cap + w;
+    return launch_dense_lds(c, a, 1);
+}
+
+// The dense tables of words whose table is implied are made when a sweep of one kernel, which draws
+// from bins, is asked for; lda_build_alias makes the form that the last sweep drew from.
+int have_implied_tables(lda_ctx* c)
+{
+    if (c->implied_built) return LDA_OK;
+    int rc = launch_implied_tables(c);
+    if (rc == LDA_OK && !c->all_dense_built) rc = launch_dense_listed(c);
+    c->implied_built = rc == LDA_OK;
+    return rc;
+}
+
+int have_all_dense_tables(lda_ctx* c)
+{
+    if (c->all_dense_built) return LDA_OK;
+    const int rc = launch_alias_build(c);
+    c->all_dense_built = rc == LDA_OK;
+    return rc;
 }
 
 namespace {
@@ -572,7 +621,7 @@ int launch_alias_build_hybrid(lda_ctx* c)
         a.nk = c->d_nk; a.K = K; a.beta = c->beta; a.betabar = c->betabar; a.alias = c->d_alias;
         a.cap = c->d_cap; a.metaA = c->d_metaA;
         if (K <= lds_max) {
-            rc = launch_dense_lds(c, a);
+            rc = launch_dense_lds(c, a, a.n_words);
         } else {
             rc = launch_big_tables(c, c->stream, c->big_dense, DenseTables{a});
         }

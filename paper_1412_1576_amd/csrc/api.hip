@@ -105,6 +105,9 @@ void free_all(lda_ctx* c)
     c->side_fork = c->side_join = nullptr;
     c->side_stream = nullptr;
     dev_free(c, c->d_woff); dev_free(c, c->d_nkw); dev_free(c, c->d_nk);
+    dev_free(c, c->d_im_words); dev_free(c, c->d_im_off); dev_free(c, c->d_im_head); dev_free(c, c->d_im_key);
+    dev_free(c, c->d_im_corr); dev_free(c, c->d_im_x); dev_free(c, c->d_im_qz); dev_free(c, c->d_im_pz);
+    dev_free(c, c->d_im_sum); dev_free(c, c->d_dense_words); dev_free(c, c->d_n_dense); dev_free(c, c->d_im_pieces);
     dev_free(c, c->d_alias); dev_free(c, c->d_cap); dev_free(c, c->d_chunk_doc); dev_free(c, c->d_chunk_tok); dev_free(c, c->d_tokdoc); dev_free(c, c->d_chunk_doc2); dev_free(c, c->d_chunk_tok2); dev_free(c, c->d_tokdoc2); dev_free(c, c->d_long_doc);
     dev_free(c, c->d_long_slot); dev_free(c, c->d_long_keys); dev_free(c, c->d_long_cnts); dev_free(c, c->d_long_first);
     dev_free(c, c->d_tiles); dev_free(c, c->d_list_tiles); dev_free(c, c->d_multi_words); dev_free(c, c->d_partial); dev_free(c, c->d_lg_terms); dev_free(c, c->d_row);
@@ -579,6 +582,7 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
         TRY(setup_hybrid(c, woff));
         any_dense_alias = c->n_dense_alias > 0;
     }
+    TRY(setup_implied(c, woff));
     TRY(setup_split_sweep(c, woff));
     TRY(dev_alloc(c, &c->d_alias, any_dense_alias ? VK : 1, "alias tables"));
     std::vector<RebuildTile> tiles, list_tiles;
@@ -640,10 +644,13 @@ int lda_build_alias(lda_ctx* c)
     if (c->state != COUNTS_VALID && c->state != ALIAS_VALID)
         return fail(c, LDA_ERR_STATE, "lda_build_alias: counts are stale (call lda_rebuild_counts)");
     int rc;
+    c->implied_built = c->all_dense_built = false;
     if (c->hybrid) {
         rc = launch_alias_build_hybrid(c);
+    } else if (c->n_implied > 0 && !c->want_all_dense) {
+        rc = have_implied_tables(c);
     } else {
-        rc = launch_alias_build(c);
+        rc = have_all_dense_tables(c);
     }
     if (rc == LDA_OK) c->state = ALIAS_VALID;
     return rc;
@@ -673,9 +680,13 @@ int lda_sweep(lda_ctx* c, int32_t mh_steps)
         c->td_valid = false;
         c->pass_ev_recorded = false;
     } else if (split_sweep_supported(c, mh_steps)) {
-        rc = launch_sweep_split(c, mh_steps);
+        rc = c->n_implied > 0 ? have_implied_tables(c) : LDA_OK;
+        if (rc == LDA_OK) rc = launch_sweep_split(c, mh_steps);
+        c->want_all_dense = false;
     } else {
-        rc = c->hybrid ? launch_sweep_hybrid(c, mh_steps) : launch_sweep(c, mh_steps);
+        rc = c->hybrid ? LDA_OK : have_all_dense_tables(c);
+        c->want_all_dense = true;
+        if (rc == LDA_OK) rc = c->hybrid ? launch_sweep_hybrid(c, mh_steps) : launch_sweep(c, mh_steps);
         c->zt_current = false;  // the fused kernels write the doc-major assignment only
         c->td_valid = false;
         c->pass_ev_recorded = false;
@@ -844,6 +855,10 @@ int lda_get_alias_row(lda_ctx* c, int32_t w, uint32_t* split, uint32_t* alias, u
     if (c->state != ALIAS_VALID) return fail(c, LDA_ERR_STATE, "lda_get_alias_row: no valid tables");
     if (c->hybrid && !(c->h_wkind[w] & 2))
         return fail(c, LDA_ERR_ARG, "lda_get_alias_row: word %d draws from the mixture", w);
+    if (!c->hybrid && !c->all_dense_built && c->h_table_form[w] != 0) {
+        const int rc = launch_dense_table(c, w);
+        if (rc != LDA_OK) return rc;
+    }
     std::vector<uint4> h((size_t)c->K);
     LDA_HIP(c, hipMemcpyAsync(h.data(), c->d_alias + (size_t)w * (size_t)c->K,
                               sizeof(uint4) * (size_t)c->K, hipMemcpyDeviceToHost, c->stream));

@@ -141,6 +141,26 @@ struct lda_ctx {
     int32_t* d_nk = nullptr;    // [K]
     uint4* d_alias = nullptr;   // [V*K] (split, alias, n_kw[bin], n_kw[alias]) per bin
     uint32_t* d_cap = nullptr;  // [V] bin capacity of the word's table
+    // Implied tables (implied.hpp): of words with few tokens, instead of K bins each.  A table's
+    // entries start at im_off[w]; h_table_form: 0 dense, 1 implied, 2 no tokens (no table is drawn from).
+    static constexpr int kImpliedClasses = 2;
+    int32_t n_implied = 0, n_im_class[kImpliedClasses] = {};
+    std::vector<uint8_t> h_table_form;   // empty: every word has its dense table
+    int32_t* d_im_words = nullptr;
+    uint32_t* d_im_off = nullptr;        // [V+1]
+    uint4* d_im_head = nullptr;          // [V]
+    uint32_t* d_im_key = nullptr;
+    uint64_t *d_im_corr = nullptr, *d_im_x = nullptr;
+    uint32_t* d_im_qz = nullptr;         // [K]
+    uint64_t* d_im_pz = nullptr;         // [K+1]
+    uint64_t* d_im_sum = nullptr;        // [3]
+    int32_t* d_dense_words = nullptr;    // words with a dense table: n_dense_fixed, and those whose sums
+    int32_t* d_n_dense = nullptr;        //   do not fit the implied form; how many there are in all
+    int32_t n_dense_fixed = 0;
+    int4* d_im_pieces = nullptr;         // pieces of the word pass, as d_gather_pieces
+    int32_t n_im_pieces = 0;
+    // which forms hold the tables of the current counts, and which one the last sweep drew from
+    bool implied_built = false, all_dense_built = false, want_all_dense = false;
     // sweep tiling: chunk c covers documents [chunk_doc[c], chunk_doc[c+1])
     int32_t* d_chunk_doc = nullptr;
     int32_t* d_chunk_tok = nullptr;  // [n_chunks+1] first token of chunk c (= doff[chunk_doc[c]])
@@ -302,6 +322,14 @@ int device_malloc(lda_ctx* c, T** p, size_t count, const char* what)
 int launch_layout(lda_ctx* c, const int32_t* h_word);      // word-major order, woff, z init
 int launch_alias_build(lda_ctx* c);
 int launch_alias_build_hybrid(lda_ctx* c);
+int launch_dense_listed(lda_ctx* c);                       // dense tables of the words in d_dense_words
+int launch_dense_table(lda_ctx* c, int32_t w);             // of one word (all-dense store)
+// implied tables (implied.hpp)
+int setup_implied(lda_ctx* c, const std::vector<int32_t>& woff);
+int launch_implied_tables(lda_ctx* c);
+// the tables a sweep draws from, if lda_build_alias has made the other form (all-dense store)
+int have_implied_tables(lda_ctx* c);
+int have_all_dense_tables(lda_ctx* c);
 int launch_rebuild_hybrid(lda_ctx* c);
 int launch_sweep_hybrid(lda_ctx* c, int32_t mh_steps);
 int launch_loglik_word_hybrid(lda_ctx* c, double* word_part);

@@ -1,0 +1,125 @@
+"""Words whose dense table is implied by a few sums: sweeps against the oracle, bit for bit, where
+the form begins and ends (words of 1, 64, 256, 1024 tokens and one more, words without tokens), where
+a word's sums do not fit it (topics of very uneven size, weights that need a shift), in turn
+with sweeps that draw from bins, and after the incremental count update.  The form is used where
+the words it suits have 2^21 bins or more together, and a word suits with at most K / 2 tokens."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import check_alias
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lda_mod():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_1412_1576_amd import lda
+    lda.load_library()
+    return lda
+
+
+def corpus_of(counts, seed, L=90):
+    """Documents of about L tokens over words with the given corpus frequencies."""
+    words = np.repeat(np.arange(len(counts), dtype=np.int32), counts)
+    np.random.default_rng(seed).shuffle(words)
+    return np.append(np.arange(0, len(words), L), len(words)).astype(np.int64), words
+
+
+def pair(lda_mod, oracle_mod, doff, words, V, K, beta=0.01, **opt):
+    return (lda_mod.Lda(doff, words, V, K, 0.1, beta, seed=3, **opt),
+            oracle_mod.Oracle(doff, words, V, K, 0.1, beta, seed=3))
+
+
+def step(g, o, m, update=False, tables=()):
+    for c in (g, o):
+        c.build_alias()
+    check_alias(g, o, tables, tag="%d steps" % m)
+    for c in (g, o):
+        c.sweep(m)
+    g.update_counts() if update else g.rebuild_counts()
+    o.rebuild_counts()
+    assert np.array_equal(g.get_z(), o.get_z()), m
+    assert np.array_equal(g.get_nk(), o.get_nk()), m
+
+
+def frequencies(V, K, seed):
+    """Few to many tokens per word, the ends of the form's ranges, words without tokens."""
+    n = (1 + 8 * np.random.default_rng(seed).pareto(1.0, V)).astype(np.int64)
+    n = np.minimum(n, 6000)
+    ends = [0, 0, 1, 2, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 2047, 2048, K // 2, K // 2 + 1, 0]
+    n[10:10 + len(ends)] = ends
+    n[-3:] = (0, 1, 0)
+    return n
+
+
+# K: one topic range below and above what a thread of the shared sums handles, odd, the largest
+@pytest.mark.parametrize("V,K", [(11000, 257), (2600, 1024), (1200, 2051), (560, 4099), (420, 12287), (420, 12288)])
+@pytest.mark.parametrize("m", [2, 3])
+def test_sweeps(lda_mod, oracle_mod, V, K, m):
+    n = frequencies(V, K, K)
+    doff, words = corpus_of(n, K)
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K)
+    some = list(range(0, 30)) + [V - 2, V - 1]
+    for it in range(3):
+        step(g, o, m, tables=some)
+    g.close(); o.close()
+
+
+# a topic size that varies by powers: bins without tokens are heavies for the rarer words
+@pytest.mark.parametrize("power", [2, 6])
+@pytest.mark.parametrize("beta", [1e-6, 0.01, 3.0])
+def test_uneven_topics(lda_mod, oracle_mod, power, beta):
+    V, K = 2600, 1024
+    doff, words = corpus_of(frequencies(V, K, 8), 8)
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K, beta=beta)
+    z = (K * np.random.default_rng(4).random(len(words)) ** power).astype(np.int32)
+    for c in (g, o):
+        c.set_z(z, 7)
+        c.rebuild_counts()
+    for m in (2, 1, 4):
+        step(g, o, m, tables=range(0, V, 97))
+    g.close(); o.close()
+
+
+def test_few_tokens(lda_mod, oracle_mod):
+    """Most words have a share of the corpus so large that their weights need a shift."""
+    V, K = 600, 4001
+    doff, words = corpus_of(np.full(V, 3) + np.arange(V) // 20, 2, L=7)
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K)
+    for m in (2, 4, 2):
+        step(g, o, m, tables=(0, 300, 599))
+    g.close(); o.close()
+
+
+def test_in_turn_with_one_pass_sweeps(lda_mod, oracle_mod):
+    V, K = 2600, 1024
+    doff, words = corpus_of(frequencies(V, K, 5), 5)
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K)
+    for m in (2, 9, 9, 2, 4, 10, 2, 2):
+        step(g, o, m, tables=(5, 13, 1000))
+    g.close(); o.close()
+
+
+def test_after_the_incremental_update(lda_mod, oracle_mod):
+    V, K = 9000, 300
+    doff, words = corpus_of(frequencies(V, K, 6), 6, L=12)
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K)
+    for m in (2, 2, 3):
+        step(g, o, m, update=True, tables=(5, 13, 8000))
+    g.close(); o.close()
+
+
+def test_record_order_and_word_chains(lda_mod, oracle_mod):
+    V, K = 2600, 1024
+    doff, words = corpus_of(frequencies(V, K, 9), 9)
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K, record_bucket_tokens=4096)
+    for m in (2, 4):
+        step(g, o, m)
+    g.close(); o.close()
+    g = lda_mod.Lda(doff, words, V, K, 0.1, 0.01, seed=3, proposal_mode=1)
+    o = oracle_mod.Oracle(doff, words, V, K, 0.1, 0.01, seed=3, proposal_mode=1)
+    for m in (1, 3, 1, 1):
+        step(g, o, m)
+    g.close(); o.close()
