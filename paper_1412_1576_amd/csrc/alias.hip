@@ -11,6 +11,7 @@
 #include "alias_build.hpp"
 #include "alias_regs.hpp"
 #include "alias_split.hpp"
+#include "implied.hpp"
 
 namespace lda {
 
@@ -24,6 +25,7 @@ __device__ __forceinline__ uint64_t quantise40(double a)
 // dense form: entry k is topic k.  A bin also carries the word-topic counts of its two outcomes,
 // so the sweep's accept test needs no second gather.
 struct DenseIo {
+    static constexpr bool kListed = false;
     const int32_t* __restrict__ row;
     const int32_t* __restrict__ nk;
     double beta, betabar;
@@ -45,9 +47,65 @@ struct DenseIo {
     }
 };
 
+// The same table from the word's list (implied.hpp) and the masses of topics without tokens; the row
+// only exists in LDS.
+struct DenseListIo {
+    static constexpr bool kListed = true;
+    const uint32_t* __restrict__ key;
+    int32_t n_key;
+    const uint64_t *__restrict__ sum0, *__restrict__ sum;
+    const uint32_t* __restrict__ qz;
+    const int32_t* __restrict__ nk;
+    double beta, betabar;
+    uint4* __restrict__ out;
+    mutable const int32_t* row;
+    struct Raw { int32_t count; };
+    struct Loaded { int32_t other; };
+    __device__ __forceinline__ uint64_t Q0() const { return *sum0; }
+    __device__ __forceinline__ uint64_t Q() const { return *sum; }
+    __device__ __forceinline__ uint64_t weight(int32_t count, int32_t k) const
+    {
+#pragma clang fp contract(off)
+        return quantise40(((double)count + beta) / ((double)nk[k] + betabar));
+    }
+    __device__ __forceinline__ uint64_t mass(int32_t k) const
+    {
+        const uint32_t q = qz[k];
+        return q == 0xFFFFFFFFu ? weight(0, k) : q;  // (saturated)
+    }
+    __device__ __forceinline__ void patch(uint64_t* m, int32_t t, int32_t threads) const
+    {
+        for (int32_t i = t; i < n_key; i += threads) {
+            const uint32_t v = key[i];
+            const int32_t k = (int32_t)(v >> kImpliedTopicShift);
+            m[k] = weight((int32_t)(v & kImpliedCount), k);
+        }
+    }
+    __device__ __forceinline__ void clear(int32_t* r, int32_t n, int32_t t, int32_t threads) const
+    {
+        row = r;
+        for (int32_t k = t; k < n; k += threads) r[k] = 0;
+    }
+    __device__ __forceinline__ void fill(int32_t* r, int32_t t, int32_t threads) const
+    {
+        for (int32_t i = t; i < n_key; i += threads) {
+            const uint32_t v = key[i];
+            r[v >> kImpliedTopicShift] = (int32_t)(v & kImpliedCount);
+        }
+    }
+    __device__ __forceinline__ Raw load(int32_t k) const { return Raw{row[k]}; }
+    __device__ __forceinline__ Loaded load(int32_t, uint32_t al, const Raw&) const { return Loaded{row[al]}; }
+    __device__ __forceinline__ void store(int32_t k, uint32_t split, uint32_t al, const Raw& r,
+                                          const Loaded& v) const
+    {
+        out[k] = make_uint4(split, al, (uint32_t)r.count, (uint32_t)v.other);
+    }
+};
+
 // sparse term of the mixture: entry i is the word's i-th non-zero topic (ascending); its bin
 // carries the topics and counts of both outcomes
 struct MixIo {
+    static constexpr bool kListed = false;
     const int32_t* __restrict__ topic;
     const int32_t* __restrict__ count;
     const int32_t* __restrict__ nk;
@@ -75,6 +133,7 @@ struct MixIo {
 
 // shared beta term of the mixture: entry k is topic k
 struct BetaIo {
+    static constexpr bool kListed = false;
     const int32_t* __restrict__ nk;
     double beta, betabar;
     uint2* __restrict__ out;
@@ -105,7 +164,12 @@ struct DenseArgs {
     uint4* alias;
     uint32_t* cap;   // nullable
     uint4* metaA;    // nullable; word w at [2w]
-    const int32_t* n_dev;  // nullable: the number of words, of which n_words is the most there can be
+    // words whose tables are made from lists: how many (n_words is the most there can be), and these
+    const int32_t* n_dev;
+    const int4* misfits;
+    const uint32_t* key;
+    const uint64_t *sum0, *sum;  // sums of the weights, in the place of a list's running sums
+    const uint32_t* qz;
     uint32_t lds_stride;  // bytes of list memory per wave of a workgroup whose waves build a table each
 };
 
@@ -115,24 +179,50 @@ __device__ __forceinline__ void dense_done(const DenseArgs& a, int32_t w, uint32
     if (a.metaA) a.metaA[2 * (size_t)w] = make_uint4((uint32_t)a.K, C, 0u, 0u);
 }
 
-// Tables in LDS: one workgroup per word, or (ONE) one wave per word.  With n_dev, whose value the
-// host does not know, the workgroups loop (LOOP; the loop costs the others 1 % where it is not needed).
-template <int E, bool ONE, int MAXB, bool LOOP>
+// Tables in LDS: one workgroup per word, or (ONE) one wave per word.
+template <int E, bool ONE, int MAXB>
 __global__ __launch_bounds__(MAXB) void alias_dense_lds_kernel(DenseArgs a)
 {
     extern __shared__ unsigned char smem_raw[];
     const int wv = ONE ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+    const int32_t i = ONE ? (int32_t)(blockIdx.x * (blockDim.x >> 6)) + wv : (int32_t)blockIdx.x;
+    if (ONE && i >= a.n_words) return;
+    const int32_t w = a.words ? a.words[i] : i;
+    const int32_t* row = a.nkw + (size_t)w * (size_t)a.K;
+    const DenseIo io{row, a.nk, a.beta, a.betabar, a.alias + (size_t)w * (size_t)a.K};
+    uint64_t Q0;
+    uint32_t C;
+    build_table_regs<E, ONE>(a.K, io, io, smem_raw + (size_t)wv * a.lds_stride, Q0, C);
+    if ((threadIdx.x & (ONE ? kWave - 1 : 1023)) == 0) dense_done(a, w, C);
+}
+
+// The same for the words whose sums did not fit the implied form, from their lists.  Only the device
+// knows how many there are, so the workgroups loop.
+template <int E, bool ONE, int MAXB>
+__global__ __launch_bounds__(MAXB, MAXB == 256 ? 8 : 1) void alias_dense_list_kernel(DenseArgs a)
+{
+    extern __shared__ unsigned char smem_raw[];
+    const int wv = ONE ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
     const int32_t step = ONE ? (int32_t)(gridDim.x * (blockDim.x >> 6)) : (int32_t)gridDim.x;
-    const int32_t n = LOOP ? *a.n_dev : a.n_words;
-    for (int32_t i = ONE ? (int32_t)(blockIdx.x * (blockDim.x >> 6)) + wv : (int32_t)blockIdx.x; i < n; i += step) {
-        const int32_t w = a.words ? a.words[i] : i;
-        const int32_t* row = a.nkw + (size_t)w * (size_t)a.K;
-        const DenseIo io{row, a.nk, a.beta, a.betabar, a.alias + (size_t)w * (size_t)a.K};
+    const int32_t n = *a.n_dev;
+    int32_t i = ONE ? (int32_t)(blockIdx.x * (blockDim.x >> 6)) + wv : (int32_t)blockIdx.x;
+    if (i >= n) return;
+    int4 next = a.misfits[i];
+    for (; i < n; i += step) {
+        const int32_t w = next.x;  // (word, list offset, entries)
+        const size_t off = (uint32_t)next.y;
+        const int32_t n_key = next.z;
+        next = a.misfits[i + step < n ? i + step : i];
+        // a fresh K every time, or the compiler keeps what it derives from it in registers over the
+        // loop (128 instead of 86 VGPRs at E = 12, and spills: twice the time)
+        int32_t K = a.K;
+        asm volatile("" : "+s"(K));
+        const DenseListIo io{a.key + off, n_key, a.sum0 + off, a.sum + off, a.qz, a.nk, a.beta, a.betabar,
+                             a.alias + (size_t)w * (size_t)K, nullptr};
         uint64_t Q0;
         uint32_t C;
-        build_table_regs<E, ONE>(a.K, io, io, smem_raw + (size_t)wv * a.lds_stride, Q0, C);
+        build_table_regs<E, ONE>(K, io, io, smem_raw + (size_t)wv * a.lds_stride, Q0, C);
         if ((threadIdx.x & (ONE ? kWave - 1 : 1023)) == 0) dense_done(a, w, C);
-        if constexpr (!LOOP) return;  // a table each
         if constexpr (ONE) wave_lds_order(); else __syncthreads();  // before the lists are written again
     }
 }
@@ -335,10 +425,9 @@ int with_shape(const TableShape& s, F&& f)
     return f(IntConst<12>{}, IntConst<0>{}, IntConst<1024>{});
 }
 
-constexpr int32_t kDenseLoopBlocks = 1024;  // beyond the tables the host knows of
-
-int launch_dense_lds(lda_ctx* c, DenseArgs a, int32_t n_known)
+int launch_dense_lds(lda_ctx* c, DenseArgs a)
 {
+    if (a.n_words <= 0) return LDA_OK;
     const TableShape s = table_shape(a.K);
     const int per = s.one ? s.threads / kWave : 1;  // tables per workgroup
     a.lds_stride = (uint32_t)alias_regs_lds_bytes((size_t)a.K);
@@ -346,11 +435,14 @@ int launch_dense_lds(lda_ctx* c, DenseArgs a, int32_t n_known)
     return with_shape(s, [&](auto e, auto one, auto maxb) -> int {
         constexpr int E = decltype(e)::value, MAXB = decltype(maxb)::value;
         constexpr bool ONE = decltype(one)::value != 0;
-        auto kern = a.n_dev ? alias_dense_lds_kernel<E, ONE, MAXB, true> : alias_dense_lds_kernel<E, ONE, MAXB, false>;
+        auto kern = a.n_dev ? alias_dense_list_kernel<E, ONE, MAXB> : alias_dense_lds_kernel<E, ONE, MAXB>;
         const int rc = set_lds(c, kern, lds);
         if (rc != LDA_OK) return rc;
-        const int32_t blocks = (n_known + per - 1) / per +
-                               std::min((a.n_words - n_known + per - 1) / per, kDenseLoopBlocks);
+        int32_t blocks = (a.n_words + per - 1) / per;
+        if (a.n_dev) {  // as many as the chip holds
+            const int32_t most = std::min<int32_t>(2048 / s.threads, (int32_t)(163840 / (lds + 1024)));
+            blocks = std::min(blocks, 256 * std::max(1, most));
+        }
         hipLaunchKernelGGL(kern, dim3(blocks), dim3(s.threads), lds, c->stream, a);
         LDA_HIP(c, hipGetLastError());
         return LDA_OK;
@@ -484,16 +576,20 @@ int launch_alias_build(lda_ctx* c)
     a.words = nullptr; a.n_words = c->V; a.nkw = c->d_nkw; a.nk = c->d_nk; a.K = K;
     a.beta = c->beta; a.betabar = c->betabar; a.alias = c->d_alias; a.cap = c->d_cap;
     a.metaA = nullptr;
-    return launch_dense_lds(c, a, a.n_words);
+    return launch_dense_lds(c, a);
 }
 
 int launch_dense_listed(lda_ctx* c)
 {
     DenseArgs a{};
-    a.words = c->d_dense_words; a.n_words = c->n_dense_fixed + c->n_implied; a.n_dev = c->d_n_dense;
+    a.words = c->d_fixed_words; a.n_words = c->n_fixed_words;
     a.nkw = c->d_nkw; a.nk = c->d_nk; a.K = c->K; a.beta = c->beta; a.betabar = c->betabar;
     a.alias = c->d_alias; a.cap = c->d_cap;
-    return launch_dense_lds(c, a, c->n_dense_fixed);
+    const int rc = launch_dense_lds(c, a);
+    if (rc != LDA_OK) return rc;
+    a.misfits = c->d_misfits; a.n_words = c->n_implied; a.n_dev = c->d_n_misfits; a.key = c->d_im_key;
+    a.sum0 = c->d_im_corr; a.sum = c->d_im_x; a.qz = c->d_im_qz;
+    return launch_dense_lds(c, a);
 }
 
 int launch_dense_table(lda_ctx* c, int32_t w)
@@ -502,7 +598,7 @@ int launch_dense_table(lda_ctx* c, int32_t w)
     const size_t wk = (size_t)w * (size_t)c->K;
     a.n_words = 1; a.nkw = c->d_nkw + wk; a.nk = c->d_nk; a.K = c->K; a.beta = c->beta; a.betabar = c->betabar;
     a.alias = c->d_alias + wk; a.cap = c->d_cap + w;
-    return launch_dense_lds(c, a, 1);
+    return launch_dense_lds(c, a);
 }
 
 // The dense tables of words whose table is implied are made when a sweep of one kernel, which draws
@@ -519,7 +615,8 @@ int have_implied_tables(lda_ctx* c)
 int have_all_dense_tables(lda_ctx* c)
 {
     if (c->all_dense_built) return LDA_OK;
-    const int rc = launch_alias_build(c);
+    int rc = c->n_implied > 0 ? launch_rows_from_lists(c, -1) : LDA_OK;
+    if (rc == LDA_OK) rc = launch_alias_build(c);
     c->all_dense_built = rc == LDA_OK;
     return rc;
 }
@@ -621,7 +718,7 @@ int launch_alias_build_hybrid(lda_ctx* c)
         a.nk = c->d_nk; a.K = K; a.beta = c->beta; a.betabar = c->betabar; a.alias = c->d_alias;
         a.cap = c->d_cap; a.metaA = c->d_metaA;
         if (K <= lds_max) {
-            rc = launch_dense_lds(c, a, a.n_words);
+            rc = launch_dense_lds(c, a);
         } else {
             rc = launch_big_tables(c, c->stream, c->big_dense, DenseTables{a});
         }

@@ -18,6 +18,10 @@
 // An Io describes one kind of table to both: Raw load(k) and void load2(Raw&) fetch what entry
 // k's weight comes from, q0(Raw) is the weight, Loaded load(k, alias, raw) gathers what the
 // entry's output needs and store(k, split, alias, raw, loaded) writes it, once per entry.
+// kListed: the entries are those of a list among n that differ from each other little: mass(k) is
+// entry k's weight if it is not in the list, patch(weights, thread, threads) writes those in it, Q0()
+// and Q() are the sums known beforehand; load() reads an array of n ints in LDS, made by
+// clear(array, n, thread, threads) and fill(array, thread, threads), and is called late.
 #pragma once
 
 #include "common.hpp"

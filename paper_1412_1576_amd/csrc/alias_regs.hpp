@@ -102,31 +102,50 @@ __device__ __forceinline__ void build_table_workgroup(int32_t n, const Src& src,
     // 1: the loads of all entries of a thread are in flight together
     typename Src::Raw raw[E];
     uint64_t m[E];
+    uint64_t p0 = 0, p1 = 0, Q0, Q;
+    if constexpr (Src::kListed) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int32_t k = e * T + t;
-        raw[e] = src.load(k < n ? k : n - 1);
-    }
-#pragma unroll
-    for (int e = 0; e < E; ++e) src.load2(raw[e]);
-    uint64_t p0 = 0, p1 = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int32_t k = e * T + t;
-        if (k < n) {
-            const uint64_t q = src.q0(raw[e]);
-            dx[k] = q;
-            p0 += q;
-            p1 += q < 1 ? 1 : q;
+        for (int e = 0; e < E; ++e) {
+            const int32_t k = e * T + t;
+            m[e] = src.mass(k < n ? k : n - 1);
         }
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int32_t k = e * T + t;
+            if (k < n) dx[k] = m[e];
+        }
+        __syncthreads();
+        src.patch(dx, t, T);
+        __syncthreads();
+        Q0 = src.Q0();
+        Q = src.Q();
+    } else {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int32_t k = e * T + t;
+            raw[e] = src.load(k < n ? k : n - 1);
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) src.load2(raw[e]);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int32_t k = e * T + t;
+            if (k < n) {
+                const uint64_t q = src.q0(raw[e]);
+                dx[k] = q;
+                p0 += q;
+                p1 += q < 1 ? 1 : q;
+            }
+        }
+        Q0 = wave_total_u64(p0);
+        Q = wave_total_u64(p1);
+        if (lane == 0) { w_a[wv] = Q0; w_q[wv] = Q; }
+        __syncthreads();
+        Q0 = Q = 0;
+        for (int i = 0; i < nw; ++i) { Q0 += w_a[i]; Q += w_q[i]; }
     }
-    uint64_t Q0 = wave_total_u64(p0), Q = wave_total_u64(p1);
-    if (lane == 0) { w_a[wv] = Q0; w_q[wv] = Q; }
-    __syncthreads();
 #pragma unroll
     for (int e = 0; e < E; ++e) m[e] = e < rn ? dx[r0 + e] : 0ull;
-    Q0 = Q = 0;
-    for (int i = 0; i < nw; ++i) { Q0 += w_a[i]; Q += w_q[i]; }
     int sh = 0;
     while ((Q0 >> sh) >= ((uint64_t)n << 31)) ++sh;
     if (sh > 0) {  // uniform
@@ -226,7 +245,16 @@ __device__ __forceinline__ void build_table_workgroup(int32_t n, const Src& src,
 #pragma unroll
     for (int e = 0; e < E; ++e)
         if (e < rn) dx[r0 + e] = m[e];
+    if constexpr (Src::kListed) {  // hidx and pq, 4 bytes an entry, are no longer read
+        sink.clear(reinterpret_cast<int32_t*>(hidx), n, t, T);
+        __syncthreads();
+        sink.fill(reinterpret_cast<int32_t*>(hidx), t, T);
+    }
     __syncthreads();
+    if constexpr (Src::kListed) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) raw[e] = src.load(e * T + t < n ? e * T + t : n - 1);
+    }
     typename Sink::Loaded got[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -263,23 +291,44 @@ __device__ __forceinline__ void build_table_wave(int32_t n, const Src& src, cons
     // 1: the loads of all entries of a lane are in flight together
     typename Src::Raw raw[E];
     uint64_t m[E];
+    uint64_t p0 = 0, p1 = 0, Q0, Q;
+    if constexpr (Src::kListed) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int32_t k = e * kWave + lane;
-        raw[e] = src.load(k < n ? k : n - 1);
-    }
-#pragma unroll
-    for (int e = 0; e < E; ++e) src.load2(raw[e]);
-    uint64_t p0 = 0, p1 = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        m[e] = src.q0(raw[e]);
-        if (e * kWave + lane < n) {
-            p0 += m[e];
-            p1 += m[e] < 1 ? 1 : m[e];
+        for (int e = 0; e < E; ++e) {
+            const int32_t k = e * kWave + lane;
+            m[e] = src.mass(k < n ? k : n - 1);
+            if (k < n) dx[k] = m[e];
         }
+        wave_lds_order();
+        src.patch(dx, lane, kWave);
+        wave_lds_order();
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int32_t k = e * kWave + lane;
+            m[e] = dx[k < n ? k : n - 1];
+        }
+        wave_lds_order();
+        Q0 = src.Q0();
+        Q = src.Q();
+    } else {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int32_t k = e * kWave + lane;
+            raw[e] = src.load(k < n ? k : n - 1);
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) src.load2(raw[e]);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            m[e] = src.q0(raw[e]);
+            if (e * kWave + lane < n) {
+                p0 += m[e];
+                p1 += m[e] < 1 ? 1 : m[e];
+            }
+        }
+        Q0 = wave_total_u64(p0);
+        Q = wave_total_u64(p1);
     }
-    uint64_t Q0 = wave_total_u64(p0), Q = wave_total_u64(p1);
     int sh = 0;
     while ((Q0 >> sh) >= ((uint64_t)n << 31)) ++sh;
     if (sh > 0) {  // uniform
@@ -377,6 +426,15 @@ __device__ __forceinline__ void build_table_wave(int32_t n, const Src& src, cons
             a_run += nl;
             b_run += (uint32_t)((n - k0 < kWave) ? n - k0 : kWave) - nl;
         }
+    }
+    if constexpr (Src::kListed) {  // hidx and pq, 4 bytes an entry, are no longer read
+        wave_lds_order();
+        sink.clear(reinterpret_cast<int32_t*>(hidx), n, lane, kWave);
+        wave_lds_order();
+        sink.fill(reinterpret_cast<int32_t*>(hidx), lane, kWave);
+        wave_lds_order();
+#pragma unroll
+        for (int e = 0; e < E; ++e) raw[e] = src.load(e * kWave + lane < n ? e * kWave + lane : n - 1);
     }
     typename Sink::Loaded got[E];
 #pragma unroll

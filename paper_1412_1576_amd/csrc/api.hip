@@ -105,9 +105,10 @@ void free_all(lda_ctx* c)
     c->side_fork = c->side_join = nullptr;
     c->side_stream = nullptr;
     dev_free(c, c->d_woff); dev_free(c, c->d_nkw); dev_free(c, c->d_nk);
-    dev_free(c, c->d_im_words); dev_free(c, c->d_im_off); dev_free(c, c->d_im_head); dev_free(c, c->d_im_key);
+    dev_free(c, c->d_im_words); dev_free(c, c->d_im_n); dev_free(c, c->d_rows_stale); dev_free(c, c->d_row_tiles);
+    dev_free(c, c->d_im_off); dev_free(c, c->d_im_head); dev_free(c, c->d_im_key);
     dev_free(c, c->d_im_corr); dev_free(c, c->d_im_x); dev_free(c, c->d_im_qz); dev_free(c, c->d_im_pz);
-    dev_free(c, c->d_im_sum); dev_free(c, c->d_dense_words); dev_free(c, c->d_n_dense); dev_free(c, c->d_im_pieces);
+    dev_free(c, c->d_im_sum); dev_free(c, c->d_fixed_words); dev_free(c, c->d_misfits); dev_free(c, c->d_n_misfits); dev_free(c, c->d_im_pieces);
     dev_free(c, c->d_alias); dev_free(c, c->d_cap); dev_free(c, c->d_chunk_doc); dev_free(c, c->d_chunk_tok); dev_free(c, c->d_tokdoc); dev_free(c, c->d_chunk_doc2); dev_free(c, c->d_chunk_tok2); dev_free(c, c->d_tokdoc2); dev_free(c, c->d_long_doc);
     dev_free(c, c->d_long_slot); dev_free(c, c->d_long_keys); dev_free(c, c->d_long_cnts); dev_free(c, c->d_long_first);
     dev_free(c, c->d_tiles); dev_free(c, c->d_list_tiles); dev_free(c, c->d_multi_words); dev_free(c, c->d_partial); dev_free(c, c->d_lg_terms); dev_free(c, c->d_row);
@@ -604,12 +605,23 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
                 tiles.push_back(RebuildTile{w, p, std::min(e, p + limit), 1});
         }
     }
+    auto wide_first = [K](std::vector<RebuildTile>& v) {
+        const int32_t n = (int32_t)(std::stable_partition(v.begin(), v.end(), [K](const RebuildTile& t) {
+            return !is_wave_tile(K, t);
+        }) - v.begin());
+        // one launch where both would not fill the chip (10^5 tokens of 1000 words: 6.6 us in one, 8 in two)
+        return (int32_t)v.size() - n < kWaveTilesLeast ? (int32_t)v.size() : n;
+    };
     c->n_tiles = (int32_t)tiles.size();
-    c->n_wide_tiles = (int32_t)(std::stable_partition(tiles.begin(), tiles.end(), [K](const RebuildTile& t) {
-        return !is_wave_tile(K, t);
-    }) - tiles.begin());
-    // one launch where both would not fill the chip (10^5 tokens of 1000 words: 6.6 us in one, 8 in two)
-    if (c->n_tiles - c->n_wide_tiles < kWaveTilesLeast) c->n_wide_tiles = c->n_tiles;
+    c->n_wide_tiles = wide_first(tiles);
+    if (c->n_implied > 0) {
+        std::vector<RebuildTile> row_tiles;
+        for (const RebuildTile& t : tiles)
+            if (c->h_table_form[t.w] == 0) row_tiles.push_back(t);
+        c->n_row_tiles = (int32_t)row_tiles.size();
+        c->n_wide_row_tiles = wide_first(row_tiles);
+        TRY(upload(c, &c->d_row_tiles, row_tiles, "rebuild tiles"));
+    }
     c->n_list_tiles = (int32_t)list_tiles.size();
     TRY(upload(c, &c->d_list_tiles, list_tiles, "rebuild tiles"));
     c->n_multi_words = (int32_t)multi.size();
@@ -829,6 +841,10 @@ int lda_get_nkw_row(lda_ctx* c, int32_t w, int32_t* row)
         for (int32_t i = 0; i < nnz; ++i) row[t[i]] = n[i];
         return LDA_OK;
     }
+    if (c->n_implied > 0 && c->h_table_form[w] != 0) {
+        const int rc = launch_rows_from_lists(c, w);
+        if (rc != LDA_OK) return rc;
+    }
     LDA_HIP(c, hipMemcpyAsync(row, c->d_nkw + (size_t)w * (size_t)c->K,
                               sizeof(int32_t) * (size_t)c->K, hipMemcpyDeviceToHost, c->stream));
     LDA_HIP(c, hipStreamSynchronize(c->stream));
@@ -856,7 +872,8 @@ int lda_get_alias_row(lda_ctx* c, int32_t w, uint32_t* split, uint32_t* alias, u
     if (c->hybrid && !(c->h_wkind[w] & 2))
         return fail(c, LDA_ERR_ARG, "lda_get_alias_row: word %d draws from the mixture", w);
     if (!c->hybrid && !c->all_dense_built && c->h_table_form[w] != 0) {
-        const int rc = launch_dense_table(c, w);
+        int rc = launch_rows_from_lists(c, w);
+        if (rc == LDA_OK) rc = launch_dense_table(c, w);
         if (rc != LDA_OK) return rc;
     }
     std::vector<uint4> h((size_t)c->K);

@@ -147,6 +147,7 @@ struct lda_ctx {
     int32_t n_implied = 0, n_im_class[kImpliedClasses] = {};
     std::vector<uint8_t> h_table_form;   // empty: every word has its dense table
     int32_t* d_im_words = nullptr;
+    int32_t* d_im_n = nullptr;           // [V] entries of the word's list (d_im_key)
     uint32_t* d_im_off = nullptr;        // [V+1]
     uint4* d_im_head = nullptr;          // [V]
     uint32_t* d_im_key = nullptr;
@@ -154,13 +155,21 @@ struct lda_ctx {
     uint32_t* d_im_qz = nullptr;         // [K]
     uint64_t* d_im_pz = nullptr;         // [K+1]
     uint64_t* d_im_sum = nullptr;        // [3]
-    int32_t* d_dense_words = nullptr;    // words with a dense table: n_dense_fixed, and those whose sums
-    int32_t* d_n_dense = nullptr;        //   do not fit the implied form; how many there are in all
-    int32_t n_dense_fixed = 0;
+    int32_t* d_fixed_words = nullptr;    // words with a dense table always
+    int32_t n_fixed_words = 0;
+    int4* d_misfits = nullptr;           // (word, list offset, entries) of the words whose sums do not fit the
+    int32_t* d_n_misfits = nullptr;      //   implied form, which have dense tables made from their lists; how many
     int4* d_im_pieces = nullptr;         // pieces of the word pass, as d_gather_pieces
     int32_t n_im_pieces = 0;
     // which forms hold the tables of the current counts, and which one the last sweep drew from
     bool implied_built = false, all_dense_built = false, want_all_dense = false;
+    // The counts of words with implied tables: in their lists alone after a recount, unless their rows
+    // are wanted (by one-pass sweeps, or lda_update_counts lately).  What holds is kept on the device,
+    // where captured work finds it too: *d_rows_stale = 1: the lists do, 0: the rows do.
+    int32_t* d_rows_stale = nullptr;
+    int32_t rows_wanted = 0;
+    lda::RebuildTile* d_row_tiles = nullptr;  // d_tiles without the words of implied tables
+    int32_t n_row_tiles = 0, n_wide_row_tiles = 0;
     // sweep tiling: chunk c covers documents [chunk_doc[c], chunk_doc[c+1])
     int32_t* d_chunk_doc = nullptr;
     int32_t* d_chunk_tok = nullptr;  // [n_chunks+1] first token of chunk c (= doff[chunk_doc[c]])
@@ -322,11 +331,14 @@ int device_malloc(lda_ctx* c, T** p, size_t count, const char* what)
 int launch_layout(lda_ctx* c, const int32_t* h_word);      // word-major order, woff, z init
 int launch_alias_build(lda_ctx* c);
 int launch_alias_build_hybrid(lda_ctx* c);
-int launch_dense_listed(lda_ctx* c);                       // dense tables of the words in d_dense_words
+int launch_dense_listed(lda_ctx* c);                       // dense tables of d_fixed_words and d_misfits
 int launch_dense_table(lda_ctx* c, int32_t w);             // of one word (all-dense store)
 // implied tables (implied.hpp)
 int setup_implied(lda_ctx* c, const std::vector<int32_t>& woff);
 int launch_implied_tables(lda_ctx* c);
+int launch_implied_lists(lda_ctx* c);                      // their lists from the word-major z
+int launch_rows_from_lists(lda_ctx* c, int32_t w);         // rows of all such words (w < 0) or one, if stale
+int launch_loglik_implied(lda_ctx* c, double lg_beta, const double* terms, int blocks, double* partial);
 // the tables a sweep draws from, if lda_build_alias has made the other form (all-dense store)
 int have_implied_tables(lda_ctx* c);
 int have_all_dense_tables(lda_ctx* c);

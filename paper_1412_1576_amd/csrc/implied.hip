@@ -5,6 +5,7 @@
 #include "alias_regs.hpp"
 #include "common.hpp"
 #include "implied.hpp"
+#include "loglik_terms.hpp"
 
 namespace lda {
 
@@ -23,7 +24,7 @@ __device__ __forceinline__ uint64_t quantise40(double a)
 
 // Shared by all words: q[k] = floor(beta / (n_k + betabar) * 2^40), saturated at 32 bits; pz[k] = sum of
 // max(1, q) below k; sum = (sum of the q, sum of max(1, q), largest max(1, q)).  One workgroup, a
-// run of consecutive topics per thread.  *n_dense starts the list of dense tables at its fixed part.
+// run of consecutive topics per thread.  The list of misfits starts empty.
 constexpr int kSumThreads = 1024;
 
 __global__ __launch_bounds__(kSumThreads) void implied_sums_kernel(const int32_t* __restrict__ nk, int32_t K,
@@ -31,7 +32,7 @@ __global__ __launch_bounds__(kSumThreads) void implied_sums_kernel(const int32_t
                                                                    uint32_t* __restrict__ qz,
                                                                    uint64_t* __restrict__ pz,
                                                                    uint64_t* __restrict__ sum,
-                                                                   int32_t* __restrict__ n_dense, int32_t n_fixed)
+                                                                   int32_t* __restrict__ n_misfits)
 {
 #pragma clang fp contract(off)
     constexpr int E = kRegsMaxEntries / kSumThreads;
@@ -84,8 +85,96 @@ __global__ __launch_bounds__(kSumThreads) void implied_sums_kernel(const int32_t
         sum[0] = q0_all;
         sum[1] = q_all;
         sum[2] = max_all;
-        *n_dense = n_fixed;
+        *n_misfits = 0;
     }
+}
+
+// A wave per word: its tokens' topics, ascending, with their counts.  The topics are marked in a
+// bitmap of K bits; a topic's place is the number of marks below it.
+// (A histogram of K counters per word, written as a row of K counts, took 4 K bytes of LDS and of
+// memory for a word however few its tokens: 137 000 words of 1.7 * 10^7 tokens, K = 10 000, 1.0 ms; lists 0.09.)
+template <int E>
+__global__ __launch_bounds__(256) void implied_lists_kernel(const int32_t* __restrict__ words, int32_t n_words,
+                                                            int32_t K, const int32_t* __restrict__ woff,
+                                                            const int32_t* __restrict__ zw, int32_t sh,
+                                                            uint32_t zmask, const int32_t* __restrict__ xmap,
+                                                            const uint32_t* __restrict__ off,
+                                                            uint32_t* __restrict__ key, int32_t* __restrict__ n_out)
+{
+    extern __shared__ uint32_t lds[];
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int32_t i = (int32_t)blockIdx.x * 4 + wv;
+    if (i >= n_words) return;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int32_t W = (K + 31) / 32;  // words of the bitmap
+    uint32_t* const bits = lds + wv * (2 * W + E * kWave);
+    uint32_t* const below = bits + W;  // marks in the words before this one
+    uint32_t* const keys = below + W;
+    const int32_t w = words[i], b = woff[w], n = woff[w + 1] - b;
+    size_t q[E];
+    uint32_t t[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int32_t p = b + (e * kWave + lane < n ? e * kWave + lane : n - 1);  // (n >= 1)
+        if (e * kWave < n) q[e] = xmap ? (size_t)xmap[p] : (size_t)p;
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (e * kWave < n) t[e] = (uint32_t)__builtin_nontemporal_load(&zw[q[e] << sh]) & zmask;
+    for (int32_t k = lane; k < W; k += kWave) bits[k] = 0u;
+    wave_lds_order();
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (e * kWave < n) atomicOr(&bits[t[e] >> 5], 1u << (t[e] & 31u));  // (clones mark the same topic)
+    wave_lds_order();
+    const int32_t R = (W + kWave - 1) / kWave, k0 = lane * R;
+    uint32_t mine = 0;
+    for (int32_t k = k0; k < k0 + R && k < W; ++k) mine += (uint32_t)__popc(bits[k]);
+    const uint32_t inc = wave_inclusive_scan_u32(mine);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+    uint32_t run = inc - mine;
+    for (int32_t k = k0; k < k0 + R && k < W; ++k) {
+        below[k] = run;
+        run += (uint32_t)__popc(bits[k]);
+    }
+    wave_lds_order();
+    uint32_t at[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        if (e * kWave >= n) continue;
+        at[e] = below[t[e] >> 5] + (uint32_t)__popc(bits[t[e] >> 5] & ((1u << (t[e] & 31u)) - 1u));
+        keys[at[e]] = t[e] << kImpliedTopicShift;  // the same value from every token of the topic
+    }
+    wave_lds_order();
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (e * kWave + lane < n) atomicAdd(&keys[at[e]], 1u);
+    wave_lds_order();
+    const size_t o = off[w];
+    for (uint32_t k = lane; k < total; k += kWave) key[o + k] = keys[k];
+    if (lane == 0) n_out[w] = (int32_t)total;
+}
+
+// Dense rows from the lists, a wave per word, unless the rows are kept.
+__global__ __launch_bounds__(256) void rows_from_lists_kernel(const int32_t* __restrict__ words, int32_t w0,
+                                                              int32_t n_words, int32_t K,
+                                                              const uint32_t* __restrict__ off,
+                                                              const uint32_t* __restrict__ key,
+                                                              const int32_t* __restrict__ n_list,
+                                                              int32_t* __restrict__ nkw,
+                                                              const int32_t* __restrict__ stale)
+{
+    if (*stale == 0) return;
+    const int32_t i = (int32_t)blockIdx.x * 4 + (int32_t)(threadIdx.x >> 6);
+    if (i >= n_words) return;
+    const int32_t w = words ? words[i] : w0;
+    const int lane = threadIdx.x & (kWave - 1);
+    int32_t* const row = nkw + (size_t)w * (size_t)K;
+    const uint32_t* __restrict__ mine = key + off[w];
+    for (int32_t k = lane; k < K; k += kWave) row[k] = 0;
+    __threadfence();  // the counts come after the zeros
+    for (int32_t e = lane, n = n_list[w]; e < n; e += kWave)
+        row[mine[e] >> kImpliedTopicShift] = (int32_t)(mine[e] & kImpliedCount);
 }
 
 struct ImpliedArgs {
@@ -98,17 +187,20 @@ struct ImpliedArgs {
     const uint64_t* __restrict__ sum;
     const uint32_t* __restrict__ off;
     uint4* __restrict__ head;
-    uint32_t* __restrict__ key;
+    uint32_t* key;
+    int32_t* n_list;
     uint64_t* __restrict__ corr;
     uint64_t* __restrict__ x;
-    int32_t* __restrict__ dense_words;
-    int32_t* __restrict__ n_dense;
+    int4* __restrict__ misfits;
+    int32_t* __restrict__ n_misfits;
+    const int32_t* __restrict__ stale;
     int32_t cap;  // keys of a wave in LDS
 };
 
-// A wave per word: its topics out of the dense row, the sums of their weights, and the two running
-// sums.  Bound by reading the rows (4 K bytes per word): 137 000 rows of 10 000 counts 1.22 ms, 4.5
-// TB/s, where the tables of their bins took 10.6 (16 bytes written per bin).
+// A wave per word: its topics from the list, or out of the dense row where that is kept, the sums of
+// their weights, and the two running sums.  Out of the rows it is bound by reading them: 137 000 rows
+// of 10 000 counts 1.22 ms, 4.5 TB/s (the tables of their bins took 10.6, 16 bytes written per bin);
+// from lists 0.15 ms.
 __global__ __launch_bounds__(256) void implied_tables_kernel(ImpliedArgs a)
 {
 #pragma clang fp contract(off)
@@ -120,27 +212,34 @@ __global__ __launch_bounds__(256) void implied_tables_kernel(ImpliedArgs a)
     const int lane = threadIdx.x & (kWave - 1);
     const int32_t w = a.words[i], K = a.K;
     const int32_t* __restrict__ row = a.nkw + (size_t)w * (size_t)K;
+    const size_t off = a.off[w];
+    const bool from_list = *a.stale != 0;
     uint32_t n = 0;
-    constexpr int U = 8;  // loads of a lane in flight
-    for (int32_t k0 = 0; k0 < K; k0 += U * kWave) {
-        int32_t v[U];
+    if (from_list) {
+        n = (uint32_t)a.n_list[w];
+        for (uint32_t e = lane; e < n; e += kWave) keys[e] = a.key[off + e] & ~kImpliedLight;
+    } else {
+        constexpr int U = 8;  // loads of a lane in flight
+        for (int32_t k0 = 0; k0 < K; k0 += U * kWave) {
+            int32_t v[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t k = k0 + u * kWave + lane;
-            v[u] = row[k < K ? k : K - 1];
-        }
+            for (int u = 0; u < U; ++u) {
+                const int32_t k = k0 + u * kWave + lane;
+                v[u] = row[k < K ? k : K - 1];
+            }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t k = k0 + u * kWave + lane;
-            const bool has = k < K && v[u] > 0;
-            const uint64_t mask = __ballot(has);
-            if (mask == 0) continue;
-            if (has) keys[n + rank_below(mask)] = ((uint32_t)k << kImpliedTopicShift) | (uint32_t)v[u];
-            n += (uint32_t)__popcll(mask);
+            for (int u = 0; u < U; ++u) {
+                const int32_t k = k0 + u * kWave + lane;
+                const bool has = k < K && v[u] > 0;
+                const uint64_t mask = __ballot(has);
+                if (mask == 0) continue;
+                if (has) keys[n + rank_below(mask)] = ((uint32_t)k << kImpliedTopicShift) | (uint32_t)v[u];
+                n += (uint32_t)__popcll(mask);
+            }
         }
+        if (lane == 0) a.n_list[w] = (int32_t)n;
     }
     wave_lds_order();
-    const size_t off = a.off[w];
     auto entry = [&](uint32_t key, uint64_t& q0, uint64_t& z0) {
         const uint32_t t = key >> kImpliedTopicShift;
         q0 = quantise40(((double)(int32_t)(key & kImpliedCount) + a.beta) / ((double)a.nk[t] + a.betabar));
@@ -162,14 +261,20 @@ __global__ __launch_bounds__(256) void implied_tables_kernel(ImpliedArgs a)
     const uint64_t pad = (uint64_t)K * C - Q;
     // (q saturates beyond 2^32, but then `most` does not pass)
     const bool fits = most < (1ull << 31) && Q0 < ((uint64_t)K << 31) && most + 1 < C;
+    if (!fits) {  // its bins are built, and until then drawn from; counts are looked up in the list
+        for (uint32_t e = lane; e < n; e += kWave) a.key[off + e] = keys[e];
+        if (lane == 0) {
+            a.head[w] = make_uint4(n | kImpliedDense, 0u, 0u, 0u);
+            a.corr[off] = Q0;  // for the builder of its bins
+            a.x[off] = Q;
+            a.misfits[atomicAdd(a.n_misfits, 1)] = make_int4(w, (int32_t)off, (int32_t)n, 0);
+        }
+        return;
+    }
     uint64_t c_run = 0, x_run = 0;
     for (uint32_t e0 = 0; e0 < n; e0 += kWave) {
         const uint32_t e = e0 + lane;
         const uint32_t key = e < n ? keys[e] : 0u;
-        if (!fits) {  // looked up by topic all the same
-            if (e < n) a.key[off + e] = key;
-            continue;
-        }
         uint64_t cor = 0, exc = 0;
         bool light = false;
         if (e < n) {
@@ -190,14 +295,48 @@ __global__ __launch_bounds__(256) void implied_tables_kernel(ImpliedArgs a)
         c_run += readlane_u64(ci, kWave - 1);
         x_run += readlane_u64(xi, kWave - 1);
     }
-    if (lane == 0) {
-        if (fits) {
-            a.head[w] = make_uint4(n, (uint32_t)C, (uint32_t)pad, 0u);
+    if (lane == 0) a.head[w] = make_uint4(n, (uint32_t)C, (uint32_t)pad, 0u);
+}
+
+// Log-likelihood, word part, of all words of an all-dense store with implied tables: a wave per word,
+// over its list, or its row where that is kept (fixed: the words whose row always is).
+__global__ __launch_bounds__(256) void loglik_implied_kernel(const int32_t* __restrict__ fixed, int32_t n_fixed,
+                                                             const int32_t* __restrict__ words, int32_t n_words,
+                                                             int32_t K, const uint32_t* __restrict__ off,
+                                                             const uint32_t* __restrict__ key,
+                                                             const int32_t* __restrict__ n_list,
+                                                             const int32_t* __restrict__ nkw,
+                                                             const int32_t* __restrict__ stale, double beta,
+                                                             double lg_beta, const double* __restrict__ terms,
+                                                             double* __restrict__ partial)
+{
+    __shared__ double wtot[4];
+    const int lane = threadIdx.x & (kWave - 1);
+    const bool lists = *stale != 0;
+    double acc = 0.0;
+    for (int32_t i = (int32_t)(blockIdx.x * 4 + (threadIdx.x >> 6)); i < n_fixed + n_words; i += (int32_t)gridDim.x * 4) {
+        const int32_t w = i < n_fixed ? fixed[i] : words[i - n_fixed];
+        if (lists && i >= n_fixed) {
+            const uint32_t* __restrict__ mine = key + off[w];
+            const int32_t n = n_list[w];
+            for (int32_t e = lane; e < n; e += kWave) acc += terms[mine[e] & kImpliedCount];  // (at most kImpliedTokens)
         } else {
-            a.head[w] = make_uint4(n | kImpliedDense, 0u, 0u, 0u);
-            a.dense_words[atomicAdd(a.n_dense, 1)] = w;
+            const int32_t* __restrict__ row = nkw + (size_t)w * (size_t)K;
+            for (int32_t k0 = 0; k0 < K; k0 += 8 * kWave) {
+                int32_t v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int32_t k = k0 + u * kWave + lane;
+                    v[u] = k < K ? row[k] : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (v[u] > 0) acc += count_term(v[u], beta, lg_beta, terms);
+            }
         }
     }
+    const double s = block_sum_f64(acc, wtot);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
 }  // namespace
@@ -231,8 +370,10 @@ int setup_implied(lda_ctx* c, const std::vector<int32_t>& woff)
     if (n * K < kImpliedLeastBins) return LDA_OK;
     std::vector<int32_t> all(words[0]);
     all.insert(all.end(), words[1].begin(), words[1].end());
-    fixed.resize((size_t)(c->n_dense_fixed = (int32_t)fixed.size()) + all.size());
+    c->n_fixed_words = (int32_t)fixed.size();
     LDA_ALLOC(c, &c->d_im_words, all.size(), "implied tables");
+    LDA_ALLOC(c, &c->d_im_n, (size_t)V, "implied tables");
+    LDA_ALLOC(c, &c->d_rows_stale, 1, "implied tables");
     LDA_ALLOC(c, &c->d_im_off, off.size(), "implied tables");
     LDA_ALLOC(c, &c->d_im_head, (size_t)V, "implied tables");
     LDA_ALLOC(c, &c->d_im_key, entries, "implied tables");
@@ -241,29 +382,34 @@ int setup_implied(lda_ctx* c, const std::vector<int32_t>& woff)
     LDA_ALLOC(c, &c->d_im_qz, (size_t)K, "implied tables");
     LDA_ALLOC(c, &c->d_im_pz, (size_t)K + 1, "implied tables");
     LDA_ALLOC(c, &c->d_im_sum, 3, "implied tables");
-    LDA_ALLOC(c, &c->d_dense_words, fixed.size(), "implied tables");
-    LDA_ALLOC(c, &c->d_n_dense, 1, "implied tables");
+    LDA_ALLOC(c, &c->d_fixed_words, fixed.size(), "implied tables");
+    LDA_ALLOC(c, &c->d_misfits, all.size(), "implied tables");
+    LDA_ALLOC(c, &c->d_n_misfits, 1, "implied tables");
     LDA_HIP(c, hipMemcpy(c->d_im_words, all.data(), sizeof(int32_t) * all.size(), hipMemcpyHostToDevice));
     LDA_HIP(c, hipMemcpy(c->d_im_off, off.data(), sizeof(uint32_t) * off.size(), hipMemcpyHostToDevice));
-    LDA_HIP(c, hipMemcpy(c->d_dense_words, fixed.data(), sizeof(int32_t) * fixed.size(), hipMemcpyHostToDevice));
-    LDA_HIP(c, hipMemset(c->d_im_head, 0, sizeof(uint4) * (size_t)V));  // words without tokens
+    if (!fixed.empty())
+        LDA_HIP(c, hipMemcpy(c->d_fixed_words, fixed.data(), sizeof(int32_t) * fixed.size(), hipMemcpyHostToDevice));
+    // words without tokens
+    LDA_HIP(c, hipMemset(c->d_im_head, 0, sizeof(uint4) * (size_t)V));
+    LDA_HIP(c, hipMemset(c->d_im_n, 0, sizeof(int32_t) * (size_t)V));
+    LDA_HIP(c, hipMemset(c->d_rows_stale, 0, sizeof(int32_t)));
     for (int i = 0; i < lda_ctx::kImpliedClasses; ++i) c->n_im_class[i] = (int32_t)words[i].size();
     c->n_implied = (int32_t)n;
     c->h_table_form = std::move(form);
     return LDA_OK;
 }
 
-// The implied tables, and in d_dense_words the list of the words that have dense ones
+// The implied tables, and in d_misfits the list of the words that have dense ones after all
 int launch_implied_tables(lda_ctx* c)
 {
     hipLaunchKernelGGL(implied_sums_kernel, dim3(1), dim3(kSumThreads), 0, c->stream, c->d_nk, c->K, c->beta,
-                       c->betabar, c->d_im_qz, c->d_im_pz, c->d_im_sum, c->d_n_dense, c->n_dense_fixed);
+                       c->betabar, c->d_im_qz, c->d_im_pz, c->d_im_sum, c->d_n_misfits);
     LDA_HIP(c, hipGetLastError());
     ImpliedArgs a{};
     a.K = c->K; a.nkw = c->d_nkw; a.nk = c->d_nk; a.beta = c->beta; a.betabar = c->betabar;
     a.qz = c->d_im_qz; a.sum = c->d_im_sum; a.off = c->d_im_off; a.head = c->d_im_head; a.key = c->d_im_key;
-    a.corr = c->d_im_corr; a.x = c->d_im_x; a.dense_words = c->d_dense_words; a.n_dense = c->d_n_dense;
-    a.words = c->d_im_words;
+    a.corr = c->d_im_corr; a.x = c->d_im_x; a.misfits = c->d_misfits; a.n_misfits = c->d_n_misfits;
+    a.words = c->d_im_words; a.n_list = c->d_im_n; a.stale = c->d_rows_stale;
     for (int i = 0; i < lda_ctx::kImpliedClasses; ++i) {
         a.n_words = c->n_im_class[i];
         a.cap = kImpliedClassCap[i];
@@ -273,6 +419,41 @@ int launch_implied_tables(lda_ctx* c)
         LDA_HIP(c, hipGetLastError());
         a.words += a.n_words;
     }
+    return LDA_OK;
+}
+
+int launch_implied_lists(lda_ctx* c)
+{
+    const int32_t* words = c->d_im_words;
+    for (int i = 0; i < lda_ctx::kImpliedClasses; ++i) {
+        const int32_t n = c->n_im_class[i];
+        const size_t lds = sizeof(uint32_t) * 4 * (size_t)(2 * ((c->K + 31) / 32) + kImpliedClassCap[i]);  // < 32 KB
+        auto kern = i == 0 ? implied_lists_kernel<kImpliedClassCap[0] / kWave> : implied_lists_kernel<kImpliedClassCap[1] / kWave>;
+        if (n > 0)
+            hipLaunchKernelGGL(kern, dim3((n + 3) / 4), dim3(256), lds, c->stream, words, n, c->K, c->d_woff, c->d_zt,
+                               c->zt_shift, c->zt_mask, c->d_xmap, c->d_im_off, c->d_im_key, c->d_im_n);
+        LDA_HIP(c, hipGetLastError());
+        words += n;
+    }
+    return LDA_OK;
+}
+
+int launch_rows_from_lists(lda_ctx* c, int32_t w)
+{
+    const int32_t n = w < 0 ? c->n_implied : 1;
+    hipLaunchKernelGGL(rows_from_lists_kernel, dim3((n + 3) / 4), dim3(256), 0, c->stream,
+                       w < 0 ? c->d_im_words : nullptr, w, n, c->K, c->d_im_off, c->d_im_key, c->d_im_n, c->d_nkw,
+                       c->d_rows_stale);
+    LDA_HIP(c, hipGetLastError());
+    return LDA_OK;
+}
+
+int launch_loglik_implied(lda_ctx* c, double lg_beta, const double* terms, int blocks, double* partial)
+{
+    hipLaunchKernelGGL(loglik_implied_kernel, dim3(blocks), dim3(256), 0, c->stream, c->d_fixed_words,
+                       c->n_fixed_words, c->d_im_words, c->n_implied, c->K, c->d_im_off, c->d_im_key, c->d_im_n,
+                       c->d_nkw, c->d_rows_stale, c->beta, lg_beta, terms, partial);
+    LDA_HIP(c, hipGetLastError());
     return LDA_OK;
 }
 

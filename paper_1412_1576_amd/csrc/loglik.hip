@@ -13,43 +13,19 @@
 
 #include "common.hpp"
 #include "doc_tile.hpp"
+#include "loglik_terms.hpp"
 
 namespace lda {
 
 namespace {
-
-__device__ __forceinline__ double block_sum_f64(double v, double* wtot)
-{
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
-    const int nw = (blockDim.x + kWave - 1) >> 6;
-#pragma unroll
-    for (int d = kWave / 2; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
-    __syncthreads();
-    if (lane == 0) wtot[wv] = v;
-    __syncthreads();
-    double s = 0.0;
-    for (int i = 0; i < nw; ++i) s += wtot[i];
-    return s;
-}
-
-// The terms of counts below kTermTable, by count: lgG(v + a) - lgG(a).  They depend on the
-// context's alpha and beta alone and are made once, by the same fp64 expression that larger
-// counts are computed with, so a sum does not depend on where a term comes from.  Nearly every
-// count is small, and lgamma is some 200 fp64 instructions that a wave runs if any of its lanes
-// needs it.
-constexpr int32_t kTermTable = 4096;
-static_assert(kMaxTileTokens < kTermTable, "a count of a document tile is in the table");
-
-__device__ __forceinline__ double count_term(int32_t v, double a, double lg_a, const double* __restrict__ table)
-{
-    return v < kTermTable ? table[v] : lgamma((double)v + a) - lg_a;
-}
 
 __global__ __launch_bounds__(256) void term_table_kernel(double a, double lg_a, double* __restrict__ table)
 {
     const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
     if (v < kTermTable) table[v] = lgamma((double)v + a) - lg_a;
 }
+
+static_assert(kMaxTileTokens < kTermTable, "a count of a document tile is in the table");
 
 // doc part over LDS document tiles: one partial per tile
 __global__ __launch_bounds__(1024) void loglik_doc_tiles_kernel(
@@ -300,7 +276,10 @@ int run_loglik(lda_ctx* c, double* d_partial, size_t cap, double* h, size_t h_ca
     }
     const double* beta_terms = c->d_lg_terms + kTermTable;
     const int64_t dense_rows = c->hybrid ? c->H : c->V;
-    if (dense_rows > 0) {
+    if (c->n_implied > 0) {
+        if (!(p = parts.take(kWordBlocks, &word, &rc))) return rc;
+        if ((rc = launch_loglik_implied(c, lgb, beta_terms, kWordBlocks, p)) != LDA_OK) return rc;
+    } else if (dense_rows > 0) {
         if (!(p = parts.take(kWordBlocks, &word, &rc))) return rc;
         hipLaunchKernelGGL(loglik_word_kernel, dim3(kWordBlocks), dim3(256), 0, c->stream, c->d_nkw,
                            dense_rows * (int64_t)c->K, c->beta, lgb, beta_terms, p);

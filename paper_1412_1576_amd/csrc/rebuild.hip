@@ -311,16 +311,19 @@ __global__ __launch_bounds__(1024, 8) void nkw_list_rows_kernel(
 
 // What the counts below add to: the rows of the words of several tiles, a workgroup each, and
 // after them n_k, kZeroNk topics to a workgroup.  One launch for both: in a corpus of 10^5 tokens
-// a launch is 4 of the 56 us of an iteration.
+// a launch is 4 of the 56 us of an iteration.  (And says what this recount leaves of the rows of
+// words with implied tables.)
 constexpr int32_t kZeroNk = 4096;
 
 __global__ __launch_bounds__(256) void zero_counts_kernel(const int32_t* __restrict__ words, int32_t n_words,
                                                           int32_t K, int32_t* __restrict__ nkw,
                                                           int32_t* __restrict__ nk,
-                                                          const int32_t* __restrict__ go)
+                                                          const int32_t* __restrict__ go,
+                                                          int32_t* __restrict__ rows_stale, int32_t stale)
 {
     if (unwanted(go)) return;
     const int32_t i = (int32_t)blockIdx.x;
+    if (rows_stale && i == 0 && threadIdx.x == 0) *rows_stale = stale;
     if (i < n_words) {
         int32_t* __restrict__ row = nkw + (size_t)words[i] * (size_t)K;
         for (int32_t k = threadIdx.x; k < K; k += blockDim.x) row[k] = 0;
@@ -381,16 +384,19 @@ __global__ __launch_bounds__(1024) void nk_hist_ranges_kernel(const int32_t* __r
 // from n_kw[w][a], n_k[a] and gives one to n_kw[w][b], n_k[b].  Integer atomics, so the result
 // equals the recount whatever the order.  The deltas of n_k are summed per workgroup in LDS
 // first (the all-dense store has K <= max_alias_topics()).  Bound by the rate of the atomics on
-// n_kw, 5 to 10 moved tokens per ns.  With `recount` set and *recount non-zero it returns at once.
+// n_kw, 5 to 10 moved tokens per ns.  With `recount` set and *recount non-zero it returns at once
+// (*copy = *recount for the kernels of the recount).
 __global__ __launch_bounds__(1024) void update_counts_kernel(const int32_t* __restrict__ z,
                                                             const int32_t* __restrict__ zprev,
                                                             const int32_t* __restrict__ word,
                                                             int64_t N, int32_t K,
                                                             int32_t* __restrict__ nkw,
                                                             int32_t* __restrict__ nk,
-                                                            const int32_t* __restrict__ recount)
+                                                            const int32_t* __restrict__ recount,
+                                                            int32_t* __restrict__ copy)
 {
     extern __shared__ int32_t dk[];
+    if (copy && blockIdx.x == 0 && threadIdx.x == 0) *copy = *recount;
     if (recount && *recount) return;
     const int tid = threadIdx.x, nt = blockDim.x;
     for (int32_t k = tid; k < K; k += nt) dk[k] = 0;
@@ -425,7 +431,8 @@ int64_t hist_blocks(const lda_ctx* c)
     return (c->N + per - 1) / per;
 }
 
-// *recount = 1 if more than `most` of the kMovedSample tokens spread evenly over z have moved.
+// *recount = 1 if more than `most` of the kMovedSample tokens spread evenly over z have moved, or there
+// are rows that +-1 cannot be added to.
 // Every sampled token is two cache lines of its own: one workgroup alone took 78 us for them,
 // sixteen, a token to a thread, 7.4 us.  *sum collects the workgroups' counts with one count of
 // arrivals above them, in one atomic; the last workgroup decides and leaves it zero.
@@ -435,7 +442,8 @@ constexpr int kArrivalShift = 20;
 __global__ __launch_bounds__(1024) void sample_moved_kernel(const int32_t* __restrict__ z,
                                                            const int32_t* __restrict__ zprev, int64_t N,
                                                            int32_t most, int32_t* __restrict__ recount,
-                                                           int32_t* __restrict__ sum)
+                                                           int32_t* __restrict__ sum,
+                                                           const int32_t* __restrict__ rows_stale)
 {
     __shared__ int32_t moved;
     if (threadIdx.x == 0) moved = 0;
@@ -447,7 +455,8 @@ __global__ __launch_bounds__(1024) void sample_moved_kernel(const int32_t* __res
     if (threadIdx.x != 0) return;
     const int32_t before = atomicAdd(sum, (1 << kArrivalShift) + moved);
     if ((before >> kArrivalShift) != (int32_t)gridDim.x - 1) return;
-    *recount = (before & ((1 << kArrivalShift) - 1)) + moved > most ? 1 : 0;
+    const bool many = (before & ((1 << kArrivalShift) - 1)) + moved > most;
+    *recount = many || (rows_stale && *rows_stale) ? 1 : 0;
     *sum = 0;
 }
 
@@ -465,10 +474,13 @@ bool is_wave_tile(int32_t K, const RebuildTile& t)
 namespace {
 
 // word-major copy of z, then the dense rows by LDS histograms over topic ranges; n_k is zeroed for
-// launch_nk_hist
-int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
+// launch_nk_hist.  lists: the words of implied tables get their lists instead (never with `go`).
+int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr, bool lists = false)
 {
     const int32_t K = c->K;
+    const RebuildTile* const tiles = lists ? c->d_row_tiles : c->d_tiles;
+    const int32_t n_tiles = lists ? c->n_row_tiles : c->n_tiles;
+    const int32_t n_wide_tiles = lists ? c->n_wide_row_tiles : c->n_wide_tiles;
     if (!c->zt_current) {  // the sweep's doc pass may have written the new assignment already
         const int rc = launch_scatter_word_major(c, c->d_z, c->d_wpos, c->N, go);
         if (rc != LDA_OK) return rc;
@@ -480,8 +492,12 @@ int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
         const int32_t n_rows = c->n_tiles > 0 ? c->n_multi_words : 0;
         if (n_rows + n_nk > 0)
             hipLaunchKernelGGL(zero_counts_kernel, dim3(n_rows + n_nk), dim3(256), 0, c->stream,
-                               c->d_multi_words, n_rows, K, c->d_nkw, c->d_nk, go);
+                               c->d_multi_words, n_rows, K, c->d_nkw, c->d_nk, go, c->d_rows_stale, lists ? 1 : 0);
         LDA_HIP(c, hipGetLastError());
+    }
+    if (lists) {
+        const int rc = launch_implied_lists(c);
+        if (rc != LDA_OK) return rc;
     }
     if (c->n_list_tiles > 0) {
         const int32_t ranges = (K + kListRowSpan - 1) / kListRowSpan;
@@ -496,7 +512,7 @@ int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
                            c->d_sp_nnz, c->d_xmap);
         LDA_HIP(c, hipGetLastError());
     }
-    if (c->n_tiles == 0) return LDA_OK;
+    if (n_tiles == 0) return LDA_OK;
     const int32_t nr = (K + max_rebuild_topics() - 1) / max_rebuild_topics();
     const int32_t span = (((K + nr - 1) / nr) + 63) / 64 * 64;
     const size_t lds = sizeof(int32_t) * (size_t)span;
@@ -507,8 +523,8 @@ int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
     A.zw = c->d_zt; A.sh = c->zt_shift; A.zmask = c->zt_mask; A.K = K; A.span = span; A.nkw = c->d_nkw;
     A.sp_off = c->d_sp_off; A.sp_topic = c->d_sp_topic; A.sp_count = c->d_sp_count; A.sp_nnz = c->d_sp_nnz;
     A.xmap = c->d_xmap; A.go = go;
-    if (c->n_wide_tiles > 0) {
-        A.tiles = c->d_tiles; A.n_tiles = c->n_wide_tiles;
+    if (n_wide_tiles > 0) {
+        A.tiles = tiles; A.n_tiles = n_wide_tiles;
         A.run = xcd_run_length(A.n_tiles, kTileRun);
         A.n_blocks = xcd_runs_grid(A.n_tiles, A.run);
         const bool loop = go && A.n_blocks > 2 * kLoopBlocks;
@@ -516,10 +532,10 @@ int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr)
         if (loop) hipLaunchKernelGGL((nkw_tiles_kernel<false, true>), grid, block, lds, c->stream, A);
         else hipLaunchKernelGGL((nkw_tiles_kernel<false, false>), grid, block, lds, c->stream, A);
     }
-    const int32_t n_short = c->n_tiles - c->n_wide_tiles;
+    const int32_t n_short = n_tiles - n_wide_tiles;
     if (n_short > 0) {  // (K <= kWaveTileTopics: one range, less than 48 KB for four histograms)
         const int32_t blocks = (n_short + 3) / 4;
-        A.tiles = c->d_tiles + c->n_wide_tiles; A.n_tiles = n_short;
+        A.tiles = tiles + n_wide_tiles; A.n_tiles = n_short;
         A.run = xcd_run_length(blocks, kTileRun / 4);
         A.n_blocks = xcd_runs_grid(blocks, A.run);
         const bool loop = go && A.n_blocks > 2 * kLoopBlocks;
@@ -586,6 +602,7 @@ int launch_update_counts(lda_ctx* c)
 {
     if (c->K > kNkRangeTopics)
         return fail(c, LDA_ERR_UNSUPPORTED, "lda_update_counts supports K <= %d", kNkRangeTopics);
+    c->rows_wanted = 2;
     const double N = (double)c->N, V = (double)c->V, K = (double)c->K;
     const double recount_ns = 2.0e4 + 2.0 * V + V * K / 1000.0 + N / 500.0;
     const double break_even = recount_ns / (0.1 * N);  // share of moved tokens
@@ -593,16 +610,21 @@ int launch_update_counts(lda_ctx* c)
     if (break_even < 1.0) {
         recount = c->d_flag + 1;
         hipLaunchKernelGGL(sample_moved_kernel, dim3(kMovedSample / 1024), dim3(1024), 0, c->stream, c->d_z,
-                           c->d_znew, c->N, (int32_t)(break_even * kMovedSample), recount, c->d_flag + 2);
+                           c->d_znew, c->N, (int32_t)(break_even * kMovedSample), recount, c->d_flag + 2,
+                           c->d_rows_stale);
         LDA_HIP(c, hipGetLastError());
     }
+    // without a sample, a recount only if rows are stale
+    const int32_t* const decided = recount ? recount : c->d_rows_stale;
+    int32_t* const copy = !recount && decided ? c->d_flag + 1 : nullptr;
+    if (copy) recount = copy;
     const int64_t blocks = std::min<int64_t>(hist_blocks(c), 2048);
     const size_t lds = sizeof(int32_t) * (size_t)c->K;
     if (lds > 48 * 1024)
         LDA_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(update_counts_kernel),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     hipLaunchKernelGGL(update_counts_kernel, dim3((unsigned)blocks), dim3(1024), lds, c->stream, c->d_z,
-                       c->d_znew, c->d_word, c->N, c->K, c->d_nkw, c->d_nk, recount);
+                       c->d_znew, c->d_word, c->N, c->K, c->d_nkw, c->d_nk, decided, copy);
     LDA_HIP(c, hipGetLastError());
     if (!recount) return LDA_OK;
     const int rc = launch_dense_rows(c, recount);
@@ -614,7 +636,11 @@ int launch_rebuild(lda_ctx* c)
     const int32_t K = c->K;
     if (K > max_rebuild_topics())
         return fail(c, LDA_ERR_UNSUPPORTED, "count rebuild supports K <= %d", max_rebuild_topics());
-    int rc = launch_dense_rows(c);
+    // Rows of words with implied tables are only made where something lately read them: the one-pass
+    // sweeps, or lda_update_counts, which may be taking turns with this.
+    const bool rows = c->n_implied == 0 || c->want_all_dense || c->rows_wanted > 0;
+    if (c->rows_wanted > 0) --c->rows_wanted;
+    int rc = launch_dense_rows(c, nullptr, !rows);
     if (rc != LDA_OK) return rc;
     return launch_nk_hist(c);
 }

@@ -29,7 +29,7 @@ def corpus_of(counts, seed, L=90):
 
 def pair(lda_mod, oracle_mod, doff, words, V, K, beta=0.01, **opt):
     return (lda_mod.Lda(doff, words, V, K, 0.1, beta, seed=3, **opt),
-            oracle_mod.Oracle(doff, words, V, K, 0.1, beta, seed=3))
+            oracle_mod.Oracle(doff, words, V, K, 0.1, beta, seed=3, proposal_mode=opt.get("proposal_mode", 0)))
 
 
 def step(g, o, m, update=False, tables=()):
@@ -42,6 +42,10 @@ def step(g, o, m, update=False, tables=()):
     o.rebuild_counts()
     assert np.array_equal(g.get_z(), o.get_z()), m
     assert np.array_equal(g.get_nk(), o.get_nk()), m
+    for w in tables:
+        assert np.array_equal(g.get_nkw_row(w), o.get_nkw_row(w)), (m, w)
+    if len(tables):
+        assert abs(g.loglik()[0] - o.loglik()[0]) <= 1e-9 * abs(o.loglik()[0])
 
 
 def frequencies(V, K, seed):
@@ -105,10 +109,59 @@ def test_in_turn_with_one_pass_sweeps(lda_mod, oracle_mod):
 def test_after_the_incremental_update(lda_mod, oracle_mod):
     V, K = 9000, 300
     doff, words = corpus_of(frequencies(V, K, 6), 6, L=12)
-    g, o = pair(lda_mod, oracle_mod, doff, words, V, K)
-    for m in (2, 2, 3):
-        step(g, o, m, update=True, tables=(5, 13, 8000))
+    for turns in ("uuu", "ruurrrru"):  # rows are kept for updates, lists for recounts
+        g, o = pair(lda_mod, oracle_mod, doff, words, V, K)
+        for i, turn in enumerate(turns):
+            step(g, o, 9 if i == 4 else 2 + i % 2, update=turn == "u", tables=(5, 13, 8000))
+        g.close(); o.close()
+
+
+def test_few_moved_tokens(lda_mod, oracle_mod):
+    """One token moved since the recount: the incremental update finds the rows stale and counts."""
+    V, K = 2600, 1024
+    doff, words = corpus_of(frequencies(V, K, 7), 7)
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K, proposal_mode=1, beta=1e-9)
+    z = words % K  # every word in one topic, which its proposals hardly leave
+    for c in (g, o):
+        c.set_z(z, 0)
+        c.rebuild_counts()
+    for update in (True, True, False, True):
+        step(g, o, 1, update=update, tables=range(0, V, 111))
     g.close(); o.close()
+
+
+def test_graph_replays_leave_lists(lda_mod, oracle_mod):
+    """What the rows hold is known on the device: iterations replayed from a graph leave lists where
+    the host, which saw an update before, would expect rows."""
+    import torch
+    V, K = 2600, 1024
+    doff, words = corpus_of(frequencies(V, K, 3), 3)
+    stream = torch.cuda.Stream()
+    g = lda_mod.Lda(doff, words, V, K, 0.1, 0.01, seed=3, stream=stream.cuda_stream)
+    for _ in range(2):
+        g.build_alias(); g.sweep(2); g.rebuild_counts()
+    g.sync()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        g.rebuild_counts()
+    g.build_alias(); g.sweep(2); g.update_counts()
+    g.build_alias(); g.sweep(2); g.update_counts()
+    z = g.get_z()
+    with torch.cuda.stream(stream):
+        for _ in range(3):
+            graph.replay()
+    g.sync()
+    rows = np.zeros((V, K), np.int32)
+    np.add.at(rows, (words, z), 1)
+    for w in range(0, V, 37):
+        assert np.array_equal(g.get_nkw_row(w), rows[w]), w
+    g.build_alias(); g.sweep(2); g.update_counts()
+    z = g.get_z()
+    rows[:] = 0
+    np.add.at(rows, (words, z), 1)
+    for w in range(0, V, 37):
+        assert np.array_equal(g.get_nkw_row(w), rows[w]), w
+    g.close()
 
 
 def test_record_order_and_word_chains(lda_mod, oracle_mod):
