@@ -105,6 +105,7 @@ void free_all(lda_ctx* c)
     c->side_fork = c->side_join = nullptr;
     c->side_stream = nullptr;
     dev_free(c, c->d_woff); dev_free(c, c->d_nkw); dev_free(c, c->d_nk);
+    dev_free(c, c->d_doc_limit);
     dev_free(c, c->d_im_words); dev_free(c, c->d_im_n); dev_free(c, c->d_rows_stale); dev_free(c, c->d_row_tiles);
     dev_free(c, c->d_im_off); dev_free(c, c->d_im_head); dev_free(c, c->d_im_key);
     dev_free(c, c->d_im_corr); dev_free(c, c->d_im_x); dev_free(c, c->d_im_qz); dev_free(c, c->d_im_pz);
@@ -346,6 +347,25 @@ void build_doc_tiles(const std::vector<int32_t>& doff, int64_t D, int32_t cap_to
     if (cur_docs > 0) chunk_doc.push_back((int32_t)D);
 }
 
+// The tiling of the documents, in such a way that K counters per document fit the LDS that a tile has for
+// its documents' tables, if that makes few more tiles (returns true; *cap_docs is then what fits).
+// Counters take one LDS access where the hash tables take a probe loop: 270 instead of 430 vector and 97
+// instead of 220 scalar instructions per token and wave in documents of 330 tokens, K = 1000.  (2 * 10^7 of
+// them: doc pass 0.390 -> 0.367 ms, which the record exchange with the word pass bounds.)
+bool tile_documents(const std::vector<int32_t>& doff, int64_t D, int32_t K, int32_t cap_tokens, int32_t* cap_docs,
+                    int32_t max_doc, std::vector<int32_t>& chunk_doc, std::vector<int32_t>& long_doc)
+{
+    build_doc_tiles(doff, D, cap_tokens, *cap_docs, max_doc, chunk_doc, long_doc);
+    const int32_t fit = std::min(*cap_docs, 2 * cap_tokens / ((K + 1) / 2));
+    if (fit < 1 || K > kNkLdsTopics) return false;
+    std::vector<int32_t> chunks, longs;
+    build_doc_tiles(doff, D, cap_tokens, fit, max_doc, chunks, longs);
+    if (chunks.size() > chunk_doc.size() + chunk_doc.size() / 16) return false;
+    chunk_doc.swap(chunks);
+    *cap_docs = fit;
+    return true;
+}
+
 }  // namespace
 }  // namespace lda
 
@@ -473,8 +493,8 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
 
     std::vector<int32_t> chunk_doc;
     std::vector<int64_t> long_slot;
-    build_doc_tiles(c->h_doff, D, c->chunk_tokens, c->chunk_docs, c->chunk_tokens, chunk_doc,
-                    c->h_long_doc);
+    c->chunk_direct = tile_documents(c->h_doff, D, K, c->chunk_tokens, &c->chunk_docs, c->chunk_tokens, chunk_doc,
+                                     c->h_long_doc);
     c->n_chunks = (int32_t)chunk_doc.size() - 1;
     // chains of one or two steps leave room for 768-thread workgroups on tiles of 1536 tokens
     // (measured: 7 % faster doc pass at K = 10 000); longer chains need the registers
@@ -484,8 +504,8 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
         c->chunk_tokens2 = 1536;
         c->chunk_docs2 = 255;
         c->sweep_block2 = 768;
-        build_doc_tiles(c->h_doff, D, c->chunk_tokens2, c->chunk_docs2, c->chunk_tokens, chunk_doc2,
-                        same_long);
+        c->chunk_direct2 = tile_documents(c->h_doff, D, K, c->chunk_tokens2, &c->chunk_docs2, c->chunk_tokens,
+                                          chunk_doc2, same_long);
         c->n_chunks2 = (int32_t)chunk_doc2.size() - 1;
     }
     c->n_long = (int32_t)c->h_long_doc.size();
@@ -582,6 +602,11 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
     if (hybrid) {
         TRY(setup_hybrid(c, woff));
         any_dense_alias = c->n_dense_alias > 0;
+    }
+    for (int32_t w = 0; w < V; ++w) c->most_word_tokens = std::max(c->most_word_tokens, woff[w + 1] - woff[w]);
+    {
+        std::vector<uint32_t> limit;
+        if (doc_limits(c->alphabar, limit)) TRY(upload(c, &c->d_doc_limit, limit, "document limits"));
     }
     TRY(setup_implied(c, woff));
     TRY(setup_split_sweep(c, woff));

@@ -94,6 +94,7 @@ struct lda_ctx {
     uint32_t sweep_index = 0;
     bool prev_valid = false;  // d_znew holds the assignment before the last sweep
     int32_t longest_doc = 0;  // tokens of the longest document
+    int32_t most_word_tokens = 0;
     std::string err;
 
     // corpus, document-major (CSR order)
@@ -184,6 +185,8 @@ struct lda_ctx {
     uint8_t* d_tokdoc2 = nullptr;
     int32_t n_chunks2 = 0;
     int32_t chunk_tokens2 = 0, chunk_docs2 = 0, sweep_block2 = 0;
+    bool chunk_direct = false, chunk_direct2 = false;  // K counters per document fit the tiles
+    uint32_t* d_doc_limit = nullptr;  // [tokens of a tile's document] (doc_limits); NULL: there is none
     // documents too long for an LDS tile: hashed in a global workspace
     int32_t* d_long_doc = nullptr;     // [n_long] document ids
     int64_t* d_long_slot = nullptr;    // [n_long+1] first hash slot of each long document
@@ -401,6 +404,7 @@ int refresh_sweep_max_doc();
 int launch_sweep_doc_refresh(lda_ctx* c, int32_t mh_steps, int32_t longest_doc);
 // Two-pass sweep (word pass over word-major tokens, doc pass over document tiles)
 bool split_sweep_supported(lda_ctx* c, int32_t mh_steps);
+bool doc_limits(double alphabar, std::vector<uint32_t>& limit);
 int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff);
 int launch_sweep_split(lda_ctx* c, int32_t mh_steps);
 int launch_tokdoc(lda_ctx* c);                               // per-token document index in its tile
@@ -462,8 +466,9 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
         // full 64-bit products: one multiply instruction yields both halves
         const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
-        const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
-        const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+        // (0x96: the exclusive or of three, one instruction instead of two)
+        const uint32_t n0 = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c1, k0, 0x96);
+        const uint32_t n2 = __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), c3, k1, 0x96);
         c1 = (uint32_t)p1;
         c3 = (uint32_t)p0;
         c0 = n0;

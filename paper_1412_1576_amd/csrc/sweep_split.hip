@@ -24,6 +24,7 @@
 // The arithmetic, the random numbers and their use are those of the fused kernel
 // (sweep.hip), so the result is bit-identical.
 #include <algorithm>
+#include <cmath>
 
 #include "common.hpp"
 #include "doc_tile.hpp"
@@ -119,6 +120,21 @@ __device__ __forceinline__ void store_ints(int32_t* __restrict__ p, const int32_
     }
 }
 
+// The accept test in 32 bits with a margin that no rounding of it can cross (StepFilter::margin):
+// decides all but some 2^-17 of the tests whose number is known, and the rest, in any lane of a wave, are
+// decided in 64.  On this chip a 32-bit multiply or add takes 2.6 cycles of a wave, a 64-bit one 4.6 to 5.1.
+struct StepFilter {
+    // (n_kd + alpha) times a power of two that keeps all products of a step in range, with the margin on
+    // the den side; on = 0: there is none, every test is made in 64 bits
+    float num_scale, num_alpha, den_scale, den_alpha;
+    float alpha, beta, betabar;
+    int32_t on;
+    // A product has at most five factors (n - m) + c: three roundings each, two for the scaled one and
+    // its constants one each, and four of the product; u two.  Both sides: 41 * 2^-24 < 2^-18.
+    static constexpr float margin = 1.0f / 262144.0f;
+    static constexpr float both = 1.0f + 2.1f * margin;  // > (1 + margin)^2 with its rounding
+};
+
 struct SplitArgs {
     const int32_t* z;
     int32_t* znew;
@@ -145,8 +161,11 @@ struct SplitArgs {
     int32_t max_doc_tokens;  // a longer document is a tile of its own, left to the long-document kernel
     int32_t doc_block;       // threads per workgroup of the doc pass
     int32_t tile_lds_ints;  // ints of a document tile in LDS (the n_k copy follows it)
+    int32_t direct;         // n_kd of the tiling's documents as counters
     double alpha, beta, alphabar, betabar;
     uint32_t seed_lo, seed_hi, sweep;
+    StepFilter filter;
+    const uint32_t* doc_limit;  // [tokens of a document] of the doc proposal's choice (doc_limits)
     // hybrid store / mixture proposal (null in the all-dense mode)
     const uint4* metaA;
     const uint4* metaB;
@@ -277,16 +296,22 @@ __device__ __forceinline__ void with_record_layout(const SplitArgs& A, F&& f)
 
 constexpr int32_t kRowItemRun = 8, kMixItemRun = 16, kPieceRun = 256;  // at most
 
+// Eq. (9): whether the doc proposal is the topic of a token of the document (of L tokens) and not a
+// uniform one.  Monotone in x0: a larger x0 never copies where a smaller one does not.
+__host__ __device__ __forceinline__ bool copies_token(uint32_t x0, int32_t L, double alphabar)
+{
+#pragma clang fp contract(off)
+    const double u0 = ((double)x0 + 0.5) * (1.0 / 4294967296.0);
+    const double Ld = (double)L;
+    return u0 * (Ld + alphabar) < Ld;
+}
+
 // Eq. (9), (12): the topic of a random token of the document, or a uniform topic.
 // zat(j) is the snapshot topic of the document's j-th token.
 template <class ZAt>
-__device__ __forceinline__ int32_t doc_proposal(uint32_t x0, uint32_t x1, int32_t L, int32_t K,
-                                                double alphabar, ZAt zat)
+__device__ __forceinline__ int32_t doc_proposal(bool copies, uint32_t x1, int32_t L, int32_t K, ZAt zat)
 {
-#pragma clang fp contract(off)
-    const double u0 = unit_open(x0);
-    const double Ld = (double)L;
-    if (u0 * (Ld + alphabar) < Ld) return zat(mulhi32(x1, (uint32_t)L));
+    if (copies) return zat(mulhi32(x1, (uint32_t)L));
     return (int32_t)mulhi32(x1, (uint32_t)K);
 }
 
@@ -312,7 +337,7 @@ __global__ __launch_bounds__(256) void doc_proposals_kernel(SplitArgs A)
             for (int k = 0; k < ND; ++k) {
                 uint32_t x[4];
                 philox4x32_10(g, 0u, A.sweep, (uint32_t)C::doc_step(k), A.seed_lo, A.seed_hi, x);
-                row[1 + k] = doc_proposal(x[0], x[1], L, A.K, A.alphabar,
+                row[1 + k] = doc_proposal(copies_token(x[0], L, A.alphabar), x[1], L, A.K,
                                           [&](uint32_t j) { return A.z[b + (int32_t)j]; });
             }
         }
@@ -784,16 +809,39 @@ __global__ __launch_bounds__(512) void word_pass_mix_rows_kernel(SplitArgs A)
 
 // ---- doc pass ------------------------------------------------------------------------
 
-struct TileDoc {  // document staged in an LDS tile
-    PackedDocTable tab;
-    const uint32_t* zs;  // the document's packed (topic | slot << 20) entries
+// Document staged in an LDS tile.  DIRECT: its n_kd are an array of K 16-bit counters; else a hash table.
+template <bool DIRECT>
+struct TileDoc {
+    const uint32_t* zs;  // the document's topics; else packed (topic | slot << 20) entries
+    const uint32_t* tab;
     int32_t L;
-    __device__ __forceinline__ int32_t count(int32_t k) const { return tab.count(k); }
+    uint32_t limit;
+    __device__ __forceinline__ int32_t count(int32_t k) const
+    {
+        if constexpr (DIRECT) return (int32_t)reinterpret_cast<const uint16_t*>(tab)[k];
+        else return table().count(k);
+    }
+    __device__ __forceinline__ int32_t own_count(int32_t topic, uint32_t slot) const
+    {
+        if constexpr (DIRECT) return count(topic);
+        else return table().count_at(slot);
+    }
     __device__ __forceinline__ void token(uint32_t j, int32_t& topic, int32_t& nd) const
     {
         const uint32_t v = zs[j];
-        topic = (int32_t)(v & kTopicMask);
-        nd = tab.count_at(v >> kTopicBits);
+        if constexpr (DIRECT) {
+            topic = (int32_t)v;
+            nd = count(topic);
+        } else {
+            topic = (int32_t)(v & kTopicMask);
+            nd = table().count_at(v >> kTopicBits);
+        }
+    }
+    // Eq. (9): the proposal is the topic of a token of the document
+    __device__ __forceinline__ bool copies(uint32_t x0, double) const { return x0 <= limit; }
+    __device__ __forceinline__ PackedDocTable table() const
+    {
+        return PackedDocTable{const_cast<uint32_t*>(tab), (uint32_t)L};
     }
 };
 
@@ -806,6 +854,10 @@ struct LongDoc {  // document hashed in the global workspace
     {
         topic = z[j];
         nd = tab.count(topic);
+    }
+    __device__ __forceinline__ bool copies(uint32_t x0, double alphabar) const
+    {
+        return copies_token(x0, L, alphabar);
     }
 };
 
@@ -857,9 +909,7 @@ __device__ __forceinline__ void doc_pass_chains(const SplitArgs& A, const DocVie
                     uint32_t x[4];
                     philox4x32_10(g[u], 0u, A.sweep, (uint32_t)j, A.seed_lo, A.seed_hi, x);
                     x2[q][u] = x[2];
-                    const double u0 = unit_open(x[0]);
-                    const double Ld = (double)doc[u].L;
-                    if (u0 * (Ld + A.alphabar) < Ld) {
+                    if (doc[u].copies(x[0], A.alphabar)) {
                         doc[u].token(mulhi32(x[1], (uint32_t)doc[u].L), t[q][u], ndt[q][u]);
                     } else {
                         t[q][u] = (int32_t)mulhi32(x[1], (uint32_t)A.K);
@@ -880,37 +930,57 @@ __device__ __forceinline__ void doc_pass_chains(const SplitArgs& A, const DocVie
                 const int32_t tt = t[q][u], nd_t = ndt[q][u], nw_t = nwt[q][u], nk_t = nkt[q][u];
                 const int32_t ms = (s[u] == z0[u]) ? 1 : 0;
                 const int32_t mt = (tt == z0[u]) ? 1 : 0;
-                // Eq. (4) ratio p(t)/p(s), the token removed at its snapshot topic
-                double num = (double)(nd_t - mt) + A.alpha;
-                num = num * ((double)(nw_t - mt) + A.beta);
-                num = num * ((double)(nks[u] - ms) + A.betabar);
-                double den = (double)(nds[u] - ms) + A.alpha;
-                den = den * ((double)(nws[u] - ms) + A.beta);
-                den = den * ((double)(nk_t - mt) + A.betabar);
-                if (word_step) {  // Eq. (8): times p_w(s)/p_w(t)
-                    num = num * ((double)nws[u] + A.beta);
-                    num = num * ((double)nk_t + A.betabar);
-                    den = den * ((double)nw_t + A.beta);
-                    den = den * ((double)nks[u] + A.betabar);
-                } else {          // Eq. (11): times p_d(s)/p_d(t)
-                    num = num * ((double)nds[u] + A.alpha);
-                    den = den * ((double)nd_t + A.alpha);
-                }
-                bool accept;
-                if (word_step) {
-                    // x2 is known up to its low bits.  The test is monotone in x2 (a rounded product
-                    // of a positive number is monotone), so if both ends of the interval agree the
-                    // test is decided; if they differ in any lane, the wave draws the number itself.
-                    const bool at_low = unit_open(x2[q][u]) * den < num;
-                    const bool at_high = unit_open(x2[q][u] | kHintSpan) * den < num;
-                    accept = at_high;
-                    if (__any((at_low != at_high) && (tt != s[u]))) {
-                        uint32_t x[4];
-                        philox4x32_10(g[u], 0u, A.sweep, (uint32_t)j, A.seed_lo, A.seed_hi, x);
-                        accept = unit_open(x[2]) * den < num;
+                bool accept = false, sure = false;
+                if (A.filter.on) {
+                    const StepFilter& F = A.filter;
+                    const float fms = ms ? 1.0f : 0.0f, fmt = mt ? 1.0f : 0.0f;
+                    const float dt = (float)nd_t, wt = (float)nw_t, kt = (float)nk_t;
+                    const float ds = (float)nds[u], ws = (float)nws[u], ks = (float)nks[u];
+                    float num = __builtin_fmaf(dt - fmt, F.num_scale, F.num_alpha);
+                    num = num * ((wt - fmt) + F.beta);
+                    num = num * ((ks - fms) + F.betabar);
+                    float den = __builtin_fmaf(ds - fms, F.den_scale, F.den_alpha);
+                    den = den * ((ws - fms) + F.beta);
+                    den = den * ((kt - fmt) + F.betabar);
+                    float low, high;  // around u
+                    if (word_step) {
+                        num = num * (ws + F.beta);
+                        num = num * (kt + F.betabar);
+                        den = den * (wt + F.beta);
+                        den = den * (ks + F.betabar);
+                        low = (float)x2[q][u] * (1.0f / 4294967296.0f);  // 12 bits: exact
+                        high = low + (float)(kHintSpan + 1u) * (1.0f / 4294967296.0f);
+                    } else {
+                        num = num * (ds + F.alpha);
+                        den = den * (dt + F.alpha);
+                        low = high = __builtin_fmaf((float)x2[q][u], 1.0f / 4294967296.0f, 0.5f / 4294967296.0f);
                     }
-                } else {
-                    accept = unit_open(x2[q][u]) * den < num;
+                    accept = high * den < num;
+                    sure = accept || low * den > num * F.both;
+                }
+                // Eq. (8), (11) in fp64, for the wave if any of its lanes needs it
+                if (__any(!sure && (tt != s[u]))) {
+                    // Eq. (4) ratio p(t)/p(s), the token removed at its snapshot topic
+                    double num = (double)(nd_t - mt) + A.alpha;
+                    num = num * ((double)(nw_t - mt) + A.beta);
+                    num = num * ((double)(nks[u] - ms) + A.betabar);
+                    double den = (double)(nds[u] - ms) + A.alpha;
+                    den = den * ((double)(nws[u] - ms) + A.beta);
+                    den = den * ((double)(nk_t - mt) + A.betabar);
+                    uint32_t r2 = x2[q][u];
+                    if (word_step) {  // Eq. (8): times p_w(s)/p_w(t)
+                        num = num * ((double)nws[u] + A.beta);
+                        num = num * ((double)nk_t + A.betabar);
+                        den = den * ((double)nw_t + A.beta);
+                        den = den * ((double)nks[u] + A.betabar);
+                        uint32_t x[4];  // the record holds x2's top bits only
+                        philox4x32_10(g[u], 0u, A.sweep, (uint32_t)j, A.seed_lo, A.seed_hi, x);
+                        r2 = x[2];
+                    } else {          // Eq. (11): times p_d(s)/p_d(t)
+                        num = num * ((double)nds[u] + A.alpha);
+                        den = den * ((double)nd_t + A.alpha);
+                    }
+                    accept = unit_open(r2) * den < num;
                 }
                 accept = accept && (tt != s[u]);
                 s[u] = accept ? tt : s[u];
@@ -929,7 +999,7 @@ struct TileTokens {
     bool valid;                  // uniform: a tile this kernel handles
     uint32_t g[T];
     int32_t wp[T], idx[T], z0[T], dl[T], r[T][R];
-    int32_t doc_end;             // doff of the thread's own document of the tile (clamped to the last)
+    int32_t doc_begin, doc_end;  // of the thread's own document of the tile (clamped to the last)
     bool live[T];
 };
 
@@ -964,7 +1034,9 @@ __device__ __forceinline__ void tile_issue_positions(const SplitArgs& A, int32_t
         t.dl[u] = (int32_t)__builtin_nontemporal_load(&A.tokdoc[t.g[u]]);
     }
     const int32_t nd = t.d1 - t.d0;
-    t.doc_end = A.doff[t.d0 + ((int32_t)threadIdx.x < nd ? (int32_t)threadIdx.x : nd)];
+    const int32_t* const of = A.doff + t.d0 + ((int32_t)threadIdx.x < nd ? (int32_t)threadIdx.x : nd - 1);
+    t.doc_begin = of[0];
+    t.doc_end = of[1];
 }
 
 // second half: the word-pass records (one random line per token)
@@ -976,53 +1048,70 @@ __device__ __forceinline__ void tile_issue_records(const SplitArgs& A, TileToken
     for (int u = 0; u < T; ++u) load_ints<R>(A.rec + ((size_t)t.wp[u] << RS), t.r[u]);
 }
 
-// Stage the tile as load_doc_tile does (doc_tile.hpp: same LDS layout, same tables) but keep
-// what each thread learns about its own tokens in registers -- the thread that inserts a
-// token into its document's table is the one that runs its chain --, run the chains, write
-// the new assignment, and from it draw the doc proposals of the next sweep.
-template <int NW, int ND, int T>
+// Stage the tile as load_doc_tile does (doc_tile.hpp) but keep what each thread learns about its own
+// tokens in registers -- the thread that inserts a token into its document's table is the one that
+// runs its chain --, run the chains, write the new assignment, and from it draw the doc proposals of
+// the next sweep.  LDS: zs [cap_tokens], the documents' tables [2 * cap_tokens], and per document
+// (begin | tokens << 16, limit).
+//
+// DIRECT: a document's table is K 16-bit counters, so that inserting and counting are one LDS access
+// each; the tiling keeps so few documents to a tile that their counters fit the tables' room.
+template <int NW, int ND, int T, bool DIRECT>
 __device__ __forceinline__ void tile_process(const SplitArgs& A, int32_t* smem,
                                              const int32_t* __restrict__ nk,
                                              const TileTokens<T, Chain<NW, ND>::R>& t)
 {
     using C = Chain<NW, ND>;
-    DocTile tile;
-    tile.zs = reinterpret_cast<uint32_t*>(smem);
-    tile.tab = reinterpret_cast<uint32_t*>(smem + A.cap_tokens);
-    tile.sdoff = smem + 3 * (size_t)A.cap_tokens;
-    tile.nd = t.d1 - t.d0;
-    tile.tok0 = t.tok0;
-    tile.ntok = t.ntok;
+    uint32_t* const zs = reinterpret_cast<uint32_t*>(smem);
+    uint32_t* const tab = reinterpret_cast<uint32_t*>(smem + A.cap_tokens);
+    uint2* const docs = reinterpret_cast<uint2*>(smem + 3 * (size_t)A.cap_tokens);
+    const int32_t nd = t.d1 - t.d0, tid = (int32_t)threadIdx.x, nt = (int32_t)blockDim.x;
+    const int32_t words = (A.K + 1) / 2;  // of a document's counters
     int32_t nd0[T], s[T];
     uint32_t slot[T];
-    // document offsets inside the tile: a thread's first one was requested with its tokens
-    if ((int32_t)threadIdx.x <= tile.nd) tile.sdoff[threadIdx.x] = t.doc_end - t.tok0;
-    for (int32_t i = threadIdx.x + blockDim.x; i <= tile.nd; i += blockDim.x) tile.sdoff[i] = A.doff[t.d0 + i] - t.tok0;
+    // the documents: a thread's first one was requested with its tokens
+    if (tid < nd) docs[tid].x = (uint32_t)(t.doc_begin - t.tok0) | ((uint32_t)(t.doc_end - t.doc_begin) << 16);
+    const uint32_t limit = A.doc_limit[tid < nd ? t.doc_end - t.doc_begin : 0];
+    for (int32_t i = tid + nt; i < nd; i += nt) {
+        const int32_t b = A.doff[t.d0 + i], L = A.doff[t.d0 + i + 1] - b;
+        docs[i] = make_uint2((uint32_t)(b - t.tok0) | ((uint32_t)L << 16), A.doc_limit[L]);
+    }
+    if constexpr (DIRECT)
+        for (int32_t i = tid; i < nd * words; i += nt) tab[i] = 0u;
 #pragma unroll
     for (int u = 0; u < T; ++u) {
         if (t.live[u]) {
-            tile.zs[t.idx[u]] = (uint32_t)t.z0[u];
-            reinterpret_cast<uint2*>(tile.tab)[t.idx[u]] = make_uint2(kEmptySlot, kEmptySlot);
+            zs[t.idx[u]] = (uint32_t)t.z0[u];
+            if constexpr (!DIRECT) reinterpret_cast<uint2*>(tab)[t.idx[u]] = make_uint2(kEmptySlot, kEmptySlot);
         }
     }
     __syncthreads();
+    if (tid < nd) docs[tid].y = limit;
 #pragma unroll
     for (int u = 0; u < T; ++u) {
         if (t.live[u]) {
-            slot[u] = tile.table(t.dl[u]).insert(t.z0[u]);
-            tile.zs[t.idx[u]] = (uint32_t)t.z0[u] | (slot[u] << kTopicBits);  // own element only
+            if constexpr (DIRECT) {
+                atomicAdd(&tab[t.dl[u] * words + (t.z0[u] >> 1)], 1u << (16 * (t.z0[u] & 1)));
+            } else {
+                const uint32_t d = docs[t.dl[u]].x;
+                slot[u] = PackedDocTable{tab + 2 * (d & 0xFFFFu), d >> 16}.insert(t.z0[u]);
+                zs[t.idx[u]] = (uint32_t)t.z0[u] | (slot[u] << kTopicBits);  // own element only
+            }
         }
     }
     __syncthreads();
-    TileDoc doc[T];
+    TileDoc<DIRECT> doc[T];
 #pragma unroll
     for (int u = 0; u < T; ++u) {
-        const int32_t b = tile.sdoff[t.dl[u]];
-        doc[u].L = tile.sdoff[t.dl[u] + 1] - b;
-        doc[u].tab = tile.table(t.dl[u]);
-        doc[u].zs = tile.zs + b;
-        if (!t.live[u]) slot[u] = tile.zs[t.idx[u]] >> kTopicBits;  // a clone of the last token
-        nd0[u] = doc[u].tab.count_at(slot[u]);
+        const uint2 d = docs[t.dl[u]];
+        const int32_t b = (int32_t)(d.x & 0xFFFFu);
+        doc[u].L = (int32_t)(d.x >> 16);
+        doc[u].limit = d.y;
+        doc[u].tab = DIRECT ? tab + t.dl[u] * words : tab + 2 * b;
+        doc[u].zs = zs + b;
+        if constexpr (!DIRECT)
+            if (!t.live[u]) slot[u] = zs[t.idx[u]] >> kTopicBits;  // a clone of the last token
+        nd0[u] = doc[u].own_count(t.z0[u], DIRECT ? 0u : slot[u]);
     }
     doc_pass_chains<NW, ND, T>(A, doc, t.g, t.r, t.z0, nd0, nk, s);
 #pragma unroll
@@ -1033,7 +1122,7 @@ __device__ __forceinline__ void tile_process(const SplitArgs& A, int32_t* smem,
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < T; ++u)
-        if (t.live[u]) tile.zs[t.idx[u]] = (uint32_t)s[u];
+        if (t.live[u]) zs[t.idx[u]] = (uint32_t)s[u];
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < T; ++u) {
@@ -1044,9 +1133,8 @@ __device__ __forceinline__ void tile_process(const SplitArgs& A, int32_t* smem,
         for (int k = 0; k < ND; ++k) {
             uint32_t x[4];
             philox4x32_10(t.g[u], 0u, A.sweep + 1u, (uint32_t)C::doc_step(k), A.seed_lo, A.seed_hi, x);
-            const uint32_t* zs = doc[u].zs;
-            row[1 + k] = doc_proposal(x[0], x[1], doc[u].L, A.K, A.alphabar,
-                                      [&](uint32_t j) { return (int32_t)zs[j]; });
+            row[1 + k] = doc_proposal(doc[u].copies(x[0], A.alphabar), x[1], doc[u].L, A.K,
+                                      [&](uint32_t j) { return (int32_t)doc[u].zs[j]; });
         }
         store_zt<ND>(A, (size_t)t.wp[u], row);
     }
@@ -1063,7 +1151,7 @@ __device__ __forceinline__ void tile_process(const SplitArgs& A, int32_t* smem,
 // three n_k reads of a token are otherwise three separate requests to L2 (the array is larger
 // than the L1), and the rate of such requests, not their bytes, is what bounded this kernel:
 // without them it ran 14.8 instead of 22.7 ms on the benchmark workload.
-template <int NW, int ND, int T, int MAXB, bool NKL>
+template <int NW, int ND, int T, int MAXB, bool NKL, bool DIRECT>
 __global__ __launch_bounds__(MAXB, (T <= 2 && NW + ND <= 2) ? (MAXB <= 256 ? 7 : (MAXB <= 768 ? 6 : 1)) : 1) void doc_pass_tiles_kernel(SplitArgs A)
 {
     using C = Chain<NW, ND>;
@@ -1103,7 +1191,7 @@ __global__ __launch_bounds__(MAXB, (T <= 2 && NW + ND <= 2) ? (MAXB <= 256 ? 7 :
     } else {
         tile_issue_records<T, C::R, C::rec_shift>(A, t);
     }
-    tile_process<NW, ND, T>(A, smem, nk, t);
+    tile_process<NW, ND, T, DIRECT>(A, smem, nk, t);
 }
 
 template <int NW, int ND>
@@ -1154,7 +1242,7 @@ __global__ __launch_bounds__(1024) void doc_pass_long_kernel(SplitArgs A)
         for (int k = 0; k < ND; ++k) {
             uint32_t x[4];
             philox4x32_10(g, 0u, A.sweep + 1u, (uint32_t)C::doc_step(k), A.seed_lo, A.seed_hi, x);
-            row[1 + k] = doc_proposal(x[0], x[1], Ld, A.K, A.alphabar, [&](uint32_t j) {
+            row[1 + k] = doc_proposal(copies_token(x[0], Ld, A.alphabar), x[1], Ld, A.K, [&](uint32_t j) {
                 return __hip_atomic_load(&A.znew[tok0 + (int32_t)j], __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);
             });
@@ -1177,7 +1265,9 @@ int raise_lds_limit(lda_ctx* c, Kern kern, size_t lds)
 template <int NW, int ND, int T, int MAXB, bool NKL>
 int launch_doc_tiles_as(lda_ctx* c, const SplitArgs& A, size_t lds)
 {
-    auto kern = doc_pass_tiles_kernel<NW, ND, T, MAXB, NKL>;
+    auto kern = doc_pass_tiles_kernel<NW, ND, T, MAXB, NKL, false>;
+    if constexpr (NKL)  // (counters of a document never fit beyond)
+        if (A.direct) kern = doc_pass_tiles_kernel<NW, ND, T, MAXB, NKL, true>;
     const int rc = raise_lds_limit(c, kern, lds);
     if (rc != LDA_OK) return rc;
     hipLaunchKernelGGL(kern, dim3(xcd_grid(A.n_chunks)), dim3(A.doc_block), lds, c->stream, A);
@@ -1376,7 +1466,46 @@ bool long_chain_in_two_passes(const lda_ctx* c, int32_t mh_steps)
     return mixture && topic_steps >= (c->N >= 10000000 ? 2000 : 3000) && (longs || c->N >= 3000000);
 }
 
+// Off where the products of a step could leave the range of 32-bit numbers: every partial product, and
+// u of at least 2^-33 times it, lies between the products of the factors' bounds that exceed 1 and of
+// those below.
+StepFilter step_filter(const lda_ctx* c)
+{
+    StepFilter F{};
+    const double a0 = c->alpha, b0 = c->beta, k0 = c->betabar;
+    const double a1 = (double)c->longest_doc + a0, b1 = (double)c->most_word_tokens + b0, k1 = (double)c->N + k0;
+    double most = 0.0, least = -33.0;  // powers of two
+    for (double f : {a1, a1, b1, b1, k1, k1}) most += std::max(0.0, std::log2(f));
+    for (double f : {a0, a0, b0, b0, k0, k0}) least += std::min(0.0, std::log2(f));
+    if (!(most - least <= 240.0)) return F;
+    const double scale = std::ldexp(1.0, (int)std::floor(-0.5 * (most + least)));
+    F.num_scale = (float)scale;
+    F.num_alpha = (float)(a0 * scale);
+    F.den_scale = (float)(scale * (1.0 + (double)StepFilter::margin));
+    F.den_alpha = (float)(a0 * scale * (1.0 + (double)StepFilter::margin));
+    F.alpha = (float)a0; F.beta = (float)b0; F.betabar = (float)k0;
+    F.on = 1;
+    return F;
+}
+
 }  // namespace
+
+// limit[L]: a doc proposal of a document of L tokens copies a token exactly if x0 <= limit[L], for tiles'
+// documents.  False if for some L none would (alpha of 10^9 and more).
+bool doc_limits(double alphabar, std::vector<uint32_t>& limit)
+{
+    limit.assign((size_t)kMaxTileTokens + 1, 0u);
+    for (int32_t L = 1; L <= kMaxTileTokens; ++L) {
+        if (!copies_token(0u, L, alphabar)) return false;
+        uint32_t lo = 0u, hi = 0xFFFFFFFFu;  // copies at lo
+        while (lo < hi) {
+            const uint32_t mid = lo + (hi - lo) / 2 + 1;
+            if (copies_token(mid, L, alphabar)) lo = mid; else hi = mid - 1;
+        }
+        limit[(size_t)L] = lo;
+    }
+    return true;
+}
 
 // Chains of 1..4 steps in the cycle mode (and the one-step word chain), tiles of at most
 // 4 tokens per thread; chains of 5..8 steps with the default tiles, one token per thread, where they
@@ -1385,6 +1514,7 @@ bool long_chain_in_two_passes(const lda_ctx* c, int32_t mh_steps)
 // 3.55 ms fused, 2.17 ms in two passes.
 bool split_sweep_supported(lda_ctx* c, int32_t mh_steps)
 {
+    if (!c->d_doc_limit) return false;
     if (mh_steps < 1 || mh_steps > 8) return false;
     if (mh_steps > 4)
         return c->opt.proposal_mode == 0 && c->n_chunks2 > 0 && c->chunk_tokens <= 1024 &&
@@ -1516,15 +1646,17 @@ int launch_sweep_split(lda_ctx* c, int32_t mh_steps)
     A.K = c->K; A.cap_tokens = c->chunk_tokens; A.max_doc_tokens = c->chunk_tokens;
     A.doc_block = c->sweep_block;
     // (rounded up to 16 bytes: the copy of n_k behind the tile is moved as int4)
-    auto tile_ints = [](int32_t tokens, int32_t docs) {
-        return (int32_t)((doc_tile_lds_bytes(tokens, docs) / sizeof(int32_t) + 3) / 4 * 4);
-    };
+    auto tile_ints = [](int32_t tokens, int32_t docs) { return (3 * tokens + 2 * docs + 3) / 4 * 4; };
     A.tile_lds_ints = tile_ints(c->chunk_tokens, c->chunk_docs);
+    A.direct = c->chunk_direct ? 1 : 0;
+    A.doc_limit = c->d_doc_limit;
+    A.filter = step_filter(c);
     if (nw + nd <= 2 && c->n_chunks2 > 0) {  // short chains: the tiling with larger tiles
         A.chunk_doc = c->d_chunk_doc2; A.chunk_tok = c->d_chunk_tok2; A.tokdoc = c->d_tokdoc2;
         A.n_chunks = c->n_chunks2;
         A.cap_tokens = c->chunk_tokens2; A.doc_block = c->sweep_block2;
         A.tile_lds_ints = tile_ints(c->chunk_tokens2, c->chunk_docs2);
+        A.direct = c->chunk_direct2 ? 1 : 0;
     } else if (c->n_chunks2 > 0) {
         // longer chains (default tiles): one token per thread.  Up to 4 steps take 64 VGPRs, which
         // leaves two 1024-thread workgroups per CU (4 steps: 28.9 instead of 33.4 ms); 5 to 8 steps
