@@ -87,7 +87,7 @@ void dev_free(lda_ctx* c, T*& p)
 void free_all(lda_ctx* c)
 {
     dev_free(c, c->d_word); dev_free(c, c->d_doff); dev_free(c, c->d_z); dev_free(c, c->d_znew);
-    dev_free(c, c->d_gid); dev_free(c, c->d_wpos); dev_free(c, c->d_xmap); dev_free(c, c->d_zt); dev_free(c, c->d_rec);
+    dev_free(c, c->d_gid); dev_free(c, c->d_wpos); dev_free(c, c->d_xmap); dev_free(c, c->d_rshift); dev_free(c, c->d_zt); dev_free(c, c->d_rec);
     dev_free(c, c->d_row_items); dev_free(c, c->d_mix_items); dev_free(c, c->d_gather_pieces);
     for (int i = 0; i < 3; ++i) dev_free(c, c->d_sort_words[i]);
     dev_free(c, c->d_long_words); dev_free(c, c->d_long_base); dev_free(c, c->d_long_tiles); dev_free(c, c->d_fill_tiles);
@@ -437,8 +437,9 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
     {   // order of the records the sweep's two passes exchange (layout.hip, launch_layout)
         int32_t bucket = o.record_bucket_tokens;
         // default: buckets for a large corpus on the all-dense store, where the doc pass gains
-        // more than the word pass and the rebuild lose (measured: 7 * 10^8 tokens gain, 10^8
-        // tokens and the hybrid store lose a few percent)
+        // more than the word pass and the rebuild lose (measured: 7 * 10^8 tokens gain 9 %; 10^8 tokens
+        // gain or lose up to 4 % with the doc pass at 0.7 of its time, chains of four steps and more
+        // lose 4 %; the hybrid store loses)
         if (bucket == 0) bucket = (H == V && N >= ((int64_t)1 << 28)) ? (1 << 22) : -1;
         if (o.stream_block_tokens > 0) bucket = -1;  // the two-pass sweep's records do not exist
         c->record_bucket_shift = 0;
@@ -446,6 +447,11 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
             while ((1 << c->record_bucket_shift) < bucket) ++c->record_bucket_shift;
         else
             c->record_bucket_shift = -1;  // one bucket
+        // Words of at least this many tokens keep word-major order (layout.hip).  7.4 * 10^8 tokens, 141 000
+        // words, K = 10 000, word pass + doc pass + recount, ms: all words in buckets 5.82 + 14.44 + 2.77, none
+        // 4.65 + 16.81 + 2.17, with N >> 14 4.89 + 14.46 + 2.33, >> 16 4.82 + 14.52 + 2.24, >> 18 4.73 + 14.85
+        // + 2.22.
+        c->bucket_below = (int32_t)std::max<int64_t>(256, N >> 16);
     }
     c->stream = reinterpret_cast<hipStream_t>(o.hip_stream);
 
@@ -602,6 +608,16 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
     if (hybrid) {
         TRY(setup_hybrid(c, woff));
         any_dense_alias = c->n_dense_alias > 0;
+    }
+    if (c->d_xmap) {
+        std::vector<int32_t> rshift((size_t)V, kMapped);
+        int32_t before = 0;  // records of the words in word-major order
+        for (int32_t w = 0; w < V; ++w) {
+            if (woff[w + 1] - woff[w] < c->bucket_below) continue;
+            rshift[w] = before - woff[w];
+            before += woff[w + 1] - woff[w];
+        }
+        TRY(upload(c, &c->d_rshift, rshift, "record order"));
     }
     for (int32_t w = 0; w < V; ++w) c->most_word_tokens = std::max(c->most_word_tokens, woff[w + 1] - woff[w]);
     {

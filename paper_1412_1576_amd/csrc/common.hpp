@@ -15,6 +15,7 @@
 namespace lda {
 
 constexpr int kWave = 64;
+constexpr int32_t kMapped = INT32_MIN;  // d_rshift: the word's records are in buckets
 
 enum State { COUNTS_VALID = 1, ALIAS_VALID = 2, SWEPT = 3 };
 
@@ -107,8 +108,12 @@ struct lda_ctx {
     int32_t* d_wpos = nullptr;  // [N] position of token g's records in zt / rec: its word-major
                                 //     position (inverse of gid), mapped through d_xmap if set
     int32_t* d_xmap = nullptr;  // [N] word-major position -> record position (NULL: identity)
-    int32_t record_bucket_shift = -1;  // records ordered by (CSR position >> shift, word-major
-                                       // position); -1: by word-major position alone
+    int32_t* d_rshift = nullptr;  // [V] with d_xmap: record position - word-major position of a word's
+                                  //     tokens where that is one number, else kMapped
+    int32_t record_bucket_shift = -1;  // records of words with fewer than bucket_below tokens ordered by (CSR
+                                       // position >> shift, word-major position), after those of the
+                                       // others, which are in word-major order; -1: all are
+    int32_t bucket_below = 0;
     // Word-major token records of 2^zt_shift ints.  Fields: the token's z, then the topic that
     // doc step i of the coming sweep proposes for it (when td_valid); one int per field, or,
     // with zt_pack16 (K <= 65536), two 16-bit fields per int.  The z field is the low

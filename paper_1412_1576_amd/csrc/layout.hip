@@ -69,13 +69,18 @@ __global__ __launch_bounds__(256) void invert_kernel(const int32_t* __restrict__
         wpos[gid[p]] = (int32_t)p;
 }
 
-// keys[p] = bucket of the token at word-major position p (its CSR position >> shift)
-__global__ __launch_bounds__(256) void bucket_keys_kernel(const int32_t* __restrict__ gid, int64_t n,
-                                                          int shift, int32_t* __restrict__ keys)
+// keys[p] = 0 for a token of a word of at least `below` tokens, else 1 + the bucket of the token at
+// word-major position p (its CSR position >> shift)
+__global__ __launch_bounds__(256) void bucket_keys_kernel(const int32_t* __restrict__ gid, int64_t n, int shift,
+                                                          const int32_t* __restrict__ word,
+                                                          const int32_t* __restrict__ woff, int32_t below,
+                                                          int32_t* __restrict__ keys)
 {
     for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n;
-         p += (int64_t)gridDim.x * blockDim.x)
-        keys[p] = gid[p] >> shift;
+         p += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t g = gid[p], w = word[g];
+        keys[p] = woff[w + 1] - woff[w] >= below ? 0 : 1 + (g >> shift);
+    }
 }
 
 // wpos[g] = xmap[wpos[g]]
@@ -120,8 +125,10 @@ namespace {
 // (inside a bucket by word-major position) confines the doc pass, which walks the corpus in
 // order, to one bucket's records at a time -- a window of some tens of megabytes that the
 // memory-side cache holds -- while the word pass still meets the records of a word in
-// ascending order, now as one run per bucket.
-//   xmap[p] = rank of word-major position p under the key (gid[p] >> shift, p)
+// ascending order, now as one run per bucket.  The records of frequent words share their lines with
+// each other in word-major order already -- the next token of the word in the corpus finds the line
+// in the L2 -- and stay in that order, ahead of the buckets: no map to read, and runs of any length.
+//   xmap[p] = rank of word-major position p under the key (0 or 1 + (gid[p] >> shift), p)
 //   wpos[g] = xmap[wpos[g]]
 int build_record_order(lda_ctx* c)
 {
@@ -147,10 +154,10 @@ int build_record_order(lda_ctx* c)
         return rc;
     }
     hipLaunchKernelGGL(bucket_keys_kernel, dim3(grid_for(N, 256)), dim3(256), 0, c->stream, c->d_gid, N,
-                       shift, keys);
+                       shift, c->d_word, c->d_woff, c->bucket_below, keys);
     hipLaunchKernelGGL(iota_kernel, dim3(grid_for(N, 256)), dim3(256), 0, c->stream, pos, N);
     int end_bit = 1;
-    while (end_bit < 31 && (1LL << end_bit) < ((long long)(N - 1) >> shift) + 1) ++end_bit;
+    while (end_bit < 31 && (1LL << end_bit) < ((long long)(N - 1) >> shift) + 2) ++end_bit;
     size_t tmp_bytes = 0;
     // stable: inside a bucket the word-major positions stay ascending
     hipError_t e = rocprim::radix_sort_pairs(nullptr, tmp_bytes, keys, keys_sorted, pos, pos_sorted,

@@ -72,6 +72,7 @@ struct TilesArgs {
     const uint32_t* __restrict__ sp_off;
     int32_t *__restrict__ sp_topic, *__restrict__ sp_count, *__restrict__ sp_nnz;
     const int32_t* __restrict__ xmap;
+    const int32_t* __restrict__ rshift;
     const int32_t* __restrict__ go;
 };
 
@@ -80,7 +81,8 @@ __device__ __forceinline__ void nkw_tile(const TilesArgs& A, const RebuildTile t
 {
     const int32_t* __restrict__ zw = A.zw;
     int32_t* __restrict__ nkw = A.nkw;
-    const int32_t* __restrict__ xmap = A.xmap;
+    const int32_t shift = A.xmap ? A.rshift[t.w] : 0;
+    const int32_t* __restrict__ xmap = shift == kMapped ? A.xmap : nullptr;
     const int32_t K = A.K, span = A.span, sh = A.sh;
     const uint32_t zmask = A.zmask;
     auto sync = [&]() {
@@ -93,7 +95,7 @@ __device__ __forceinline__ void nkw_tile(const TilesArgs& A, const RebuildTile t
         const uint32_t r = ((uint32_t)rec & zmask) - (uint32_t)k0;
         if (r < (uint32_t)nk_r) atomicAdd(&hist[r], 1);
     };
-    auto at = [&](int32_t p) -> size_t { return xmap ? (size_t)xmap[p] : (size_t)p; };
+    auto at = [&](int32_t p) -> size_t { return xmap ? (size_t)xmap[p] : (size_t)(p + shift); };
     int32_t p = t.p0 + tid;
     // The thread's first records are requested before the histogram is cleared: most tiles are
     // short (a word of a thousand tokens), and the clearing and its barrier then hide the two
@@ -522,7 +524,7 @@ int launch_dense_rows(lda_ctx* c, const int32_t* go = nullptr, bool lists = fals
     TilesArgs A{};
     A.zw = c->d_zt; A.sh = c->zt_shift; A.zmask = c->zt_mask; A.K = K; A.span = span; A.nkw = c->d_nkw;
     A.sp_off = c->d_sp_off; A.sp_topic = c->d_sp_topic; A.sp_count = c->d_sp_count; A.sp_nnz = c->d_sp_nnz;
-    A.xmap = c->d_xmap; A.go = go;
+    A.xmap = c->d_xmap; A.rshift = c->d_rshift; A.go = go;
     if (n_wide_tiles > 0) {
         A.tiles = tiles; A.n_tiles = n_wide_tiles;
         A.run = xcd_run_length(A.n_tiles, kTileRun);

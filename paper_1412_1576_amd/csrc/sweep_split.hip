@@ -144,6 +144,7 @@ struct SplitArgs {
     const uint8_t* tokdoc;
     const int32_t* wpos;
     const int32_t* xmap;  // word-major position -> record position (NULL: identity)
+    const int32_t* rshift;  // with xmap, per word
     const int32_t* gid;
     const int32_t* woff;
     const int32_t* nkw;
@@ -253,12 +254,13 @@ struct TokenFetch {
     size_t q[U];
     uint32_t g[U];
     int32_t w[U][W];
+    int32_t shift;  // record position - word-major position (not XM)
     template <bool GID>
     __device__ __forceinline__ void positions(const SplitArgs& A, const int32_t (&p)[U])
     {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if constexpr (XM) q[u] = (size_t)A.xmap[p[u]]; else q[u] = (size_t)p[u];
+            if constexpr (XM) q[u] = (size_t)A.xmap[p[u]]; else q[u] = (size_t)(p[u] + shift);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -284,10 +286,11 @@ struct TokenFetch {
 template <bool B>
 struct Flag { static constexpr bool value = B; };
 
+// shift: of the one word whose tokens are served, kMapped if there are several
 template <class F>
-__device__ __forceinline__ void with_record_layout(const SplitArgs& A, F&& f)
+__device__ __forceinline__ void with_record_layout(const SplitArgs& A, int32_t shift, F&& f)
 {
-    if (A.xmap) {
+    if (A.xmap && shift == kMapped) {
         if (A.zt_pack16) f(Flag<true>{}, Flag<true>{}); else f(Flag<true>{}, Flag<false>{});
     } else {
         if (A.zt_pack16) f(Flag<false>{}, Flag<true>{}); else f(Flag<false>{}, Flag<false>{});
@@ -383,7 +386,8 @@ __global__ __launch_bounds__(1024) void word_pass_rows_kernel(SplitArgs A)
     }
     __syncthreads();
     const uint32_t capw = A.cap[it.x];
-    with_record_layout(A, [&](auto xm, auto p16) {
+    const int32_t shift = A.xmap ? A.rshift[it.x] : 0;
+    with_record_layout(A, shift, [&](auto xm, auto p16) {
         // U tokens per thread and round, their loads issued together stage by stage
         constexpr int U = C::M <= 4 ? 4 : 2;
         for (int32_t i0 = 0; i0 < it.z; i0 += U * nt) {
@@ -397,6 +401,7 @@ __global__ __launch_bounds__(1024) void word_pass_rows_kernel(SplitArgs A)
                 if (!live[u]) i = it.z - 1;  // redo the item's last token, drop the result
                 p[u] = it.y + i;
             }
+            f.shift = shift;
             f.template positions<(NW > 0)>(A, p);
             f.records(A);
 #pragma unroll
@@ -455,8 +460,9 @@ __global__ __launch_bounds__(256) void word_pass_gather_kernel(SplitArgs A)
     const int tid = threadIdx.x, nt = blockDim.x;
     for (int32_t i = tid; i <= nwords; i += nt) soff[i] = A.woff[pc.x + i];
     __syncthreads();
+    const int32_t shift = !A.xmap ? 0 : (nwords == 1 ? A.rshift[pc.x] : kMapped);
     if constexpr (STORE == 0) {
-        with_record_layout(A, [&](auto xm, auto p16) {
+        with_record_layout(A, shift, [&](auto xm, auto p16) {
             constexpr int U = C::M <= 4 ? 4 : 2;
             for (int32_t i0 = 0; i0 < pc.w; i0 += U * nt) {
                 int32_t p[U], zt[U][1 + ND], out[U][C::R];
@@ -471,6 +477,7 @@ __global__ __launch_bounds__(256) void word_pass_gather_kernel(SplitArgs A)
                     if (!live[u]) i = pc.w - 1;  // redo the piece's last token, drop the result
                     p[u] = pc.z + i;
                 }
+                f.shift = shift;
                 f.template positions<(NW > 0)>(A, p);
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -522,7 +529,7 @@ __global__ __launch_bounds__(256) void word_pass_gather_kernel(SplitArgs A)
     } else {
         BetaTable bt{};
         if constexpr (NW > 0) bt = load_beta_table(A);
-        with_record_layout(A, [&](auto xm, auto p16) {
+        with_record_layout(A, shift, [&](auto xm, auto p16) {
             constexpr int U = C::M <= 4 ? 2 : 1;
             for (int32_t i0 = 0; i0 < pc.w; i0 += U * nt) {
                 int32_t p[U], w[U], zt[U][1 + ND], out[U][C::R];
@@ -540,6 +547,7 @@ __global__ __launch_bounds__(256) void word_pass_gather_kernel(SplitArgs A)
                     if (!live[u]) i = pc.w - 1;
                     p[u] = pc.z + i;
                 }
+                f.shift = shift;
                 f.template positions<(NW > 0)>(A, p);
 #pragma unroll
                 for (int u = 0; u < U; ++u) w[u] = pc.x + piece_word(soff, nwords, p[u]);
@@ -658,7 +666,8 @@ __global__ __launch_bounds__(256) void word_pass_implied_kernel(SplitArgs A)
         }
     }
     __syncthreads();
-    with_record_layout(A, [&](auto xm, auto p16) {
+    const int32_t shift = A.xmap ? kMapped : 0;
+    with_record_layout(A, shift, [&](auto xm, auto p16) {
         constexpr int U = 2;
         for (int32_t i0 = 0; i0 < pc.w; i0 += U * nt) {
             int32_t p[U], w[U], zt[1 + ND], out[C::R];
@@ -672,6 +681,7 @@ __global__ __launch_bounds__(256) void word_pass_implied_kernel(SplitArgs A)
                 if (!live[u]) i = pc.w - 1;  // redo the piece's last token, drop the result
                 p[u] = pc.z + i;
             }
+            f.shift = shift;
             f.template positions<(NW > 0)>(A, p);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -728,7 +738,8 @@ __global__ __launch_bounds__(512) void word_pass_mix_rows_kernel(SplitArgs A)
     const int4 it = A.mix_items[it_i];  // (w, p0, n, 0)
     const int32_t K = A.K, w = it.x;
     const int tid = threadIdx.x, nt = blockDim.x;
-    with_record_layout(A, [&](auto xm, auto p16) {
+    const int32_t shift = A.xmap ? A.rshift[w] : 0;
+    with_record_layout(A, shift, [&](auto xm, auto p16) {
         constexpr int U = 2;
         int32_t p[U];
         bool live[U];
@@ -745,6 +756,7 @@ __global__ __launch_bounds__(512) void word_pass_mix_rows_kernel(SplitArgs A)
         // The first round's token loads and the thread's first list entry are requested before
         // the row is built: they do not depend on it, and its two barriers hide their latency.
         place(0);
+        f.shift = shift;
         f.template positions<(NW > 0)>(A, p);
         f.records(A);
         const size_t off = A.sp_off[w];
@@ -1636,7 +1648,7 @@ int launch_sweep_split(lda_ctx* c, int32_t mh_steps)
                                    c->td_nd == nd));
     SplitArgs A{};
     A.z = c->d_z; A.znew = c->d_znew; A.doff = c->d_doff; A.chunk_doc = c->d_chunk_doc; A.chunk_tok = c->d_chunk_tok;
-    A.tokdoc = c->d_tokdoc; A.wpos = c->d_wpos; A.xmap = c->d_xmap; A.gid = c->d_gid; A.woff = c->d_woff;
+    A.tokdoc = c->d_tokdoc; A.wpos = c->d_wpos; A.xmap = c->d_xmap; A.rshift = c->d_rshift; A.gid = c->d_gid; A.woff = c->d_woff;
     A.nkw = c->d_nkw; A.nk = c->d_nk; A.alias = c->d_alias; A.cap = c->d_cap;
     A.zt = c->d_zt; A.zt_pack16 = c->zt_pack16 ? 1 : 0; A.rec = c->d_rec; A.row_items = c->d_row_items; A.pieces = c->d_gather_pieces;
     A.n_chunks = c->n_chunks; A.n_row_items = c->n_row_items; A.n_pieces = c->n_gather_pieces;
