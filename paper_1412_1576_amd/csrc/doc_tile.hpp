@@ -65,7 +65,28 @@ __device__ __forceinline__ DocTile load_doc_tile(int32_t* smem, int32_t cap_toke
     return t;
 }
 
-// A document too long for an LDS tile: its table lives in a global workspace
+// A document too long for an LDS tile, with up to this many topics: K counters in the LDS of every
+// workgroup that works for it.  All threads call it; it ends with a barrier.
+constexpr int32_t kLongDocTopics = 32768;  // 128 KB
+
+__device__ __forceinline__ void count_long_doc(int32_t* cnt, int32_t K, const int32_t* __restrict__ zdoc, int32_t L)
+{
+    const int tid = threadIdx.x, nt = blockDim.x;
+    for (int32_t k = tid; k < K; k += nt) cnt[k] = 0;
+    __syncthreads();
+    int32_t i = tid;
+    for (; i + 3 * nt < L; i += 4 * nt) {
+        int32_t t[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) t[u] = zdoc[i + u * nt];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) atomicAdd(&cnt[t[u]], 1);
+    }
+    for (; i < L; i += nt) atomicAdd(&cnt[zdoc[i]], 1);
+    __syncthreads();
+}
+
+// A document too long for an LDS tile, with more topics: its table lives in a global workspace
 // (keys/cnts of 2*L slots), cleared and filled by the calling workgroup.
 __device__ __forceinline__ GlobalDocTable load_long_doc(int32_t* keys, int32_t* cnts,
                                                         const int32_t* __restrict__ zdoc,

@@ -873,6 +873,22 @@ struct LongDoc {  // document hashed in the global workspace
     }
 };
 
+struct LongDocCounters {  // document with K counters in LDS
+    const int32_t* cnt;
+    const int32_t* z;
+    int32_t L;
+    __device__ __forceinline__ int32_t count(int32_t k) const { return cnt[k]; }
+    __device__ __forceinline__ void token(uint32_t j, int32_t& topic, int32_t& nd) const
+    {
+        topic = z[j];
+        nd = cnt[topic];
+    }
+    __device__ __forceinline__ bool copies(uint32_t x0, double alphabar) const
+    {
+        return copies_token(x0, L, alphabar);
+    }
+};
+
 // The chains of T tokens of one thread, advanced together stage by stage.  doc[u] is
 // token u's document, g[u] its CSR position (the Philox counter), r[u] its word-pass record, z0[u] its snapshot topic and nd0[u] = n_kd of it.
 template <int NW, int ND, int T, class DocView>
@@ -1206,6 +1222,62 @@ __global__ __launch_bounds__(MAXB, (T <= 2 && NW + ND <= 2) ? (MAXB <= 256 ? 7 :
     tile_process<NW, ND, T, DIRECT>(A, smem, nk, t);
 }
 
+// Long documents, K <= kLongDocTopics: a workgroup (blockIdx.x, blockIdx.y) runs the chains of a slice
+// of a document with counters of the whole of it; the doc proposals of the next sweep, which need the
+// document's new assignment, are a launch of their own.  One workgroup per document with a hash table
+// filled by global atomics was 57 us of an iteration's 150 in a corpus of 7 * 10^4 tokens, 10 % of them in
+// seven such documents; these two 6.3 + 3.4.
+constexpr int32_t kLongSlice = 1024;    // tokens at least
+constexpr int32_t kLongSlices = 64;     // of a document at most: each reads all of it
+
+template <int NW, int ND>
+__global__ __launch_bounds__(1024) void doc_pass_long_slices_kernel(SplitArgs A)
+{
+    using C = Chain<NW, ND>;
+    extern __shared__ int32_t smem[];
+    const int32_t d = A.long_doc[blockIdx.y];
+    const int32_t tok0 = A.doff[d], L = A.doff[d + 1] - tok0;
+    const int32_t slices = (int32_t)gridDim.x;
+    const int32_t per = ((L + slices - 1) / slices + kLongSlice - 1) / kLongSlice * kLongSlice;
+    const int32_t i0 = (int32_t)blockIdx.x * per, i1 = L - i0 < per ? L : i0 + per;  // (i0 < 64 * 2^25)
+    if (i0 >= L) return;
+    count_long_doc(smem, A.K, A.z + tok0, L);
+    for (int32_t base = i0; base < i1; base += (int32_t)blockDim.x) {
+        const bool live = base + (int32_t)threadIdx.x < i1;
+        const int32_t i = live ? base + (int32_t)threadIdx.x : i1 - 1;  // past the end: the last token again
+        const uint32_t g[1] = {(uint32_t)(tok0 + i)};
+        const LongDocCounters doc[1] = {LongDocCounters{smem, A.z + tok0, L}};
+        int32_t r[1][C::R], s[1];
+        load_ints<C::R>(A.rec + ((size_t)A.wpos[g[0]] << C::rec_shift), r[0]);
+        const int32_t z0[1] = {A.z[g[0]]};
+        const int32_t nd0[1] = {smem[z0[0]]};
+        doc_pass_chains<NW, ND, 1>(A, doc, g, r, z0, nd0, A.nk, s);
+        if (live) A.znew[g[0]] = s[0];
+    }
+}
+
+template <int NW, int ND>
+__global__ __launch_bounds__(256) void long_doc_proposals_kernel(SplitArgs A)
+{
+    using C = Chain<NW, ND>;
+    const int32_t d = A.long_doc[blockIdx.y];
+    const int32_t tok0 = A.doff[d], L = A.doff[d + 1] - tok0;
+    const int64_t step = (int64_t)gridDim.x * 256;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < L; i += step) {
+        const uint32_t g = (uint32_t)(tok0 + (int32_t)i);
+        int32_t row[1 + ND];
+        row[0] = A.znew[g];
+#pragma unroll
+        for (int k = 0; k < ND; ++k) {
+            uint32_t x[4];
+            philox4x32_10(g, 0u, A.sweep + 1u, (uint32_t)C::doc_step(k), A.seed_lo, A.seed_hi, x);
+            row[1 + k] = doc_proposal(copies_token(x[0], L, A.alphabar), x[1], L, A.K,
+                                      [&](uint32_t j) { return A.znew[tok0 + (int32_t)j]; });
+        }
+        store_zt<ND>(A, (size_t)A.wpos[g], row);
+    }
+}
+
 template <int NW, int ND>
 __global__ __launch_bounds__(1024) void doc_pass_long_kernel(SplitArgs A)
 {
@@ -1370,7 +1442,21 @@ int launch_chain(lda_ctx* c, const SplitArgs& A, bool need_proposals)
         LDA_HIP(c, hipEventRecord(c->pass_ev[2], c->stream));
         c->pass_ev_recorded = true;
     }
-    if (c->n_long > 0) {
+    if (c->n_long > 0 && c->K <= kLongDocTopics) {
+        auto kern = doc_pass_long_slices_kernel<NW, ND>;
+        const size_t lds = sizeof(int32_t) * (size_t)c->K;
+        if ((rc = raise_lds_limit(c, kern, lds)) != LDA_OK) return rc;
+        for (int32_t i = 0; i < c->n_long; i += 65535) {  // (the grid's second dimension)
+            SplitArgs B = A;
+            B.long_doc += i;
+            const unsigned n = (unsigned)std::min(c->n_long - i, 65535);
+            const unsigned slices = (unsigned)std::min((c->longest_doc + kLongSlice - 1) / kLongSlice, kLongSlices);
+            hipLaunchKernelGGL(kern, dim3(slices, n), dim3(1024), lds, c->stream, B);
+            const unsigned parts = (unsigned)std::min((c->longest_doc + 255) / 256, 1024);
+            hipLaunchKernelGGL((long_doc_proposals_kernel<NW, ND>), dim3(parts, n), dim3(256), 0, c->stream, B);
+            LDA_HIP(c, hipGetLastError());
+        }
+    } else if (c->n_long > 0) {
         hipLaunchKernelGGL((doc_pass_long_kernel<NW, ND>), dim3(c->n_long), dim3(1024), 0, c->stream,
                            A);
         LDA_HIP(c, hipGetLastError());

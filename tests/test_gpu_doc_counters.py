@@ -63,3 +63,19 @@ def test_range_of_alpha_and_beta(lda_mod, oracle_mod, alpha, beta, K):
     lens = np.concatenate([np.random.default_rng(K).integers(1, 200, 80), [1500, 5]])
     doff, words = make(lens, 90, K)
     check(lda_mod, oracle_mod, doff, words, 90, K, alpha, beta, (2, 4, 2, 8, 2))
+
+
+# documents beyond a tile: counters in LDS up to 32 768 topics, slices of 1024 tokens and, beyond 64 of
+# them, longer ones
+@pytest.mark.parametrize("K", [1, 40, 32768, 32769])
+def test_long_documents(lda_mod, oracle_mod, K):
+    doff, words = make([1025, 70001, 0, 2048, 3, 2049, 66000, 5000], 40, K)
+    g = lda_mod.Lda(doff, words, 40, K, 0.1, 0.01, seed=2)
+    o = oracle_mod.Oracle(doff, words, 40, K, 0.1, 0.01, seed=2)
+    for m in (2, 2, 3, 1, 4):
+        for c in (g, o):
+            c.build_alias(); c.sweep(m); c.rebuild_counts()
+        assert np.array_equal(g.get_z(), o.get_z()), m
+    a, b = g.loglik(), o.loglik()
+    assert abs(a[0] - b[0]) <= 1e-9 * max(abs(b[0]), 1e6) and g.loglik()[0] == g.loglik_noalloc()[0] == a[0]
+    g.close(); o.close()
