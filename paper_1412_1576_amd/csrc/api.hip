@@ -116,7 +116,7 @@ void free_all(lda_ctx* c)
     dev_free(c, c->d_flag);
     dev_free(c, c->d_dense_alias_words);
     for (int i = 0; i < kMixClasses; ++i) dev_free(c, c->d_mix_class[i]);
-    dev_free(c, c->d_sparse_words); dev_free(c, c->d_compact_words); dev_free(c, c->d_sp_off);
+    dev_free(c, c->d_sparse_words); dev_free(c, c->d_row_words); dev_free(c, c->d_compact_words); dev_free(c, c->d_sp_off);
     dev_free(c, c->d_sp_topic); dev_free(c, c->d_sp_count); dev_free(c, c->d_sp_nnz); dev_free(c, c->d_hs_off);
     dev_free(c, c->d_hs); dev_free(c, c->d_ma); dev_free(c, c->d_metaA); c->d_metaB = nullptr;
     dev_free(c, c->d_beta_alias); dev_free(c, c->d_beta_hdr);
@@ -221,7 +221,7 @@ int setup_hybrid(lda_ctx* c, const std::vector<int32_t>& woff)
     c->h_wkind.resize(V);
     c->h_sp_off.assign((size_t)V + 1, 0);
     c->h_hs_off.assign((size_t)V + 1, 0);
-    std::vector<int32_t> dense_alias, mix, sparse, compact, list_only, mixc[kMixClasses];
+    std::vector<int32_t> dense_alias, mix, sparse, compact, listed, row_words, mixc[kMixClasses];
     std::vector<uint4> meta(2 * (size_t)V, make_uint4(0u, 0u, 0u, 0u));
     const int32_t lds_max = max_lds_table_entries();
     uint64_t list_total = 0, hash_total = 0;
@@ -241,6 +241,7 @@ int setup_hybrid(lda_ctx* c, const std::vector<int32_t>& woff)
         uint32_t lg = 0;
         if (dense_alias_w) {
             dense_alias.push_back(w);
+            row_words.push_back(w);
         } else {
             if ((uint32_t)cw >> kMixCountBits)
                 return fail(c, LDA_ERR_UNSUPPORTED,
@@ -256,10 +257,14 @@ int setup_hybrid(lda_ctx* c, const std::vector<int32_t>& woff)
             if (dense_row) {
                 if (!list_from_rebuild(c, w)) {
                     compact.push_back(w);
-                } else if (K <= kMixRowTopics && cw >= kMixRowMinTokens) {
-                    kind |= (uint8_t)kKindListOnly;  // served from its list everywhere
-                    c->h_wkind[w] = kind;
-                    list_only.push_back(w);
+                    row_words.push_back(w);
+                } else {
+                    listed.push_back(w);
+                    if (K <= kMixRowTopics && cw >= kMixRowMinTokens) {
+                        kind |= (uint8_t)kKindListOnly;  // served from its list everywhere
+                        c->h_wkind[w] = kind;
+                        ++c->n_list_only;
+                    }
                 }
             } else {
                 sparse.push_back(w);
@@ -279,9 +284,9 @@ int setup_hybrid(lda_ctx* c, const std::vector<int32_t>& woff)
     c->total_hash = (int64_t)hash_total;
     c->n_dense_alias = (int32_t)dense_alias.size();
     c->n_mix = (int32_t)mix.size();
-    c->n_list_only = (int32_t)list_only.size();
-    sparse.insert(sparse.end(), list_only.begin(), list_only.end());  // d_sparse_words: see common.hpp
+    sparse.insert(sparse.end(), listed.begin(), listed.end());  // d_sparse_words: see common.hpp
     c->n_sparse = (int32_t)sparse.size();
+    c->n_row_words = (int32_t)row_words.size();
     c->n_compact = (int32_t)compact.size();
     if (c->n_dense_alias > 0 && K > lds_max && (double)H * (double)K > 4.0e9)
         return fail(c, LDA_ERR_UNSUPPORTED, "lda_init: dense tables for %d words at K = %d", H, K);
@@ -291,6 +296,7 @@ int setup_hybrid(lda_ctx* c, const std::vector<int32_t>& woff)
     UP(d_dense_alias_words, dense_alias, "dense-table words");
     UP(d_sparse_words, sparse, "sparse-row words");
     UP(d_compact_words, compact, "compaction words");
+    UP(d_row_words, row_words, "dense-row words");
     for (int i = 0; i < kMixClasses; ++i) {
         c->n_mix_class[i] = (int32_t)mixc[i].size();
         UP(d_mix_class[i], mixc[i], "mixture class");

@@ -222,9 +222,11 @@ struct lda_ctx {
     // many workgroups each)
     int32_t* d_mix_class[lda::kMixClasses] = {};
     int32_t n_mix_class[lda::kMixClasses] = {};
-    int32_t* d_sparse_words = nullptr;   // words whose n_kw row lives as a list: sparse rows and
-                                         // list-only words (the log-likelihood sums over these lists)
+    int32_t* d_sparse_words = nullptr;   // words whose list the recount makes (the log-likelihood sums
+                                         // over it): sparse rows, and most of the mixture's dense rows
     int32_t n_sparse = 0;
+    int32_t* d_row_words = nullptr;      // the other words: the log-likelihood sums over their rows
+    int32_t n_row_words = 0;
     int32_t n_list_only = 0;             // words marked kKindListOnly
     int32_t* d_compact_words = nullptr;  // mixture words with a dense row (list made by compaction)
     int32_t n_compact = 0;

@@ -300,7 +300,7 @@ __global__ __launch_bounds__(256) void implied_tables_kernel(ImpliedArgs a)
 
 // Log-likelihood, word part, of all words of an all-dense store with implied tables: a wave per word,
 // over its list, or its row where that is kept (fixed: the words whose row always is).
-__global__ __launch_bounds__(256) void loglik_implied_kernel(const int32_t* __restrict__ fixed, int32_t n_fixed,
+__global__ __launch_bounds__(1024) void loglik_implied_kernel(const int32_t* __restrict__ fixed, int32_t n_fixed,
                                                              const int32_t* __restrict__ words, int32_t n_words,
                                                              int32_t K, const uint32_t* __restrict__ off,
                                                              const uint32_t* __restrict__ key,
@@ -310,18 +310,31 @@ __global__ __launch_bounds__(256) void loglik_implied_kernel(const int32_t* __re
                                                              double lg_beta, const double* __restrict__ terms,
                                                              double* __restrict__ partial)
 {
-    __shared__ double wtot[4];
-    const int lane = threadIdx.x & (kWave - 1);
+    __shared__ double wtot[16];
+    __shared__ uint16_t counts[16][kImpliedTokens];
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
     const bool lists = *stale != 0;
     double acc = 0.0;
-    for (int32_t i = (int32_t)(blockIdx.x * 4 + (threadIdx.x >> 6)); i < n_fixed + n_words; i += (int32_t)gridDim.x * 4) {
-        const int32_t w = i < n_fixed ? fixed[i] : words[i - n_fixed];
-        if (lists && i >= n_fixed) {
+    // a row's pieces of kRowPiece counts are dealt out like words
+    const int32_t pieces = (K + kRowPiece - 1) / kRowPiece;
+    const int64_t row_pieces = (int64_t)n_fixed * pieces, total = row_pieces + n_words;
+    for (int64_t i = (int64_t)blockIdx.x * 16 + wv; i < total; i += (int64_t)gridDim.x * 16) {
+        if (i < row_pieces) {
+            const int32_t r = (int32_t)(i / pieces), p = (int32_t)(i - (int64_t)r * pieces);
+            acc += row_terms(nkw + (size_t)fixed[r] * (size_t)K, p * kRowPiece,
+                             K - p * kRowPiece < kRowPiece ? K : (p + 1) * kRowPiece, beta, lg_beta, terms);
+            continue;
+        }
+        const int32_t w = words[i - row_pieces];
+        if (lists) {
             const uint32_t* __restrict__ mine = key + off[w];
             const int32_t n = n_list[w];
             for (int32_t e = lane; e < n; e += kWave) acc += terms[mine[e] & kImpliedCount];  // (at most kImpliedTokens)
         } else {
+            // the list out of the row first: the same terms in the same order either way
             const int32_t* __restrict__ row = nkw + (size_t)w * (size_t)K;
+            uint32_t n = 0;
+            wave_lds_order();
             for (int32_t k0 = 0; k0 < K; k0 += 8 * kWave) {
                 int32_t v[8];
 #pragma unroll
@@ -330,9 +343,14 @@ __global__ __launch_bounds__(256) void loglik_implied_kernel(const int32_t* __re
                     v[u] = k < K ? row[k] : 0;
                 }
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (v[u] > 0) acc += count_term(v[u], beta, lg_beta, terms);
+                for (int u = 0; u < 8; ++u) {
+                    const uint64_t mask = __ballot(v[u] > 0);
+                    if (v[u] > 0) counts[wv][n + rank_below(mask)] = (uint16_t)v[u];
+                    n += (uint32_t)__popcll(mask);
+                }
             }
+            wave_lds_order();
+            for (uint32_t e = lane; e < n; e += kWave) acc += terms[counts[wv][e]];
         }
     }
     const double s = block_sum_f64(acc, wtot);
@@ -450,7 +468,7 @@ int launch_rows_from_lists(lda_ctx* c, int32_t w)
 
 int launch_loglik_implied(lda_ctx* c, double lg_beta, const double* terms, int blocks, double* partial)
 {
-    hipLaunchKernelGGL(loglik_implied_kernel, dim3(blocks), dim3(256), 0, c->stream, c->d_fixed_words,
+    hipLaunchKernelGGL(loglik_implied_kernel, dim3(blocks), dim3(1024), 0, c->stream, c->d_fixed_words,
                        c->n_fixed_words, c->d_im_words, c->n_implied, c->K, c->d_im_off, c->d_im_key, c->d_im_n,
                        c->d_nkw, c->d_rows_stale, c->beta, lg_beta, terms, partial);
     LDA_HIP(c, hipGetLastError());

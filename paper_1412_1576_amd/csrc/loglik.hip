@@ -27,19 +27,37 @@ __global__ __launch_bounds__(256) void term_table_kernel(double a, double lg_a, 
 
 static_assert(kMaxTileTokens < kTermTable, "a count of a document tile is in the table");
 
-// doc part over LDS document tiles: one partial per tile
+// doc part over LDS document tiles: one partial per tile.  (1.9 * 10^6 tokens in documents of 170, K = 500:
+// 36 us with hash tables, 19 with counters.)
 __global__ __launch_bounds__(1024) void loglik_doc_tiles_kernel(
     const int32_t* __restrict__ z, const int32_t* __restrict__ doff,
     const int32_t* __restrict__ chunk_doc, const uint8_t* __restrict__ tokdoc, int32_t cap_tokens,
     int32_t cap_docs, double alpha, double alphabar, double lg_alpha, double lg_alphabar,
-    const double* __restrict__ terms, double* __restrict__ partial)
+    const double* __restrict__ terms, double* __restrict__ partial, int32_t words)
 {
     extern __shared__ int32_t smem[];
     __shared__ double wtot[16];
     const int32_t c = blockIdx.x;
     const int32_t d0 = chunk_doc[c], d1 = chunk_doc[c + 1];
     double acc = 0.0;
-    if (doff[d1] - doff[d0] <= cap_tokens) {
+    if (words > 0 && doff[d1] - doff[d0] <= cap_tokens) {
+        // K counters of 16 bits per document (`words` ints) fit the tile: summed in their order
+        const int32_t tok0 = doff[d0], n = doff[d1] - tok0, nd = d1 - d0;
+        for (int32_t i = threadIdx.x; i < nd * words; i += blockDim.x) smem[i] = 0;
+        __syncthreads();
+        for (int32_t i = threadIdx.x; i < n; i += blockDim.x) {
+            const int32_t k = z[tok0 + i];
+            atomicAdd(&smem[(int32_t)tokdoc[tok0 + i] * words + (k >> 1)], 1 << (16 * (k & 1)));
+        }
+        __syncthreads();
+        for (int32_t i = threadIdx.x; i < nd; i += blockDim.x)
+            acc += lg_alphabar - lgamma((double)(doff[d0 + i + 1] - doff[d0 + i]) + alphabar);
+        for (int32_t i = threadIdx.x; i < nd * words; i += blockDim.x) {
+            const uint32_t v = (uint32_t)smem[i];
+            if (v & 0xFFFFu) acc += terms[v & 0xFFFFu];  // (at most kMaxTileTokens)
+            if (v >> 16) acc += terms[v >> 16];
+        }
+    } else if (doff[d1] - doff[d0] <= cap_tokens) {
         const DocTile T = load_doc_tile(smem, cap_tokens, z, doff, tokdoc, d0, d1);
         // first[s] = the lowest token of the tile whose topic sits in slot s
         int32_t* first = smem + doc_tile_lds_bytes(cap_tokens, cap_docs) / sizeof(int32_t);
@@ -92,8 +110,29 @@ __global__ __launch_bounds__(1024) void loglik_long_docs_kernel(
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
+// the same with K counters in LDS (K <= kLongDocTopics), summed by topic
+__global__ __launch_bounds__(1024) void loglik_long_counters_kernel(
+    const int32_t* __restrict__ z, const int32_t* __restrict__ doff, const int32_t* __restrict__ long_doc,
+    int32_t K, double alpha, double alphabar, double lg_alpha, double lg_alphabar,
+    const double* __restrict__ terms, double* __restrict__ partial)
+{
+    extern __shared__ int32_t smem[];
+    __shared__ double wtot[16];
+    const int32_t d = long_doc[blockIdx.x];
+    const int32_t tok0 = doff[d], L = doff[d + 1] - tok0;
+    count_long_doc(smem, K, z + tok0, L);
+    double acc = 0.0;
+    if (threadIdx.x == 0) acc += lg_alphabar - lgamma((double)L + alphabar);
+    for (int32_t k = threadIdx.x; k < K; k += blockDim.x) {
+        const int32_t v = smem[k];
+        if (v > 0) acc += count_term(v, alpha, lg_alpha, terms);
+    }
+    const double s = block_sum_f64(acc, wtot);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+}
+
 // word part: grid-stride over the dense table, one partial per block; a thread adds its terms in
-// the order of their places, four counts in flight.  Bound by reading the rows: 2.7 * 10^7 counts
+// the order of their places, eight counts in flight.  Bound by reading the rows: 2.7 * 10^7 counts
 // (108 MB) took 97 us with an lgamma per non-zero.  With the table, and one copy and one wait for
 // all partial sums instead of four, a likelihood of 1.9 * 10^6 tokens at K = 500 costs 0.12 ms less.
 __global__ __launch_bounds__(256) void loglik_word_kernel(const int32_t* __restrict__ nkw,
@@ -106,13 +145,11 @@ __global__ __launch_bounds__(256) void loglik_word_kernel(const int32_t* __restr
     double acc = 0.0;
     const int64_t step = (int64_t)gridDim.x * blockDim.x;
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (; i + 3 * step < total; i += 4 * step) {
-        int32_t v[4];
+    for (; i + 7 * step < total; i += 8 * step) {
+        int32_t v[8];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = nkw[i + u * step];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (v[u] > 0) acc += count_term(v[u], beta, lg_beta, terms);
+        for (int u = 0; u < 8; ++u) v[u] = nkw[i + u * step];
+        acc = add_terms<8>(acc, v, beta, lg_beta, terms);
     }
     for (; i < total; i += step) {
         const int32_t v = nkw[i];
@@ -134,26 +171,57 @@ __global__ __launch_bounds__(256) void loglik_nk_kernel(const int32_t* __restric
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
-// word part over the sparse rows: one wave per word of the list, grid-stride
-__global__ __launch_bounds__(256) void loglik_sparse_kernel(const int32_t* __restrict__ words,
-                                                            int32_t n_words,
-                                                            const uint32_t* __restrict__ sp_off,
-                                                            const int32_t* __restrict__ sp_count,
-                                                            const int32_t* __restrict__ sp_nnz,
-                                                            double beta, double lg_beta,
-                                                            const double* __restrict__ terms,
-                                                            double* __restrict__ partial)
+// word part of a store with lists: a wave per piece of a row or per kListGroup words, grid-stride; the words
+// of `rows` over their dense rows, those of `lists` over their lists, which are shorter for words of few
+// tokens even where there is a row too.  A group's list bounds are read together, and four lists at a time:
+// a wave per word waited for three loads in a row for each of its words, 39 us in all.  (54 000 words of 35 tokens, K = 500: 66 us over all rows, 9 more over the lists without a
+// row; so 19.)
+constexpr int32_t kListGroup = 16;
+
+__global__ __launch_bounds__(256) void loglik_lists_kernel(const int32_t* __restrict__ rows, int32_t n_rows,
+                                                           const int32_t* __restrict__ nkw, int32_t K,
+                                                           const int32_t* __restrict__ lists, int32_t n_lists,
+                                                           const uint32_t* __restrict__ sp_off,
+                                                           const int32_t* __restrict__ sp_count,
+                                                           const int32_t* __restrict__ sp_nnz,
+                                                           double beta, double lg_beta,
+                                                           const double* __restrict__ terms,
+                                                           double* __restrict__ partial)
 {
     __shared__ double wtot[4];
     const int lane = threadIdx.x & (kWave - 1);
-    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int nwaves = (gridDim.x * blockDim.x) >> 6;
     double acc = 0.0;
-    for (int32_t i = wave; i < n_words; i += nwaves) {
-        const int32_t w = words[i];
-        const int32_t nnz = sp_nnz[w];
-        const int32_t* __restrict__ cnt = sp_count + sp_off[w];
-        for (int32_t e = lane; e < nnz; e += kWave) acc += count_term(cnt[e], beta, lg_beta, terms);
+    // a row's pieces of kRowPiece counts are dealt out like words
+    const int32_t pieces = (K + kRowPiece - 1) / kRowPiece;
+    const int64_t total = (int64_t)n_rows * pieces + (n_lists + kListGroup - 1) / kListGroup;
+    for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < total; i += (int64_t)gridDim.x * 4) {
+        if (i < (int64_t)n_rows * pieces) {
+            const int32_t r = (int32_t)(i / pieces), p = (int32_t)(i - (int64_t)r * pieces);
+            acc += row_terms(nkw + (size_t)rows[r] * (size_t)K, p * kRowPiece,
+                             K - p * kRowPiece < kRowPiece ? K : (p + 1) * kRowPiece, beta, lg_beta, terms);
+        } else {
+            const int32_t j0 = (int32_t)(i - (int64_t)n_rows * pieces) * kListGroup;
+            int32_t n_mine = 0, off_mine = 0;  // (list offsets are below 2^31)
+            if (lane < kListGroup && j0 + lane < n_lists) {
+                const int32_t w = lists[j0 + lane];
+                n_mine = sp_nnz[w];
+                off_mine = (int32_t)sp_off[w];
+            }
+            for (int j = 0; j < kListGroup; j += 4) {
+                int32_t n[4], v[4];
+                const int32_t* cnt[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    n[u] = __builtin_amdgcn_readlane(n_mine, j + u);
+                    cnt[u] = sp_count + __builtin_amdgcn_readlane(off_mine, j + u);
+                    v[u] = lane < n[u] ? cnt[u][lane] : 0;
+                }
+                acc = add_terms<4>(acc, v, beta, lg_beta, terms);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    for (int32_t e = lane + kWave; e < n[u]; e += kWave) acc += count_term(cnt[u][e], beta, lg_beta, terms);
+            }
+        }
     }
     const double s = block_sum_f64(acc, wtot);
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
@@ -251,6 +319,9 @@ private:
 
 constexpr int kWordBlocks = 4096, kNkBlocks = 64;
 
+// Workgroups of the word part, whose sums the host adds: at most kWordBlocks, one for every 8192 tokens
+int word_blocks(const lda_ctx* c) { return (int)std::min<int64_t>(kWordBlocks, 256 + c->N / 8192); }
+
 // The log-likelihood with the partial sums in d_partial (device memory of cap doubles, at least
 // max(n_chunks, n_long, kWordBlocks)) and host staging in `h` (h_cap doubles).
 int run_loglik(lda_ctx* c, double* d_partial, size_t cap, double* h, size_t h_cap, double* doc_part,
@@ -269,27 +340,33 @@ int run_loglik(lda_ctx* c, double* d_partial, size_t cap, double* h, size_t h_ca
     }
     if (c->n_long > 0) {
         if (!(p = parts.take((size_t)c->n_long, &doc, &rc))) return rc;
-        hipLaunchKernelGGL(loglik_long_docs_kernel, dim3(c->n_long), dim3(1024), 0, c->stream,
-                           c->d_z, c->d_doff, c->d_long_doc, c->d_long_slot, c->d_long_keys,
-                           c->d_long_cnts, c->d_long_first, c->alpha, c->alphabar, lga, lgab, c->d_lg_terms, p);
+        if (c->K <= kLongDocTopics) {
+            const size_t lds = sizeof(int32_t) * (size_t)c->K;
+            if (lds > 48 * 1024)
+                LDA_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(loglik_long_counters_kernel),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            hipLaunchKernelGGL(loglik_long_counters_kernel, dim3(c->n_long), dim3(1024), lds, c->stream, c->d_z,
+                               c->d_doff, c->d_long_doc, c->K, c->alpha, c->alphabar, lga, lgab, c->d_lg_terms, p);
+        } else {
+            hipLaunchKernelGGL(loglik_long_docs_kernel, dim3(c->n_long), dim3(1024), 0, c->stream,
+                               c->d_z, c->d_doff, c->d_long_doc, c->d_long_slot, c->d_long_keys,
+                               c->d_long_cnts, c->d_long_first, c->alpha, c->alphabar, lga, lgab, c->d_lg_terms, p);
+        }
         LDA_HIP(c, hipGetLastError());
     }
     const double* beta_terms = c->d_lg_terms + kTermTable;
-    const int64_t dense_rows = c->hybrid ? c->H : c->V;
+    const int blocks = word_blocks(c);
+    if (!(p = parts.take((size_t)blocks, &word, &rc))) return rc;
     if (c->n_implied > 0) {
-        if (!(p = parts.take(kWordBlocks, &word, &rc))) return rc;
-        if ((rc = launch_loglik_implied(c, lgb, beta_terms, kWordBlocks, p)) != LDA_OK) return rc;
-    } else if (dense_rows > 0) {
-        if (!(p = parts.take(kWordBlocks, &word, &rc))) return rc;
-        hipLaunchKernelGGL(loglik_word_kernel, dim3(kWordBlocks), dim3(256), 0, c->stream, c->d_nkw,
-                           dense_rows * (int64_t)c->K, c->beta, lgb, beta_terms, p);
+        if ((rc = launch_loglik_implied(c, lgb, beta_terms, blocks, p)) != LDA_OK) return rc;
+    } else if (c->hybrid) {
+        hipLaunchKernelGGL(loglik_lists_kernel, dim3(blocks), dim3(256), 0, c->stream, c->d_row_words,
+                           c->n_row_words, c->d_nkw, c->K, c->d_sparse_words, c->n_sparse, c->d_sp_off,
+                           c->d_sp_count, c->d_sp_nnz, c->beta, lgb, beta_terms, p);
         LDA_HIP(c, hipGetLastError());
-    }
-    if (c->hybrid && c->n_sparse > 0) {
-        if (!(p = parts.take(kWordBlocks, &word, &rc))) return rc;
-        hipLaunchKernelGGL(loglik_sparse_kernel, dim3(kWordBlocks), dim3(256), 0, c->stream,
-                           c->d_sparse_words, c->n_sparse, c->d_sp_off, c->d_sp_count,
-                           c->d_sp_nnz, c->beta, lgb, beta_terms, p);
+    } else {
+        hipLaunchKernelGGL(loglik_word_kernel, dim3(blocks), dim3(256), 0, c->stream, c->d_nkw,
+                           (int64_t)c->V * c->K, c->beta, lgb, beta_terms, p);
         LDA_HIP(c, hipGetLastError());
     }
     if (!(p = parts.take(kNkBlocks, &word, &rc))) return rc;
@@ -307,7 +384,7 @@ int run_loglik(lda_ctx* c, double* d_partial, size_t cap, double* h, size_t h_ca
 // largest number of partial sums one log-likelihood has
 size_t loglik_partials(const lda_ctx* c)
 {
-    return (size_t)c->n_chunks + (size_t)c->n_long + 2 * kWordBlocks + kNkBlocks;
+    return (size_t)c->n_chunks + (size_t)c->n_long + kWordBlocks + kNkBlocks;
 }
 
 // the term tables of alpha and beta
@@ -334,7 +411,8 @@ int launch_loglik_doc_tiles(lda_ctx* c, double* d_partial)
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     hipLaunchKernelGGL(loglik_doc_tiles_kernel, dim3(c->n_chunks), dim3(c->sweep_block), lds, c->stream,
                        c->d_z, c->d_doff, c->d_chunk_doc, c->d_tokdoc, c->chunk_tokens, c->chunk_docs,
-                       c->alpha, c->alphabar, lga, lgab, c->d_lg_terms, d_partial);
+                       c->alpha, c->alphabar, lga, lgab, c->d_lg_terms, d_partial,
+                       c->chunk_direct && c->d_tokdoc ? (c->K + 1) / 2 : 0);
     LDA_HIP(c, hipGetLastError());
     return LDA_OK;
 }

@@ -32,4 +32,47 @@ __device__ __forceinline__ double count_term(int32_t v, double a, double lg_a, c
     return v < kTermTable ? table[v] : lgamma((double)v + a) - lg_a;
 }
 
+// acc plus the terms of U counts, zero where there is none.  The look-ups are all in flight together; a
+// test for each of them made them wait for one another (10^8 counts, a fifth of them not zero, 339 us).
+template <int U>
+__device__ __forceinline__ double add_terms(double acc, const int32_t (&v)[U], double a, double lg_a,
+                                            const double* __restrict__ table)
+{
+    double t[U];
+    bool large = false;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        t[u] = table[v[u] < kTermTable ? v[u] : 0];
+        large = large || v[u] >= kTermTable;
+    }
+    if (__any(large)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (v[u] >= kTermTable) t[u] = lgamma((double)v[u] + a) - lg_a;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc += v[u] > 0 ? t[u] : 0.0;
+    return acc;
+}
+
+// A wave's terms of the counts [k0, k1) of a dense row, lane by lane, eight loads in flight
+constexpr int32_t kRowPiece = 2048;
+
+__device__ __forceinline__ double row_terms(const int32_t* __restrict__ row, int32_t k0, int32_t k1, double beta,
+                                            double lg_beta, const double* __restrict__ terms)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    double acc = 0.0;
+    for (int32_t kb = k0; kb < k1; kb += 8 * kWave) {
+        int32_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int32_t k = kb + u * kWave + lane;
+            v[u] = k < k1 ? row[k] : 0;
+        }
+        acc = add_terms<8>(acc, v, beta, lg_beta, terms);
+    }
+    return acc;
+}
+
 }  // namespace lda
