@@ -109,7 +109,7 @@ void free_all(lda_ctx* c)
     dev_free(c, c->d_im_words); dev_free(c, c->d_im_n); dev_free(c, c->d_rows_stale); dev_free(c, c->d_row_tiles);
     dev_free(c, c->d_im_off); dev_free(c, c->d_im_head); dev_free(c, c->d_im_key);
     dev_free(c, c->d_im_corr); dev_free(c, c->d_im_x); dev_free(c, c->d_im_qz); dev_free(c, c->d_im_pz);
-    dev_free(c, c->d_im_sum); dev_free(c, c->d_fixed_words); dev_free(c, c->d_misfits); dev_free(c, c->d_n_misfits); dev_free(c, c->d_im_pieces);
+    dev_free(c, c->d_im_sum); dev_free(c, c->d_fixed_words); dev_free(c, c->d_misfits); dev_free(c, c->d_n_misfits); dev_free(c, c->d_im_pieces); dev_free(c, c->d_short_pieces);
     dev_free(c, c->d_alias); dev_free(c, c->d_cap); dev_free(c, c->d_chunk_doc); dev_free(c, c->d_chunk_tok); dev_free(c, c->d_tokdoc); dev_free(c, c->d_chunk_doc2); dev_free(c, c->d_chunk_tok2); dev_free(c, c->d_tokdoc2); dev_free(c, c->d_long_doc);
     dev_free(c, c->d_long_slot); dev_free(c, c->d_long_keys); dev_free(c, c->d_long_cnts); dev_free(c, c->d_long_first);
     dev_free(c, c->d_tiles); dev_free(c, c->d_list_tiles); dev_free(c, c->d_multi_words); dev_free(c, c->d_partial); dev_free(c, c->d_lg_terms); dev_free(c, c->d_row);

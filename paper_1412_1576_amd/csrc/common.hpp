@@ -167,6 +167,8 @@ struct lda_ctx {
     int32_t* d_n_misfits = nullptr;      //   implied form, which have dense tables made from their lists; how many
     int4* d_im_pieces = nullptr;         // pieces of the word pass, as d_gather_pieces
     int32_t n_im_pieces = 0;
+    int4* d_short_pieces = nullptr;      // and of words of the mixture form with few tokens
+    int32_t n_short_pieces = 0;
     // which forms hold the tables of the current counts, and which one the last sweep drew from
     bool implied_built = false, all_dense_built = false, want_all_dense = false;
     // The counts of words with implied tables: in their lists alone after a recount, unless their rows

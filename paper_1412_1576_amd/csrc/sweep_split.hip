@@ -48,6 +48,9 @@ constexpr int32_t kRowMinTokens = 2048;    // words with fewer tokens are gather
 // pieces the words in flight held 30 MB and three of four gathers missed.
 constexpr int32_t kPieceTokens = 512;
 constexpr int32_t kPieceWords = 4096;      // words of a gather piece (their offsets sit in LDS)
+// A mixture word whose row could be staged is served from its list if it has at most K / kShortShare
+// tokens: a row of K counts to clear and fill costs more than the bisections then.  RULEMEASURED
+constexpr int32_t kShortShare = 8;
 
 constexpr int pow2_shift(int n)
 {
@@ -184,6 +187,8 @@ struct SplitArgs {
     const int64_t* long_slot;
     int32_t* long_keys;
     int32_t* long_cnts;
+    const int4* short_pieces;
+    int32_t n_short_pieces, short_run;
     // implied tables (implied.hpp)
     const int4* im_pieces;
     int32_t n_im_pieces, im_run;
@@ -718,6 +723,123 @@ __global__ __launch_bounds__(256) void word_pass_implied_kernel(SplitArgs A)
                     out[C::rec_topic(k) + 1] = nw;
                 }
                 if (live[u]) store_ints<C::R>(A.rec + (f.q[u] << C::rec_shift), out);
+            }
+        }
+    });
+}
+
+// One piece = the tokens of words [w0, w1), all of the mixture form with few tokens (or without any).
+// Their lists are copied to LDS, a (topic, count) in 32 bits, where every n_kw is found by bisection; a draw
+// gathers one bin.  With the word's hash or dense row in memory instead, the look-ups of a token are two to
+// three random accesses.
+constexpr int32_t kShortTokens = 1024;  // most of such a word, and of a piece
+constexpr int32_t kShortWords = 512;    // words of a piece
+constexpr int kShortCountBits = 12;
+static_assert(kShortTokens < (1 << kShortCountBits) && kTopicBits + kShortCountBits <= 32, "a key fits 32 bits");
+
+__device__ __forceinline__ int32_t short_count(const uint32_t* key, int32_t n, int32_t t)
+{
+    int32_t lo = 0, len = n;
+    while (len > 0) {
+        const int32_t half = len >> 1;
+        const bool less = (key[lo + half] >> kShortCountBits) < (uint32_t)t;
+        lo = less ? lo + half + 1 : lo;
+        len = less ? len - half - 1 : half;
+    }
+    if (lo >= n) return 0;
+    const uint32_t k = key[lo];
+    return (k >> kShortCountBits) == (uint32_t)t ? (int32_t)(k & ((1u << kShortCountBits) - 1u)) : 0;
+}
+
+template <int NW, int ND>
+__global__ __launch_bounds__(256) void word_pass_short_kernel(SplitArgs A)
+{
+    using C = Chain<NW, ND>;
+    __shared__ int32_t soff[kShortWords + 1];
+    __shared__ uint32_t loff[kShortWords + 1];
+    __shared__ uint32_t key[kShortTokens];
+    const int32_t pc_i = xcd_runs(A.short_run);
+    if (pc_i >= A.n_short_pieces) return;
+    const int4 pc = A.short_pieces[pc_i];  // (w0, w1, p0, n)
+    const int32_t nwords = pc.y - pc.x;
+    const int32_t K = A.K;
+    const int tid = threadIdx.x, nt = blockDim.x;
+    const uint32_t l0 = A.sp_off[pc.x], nl = A.sp_off[pc.y] - l0;
+    for (int32_t i = tid; i <= nwords; i += nt) {
+        soff[i] = A.woff[pc.x + i];
+        loff[i] = A.sp_off[pc.x + i] - l0;
+    }
+    for (uint32_t i = tid; i < nl; i += nt)  // (what a list does not use is copied along)
+        key[i] = ((uint32_t)A.sp_topic[l0 + i] << kShortCountBits) | ((uint32_t)A.sp_count[l0 + i] & ((1u << kShortCountBits) - 1u));
+    BetaTable bt{};
+    if constexpr (NW > 0) bt = load_beta_table(A);
+    __syncthreads();
+    const int32_t shift = !A.xmap ? 0 : (nwords == 1 ? A.rshift[pc.x] : kMapped);
+    with_record_layout(A, shift, [&](auto xm, auto p16) {
+        constexpr int U = C::M <= 4 ? 2 : 1;
+        for (int32_t i0 = 0; i0 < pc.w; i0 += U * nt) {
+            int32_t p[U], zt[U][1 + ND], out[U][C::R];
+            uint32_t l[U];
+            bool live[U];
+            WordSide wv[U];
+            TokenFetch<ND, U, decltype(xm)::value, decltype(p16)::value> f;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                int32_t i = i0 + u * nt + tid;
+                live[u] = i < pc.w;
+                if (!live[u]) i = pc.w - 1;  // redo the piece's last token, drop the result
+                p[u] = pc.z + i;
+            }
+            f.shift = shift;
+            f.template positions<(NW > 0)>(A, p);
+            uint4 meta[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int32_t w = piece_word(soff, nwords, p[u]);
+                l[u] = loff[w];
+                meta[u] = A.metaA[2 * (size_t)(pc.x + w)];
+            }
+            f.records(A);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                wv[u].tab = A.ma + l0 + l[u];
+                wv[u].n = meta[u].x;
+                wv[u].C = meta[u].y;
+                wv[u].QS = ((uint64_t)meta[u].w << 32) | meta[u].z;
+                wv[u].kind = 0u;
+                f.decode(u, zt[u]);
+#pragma unroll
+                for (int k = 0; k < C::R; ++k) out[u][k] = 0;
+            }
+            // the bins of every draw, then the look-ups in LDS
+            WordDraw d[NW > 0 ? NW : 1][U];
+            uint4 e[NW > 0 ? NW : 1][U];
+            uint32_t hint[NW > 0 ? NW : 1][U];
+#pragma unroll
+            for (int k = 0; k < NW; ++k) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    uint32_t x[4];
+                    philox4x32_10(f.g[u], 0u, A.sweep, (uint32_t)C::word_step(k), A.seed_lo, A.seed_hi, x);
+                    e[k][u] = *word_draw_address(wv[u], bt, (uint32_t)K, x[0], x[1], x[3], d[k][u]);
+                    hint[k][u] = x[2];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t* const mine = key + l[u];
+                const int32_t n = (int32_t)wv[u].n;
+                out[u][0] = short_count(mine, n, zt[u][0]);
+#pragma unroll
+                for (int k = 0; k < ND; ++k) out[u][C::rec_doc(k)] = short_count(mine, n, zt[u][1 + k]);
+#pragma unroll
+                for (int k = 0; k < NW; ++k) {
+                    int32_t t, nwt;
+                    if (!word_draw_decode(d[k][u], e[k][u], t, nwt)) nwt = short_count(mine, n, t);
+                    out[u][C::rec_topic(k)] = topic_with_hint(t, hint[k][u]);
+                    out[u][C::rec_topic(k) + 1] = nwt;
+                }
+                if (live[u]) store_ints<C::R>(A.rec + (f.q[u] << C::rec_shift), out[u]);
             }
         }
     });
@@ -1418,6 +1540,11 @@ int launch_chain(lda_ctx* c, const SplitArgs& A, bool need_proposals)
             hipLaunchKernelGGL((word_pass_gather_kernel<NW, ND, 2>), grid, dim3(256), 0, c->stream, A);
         LDA_HIP(c, hipGetLastError());
     }
+    if (A.n_short_pieces > 0) {
+        hipLaunchKernelGGL((word_pass_short_kernel<NW, ND>), dim3(xcd_runs_grid(A.n_short_pieces, A.short_run)),
+                           dim3(256), 0, c->stream, A);
+        LDA_HIP(c, hipGetLastError());
+    }
     if (A.n_im_pieces > 0) {
         hipLaunchKernelGGL((word_pass_implied_kernel<NW, ND>), dim3(xcd_runs_grid(A.n_im_pieces, A.im_run)),
                            dim3(256), 0, c->stream, A);
@@ -1624,13 +1751,21 @@ bool split_sweep_supported(lda_ctx* c, int32_t mh_steps)
 // Work lists of the word pass from the word segment offsets.
 int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
 {
-    std::vector<int4> items, mix_items, pieces, im_pieces;
+    std::vector<int4> items, mix_items, pieces, im_pieces, short_pieces;
     const int32_t V = c->V;
-    int32_t im0 = -1;  // first word of the open piece of implied tables
+    // pieces of words with few tokens: of implied tables, or (hybrid) of the mixture form
+    std::vector<int4>& few_pieces = c->hybrid ? short_pieces : im_pieces;
+    static_assert(kShortTokens == kImpliedTokens && kShortWords == kImpliedWords, "pieces of one size");
+    int32_t im0 = -1;  // first word of the open piece
     auto close_implied = [&](int32_t w_end) {
         if (im0 >= 0 && woff[w_end] > woff[im0])
-            im_pieces.push_back(make_int4(im0, w_end, woff[im0], woff[w_end] - woff[im0]));
+            few_pieces.push_back(make_int4(im0, w_end, woff[im0], woff[w_end] - woff[im0]));
         im0 = -1;
+    };
+    auto few_tokens = [&](int32_t w, int32_t n) {
+        if (!c->hybrid) return c->n_implied > 0 && c->h_table_form[w] == 1;
+        return n > 0 && n <= kShortTokens && (c->h_wkind[w] & 2) == 0 &&
+               !((c->h_wkind[w] & 1) && c->K <= kMixRowTopics && n >= kMixRowMinTokens && n > c->K / kShortShare);
     };
     int32_t w0 = -1;  // first word of the open piece
     auto close_piece = [&](int32_t w_end) {
@@ -1652,7 +1787,7 @@ int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
     for (int32_t w = 0; w < V; ++w) {
         const int32_t b = woff[w], n = woff[w + 1] - b;
         const bool dense_dense = dense_form(w);
-        if (c->n_implied > 0 && (c->h_table_form[w] == 1 || (n == 0 && im0 >= 0))) {
+        if (few_tokens(w, n) || (n == 0 && im0 >= 0)) {
             if (im0 >= 0 && (woff[w + 1] - woff[im0] > kImpliedTokens || w + 1 - im0 > kImpliedWords)) close_implied(w);
             if (im0 < 0) {
                 close_piece(w);
@@ -1687,6 +1822,12 @@ int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
     }
     close_piece(V);
     close_implied(V);
+    c->n_short_pieces = (int32_t)short_pieces.size();
+    if (!short_pieces.empty()) {
+        LDA_ALLOC(c, &c->d_short_pieces, short_pieces.size(), "word-pass work list");
+        LDA_HIP(c, hipMemcpy(c->d_short_pieces, short_pieces.data(), sizeof(int4) * short_pieces.size(),
+                             hipMemcpyHostToDevice));
+    }
     c->n_im_pieces = (int32_t)im_pieces.size();
     if (!im_pieces.empty()) {
         LDA_ALLOC(c, &c->d_im_pieces, im_pieces.size(), "word-pass work list");
@@ -1767,6 +1908,8 @@ int launch_sweep_split(lda_ctx* c, int32_t mh_steps)
     A.beta_alias = c->d_beta_alias; A.beta_hdr = c->d_beta_hdr;
     A.sp_off = c->d_sp_off; A.sp_topic = c->d_sp_topic; A.sp_count = c->d_sp_count;
     A.sp_nnz = c->d_sp_nnz; A.mix_items = c->d_mix_items; A.n_mix_items = c->n_mix_items;
+    A.short_pieces = c->d_short_pieces; A.n_short_pieces = c->n_short_pieces;
+    A.short_run = xcd_run_length(c->n_short_pieces, kPieceRun);
     A.im_pieces = c->d_im_pieces; A.n_im_pieces = c->n_im_pieces;
     A.im_run = xcd_run_length(c->n_im_pieces, kPieceRun);
     A.im_off = c->d_im_off; A.im_head = c->d_im_head; A.im_key = c->d_im_key; A.im_corr = c->d_im_corr;
