@@ -224,6 +224,8 @@ int setup_hybrid(lda_ctx* c, const std::vector<int32_t>& woff)
     std::vector<int32_t> dense_alias, mix, sparse, compact, listed, row_words, mixc[kMixClasses];
     std::vector<uint4> meta(2 * (size_t)V, make_uint4(0u, 0u, 0u, 0u));
     const int32_t lds_max = max_lds_table_entries();
+    const bool two_pass = c->opt.stream_block_tokens == 0 && c->opt.proposal_mode != 2 &&
+                          (c->chunk_tokens + c->sweep_block - 1) / c->sweep_block <= 4;
     uint64_t list_total = 0, hash_total = 0;
     for (int32_t w = 0; w < V; ++w) {
         const int32_t cw = woff[w + 1] - woff[w];
@@ -260,7 +262,7 @@ int setup_hybrid(lda_ctx* c, const std::vector<int32_t>& woff)
                     row_words.push_back(w);
                 } else {
                     listed.push_back(w);
-                    if (K <= kMixRowTopics && cw >= kMixRowMinTokens) {
+                    if (K <= kMixRowTopics ? cw >= kMixRowMinTokens : cw <= kShortTokens && two_pass) {
                         kind |= (uint8_t)kKindListOnly;  // served from its list everywhere
                         c->h_wkind[w] = kind;
                         ++c->n_list_only;
@@ -642,6 +644,7 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
         if (e - b <= limit) {
             const int32_t form = !list_from_rebuild(c, w) ? 0 : ((c->h_wkind[w] & kKindListOnly) ? 3 : 2);
             // rows of several topic ranges that also give a list have a kernel of their own
+            if (form == 3 && K > max_rebuild_topics()) continue;  // sorted with the sparse rows
             if (form == 2 && K > max_rebuild_topics())
                 list_tiles.push_back(RebuildTile{w, b, e, form});
             else

@@ -390,7 +390,9 @@ __host__ __device__ inline uint4 pack_mix_bin(uint32_t split, int32_t t_own, int
 // A mixture word with a dense row, at least kMixRowMinTokens tokens, K <= kMixRowTopics and a
 // segment that fits one rebuild tile is served everywhere from its list of non-zeros: the
 // word pass rebuilds its row in LDS from the list, the table build reads the list, the
-// log-likelihood sums over it.  Rewriting its K-entry dense row at every count rebuild would
+// log-likelihood sums over it.  So is, in a larger K, one of at most kShortTokens tokens, whose list the
+// word pass keeps in LDS (12 600 rows of 10^5 topics were two thirds of those that a recount wrote, 1.2
+// of 1.85 ms).  Rewriting its K-entry dense row at every count rebuild would
 // be the largest write of the rebuild (c3: 5.4 of 6.4 GB) for nobody to read, so the row is
 // left untouched (all zero since lda_init) and the word is marked with this bit; the rare
 // lookup outside the word pass (fused sweep) searches the word's mixture table, whose bins
@@ -398,6 +400,7 @@ __host__ __device__ inline uint4 pack_mix_bin(uint32_t split, int32_t t_own, int
 constexpr uint32_t kKindListOnly = 4u;
 constexpr int32_t kMixRowTopics = 16384;   // largest K whose n_kw row a mixture item keeps in LDS
 constexpr int32_t kMixRowMinTokens = 128;
+constexpr int32_t kShortTokens = 1024;     // tokens of a mixture word that the word pass serves from its list
 
 __host__ __device__ inline void unpack_mix_bin(const uint4& e, bool own, int32_t& topic,
                                                int32_t& count)

@@ -660,7 +660,7 @@ int launch_rebuild_hybrid(lda_ctx* c)
         if (rc != LDA_OK) return rc;
     }
     // ---- sparse rows: lists, lengths and hash rows (sparse_rows.hip) ----
-    if (c->V > c->H) {
+    {
         const int rc = launch_sparse_rows(c);
         if (rc != LDA_OK) return rc;
     }

@@ -170,7 +170,7 @@ __global__ __launch_bounds__(BLOCK * WORDS) void sparse_sort_words_kernel(
         // the hash row (at most 2 CAP slots) is filled in LDS and written out whole, empty slots
         // included: no global atomics, and the row needs no clearing beforehand
         uint2* __restrict__ rl = rowl_all[sub];
-        const uint32_t lg = 31u - (uint32_t)__clz((int)cap);
+        const uint32_t lg = cap ? 31u - (uint32_t)__clz((int)cap) : 1u;  // (no row: a list-only word)
         for (uint32_t i = tid; i < cap; i += BLOCK) rl[i] = make_uint2(0xFFFFFFFFu, 0u);
         sync(true);
         for (int32_t q = tid; q < total; q += BLOCK) {
@@ -473,7 +473,11 @@ int setup_sparse_rows(lda_ctx* c, const std::vector<int32_t>& woff)
     std::vector<uint32_t> base;
     std::vector<PartTile> tiles, fill;
     uint32_t total = 0;
-    for (int32_t w = H; w < V; ++w) {
+    // words without a dense row, and list-only words whose list does not come out of a histogram
+    auto sorted = [&](int32_t w) { return w >= H || (c->K > max_rebuild_topics() && (c->h_wkind[w] & kKindListOnly)); };
+    static_assert(kShortTokens <= kSortTokensB, "their rows, of no slots, are filled in LDS");
+    for (int32_t w = 0; w < V; ++w) {
+        if (!sorted(w)) continue;
         const int32_t n = woff[w + 1] - woff[w];
         if (n <= kSortTokensA) cls[0].push_back(w);
         else if (n <= kSortTokensB) cls[1].push_back(w);
@@ -526,10 +530,10 @@ int setup_sparse_rows(lda_ctx* c, const std::vector<int32_t>& woff)
     return LDA_OK;
 }
 
-// Lists, list lengths and hash rows of every word without a dense row, from the word-major z.
+// Lists, list lengths and hash rows of every word without a dense row, and the lists of list-only words
+// beyond the histograms' topics, from the word-major z.
 int launch_sparse_rows(lda_ctx* c)
 {
-    if (c->V <= c->H) return LDA_OK;
     const TopicSource T = word_major_source(c);
     // rows that are filled by global atomics start empty: class 2 and the long words, word by
     // word, or the whole array at once when they own most of it

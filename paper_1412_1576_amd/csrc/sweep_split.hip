@@ -732,8 +732,7 @@ __global__ __launch_bounds__(256) void word_pass_implied_kernel(SplitArgs A)
 // Their lists are copied to LDS, a (topic, count) in 32 bits, where every n_kw is found by bisection; a draw
 // gathers one bin.  With the word's hash or dense row in memory instead, the look-ups of a token are two to
 // three random accesses.
-constexpr int32_t kShortTokens = 1024;  // most of such a word, and of a piece
-constexpr int32_t kShortWords = 512;    // words of a piece
+constexpr int32_t kShortWords = 512;  // words of a piece, which has at most kShortTokens tokens
 constexpr int kShortCountBits = 12;
 static_assert(kShortTokens < (1 << kShortCountBits) && kTopicBits + kShortCountBits <= 32, "a key fits 32 bits");
 
