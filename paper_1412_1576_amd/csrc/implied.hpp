@@ -86,63 +86,110 @@ __device__ __forceinline__ uint64_t implied_delta(const ImpliedWord& w, const ui
     return i > 0 ? full - w.corr[i - 1] : full;
 }
 
-// The topic that bin `bin` and height rr < C give, and the word's count of it
-__device__ __forceinline__ void implied_draw(const ImpliedWord& w, const uint64_t* __restrict__ pz,
-                                             const uint32_t* __restrict__ qz, uint32_t K, uint32_t bin,
-                                             uint32_t rr, int32_t& t, int32_t& nw)
+// A draw: bin `bin`, height rr < C.  One that hits a heavy needs a search in memory, which a wave
+// makes for all its lanes' draws together (implied_heavy), so it is left pending.
+struct ImpliedDraw {
+    uint32_t bin, rr;
+    int32_t i;      // the word's topics below bin
+    bool pending;
+};
+
+// The topic, and the word's count of it, unless the draw is left pending
+__device__ __forceinline__ ImpliedDraw implied_draw(const ImpliedWord& w, const uint64_t* __restrict__ pz,
+                                                    uint32_t q, uint32_t bin, uint32_t rr, int32_t& t, int32_t& nw)
 {
     const int32_t i = implied_below(w, bin);
-    const uint32_t q = qz[bin];
     uint32_t split = (q < 1u ? 1u : q) + (bin < w.pad ? 1u : 0u);
     uint32_t own = 0u;  // key of the bin's own topic
-    bool heavy = false;
     if (i < w.n) {
         const uint32_t k = w.key[i];
         if ((k >> kImpliedTopicShift) == bin) {
+            if ((k & kImpliedLight) == 0u) return ImpliedDraw{bin, rr, i, true};
             own = k;
-            heavy = (k & kImpliedLight) == 0u;
-            if (!heavy) split += (uint32_t)(w.corr[i] - (i > 0 ? w.corr[i - 1] : 0ull));
+            split += (uint32_t)(w.corr[i] - (i > 0 ? w.corr[i - 1] : 0ull));
         }
     }
-    int32_t j;
-    if (heavy) {
-        // the smallest Delta that is not below X: first between which topics, then at which bin
-        const uint64_t x = w.x[i];
-        int32_t lo = 0, hi = w.n;
-        while (lo < hi) {
-            const int32_t mid = (lo + hi) >> 1;
-            const bool ge = implied_delta(w, pz, w.key[mid] >> kImpliedTopicShift, mid) >= x;
-            hi = ge ? mid : hi;
-            lo = ge ? lo : mid + 1;
-        }
-        const int32_t e = lo;  // Delta >= x holds at topic e (or, past the last one, at K)
-        uint32_t a = e > 0 ? (w.key[e - 1] >> kImpliedTopicShift) + 1u : 0u;
-        uint32_t b = e < w.n ? w.key[e] >> kImpliedTopicShift : K;
-        while (a < b) {
-            const uint32_t mid = (a + b) >> 1;
-            const bool ge = implied_delta(w, pz, mid, e) >= x;
-            b = ge ? mid : b;
-            a = ge ? a : mid + 1u;
-        }
-        const uint64_t past = implied_delta(w, pz, a, e) - x;
-        // (a split of C keeps every rr, so the last heavy never looks for a next one)
-        if ((uint64_t)rr + past < (uint64_t)w.C) {
-            t = (int32_t)bin;
-            nw = (int32_t)(own & kImpliedCount);
-            return;
-        }
-        for (j = i + 1; j < w.n - 1 && (w.key[j] & kImpliedLight); ++j) {}
-    } else {
-        if (rr < split) {
-            t = (int32_t)bin;
-            nw = (int32_t)(own & kImpliedCount);
-            return;
-        }
-        j = implied_heavy_above(w, implied_delta(w, pz, bin, i));
+    t = (int32_t)bin;
+    nw = (int32_t)(own & kImpliedCount);
+    if (rr >= split) {
+        const uint32_t k = w.key[implied_heavy_above(w, implied_delta(w, pz, bin, i))];
+        t = (int32_t)(k >> kImpliedTopicShift);
+        nw = (int32_t)(k & kImpliedCount);
     }
-    const uint32_t k = w.key[j];
-    t = (int32_t)(k >> kImpliedTopicShift);
-    nw = (int32_t)(k & kImpliedCount);
+    return ImpliedDraw{bin, rr, i, false};
+}
+
+// A pending draw.  The split is C + X - (the smallest Delta that is not below X), found from an estimate
+// with the mean mass in the place of PZ: topics of even sizes leave two or three looks at PZ to each of
+// the two searches, where bisections took some fifteen, one after the other.
+__device__ __forceinline__ void implied_heavy(const ImpliedWord& w, const uint64_t* __restrict__ pz, uint32_t K,
+                                              const ImpliedDraw& d, int32_t& t, int32_t& nw)
+{
+    const uint64_t x = w.x[d.i];
+    const uint32_t own = w.key[d.i];
+    const double step = (double)w.C - (double)pz[K] / (double)K;  // (positive: every q is below C)
+    // the first of the word's topics with Delta >= X (n: none, but Delta(K) is)
+    int32_t lo = 0, hi = w.n;
+    while (lo < hi) {
+        const int32_t mid = (lo + hi) >> 1;
+        const double est = (double)(w.key[mid] >> kImpliedTopicShift) * step - (double)(mid > 0 ? w.corr[mid - 1] : 0ull);
+        const bool ge = est >= (double)x;
+        hi = ge ? mid : hi;
+        lo = ge ? lo : mid + 1;
+    }
+    int32_t e = lo;
+    {
+        // bracket [el, eh): Delta(topic el - 1) < X <= Delta(topic eh), by doubling steps from the estimate
+        auto reaches = [&](int32_t i) { return implied_delta(w, pz, w.key[i] >> kImpliedTopicShift, i) >= x; };
+        int32_t el = 0, eh = w.n;
+        if (e < w.n && !reaches(e)) {
+            el = e + 1;
+            for (int32_t s = 1; el < eh; s *= 2) {
+                const int32_t at = el + s - 1 < eh ? el + s - 1 : eh - 1;
+                if (reaches(at)) { eh = at; break; }
+                el = at + 1;
+            }
+        } else {
+            eh = e;
+            for (int32_t s = 1; el < eh; s *= 2) {
+                const int32_t at = eh - s > el ? eh - s : el;
+                if (!reaches(at)) { el = at + 1; break; }
+                eh = at;
+            }
+        }
+        while (el < eh) {
+            const int32_t mid = (el + eh) >> 1;
+            if (reaches(mid)) eh = mid; else el = mid + 1;
+        }
+        e = el;
+    }
+    // and the first bin up to it: Delta(below) < X <= Delta(b)
+    uint32_t a = e > 0 ? (w.key[e - 1] >> kImpliedTopicShift) + 1u : 0u;
+    uint32_t b = e < w.n ? w.key[e] >> kImpliedTopicShift : K;
+    uint64_t da = implied_delta(w, pz, a, e), db = da;
+    if (da < x) {
+        db = implied_delta(w, pz, b, e);
+        for (int tries = 0; b - a > 1u; ++tries) {
+            uint32_t mid = (a + b) >> 1;
+            if (tries < 4) {
+                const double g = (double)a + ceil((double)(x - da) / step);
+                mid = g < (double)b ? (uint32_t)g : b - 1u;
+                mid = mid > a ? mid : a + 1u;
+            }
+            const uint64_t dm = implied_delta(w, pz, mid, e);
+            if (dm >= x) { b = mid; db = dm; } else { a = mid; da = dm; }
+        }
+    }
+    t = (int32_t)d.bin;
+    nw = (int32_t)(own & kImpliedCount);
+    // (a split of C keeps every rr, so the last heavy never looks for a next one)
+    if ((uint64_t)d.rr + (db - x) >= (uint64_t)w.C) {
+        int32_t j = d.i + 1;
+        while (j < w.n - 1 && (w.key[j] & kImpliedLight)) ++j;
+        const uint32_t k = w.key[j];
+        t = (int32_t)(k >> kImpliedTopicShift);
+        nw = (int32_t)(k & kImpliedCount);
+    }
 }
 
 }  // namespace lda

@@ -49,7 +49,8 @@ constexpr int32_t kRowMinTokens = 2048;    // words with fewer tokens are gather
 constexpr int32_t kPieceTokens = 512;
 constexpr int32_t kPieceWords = 4096;      // words of a gather piece (their offsets sit in LDS)
 // A mixture word whose row could be staged is served from its list if it has at most K / kShortShare
-// tokens: a row of K counts to clear and fill costs more than the bisections then.  RULEMEASURED
+// tokens: a row of K counts to clear and fill costs more than the bisections then.  9.9 * 10^7 tokens, K = 1000:
+// staged rows and short words 380 us when words from 128 tokens on were staged, 338 so.
 constexpr int32_t kShortShare = 8;
 
 constexpr int pow2_shift(int n)
@@ -642,8 +643,9 @@ __global__ __launch_bounds__(256) void word_pass_gather_kernel(SplitArgs A)
 
 // One piece = the tokens of words [w0, w1), all with implied tables (or without tokens).  The tables'
 // entries are copied to LDS, where every n_kw of the words and nearly all of a draw is found by
-// bisection.  (1.5 * 10^7 tokens of 137 000 words, K = 10 000, four steps: 0.61 ms; gathering n_kw and bins
-// took 1.25.)
+// bisection.  (1.3 * 10^7 tokens of 137 000 words, K = 10 000, four steps: 0.51 ms, instruction issue;
+// gathering n_kw and bins took 1.12, and 0.61 with the search for a heavy's split made for one draw after the
+// other and by bisection in memory.)
 template <int NW, int ND>
 __global__ __launch_bounds__(256) void word_pass_implied_kernel(SplitArgs A)
 {
@@ -673,9 +675,9 @@ __global__ __launch_bounds__(256) void word_pass_implied_kernel(SplitArgs A)
     __syncthreads();
     const int32_t shift = A.xmap ? kMapped : 0;
     with_record_layout(A, shift, [&](auto xm, auto p16) {
-        constexpr int U = 2;
+        constexpr int U = C::M <= 4 ? 2 : 1;
         for (int32_t i0 = 0; i0 < pc.w; i0 += U * nt) {
-            int32_t p[U], w[U], zt[1 + ND], out[C::R];
+            int32_t p[U], w[U], zt[1 + ND], out[U][C::R];
             uint4 head[U];
             bool live[U];
             TokenFetch<ND, U, decltype(xm)::value, decltype(p16)::value> f;
@@ -694,36 +696,88 @@ __global__ __launch_bounds__(256) void word_pass_implied_kernel(SplitArgs A)
                 head[u] = A.im_head[pc.x + w[u]];
             }
             f.records(A);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
+            auto table = [&](int u) {
                 const uint32_t l = loff[w[u]];
-                const ImpliedWord tab{key + l, corr + l, x + l, (int32_t)(head[u].x & ~kImpliedDense), head[u].y, head[u].z};
-                f.decode(u, zt);
+                return ImpliedWord{key + l, corr + l, x + l, (int32_t)(head[u].x & ~kImpliedDense), head[u].y, head[u].z};
+            };
+            // the masses of all drawn bins are asked for together
+            constexpr int M = NW > 0 ? NW : 1;
+            uint32_t bin[M][U], r1[M][U], hint[M][U], q[M][U];
 #pragma unroll
-                for (int k = 0; k < C::R; ++k) out[k] = 0;
-                out[0] = implied_count(tab, zt[0]);
+            for (int k = 0; k < NW; ++k) {
 #pragma unroll
-                for (int k = 0; k < ND; ++k) out[C::rec_doc(k)] = implied_count(tab, zt[1 + k]);
-#pragma unroll
-                for (int k = 0; k < NW; ++k) {
+                for (int u = 0; u < U; ++u) {
                     uint32_t r[4];
                     philox4x32_10(f.g[u], 0u, A.sweep, (uint32_t)C::word_step(k), A.seed_lo, A.seed_hi, r);
-                    const uint32_t bin = mulhi32(r[0], (uint32_t)K);
-                    int32_t t, nw;
+                    bin[k][u] = mulhi32(r[0], (uint32_t)K);
+                    r1[k][u] = r[1];
+                    hint[k][u] = r[2];
+                    q[k][u] = A.im_qz[bin[k][u]];
+                }
+            }
+            uint32_t pending = 0u;  // of the thread's draws, k * U + u
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const ImpliedWord tab = table(u);
+                f.decode(u, zt);
+#pragma unroll
+                for (int k = 0; k < C::R; ++k) out[u][k] = 0;
+                out[u][0] = implied_count(tab, zt[0]);
+#pragma unroll
+                for (int k = 0; k < ND; ++k) out[u][C::rec_doc(k)] = implied_count(tab, zt[1 + k]);
+#pragma unroll
+                for (int k = 0; k < NW; ++k) {
+                    int32_t t = 0, nw = 0;
                     if (head[u].x & kImpliedDense) {
                         const int32_t word = pc.x + w[u];
-                        const uint4 e = A.alias[(size_t)word * (size_t)K + bin];
-                        const bool keep = mulhi32(r[1], A.cap[word]) < e.x;
-                        t = keep ? (int32_t)bin : (int32_t)e.y;
+                        const uint4 e = A.alias[(size_t)word * (size_t)K + bin[k][u]];
+                        const bool keep = mulhi32(r1[k][u], A.cap[word]) < e.x;
+                        t = keep ? (int32_t)bin[k][u] : (int32_t)e.y;
                         nw = keep ? (int32_t)e.z : (int32_t)e.w;
                     } else {
-                        implied_draw(tab, A.im_pz, A.im_qz, (uint32_t)K, bin, mulhi32(r[1], tab.C), t, nw);
+                        const ImpliedDraw d = implied_draw(tab, A.im_pz, q[k][u], bin[k][u], mulhi32(r1[k][u], tab.C), t, nw);
+                        pending |= d.pending ? 1u << (k * U + u) : 0u;
                     }
-                    out[C::rec_topic(k)] = topic_with_hint(t, r[2]);
-                    out[C::rec_topic(k) + 1] = nw;
+                    out[u][C::rec_topic(k)] = topic_with_hint(t, hint[k][u]);
+                    out[u][C::rec_topic(k) + 1] = nw;
                 }
-                if (live[u]) store_ints<C::R>(A.rec + (f.q[u] << C::rec_shift), out);
             }
+            // the pending draws, one of every lane at a time
+            while (__any(pending != 0u)) {
+                if (pending != 0u) {
+                    const int at = __ffs((int)pending) - 1;
+                    pending &= pending - 1u;
+                    uint32_t bn = 0u, rr = 0u, hn = 0u;
+                    int uu = 0;
+#pragma unroll
+                    for (int k = 0; k < NW; ++k) {
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            if (at == k * U + u) { bn = bin[k][u]; rr = r1[k][u]; hn = hint[k][u]; uu = u; }
+                        }
+                    }
+                    ImpliedWord tab = table(0);
+#pragma unroll
+                    for (int u = 1; u < U; ++u)
+                        if (uu == u) tab = table(u);
+                    const ImpliedDraw d{bn, mulhi32(rr, tab.C), implied_below(tab, bn), true};
+                    int32_t t, nw;
+                    implied_heavy(tab, A.im_pz, (uint32_t)K, d, t, nw);
+#pragma unroll
+                    for (int k = 0; k < NW; ++k) {
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            if (at == k * U + u) {
+                                out[u][C::rec_topic(k)] = topic_with_hint(t, hn);
+                                out[u][C::rec_topic(k) + 1] = nw;
+                            }
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (live[u]) store_ints<C::R>(A.rec + (f.q[u] << C::rec_shift), out[u]);
         }
     });
 }
