@@ -91,7 +91,8 @@ typedef struct lda_options {
                                       tokens (a power of two), inside a bucket by word; 0: default
                                       (2^22 when every n_kw row is dense and the corpus has at
                                       least 2^28 tokens, else one bucket);
-                                      -1: one bucket (plain word order) */
+                                      -1: one bucket (plain word order).  Words of at least
+                                      max(256, N / 2^16) tokens keep word order either way */
     int32_t doc_refresh;           /* 1: lda_sweep refreshes the doc side after every token (Sec. 4.2,
                                       footnote 4): the tokens of a document are visited in order
                                       and each sees, in n_kd and in the doc-proposal's draw, the
@@ -139,7 +140,10 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
  * bin capacity of the table.  Words of the dense form get one table over all K
  * topics; words of the mixture form (Sec. 4.2, the sparsified table) one table
  * over their non-zero topics, and all of them share one table over
- * beta/(n_k + V beta).  COUNTS_VALID -> ALIAS_VALID.
+ * beta/(n_k + V beta).  In the all-dense store the table of a word with few tokens may be held as
+ * its topics with running sums, from which a draw computes the bin it hits; sweeps that run as one
+ * kernel and lda_get_alias_row make such words' bins when they need them.
+ * COUNTS_VALID -> ALIAS_VALID.
  */
 int lda_build_alias(lda_ctx* ctx);
 

@@ -52,6 +52,9 @@ constexpr int32_t kPieceWords = 4096;      // words of a gather piece (their off
 // tokens: a row of K counts to clear and fill costs more than the bisections then.  9.9 * 10^7 tokens, K = 1000:
 // staged rows and short words 380 us when words from 128 tokens on were staged, 338 so.
 constexpr int32_t kShortShare = 8;
+// Tokens of such words below which their launch costs more than it saves (5.6 * 10^4 tokens, K = 51: an
+// iteration 145 us without, 153 with).
+constexpr int64_t kShortLeast = (int64_t)1 << 17;
 
 constexpr int pow2_shift(int n)
 {
@@ -1775,12 +1778,11 @@ bool doc_limits(double alphabar, std::vector<uint32_t>& limit)
     limit.assign((size_t)kMaxTileTokens + 1, 0u);
     for (int32_t L = 1; L <= kMaxTileTokens; ++L) {
         if (!copies_token(0u, L, alphabar)) return false;
-        uint32_t lo = 0u, hi = 0xFFFFFFFFu;  // copies at lo
-        while (lo < hi) {
-            const uint32_t mid = lo + (hi - lo) / 2 + 1;
-            if (copies_token(mid, L, alphabar)) lo = mid; else hi = mid - 1;
-        }
-        limit[(size_t)L] = lo;
+        const double guess = 4294967296.0 * ((double)L / ((double)L + alphabar));
+        uint32_t x = guess < 4294967295.0 ? (uint32_t)guess : 0xFFFFFFFFu;
+        while (x > 0u && !copies_token(x, L, alphabar)) --x;
+        while (x < 0xFFFFFFFFu && copies_token(x + 1u, L, alphabar)) ++x;
+        limit[(size_t)L] = x;
     }
     return true;
 }
@@ -1815,9 +1817,10 @@ int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
             few_pieces.push_back(make_int4(im0, w_end, woff[im0], woff[w_end] - woff[im0]));
         im0 = -1;
     };
+    bool use_short = true;
     auto few_tokens = [&](int32_t w, int32_t n) {
         if (!c->hybrid) return c->n_implied > 0 && c->h_table_form[w] == 1;
-        return n > 0 && n <= kShortTokens && (c->h_wkind[w] & 2) == 0 &&
+        return use_short && n > 0 && n <= kShortTokens && (c->h_wkind[w] & 2) == 0 &&
                !((c->h_wkind[w] & 1) && c->K <= kMixRowTopics && n >= kMixRowMinTokens && n > c->K / kShortShare);
     };
     int32_t w0 = -1;  // first word of the open piece
@@ -1826,6 +1829,13 @@ int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
             pieces.push_back(make_int4(w0, w_end, woff[w0], woff[w_end] - woff[w0]));
         w0 = -1;
     };
+    int64_t tokens_few = 0;
+    for (int32_t w = 0; w < V; ++w)
+        if (few_tokens(w, woff[w + 1] - woff[w])) tokens_few += woff[w + 1] - woff[w];
+    if (c->hybrid && c->K <= kMixRowTopics)  // (beyond, such words have no row to gather from)
+        use_short = tokens_few >= kShortLeast;
+    // words are put together up to this many tokens, fewer where there would be less than six pieces to a CU
+    const int32_t few_piece = (int32_t)std::min<int64_t>(kShortTokens, std::max<int64_t>(256, tokens_few / 1536));
     // rows are staged for frequent words with a dense row and a dense table of at most
     // max_alias_topics() bins (12 bytes of LDS per topic)
     const bool rows_fit = c->K <= max_alias_topics();
@@ -1841,7 +1851,7 @@ int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
         const int32_t b = woff[w], n = woff[w + 1] - b;
         const bool dense_dense = dense_form(w);
         if (few_tokens(w, n) || (n == 0 && im0 >= 0)) {
-            if (im0 >= 0 && (woff[w + 1] - woff[im0] > kImpliedTokens || w + 1 - im0 > kImpliedWords)) close_implied(w);
+            if (im0 >= 0 && (woff[w + 1] - woff[im0] > few_piece || w + 1 - im0 > kImpliedWords)) close_implied(w);
             if (im0 < 0) {
                 close_piece(w);
                 im0 = w;

@@ -2,7 +2,7 @@
 the form begins and ends (words of 1, 64, 256, 1024 tokens and one more, words without tokens), where
 a word's sums do not fit it (topics of very uneven size, weights that need a shift), in turn
 with sweeps that draw from bins, and after the incremental count update.  The form is used where
-the words it suits have 2^21 bins or more together, and a word suits with at most K / 2 tokens."""
+the words it suits have 2^23 bins or more together, and a word suits with at most K / 2 tokens."""
 import numpy as np
 import pytest
 
@@ -50,7 +50,7 @@ def step(g, o, m, update=False, tables=()):
 
 def frequencies(V, K, seed):
     """Few to many tokens per word, the ends of the form's ranges, words without tokens."""
-    n = (1 + 8 * np.random.default_rng(seed).pareto(1.0, V)).astype(np.int64)
+    n = (1 + max(8, 20 * K / V) * np.random.default_rng(seed).pareto(1.0, V)).astype(np.int64)
     n = np.minimum(n, 6000)
     ends = [0, 0, 1, 2, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 2047, 2048, K // 2, K // 2 + 1, 0]
     n[10:10 + len(ends)] = ends
@@ -59,12 +59,12 @@ def frequencies(V, K, seed):
 
 
 # K: one topic range below and above what a thread of the shared sums handles, odd, the largest
-@pytest.mark.parametrize("V,K", [(11000, 257), (2600, 1024), (1200, 2051), (560, 4099), (420, 12287), (420, 12288)])
+@pytest.mark.parametrize("V,K", [(46000, 257), (12000, 1024), (6200, 2051), (3400, 4099), (1400, 12287), (1400, 12288)])
 @pytest.mark.parametrize("m", [2, 3])
 def test_sweeps(lda_mod, oracle_mod, V, K, m):
     n = frequencies(V, K, K)
     doff, words = corpus_of(n, K)
-    g, o = pair(lda_mod, oracle_mod, doff, words, V, K)
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K, beta=1e-4)
     some = list(range(0, 30)) + [V - 2, V - 1]
     for it in range(3):
         step(g, o, m, tables=some)
@@ -75,7 +75,7 @@ def test_sweeps(lda_mod, oracle_mod, V, K, m):
 @pytest.mark.parametrize("power", [2, 6])
 @pytest.mark.parametrize("beta", [1e-6, 0.01, 3.0])
 def test_uneven_topics(lda_mod, oracle_mod, power, beta):
-    V, K = 2600, 1024
+    V, K = 24000, 1024
     doff, words = corpus_of(frequencies(V, K, 8), 8)
     g, o = pair(lda_mod, oracle_mod, doff, words, V, K, beta=beta)
     z = (K * np.random.default_rng(4).random(len(words)) ** power).astype(np.int32)
@@ -83,31 +83,33 @@ def test_uneven_topics(lda_mod, oracle_mod, power, beta):
         c.set_z(z, 7)
         c.rebuild_counts()
     for m in (2, 1, 4):
-        step(g, o, m, tables=range(0, V, 97))
+        step(g, o, m, tables=range(0, V, 397))
     g.close(); o.close()
 
 
 def test_few_tokens(lda_mod, oracle_mod):
-    """Most words have a share of the corpus so large that their weights need a shift."""
-    V, K = 600, 4001
-    doff, words = corpus_of(np.full(V, 3) + np.arange(V) // 20, 2, L=7)
-    g, o = pair(lda_mod, oracle_mod, doff, words, V, K)
+    """Some words have a share of the corpus so large that their weights need a shift."""
+    V, K = 2600, 4001
+    n = np.full(V, 27) + np.arange(V) // 120
+    n[100:140] = np.linspace(150, 1024, 40).astype(int)
+    doff, words = corpus_of(n, 2, L=7)
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K, beta=1e-5)
     for m in (2, 4, 2):
-        step(g, o, m, tables=(0, 300, 599))
+        step(g, o, m, tables=(0, 100, 110, 139, 599))
     g.close(); o.close()
 
 
 def test_in_turn_with_one_pass_sweeps(lda_mod, oracle_mod):
-    V, K = 2600, 1024
+    V, K = 12000, 1024
     doff, words = corpus_of(frequencies(V, K, 5), 5)
-    g, o = pair(lda_mod, oracle_mod, doff, words, V, K)
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K, beta=1e-4)
     for m in (2, 9, 9, 2, 4, 10, 2, 2):
         step(g, o, m, tables=(5, 13, 1000))
     g.close(); o.close()
 
 
 def test_after_the_incremental_update(lda_mod, oracle_mod):
-    V, K = 9000, 300
+    V, K = 36000, 300
     doff, words = corpus_of(frequencies(V, K, 6), 6, L=12)
     for turns in ("uuu", "ruurrrru"):  # rows are kept for updates, lists for recounts
         g, o = pair(lda_mod, oracle_mod, doff, words, V, K)
@@ -118,7 +120,7 @@ def test_after_the_incremental_update(lda_mod, oracle_mod):
 
 def test_few_moved_tokens(lda_mod, oracle_mod):
     """One token moved since the recount: the incremental update finds the rows stale and counts."""
-    V, K = 2600, 1024
+    V, K = 12000, 1024
     doff, words = corpus_of(frequencies(V, K, 7), 7)
     g, o = pair(lda_mod, oracle_mod, doff, words, V, K, proposal_mode=1, beta=1e-9)
     z = words % K  # every word in one topic, which its proposals hardly leave
@@ -126,7 +128,7 @@ def test_few_moved_tokens(lda_mod, oracle_mod):
         c.set_z(z, 0)
         c.rebuild_counts()
     for update in (True, True, False, True):
-        step(g, o, 1, update=update, tables=range(0, V, 111))
+        step(g, o, 1, update=update, tables=range(0, V, 411))
     g.close(); o.close()
 
 
@@ -134,10 +136,10 @@ def test_graph_replays_leave_lists(lda_mod, oracle_mod):
     """What the rows hold is known on the device: iterations replayed from a graph leave lists where
     the host, which saw an update before, would expect rows."""
     import torch
-    V, K = 2600, 1024
+    V, K = 12000, 1024
     doff, words = corpus_of(frequencies(V, K, 3), 3)
     stream = torch.cuda.Stream()
-    g = lda_mod.Lda(doff, words, V, K, 0.1, 0.01, seed=3, stream=stream.cuda_stream)
+    g = lda_mod.Lda(doff, words, V, K, 0.1, 1e-4, seed=3, stream=stream.cuda_stream)
     for _ in range(2):
         g.build_alias(); g.sweep(2); g.rebuild_counts()
     g.sync()
@@ -153,26 +155,26 @@ def test_graph_replays_leave_lists(lda_mod, oracle_mod):
     g.sync()
     rows = np.zeros((V, K), np.int32)
     np.add.at(rows, (words, z), 1)
-    for w in range(0, V, 37):
+    for w in range(0, V, 137):
         assert np.array_equal(g.get_nkw_row(w), rows[w]), w
     g.build_alias(); g.sweep(2); g.update_counts()
     z = g.get_z()
     rows[:] = 0
     np.add.at(rows, (words, z), 1)
-    for w in range(0, V, 37):
+    for w in range(0, V, 137):
         assert np.array_equal(g.get_nkw_row(w), rows[w]), w
     g.close()
 
 
 def test_record_order_and_word_chains(lda_mod, oracle_mod):
-    V, K = 2600, 1024
+    V, K = 12000, 1024
     doff, words = corpus_of(frequencies(V, K, 9), 9)
-    g, o = pair(lda_mod, oracle_mod, doff, words, V, K, record_bucket_tokens=4096)
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K, beta=1e-4, record_bucket_tokens=4096)
     for m in (2, 4):
         step(g, o, m)
     g.close(); o.close()
-    g = lda_mod.Lda(doff, words, V, K, 0.1, 0.01, seed=3, proposal_mode=1)
-    o = oracle_mod.Oracle(doff, words, V, K, 0.1, 0.01, seed=3, proposal_mode=1)
+    g = lda_mod.Lda(doff, words, V, K, 0.1, 1e-4, seed=3, proposal_mode=1)
+    o = oracle_mod.Oracle(doff, words, V, K, 0.1, 1e-4, seed=3, proposal_mode=1)
     for m in (1, 3, 1, 1):
         step(g, o, m)
     g.close(); o.close()
