@@ -1089,9 +1089,9 @@ __device__ __forceinline__ void doc_pass_chains(const SplitArgs& A, const DocVie
     // Proposals do not depend on the chain's state, so every step's proposal, its n_kd probe
     // and its n_k gather are issued before the first accept test: one round trip to L2
     // for all of them instead of one per step.
-    // Four steps at a time: 66, 70, 72, 72 VGPRs for 5 to 8 steps with one token per thread, where all
-    // at once take 66, 78, 80, 92.  Above 64 one 1024-thread workgroup is resident on a CU; chains of
-    // up to four steps have two.
+    // Four steps at a time: 64, 66, 68, 68 VGPRs for 5 to 8 steps with one token per thread over hash
+    // tables, where above 64 one 1024-thread workgroup is resident on a CU.  Over counters they are
+    // held to 64, and two are resident, as for chains of up to four steps.
     constexpr int B = C::M < 4 ? C::M : 4;
 #pragma unroll
     for (int j0 = 0; j0 < C::M; j0 += B) {
@@ -1351,14 +1351,17 @@ __device__ __forceinline__ void tile_process(const SplitArgs& A, int32_t* smem,
 // a fixed number of waves per SIMD (7 in blocks of up to 256 threads, 6 up to 768): one more
 // resident workgroup per CU hides more of the gather latency than the few registers it
 // costs.  Longer chains take the registers they need: two interleaved four-step chains use
-// about 100, one uses 62, which is why the launcher gives them one token per thread.
+// about 100, one uses 62, which is why the launcher gives them one token per thread.  Five to
+// eight steps over counters are held to 64 registers, for two resident workgroups of 1024 threads:
+// at most two registers spill, and a pass of 8 steps over 2 * 10^7 tokens, K = 1000, takes 4.95 instead
+// of about 5.25 ms.  Over hash tables up to six would spill; that form keeps its registers.
 //
 // NKL: the workgroup keeps a copy of n_k in LDS behind the tile (K <= kNkLdsTopics).  The
 // three n_k reads of a token are otherwise three separate requests to L2 (the array is larger
 // than the L1), and the rate of such requests, not their bytes, is what bounded this kernel:
 // without them it ran 14.8 instead of 22.7 ms on the benchmark workload.
 template <int NW, int ND, int T, int MAXB, bool NKL, bool DIRECT>
-__global__ __launch_bounds__(MAXB, (T <= 2 && NW + ND <= 2) ? (MAXB <= 256 ? 7 : (MAXB <= 768 ? 6 : 1)) : 1) void doc_pass_tiles_kernel(SplitArgs A)
+__global__ __launch_bounds__(MAXB, (T <= 2 && NW + ND <= 2) ? (MAXB <= 256 ? 7 : (MAXB <= 768 ? 6 : 1)) : (DIRECT && T == 1 && MAXB == 1024 && NW + ND > 4 ? 8 : 1)) void doc_pass_tiles_kernel(SplitArgs A)
 {
     using C = Chain<NW, ND>;
     extern __shared__ int32_t smem[];
@@ -1962,7 +1965,7 @@ int launch_sweep_split(lda_ctx* c, int32_t mh_steps)
     } else if (c->n_chunks2 > 0) {
         // longer chains (default tiles): one token per thread.  Up to 4 steps take 64 VGPRs, which
         // leaves two 1024-thread workgroups per CU (4 steps: 28.9 instead of 33.4 ms); 5 to 8 steps
-        // take 66 to 72, and one workgroup is resident
+        // take 64 too over counters, and up to 68, one workgroup resident, over hash tables
         A.doc_block = std::min(1024, (c->chunk_tokens + 63) / 64 * 64);
     }
     A.alpha = c->alpha; A.beta = c->beta; A.alphabar = c->alphabar; A.betabar = c->betabar;
