@@ -1353,7 +1353,7 @@ __device__ __forceinline__ void tile_process(const SplitArgs& A, int32_t* smem,
 // costs.  Longer chains take the registers they need: two interleaved four-step chains use
 // about 100, one uses 62, which is why the launcher gives them one token per thread.  Five to
 // eight steps over counters are held to 64 registers, for two resident workgroups of 1024 threads:
-// at most two registers spill, and a pass of 8 steps over 2 * 10^7 tokens, K = 1000, takes 4.95 instead
+// at most two registers spill, and a pass of 8 steps over 2 * 10^7 tokens, K = 1000, takes 5.02 instead
 // of about 5.25 ms.  Over hash tables up to six would spill; that form keeps its registers.
 //
 // NKL: the workgroup keeps a copy of n_k in LDS behind the tile (K <= kNkLdsTopics).  The
