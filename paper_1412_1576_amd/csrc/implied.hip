@@ -421,6 +421,9 @@ int setup_implied(lda_ctx* c, const std::vector<int32_t>& woff)
     LDA_HIP(c, hipMemset(c->d_im_head, 0, sizeof(uint4) * (size_t)V));
     LDA_HIP(c, hipMemset(c->d_im_n, 0, sizeof(int32_t) * (size_t)V));
     LDA_HIP(c, hipMemset(c->d_rows_stale, 0, sizeof(int32_t)));
+    // The recounts that make lists write no rows of words without tokens; the tables over all K bins are
+    // built from those rows too.
+    LDA_HIP(c, hipMemsetAsync(c->d_nkw, 0, sizeof(int32_t) * (size_t)V * (size_t)K, c->stream));
     for (int i = 0; i < lda_ctx::kImpliedClasses; ++i) c->n_im_class[i] = (int32_t)words[i].size();
     c->n_implied = (int32_t)n;
     c->h_table_form = std::move(form);

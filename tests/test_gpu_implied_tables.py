@@ -108,6 +108,46 @@ def test_in_turn_with_one_pass_sweeps(lda_mod, oracle_mod):
     g.close(); o.close()
 
 
+def test_words_without_tokens_in_used_memory(lda_mod, oracle_mod):
+    """The first sweep of a new sampler is one kernel, which draws from bins, and the caller's memory
+    has been used before: the rows that the bins of words without tokens are made from are zero."""
+    import torch
+    V, K = 12000, 1024
+    n = frequencies(V, K, 5)
+    empty = [0, 1, 2, V // 2, V - 2, V - 1]
+    n[empty] = 0
+    doff, words = corpus_of(n, 5)
+    live = {}
+
+    def alloc(nbytes):
+        t = torch.full((nbytes,), 0x3b, dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        live[t.data_ptr()] = t
+        return t.data_ptr()
+
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K, beta=1e-4, dev_alloc=alloc, dev_free=lambda p: live.pop(p))
+
+    def array(counts):
+        t, = [t for t in live.values() if t.numel() == 4 * counts]
+        return t.view(torch.int32)
+
+    # before any kernel reads them
+    assert not array(V * K).view(V, K)[torch.tensor(empty, device="cuda")].any()
+    o.build_alias()
+    split, alias, cap = zip(*[o.get_alias_row(w) for w in empty])
+    g.build_alias(); g.sweep(9); o.sweep(9)
+    g.sync()
+    bins = array(V * K * 4).view(V, K, 4)[torch.tensor(empty, device="cuda")].cpu().numpy()
+    assert np.array_equal(bins[:, :, 0].view(np.uint32), np.stack(split))
+    assert np.array_equal(bins[:, :, 1].view(np.uint32), np.stack(alias))
+    assert not bins[:, :, 2:].any()
+    g.rebuild_counts(); o.rebuild_counts()
+    for m in (2, 9, 2):
+        step(g, o, m, tables=empty + [5, 13])
+    g.close(); o.close()
+    assert not live
+
+
 def test_after_the_incremental_update(lda_mod, oracle_mod):
     V, K = 36000, 300
     doff, words = corpus_of(frequencies(V, K, 6), 6, L=12)
