@@ -112,6 +112,7 @@ void free_all(lda_ctx* c)
     dev_free(c, c->d_im_sum); dev_free(c, c->d_fixed_words); dev_free(c, c->d_misfits); dev_free(c, c->d_n_misfits); dev_free(c, c->d_im_pieces); dev_free(c, c->d_short_pieces);
     dev_free(c, c->d_alias); dev_free(c, c->d_cap); dev_free(c, c->d_chunk_doc); dev_free(c, c->d_chunk_tok); dev_free(c, c->d_tokdoc); dev_free(c, c->d_chunk_doc2); dev_free(c, c->d_chunk_tok2); dev_free(c, c->d_tokdoc2); dev_free(c, c->d_long_doc);
     dev_free(c, c->d_long_slot); dev_free(c, c->d_long_keys); dev_free(c, c->d_long_cnts); dev_free(c, c->d_long_first);
+    dev_free(c, c->d_long_slices); dev_free(c, c->d_long_parts);
     dev_free(c, c->d_tiles); dev_free(c, c->d_list_tiles); dev_free(c, c->d_multi_words); dev_free(c, c->d_partial); dev_free(c, c->d_lg_terms); dev_free(c, c->d_row);
     dev_free(c, c->d_flag);
     dev_free(c, c->d_dense_alias_words);

@@ -200,6 +200,9 @@ struct lda_ctx {
     int32_t* d_long_keys = nullptr;    // [total slots]
     int32_t* d_long_cnts = nullptr;
     int32_t* d_long_first = nullptr;   // [total slots] log-likelihood: first token of every topic
+    int4* d_long_slices = nullptr;     // (first token, tokens, begin of the slice, its tokens): doc pass
+    int4* d_long_parts = nullptr;      // the same for the doc proposals of the next sweep
+    int32_t n_long_slices = 0, n_long_parts = 0;
     int32_t n_long = 0;
     int64_t long_slots = 0;
     int64_t long_tokens = 0;           // tokens of these documents

@@ -191,6 +191,8 @@ struct SplitArgs {
     const int64_t* long_slot;
     int32_t* long_keys;
     int32_t* long_cnts;
+    const int4* long_slices;
+    const int4* long_parts;
     const int4* short_pieces;
     int32_t n_short_pieces, short_run;
     // implied tables (implied.hpp)
@@ -1403,27 +1405,21 @@ __global__ __launch_bounds__(MAXB, (T <= 2 && NW + ND <= 2) ? (MAXB <= 256 ? 7 :
     tile_process<NW, ND, T, DIRECT>(A, smem, nk, t);
 }
 
-// Long documents, K <= kLongDocTopics: a workgroup (blockIdx.x, blockIdx.y) runs the chains of a slice
-// of a document with counters of the whole of it; the doc proposals of the next sweep, which need the
-// document's new assignment, are a launch of their own.  One workgroup per document with a hash table
-// filled by global atomics was 57 us of an iteration's 150 in a corpus of 7 * 10^4 tokens, 10 % of them in
-// seven such documents; these two 6.3 + 3.4.
-constexpr int32_t kLongSlice = 1024;    // tokens at least
-constexpr int32_t kLongSlices = 64;     // of a document at most: each reads all of it
-
+// Long documents, K <= kLongDocTopics: a workgroup runs the chains of a slice of a document, an item
+// (first token, tokens of the document, begin and tokens of the slice), with counters of the whole of it;
+// the doc proposals of the next sweep, which need the document's new assignment, are a launch of their own,
+// kLongPart tokens to a workgroup.  One workgroup per document with a hash table filled by global
+// atomics was 57 us of an iteration's 150 in a corpus of 7 * 10^4 tokens, 10 % of them in seven such documents;
+// these two 6.3 + 3.4.
 template <int NW, int ND>
 __global__ __launch_bounds__(1024) void doc_pass_long_slices_kernel(SplitArgs A)
 {
     using C = Chain<NW, ND>;
     extern __shared__ int32_t smem[];
-    const int32_t d = A.long_doc[blockIdx.y];
-    const int32_t tok0 = A.doff[d], L = A.doff[d + 1] - tok0;
-    const int32_t slices = (int32_t)gridDim.x;
-    const int32_t per = ((L + slices - 1) / slices + kLongSlice - 1) / kLongSlice * kLongSlice;
-    const int32_t i0 = (int32_t)blockIdx.x * per, i1 = L - i0 < per ? L : i0 + per;  // (i0 < 64 * 2^25)
-    if (i0 >= L) return;
+    const int4 it = A.long_slices[blockIdx.x];
+    const int32_t tok0 = it.x, L = it.y, i1 = it.z + it.w;
     count_long_doc(smem, A.K, A.z + tok0, L);
-    for (int32_t base = i0; base < i1; base += (int32_t)blockDim.x) {
+    for (int32_t base = it.z; base < i1; base += (int32_t)blockDim.x) {
         const bool live = base + (int32_t)threadIdx.x < i1;
         const int32_t i = live ? base + (int32_t)threadIdx.x : i1 - 1;  // past the end: the last token again
         const uint32_t g[1] = {(uint32_t)(tok0 + i)};
@@ -1437,26 +1433,26 @@ __global__ __launch_bounds__(1024) void doc_pass_long_slices_kernel(SplitArgs A)
     }
 }
 
+constexpr int32_t kLongPart = 256;
+
 template <int NW, int ND>
-__global__ __launch_bounds__(256) void long_doc_proposals_kernel(SplitArgs A)
+__global__ __launch_bounds__(kLongPart) void long_doc_proposals_kernel(SplitArgs A)
 {
     using C = Chain<NW, ND>;
-    const int32_t d = A.long_doc[blockIdx.y];
-    const int32_t tok0 = A.doff[d], L = A.doff[d + 1] - tok0;
-    const int64_t step = (int64_t)gridDim.x * 256;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < L; i += step) {
-        const uint32_t g = (uint32_t)(tok0 + (int32_t)i);
-        int32_t row[1 + ND];
-        row[0] = A.znew[g];
+    const int4 it = A.long_parts[blockIdx.x];
+    const int32_t tok0 = it.x, L = it.y;
+    if ((int32_t)threadIdx.x >= it.w) return;
+    const uint32_t g = (uint32_t)(tok0 + it.z + (int32_t)threadIdx.x);
+    int32_t row[1 + ND];
+    row[0] = A.znew[g];
 #pragma unroll
-        for (int k = 0; k < ND; ++k) {
-            uint32_t x[4];
-            philox4x32_10(g, 0u, A.sweep + 1u, (uint32_t)C::doc_step(k), A.seed_lo, A.seed_hi, x);
-            row[1 + k] = doc_proposal(copies_token(x[0], L, A.alphabar), x[1], L, A.K,
-                                      [&](uint32_t j) { return A.znew[tok0 + (int32_t)j]; });
-        }
-        store_zt<ND>(A, (size_t)A.wpos[g], row);
+    for (int k = 0; k < ND; ++k) {
+        uint32_t x[4];
+        philox4x32_10(g, 0u, A.sweep + 1u, (uint32_t)C::doc_step(k), A.seed_lo, A.seed_hi, x);
+        row[1 + k] = doc_proposal(copies_token(x[0], L, A.alphabar), x[1], L, A.K,
+                                  [&](uint32_t j) { return A.znew[tok0 + (int32_t)j]; });
     }
+    store_zt<ND>(A, (size_t)A.wpos[g], row);
 }
 
 template <int NW, int ND>
@@ -1632,16 +1628,9 @@ int launch_chain(lda_ctx* c, const SplitArgs& A, bool need_proposals)
         auto kern = doc_pass_long_slices_kernel<NW, ND>;
         const size_t lds = sizeof(int32_t) * (size_t)c->K;
         if ((rc = raise_lds_limit(c, kern, lds)) != LDA_OK) return rc;
-        for (int32_t i = 0; i < c->n_long; i += 65535) {  // (the grid's second dimension)
-            SplitArgs B = A;
-            B.long_doc += i;
-            const unsigned n = (unsigned)std::min(c->n_long - i, 65535);
-            const unsigned slices = (unsigned)std::min((c->longest_doc + kLongSlice - 1) / kLongSlice, kLongSlices);
-            hipLaunchKernelGGL(kern, dim3(slices, n), dim3(1024), lds, c->stream, B);
-            const unsigned parts = (unsigned)std::min((c->longest_doc + 255) / 256, 1024);
-            hipLaunchKernelGGL((long_doc_proposals_kernel<NW, ND>), dim3(parts, n), dim3(256), 0, c->stream, B);
-            LDA_HIP(c, hipGetLastError());
-        }
+        hipLaunchKernelGGL(kern, dim3(c->n_long_slices), dim3(1024), lds, c->stream, A);
+        hipLaunchKernelGGL((long_doc_proposals_kernel<NW, ND>), dim3(c->n_long_parts), dim3(kLongPart), 0, c->stream, A);
+        LDA_HIP(c, hipGetLastError());
     } else if (c->n_long > 0) {
         hipLaunchKernelGGL((doc_pass_long_kernel<NW, ND>), dim3(c->n_long), dim3(1024), 0, c->stream,
                            A);
@@ -1806,6 +1795,40 @@ bool split_sweep_supported(lda_ctx* c, int32_t mh_steps)
     return (c->chunk_tokens + c->sweep_block - 1) / c->sweep_block <= 4;
 }
 
+// Work lists of the doc pass's kernels for long documents.  A slice has kLongSlice tokens, more where there
+// would be more than kLongSlicesWanted of them or more than kLongSlices of a document, as every slice reads
+// the whole document and clears K counters.  The longest slices come first.
+// (2 * 10^4 documents of 1100 tokens and one of 3 * 10^5; a sweep of 2 steps, ms, K = 257, 4000, 32 768: with as
+// many slices of every document as the longest has 12.1, 12.5, 19.6, one workgroup per document with a hash
+// table in memory 5.6, 6.1, 8.2, these lists 0.78, 0.89, 1.28.)
+constexpr int32_t kLongSlice = 1024;
+constexpr int32_t kLongSlices = 64;
+constexpr int64_t kLongSlicesWanted = 1024;
+
+static int setup_long_docs(lda_ctx* c)
+{
+    if (c->n_long == 0 || c->K > kLongDocTopics) return LDA_OK;
+    std::vector<int4> slices, parts;
+    auto rounded = [](int64_t n) { return (int32_t)((n + kLongSlice - 1) / kLongSlice * kLongSlice); };
+    const int32_t least = rounded((c->long_tokens + kLongSlicesWanted - 1) / kLongSlicesWanted);
+    for (int32_t d : c->h_long_doc) {
+        const int32_t tok0 = c->h_doff[d], L = c->h_doff[d + 1] - tok0;
+        const int32_t per = std::max(least, rounded((L + kLongSlices - 1) / kLongSlices));
+        for (int64_t i = 0; i < L; i += per)
+            slices.push_back(make_int4(tok0, L, (int32_t)i, (int32_t)std::min<int64_t>(per, L - i)));
+        for (int64_t i = 0; i < L; i += kLongPart)
+            parts.push_back(make_int4(tok0, L, (int32_t)i, (int32_t)std::min<int64_t>(kLongPart, L - i)));
+    }
+    std::stable_sort(slices.begin(), slices.end(), [](const int4& a, const int4& b) { return a.w > b.w; });
+    LDA_ALLOC(c, &c->d_long_slices, slices.size(), "long documents");
+    LDA_ALLOC(c, &c->d_long_parts, parts.size(), "long documents");
+    LDA_HIP(c, hipMemcpy(c->d_long_slices, slices.data(), sizeof(int4) * slices.size(), hipMemcpyHostToDevice));
+    LDA_HIP(c, hipMemcpy(c->d_long_parts, parts.data(), sizeof(int4) * parts.size(), hipMemcpyHostToDevice));
+    c->n_long_slices = (int32_t)slices.size();
+    c->n_long_parts = (int32_t)parts.size();
+    return LDA_OK;
+}
+
 // Work lists of the word pass from the word segment offsets.
 int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
 {
@@ -1918,7 +1941,7 @@ int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
         LDA_HIP(c, hipMemcpy(c->d_gather_pieces, pieces.data(), sizeof(int4) * pieces.size(),
                              hipMemcpyHostToDevice));
     }
-    return LDA_OK;
+    return setup_long_docs(c);
 }
 
 int launch_sweep_split(lda_ctx* c, int32_t mh_steps)
@@ -1982,6 +2005,7 @@ int launch_sweep_split(lda_ctx* c, int32_t mh_steps)
     A.im_x = c->d_im_x; A.im_qz = c->d_im_qz; A.im_pz = c->d_im_pz;
     A.long_doc = c->d_long_doc; A.long_slot = c->d_long_slot;
     A.long_keys = c->d_long_keys; A.long_cnts = c->d_long_cnts;
+    A.long_slices = c->d_long_slices; A.long_parts = c->d_long_parts;
     // from here on the records are being rewritten: valid again only if every launch succeeds
     c->zt_current = false;
     c->td_valid = false;

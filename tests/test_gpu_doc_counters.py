@@ -79,3 +79,12 @@ def test_long_documents(lda_mod, oracle_mod, K):
     a, b = g.loglik(), o.loglik()
     assert abs(a[0] - b[0]) <= 1e-9 * max(abs(b[0]), 1e6) and g.loglik()[0] == g.loglik_noalloc()[0] == a[0]
     g.close(); o.close()
+
+
+# slices longer than 1024 tokens because there are many long documents, and one far longer than the others
+@pytest.mark.parametrize("K", [40, 4099])
+def test_many_long_documents(lda_mod, oracle_mod, K):
+    lens = np.concatenate([np.random.default_rng(K).integers(1000, 2060, 800), [70001, 1024, 1025, 0, 2048, 2049, 5]])
+    assert lens[lens > 1024].sum() > 1024 * 1024
+    doff, words = make(lens, 40, K)
+    check(lda_mod, oracle_mod, doff, words, 40, K, 0.1, 0.01, (2, 4, 2))
