@@ -601,8 +601,8 @@ int launch_dense_table(lda_ctx* c, int32_t w)
     return launch_dense_lds(c, a);
 }
 
-// The dense tables of words whose table is implied are made when a sweep of one kernel, which draws
-// from bins, is asked for; lda_build_alias makes the form that the last sweep drew from.
+// lda_build_alias makes the form that the last sweeps drew from; the bins of all words are made late when
+// a sweep of one kernel comes after two-pass ones.
 int have_implied_tables(lda_ctx* c)
 {
     if (c->implied_built) return LDA_OK;

@@ -109,7 +109,7 @@ void free_all(lda_ctx* c)
     dev_free(c, c->d_im_words); dev_free(c, c->d_im_n); dev_free(c, c->d_rows_stale); dev_free(c, c->d_row_tiles);
     dev_free(c, c->d_im_off); dev_free(c, c->d_im_head); dev_free(c, c->d_im_key);
     dev_free(c, c->d_im_corr); dev_free(c, c->d_im_x); dev_free(c, c->d_im_qz); dev_free(c, c->d_im_pz);
-    dev_free(c, c->d_im_sum); dev_free(c, c->d_fixed_words); dev_free(c, c->d_misfits); dev_free(c, c->d_n_misfits); dev_free(c, c->d_im_pieces); dev_free(c, c->d_short_pieces);
+    dev_free(c, c->d_im_sum); dev_free(c, c->d_fixed_words); dev_free(c, c->d_misfits); dev_free(c, c->d_n_misfits); dev_free(c, c->d_im_pieces); dev_free(c, c->d_bins_pieces); dev_free(c, c->d_short_pieces);
     dev_free(c, c->d_alias); dev_free(c, c->d_cap); dev_free(c, c->d_chunk_doc); dev_free(c, c->d_chunk_tok); dev_free(c, c->d_tokdoc); dev_free(c, c->d_chunk_doc2); dev_free(c, c->d_chunk_tok2); dev_free(c, c->d_tokdoc2); dev_free(c, c->d_long_doc);
     dev_free(c, c->d_long_slot); dev_free(c, c->d_long_keys); dev_free(c, c->d_long_cnts); dev_free(c, c->d_long_first);
     dev_free(c, c->d_long_slices); dev_free(c, c->d_long_parts);
@@ -710,7 +710,7 @@ int lda_build_alias(lda_ctx* c)
     c->implied_built = c->all_dense_built = false;
     if (c->hybrid) {
         rc = launch_alias_build_hybrid(c);
-    } else if (c->n_implied > 0 && !c->want_all_dense) {
+    } else if (c->n_implied > 0 && c->bins_left == 0) {
         rc = have_implied_tables(c);
     } else {
         rc = have_all_dense_tables(c);
@@ -743,12 +743,11 @@ int lda_sweep(lda_ctx* c, int32_t mh_steps)
         c->td_valid = false;
         c->pass_ev_recorded = false;
     } else if (split_sweep_supported(c, mh_steps)) {
-        rc = c->n_implied > 0 ? have_implied_tables(c) : LDA_OK;
-        if (rc == LDA_OK) rc = launch_sweep_split(c, mh_steps);
-        c->want_all_dense = false;
+        rc = launch_sweep_split(c, mh_steps);
+        if (rc == LDA_OK && c->bins_left > 0) --c->bins_left;
     } else {
         rc = c->hybrid ? LDA_OK : have_all_dense_tables(c);
-        c->want_all_dense = true;
+        c->bins_left = lda_ctx::kBinsSweeps;
         if (rc == LDA_OK) rc = c->hybrid ? launch_sweep_hybrid(c, mh_steps) : launch_sweep(c, mh_steps);
         c->zt_current = false;  // the fused kernels write the doc-major assignment only
         c->td_valid = false;

@@ -167,10 +167,16 @@ struct lda_ctx {
     int32_t* d_n_misfits = nullptr;      //   implied form, which have dense tables made from their lists; how many
     int4* d_im_pieces = nullptr;         // pieces of the word pass, as d_gather_pieces
     int32_t n_im_pieces = 0;
+    int4* d_bins_pieces = nullptr;       // d_gather_pieces where words with implied tables are drawn from bins too
+    int32_t n_bins_pieces = 0;
     int4* d_short_pieces = nullptr;      // and of words of the mixture form with few tokens
     int32_t n_short_pieces = 0;
-    // which forms hold the tables of the current counts, and which one the last sweep drew from
-    bool implied_built = false, all_dense_built = false, want_all_dense = false;
+    // Which forms hold the tables of the current counts.  One-pass sweeps draw from bins, two-pass ones from
+    // either; after a one-pass sweep the next kBinsSweeps two-pass ones draw from bins as well, so that a
+    // program that takes the two in turn has its tables made once (api.hip).
+    static constexpr int32_t kBinsSweeps = 4;
+    bool implied_built = false, all_dense_built = false;
+    int32_t bins_left = 0;
     // The counts of words with implied tables: in their lists alone after a recount, unless their rows
     // are wanted (by one-pass sweeps, or lda_update_counts lately).  What holds is kept on the device,
     // where captured work finds it too: *d_rows_stale = 1: the lists do, 0: the rows do.
@@ -354,7 +360,7 @@ int launch_implied_tables(lda_ctx* c);
 int launch_implied_lists(lda_ctx* c);                      // their lists from the word-major z
 int launch_rows_from_lists(lda_ctx* c, int32_t w);         // rows of all such words (w < 0) or one, if stale
 int launch_loglik_implied(lda_ctx* c, double lg_beta, const double* terms, int blocks, double* partial);
-// the tables a sweep draws from, if lda_build_alias has made the other form (all-dense store)
+// the tables of either form, unless they are made (all-dense store)
 int have_implied_tables(lda_ctx* c);
 int have_all_dense_tables(lda_ctx* c);
 int launch_rebuild_hybrid(lda_ctx* c);

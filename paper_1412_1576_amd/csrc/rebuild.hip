@@ -638,9 +638,9 @@ int launch_rebuild(lda_ctx* c)
     const int32_t K = c->K;
     if (K > max_rebuild_topics())
         return fail(c, LDA_ERR_UNSUPPORTED, "count rebuild supports K <= %d", max_rebuild_topics());
-    // Rows of words with implied tables are only made where something lately read them: the one-pass
-    // sweeps, or lda_update_counts, which may be taking turns with this.
-    const bool rows = c->n_implied == 0 || c->want_all_dense || c->rows_wanted > 0;
+    // Rows of words with implied tables are only made where something lately read them: the sweeps that
+    // draw from bins, or lda_update_counts, which may be taking turns with this.
+    const bool rows = c->n_implied == 0 || c->bins_left > 0 || c->rows_wanted > 0;
     if (c->rows_wanted > 0) --c->rows_wanted;
     int rc = launch_dense_rows(c, nullptr, !rows);
     if (rc != LDA_OK) return rc;

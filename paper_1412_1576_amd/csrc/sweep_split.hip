@@ -1585,8 +1585,8 @@ int launch_chain(lda_ctx* c, const SplitArgs& A, bool need_proposals)
         hipLaunchKernelGGL(kern, dim3(xcd_runs_grid(c->n_mix_items, A.mix_run)), dim3(512), lds, c->stream, A);
         LDA_HIP(c, hipGetLastError());
     }
-    if (c->n_gather_pieces > 0) {
-        const dim3 grid(xcd_runs_grid(c->n_gather_pieces, A.piece_run));
+    if (A.n_pieces > 0) {
+        const dim3 grid(xcd_runs_grid(A.n_pieces, A.piece_run));
         if (!c->hybrid)
             hipLaunchKernelGGL((word_pass_gather_kernel<NW, ND, 0>), grid, dim3(256), 0, c->stream, A);
         else if (c->H == c->V)
@@ -1843,9 +1843,9 @@ int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
             few_pieces.push_back(make_int4(im0, w_end, woff[im0], woff[w_end] - woff[im0]));
         im0 = -1;
     };
-    bool use_short = true;
+    bool use_short = true, use_implied = c->n_implied > 0;
     auto few_tokens = [&](int32_t w, int32_t n) {
-        if (!c->hybrid) return c->n_implied > 0 && c->h_table_form[w] == 1;
+        if (!c->hybrid) return use_implied && c->h_table_form[w] == 1;
         return use_short && n > 0 && n <= kShortTokens && (c->h_wkind[w] & 2) == 0 &&
                !((c->h_wkind[w] & 1) && c->K <= kMixRowTopics && n >= kMixRowMinTokens && n > c->K / kShortShare);
     };
@@ -1873,44 +1873,57 @@ int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
     }
     const int32_t row_item = (int32_t)std::min<int64_t>(
         kRowItemTokens, std::max<int64_t>(std::max(kRowItemLeast, c->K), row_tokens / kRowItemsWanted));
-    for (int32_t w = 0; w < V; ++w) {
-        const int32_t b = woff[w], n = woff[w + 1] - b;
-        const bool dense_dense = dense_form(w);
-        if (few_tokens(w, n) || (n == 0 && im0 >= 0)) {
-            if (im0 >= 0 && (woff[w + 1] - woff[im0] > few_piece || w + 1 - im0 > kImpliedWords)) close_implied(w);
-            if (im0 < 0) {
-                close_piece(w);
-                im0 = w;
+    auto list_words = [&]() {
+        for (int32_t w = 0; w < V; ++w) {
+            const int32_t b = woff[w], n = woff[w + 1] - b;
+            const bool dense_dense = dense_form(w);
+            if (few_tokens(w, n) || (n == 0 && im0 >= 0)) {
+                if (im0 >= 0 && (woff[w + 1] - woff[im0] > few_piece || w + 1 - im0 > kImpliedWords)) close_implied(w);
+                if (im0 < 0) {
+                    close_piece(w);
+                    im0 = w;
+                }
+                continue;
             }
-            continue;
+            close_implied(w);
+            if (n >= kRowMinTokens && rows_fit && dense_dense) {
+                close_piece(w);
+                for (int32_t p = b; p < b + n; p += row_item)
+                    items.push_back(make_int4(w, p, std::min(row_item, b + n - p), 0));
+                continue;
+            }
+            // a mixture word with a dense row of at most kMixRowTopics topics and enough
+            // tokens to pay for clearing an LDS row
+            if (c->hybrid && (c->h_wkind[w] & 3) == 1 && c->K <= kMixRowTopics && n >= kMixRowMinTokens) {
+                close_piece(w);
+                for (int32_t p = b; p < b + n; p += kRowItemTokens)
+                    mix_items.push_back(make_int4(w, p, std::min(kRowItemTokens, b + n - p), 0));
+                continue;
+            }
+            if (n > kPieceTokens) {  // a long word that cannot be staged: pieces of its own
+                close_piece(w);
+                for (int32_t p = b; p < b + n; p += kPieceTokens)
+                    pieces.push_back(make_int4(w, w + 1, p, std::min(kPieceTokens, b + n - p)));
+                continue;
+            }
+            if (w0 >= 0 && (woff[w + 1] - woff[w0] > kPieceTokens || w + 1 - w0 > kPieceWords))
+                close_piece(w);
+            if (w0 < 0) w0 = w;
         }
-        close_implied(w);
-        if (n >= kRowMinTokens && rows_fit && dense_dense) {
-            close_piece(w);
-            for (int32_t p = b; p < b + n; p += row_item)
-                items.push_back(make_int4(w, p, std::min(row_item, b + n - p), 0));
-            continue;
-        }
-        // a mixture word with a dense row of at most kMixRowTopics topics and enough
-        // tokens to pay for clearing an LDS row
-        if (c->hybrid && (c->h_wkind[w] & 3) == 1 && c->K <= kMixRowTopics && n >= kMixRowMinTokens) {
-            close_piece(w);
-            for (int32_t p = b; p < b + n; p += kRowItemTokens)
-                mix_items.push_back(make_int4(w, p, std::min(kRowItemTokens, b + n - p), 0));
-            continue;
-        }
-        if (n > kPieceTokens) {  // a long word that cannot be staged: pieces of its own
-            close_piece(w);
-            for (int32_t p = b; p < b + n; p += kPieceTokens)
-                pieces.push_back(make_int4(w, w + 1, p, std::min(kPieceTokens, b + n - p)));
-            continue;
-        }
-        if (w0 >= 0 && (woff[w + 1] - woff[w0] > kPieceTokens || w + 1 - w0 > kPieceWords))
-            close_piece(w);
-        if (w0 < 0) w0 = w;
+        close_piece(V);
+        close_implied(V);
+    };
+    if (use_implied) {  // first the pieces of all words without implied tables
+        use_implied = false;
+        list_words();
+        c->n_bins_pieces = (int32_t)pieces.size();
+        LDA_ALLOC(c, &c->d_bins_pieces, pieces.size(), "word-pass work list");
+        LDA_HIP(c, hipMemcpy(c->d_bins_pieces, pieces.data(), sizeof(int4) * pieces.size(), hipMemcpyHostToDevice));
+        items.clear();
+        pieces.clear();
+        use_implied = true;
     }
-    close_piece(V);
-    close_implied(V);
+    list_words();
     c->n_short_pieces = (int32_t)short_pieces.size();
     if (!short_pieces.empty()) {
         LDA_ALLOC(c, &c->d_short_pieces, short_pieces.size(), "word-pass work list");
@@ -1968,9 +1981,14 @@ int launch_sweep_split(lda_ctx* c, int32_t mh_steps)
     A.nkw = c->d_nkw; A.nk = c->d_nk; A.alias = c->d_alias; A.cap = c->d_cap;
     A.zt = c->d_zt; A.zt_pack16 = c->zt_pack16 ? 1 : 0; A.rec = c->d_rec; A.row_items = c->d_row_items; A.pieces = c->d_gather_pieces;
     A.n_chunks = c->n_chunks; A.n_row_items = c->n_row_items; A.n_pieces = c->n_gather_pieces;
+    A.im_pieces = c->d_im_pieces; A.n_im_pieces = c->n_im_pieces;
+    if (c->all_dense_built && c->n_implied > 0) {  // bins for every word
+        A.pieces = c->d_bins_pieces; A.n_pieces = c->n_bins_pieces;
+        A.n_im_pieces = 0;
+    }
     A.row_run = xcd_run_length(c->n_row_items, kRowItemRun);
     A.mix_run = xcd_run_length(c->n_mix_items, kMixItemRun);
-    A.piece_run = xcd_run_length(c->n_gather_pieces, kPieceRun);
+    A.piece_run = xcd_run_length(A.n_pieces, kPieceRun);
     A.K = c->K; A.cap_tokens = c->chunk_tokens; A.max_doc_tokens = c->chunk_tokens;
     A.doc_block = c->sweep_block;
     // (rounded up to 16 bytes: the copy of n_k behind the tile is moved as int4)
@@ -1999,8 +2017,7 @@ int launch_sweep_split(lda_ctx* c, int32_t mh_steps)
     A.sp_nnz = c->d_sp_nnz; A.mix_items = c->d_mix_items; A.n_mix_items = c->n_mix_items;
     A.short_pieces = c->d_short_pieces; A.n_short_pieces = c->n_short_pieces;
     A.short_run = xcd_run_length(c->n_short_pieces, kPieceRun);
-    A.im_pieces = c->d_im_pieces; A.n_im_pieces = c->n_im_pieces;
-    A.im_run = xcd_run_length(c->n_im_pieces, kPieceRun);
+    A.im_run = xcd_run_length(A.n_im_pieces, kPieceRun);
     A.im_off = c->d_im_off; A.im_head = c->d_im_head; A.im_key = c->d_im_key; A.im_corr = c->d_im_corr;
     A.im_x = c->d_im_x; A.im_qz = c->d_im_qz; A.im_pz = c->d_im_pz;
     A.long_doc = c->d_long_doc; A.long_slot = c->d_long_slot;

@@ -108,6 +108,17 @@ def test_in_turn_with_one_pass_sweeps(lda_mod, oracle_mod):
     g.close(); o.close()
 
 
+@pytest.mark.parametrize("update", [False, True])
+def test_back_to_implied_tables(lda_mod, oracle_mod, update):
+    """Two-pass sweeps after a one-pass sweep: four that draw from bins, then from implied tables again."""
+    V, K = 12000, 1024
+    doff, words = corpus_of(frequencies(V, K, 5), 5)
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K, beta=1e-4, record_bucket_tokens=4096)
+    for i, m in enumerate((9, 2, 4, 1, 2, 2, 2, 9, 3, 10, 2, 2, 2, 2, 2, 2)):
+        step(g, o, m, update=update and i in (3, 6, 12), tables=(0, 5, 13, 1000))
+    g.close(); o.close()
+
+
 def test_words_without_tokens_in_used_memory(lda_mod, oracle_mod):
     """The first sweep of a new sampler is one kernel, which draws from bins, and the caller's memory
     has been used before: the rows that the bins of words without tokens are made from are zero."""
