@@ -708,6 +708,7 @@ int lda_build_alias(lda_ctx* c)
         return fail(c, LDA_ERR_STATE, "lda_build_alias: counts are stale (call lda_rebuild_counts)");
     int rc;
     c->implied_built = c->all_dense_built = false;
+    c->state = COUNTS_VALID;  // a build that fails leaves no tables
     if (c->hybrid) {
         rc = launch_alias_build_hybrid(c);
     } else if (c->n_implied > 0 && c->bins_left == 0) {

@@ -229,3 +229,23 @@ def test_record_order_and_word_chains(lda_mod, oracle_mod):
     for m in (1, 3, 1, 1):
         step(g, o, m)
     g.close(); o.close()
+
+
+@pytest.mark.parametrize("V", [40, 12000])
+def test_a_failed_build_leaves_no_tables(lda_mod, oracle_mod, V):
+    """The library reports an error that an earlier HIP call of the thread left; no table is given out
+    or drawn from until they are built again."""
+    K = 1024
+    doff, words = corpus_of(np.full(V, 40), 4)
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K)
+    g.build_alias(); o.build_alias()
+    assert lda_mod.load_library().hipSetDevice(999) != 0
+    with pytest.raises(lda_mod.LdaError) as e:
+        g.build_alias()
+    assert e.value.code == lda_mod.LDA_ERR_HIP
+    for call in (lambda: g.get_alias_row(3), lambda: g.sweep(2)):
+        with pytest.raises(lda_mod.LdaError) as e:
+            call()
+        assert e.value.code == lda_mod.LDA_ERR_STATE
+    step(g, o, 2, tables=(0, 3))
+    g.close(); o.close()
