@@ -51,12 +51,18 @@ void device_free(lda_ctx* c, void* p)
     else (void)hipFree(p);
 }
 
+bool stream_is_captured(lda_ctx* c)
+{
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &capture) == hipSuccess) return capture != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 void device_release(lda_ctx* c, void* p)
 {
     if (!p) return;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
+    if (stream_is_captured(c)) {
         try {
             c->kept.push_back(p);
         } catch (...) {  // no room to remember it: not given back at all
@@ -711,10 +717,10 @@ int lda_build_alias(lda_ctx* c)
     c->state = COUNTS_VALID;  // a build that fails leaves no tables
     if (c->hybrid) {
         rc = launch_alias_build_hybrid(c);
-    } else if (c->n_implied > 0 && c->bins_left == 0) {
-        rc = have_implied_tables(c);
     } else {
-        rc = have_all_dense_tables(c);
+        const bool bins = c->n_implied == 0 || c->bins_left > 0;
+        rc = bins || c->bins_captured ? have_all_dense_tables(c) : LDA_OK;
+        if (rc == LDA_OK && (!bins || c->implied_captured)) rc = have_implied_tables(c);
     }
     if (rc == LDA_OK) c->state = ALIAS_VALID;
     return rc;
@@ -744,11 +750,14 @@ int lda_sweep(lda_ctx* c, int32_t mh_steps)
         c->td_valid = false;
         c->pass_ev_recorded = false;
     } else if (split_sweep_supported(c, mh_steps)) {
-        rc = launch_sweep_split(c, mh_steps);
+        const bool bins = !c->implied_built || (c->all_dense_built && c->bins_left > 0);
+        if (c->n_implied > 0 && stream_is_captured(c)) (bins ? c->bins_captured : c->implied_captured) = true;
+        rc = launch_sweep_split(c, mh_steps, bins);
         if (rc == LDA_OK && c->bins_left > 0) --c->bins_left;
     } else {
         rc = c->hybrid ? LDA_OK : have_all_dense_tables(c);
         c->bins_left = lda_ctx::kBinsSweeps;
+        if (c->n_implied > 0 && stream_is_captured(c)) c->bins_captured = true;
         if (rc == LDA_OK) rc = c->hybrid ? launch_sweep_hybrid(c, mh_steps) : launch_sweep(c, mh_steps);
         c->zt_current = false;  // the fused kernels write the doc-major assignment only
         c->td_valid = false;

@@ -177,6 +177,9 @@ struct lda_ctx {
     static constexpr int32_t kBinsSweeps = 4;
     bool implied_built = false, all_dense_built = false;
     int32_t bins_left = 0;
+    // A sweep was captured into a graph that draws from these: lda_build_alias makes them from then on, as
+    // the host does not see the replays.
+    bool implied_captured = false, bins_captured = false;
     // The counts of words with implied tables: in their lists alone after a recount, unless their rows
     // are wanted (by one-pass sweeps, or lda_update_counts lately).  What holds is kept on the device,
     // where captured work finds it too: *d_rows_stale = 1: the lists do, 0: the rows do.
@@ -327,6 +330,7 @@ void device_free(lda_ctx* c, void* p);
 // first (a caller's allocator may hand the block to other work at once), or, while the stream is
 // being captured and cannot be waited for, keeps the block until lda_destroy.
 void device_release(lda_ctx* c, void* p);
+bool stream_is_captured(lda_ctx* c);
 
 template <class T>
 int device_malloc(lda_ctx* c, T** p, size_t count, const char* what)
@@ -427,7 +431,7 @@ int launch_sweep_doc_refresh(lda_ctx* c, int32_t mh_steps, int32_t longest_doc);
 bool split_sweep_supported(lda_ctx* c, int32_t mh_steps);
 bool doc_limits(double alphabar, std::vector<uint32_t>& limit);
 int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff);
-int launch_sweep_split(lda_ctx* c, int32_t mh_steps);
+int launch_sweep_split(lda_ctx* c, int32_t mh_steps, bool bins);  // bins: no word's table is implied
 int launch_tokdoc(lda_ctx* c);                               // per-token document index in its tile
 int launch_rebuild(lda_ctx* c);
 int launch_update_counts(lda_ctx* c);  // n_kw, n_k by +-1 for the tokens the last sweep moved

@@ -1683,11 +1683,7 @@ bool have_split_records(lda_ctx* c, int32_t mh_steps)
     const size_t more_zt = c->zt_ints >= zt ? 0 : zt, more_rec = c->rec_ints >= rec ? 0 : rec;
     if (more_zt + more_rec == 0) return true;
     if (more_zt + more_rec >= c->refused_ints) return false;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return false;  // no allocation into a graph
-    }
+    if (stream_is_captured(c)) return false;  // no allocation into a graph
     auto ask = [&](size_t ints) {
         return ints ? static_cast<int32_t*>(try_device_malloc(c, sizeof(int32_t) * ints)) : nullptr;
     };
@@ -1957,7 +1953,7 @@ int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
     return setup_long_docs(c);
 }
 
-int launch_sweep_split(lda_ctx* c, int32_t mh_steps)
+int launch_sweep_split(lda_ctx* c, int32_t mh_steps, bool bins)
 {
     int32_t nw, nd;
     chain_shape(c->opt.proposal_mode, mh_steps, nw, nd);
@@ -1982,7 +1978,7 @@ int launch_sweep_split(lda_ctx* c, int32_t mh_steps)
     A.zt = c->d_zt; A.zt_pack16 = c->zt_pack16 ? 1 : 0; A.rec = c->d_rec; A.row_items = c->d_row_items; A.pieces = c->d_gather_pieces;
     A.n_chunks = c->n_chunks; A.n_row_items = c->n_row_items; A.n_pieces = c->n_gather_pieces;
     A.im_pieces = c->d_im_pieces; A.n_im_pieces = c->n_im_pieces;
-    if (c->all_dense_built && c->n_implied > 0) {  // bins for every word
+    if (bins && c->n_implied > 0) {  // for every word
         A.pieces = c->d_bins_pieces; A.n_pieces = c->n_bins_pieces;
         A.n_im_pieces = 0;
     }

@@ -217,6 +217,38 @@ def test_graph_replays_leave_lists(lda_mod, oracle_mod):
     g.close()
 
 
+@pytest.mark.parametrize("captured,others", [(2, (9,)), (9, (2, 2, 2, 2, 2))])
+def test_a_captured_sweep_finds_its_tables(lda_mod, oracle_mod, captured, others):
+    """A graph of a sweep and its recount, replayed after builds that the host made between sweeps that
+    draw from the other form of the tables."""
+    import torch
+    V, K = 12000, 1024
+    doff, words = corpus_of(frequencies(V, K, 4), 4)
+    stream = torch.cuda.Stream()
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K, beta=1e-4, stream=stream.cuda_stream)
+    g.build_alias(); g.sweep(2)  # takes the records, which a capture cannot
+    z = np.random.default_rng(1).integers(0, K, len(words)).astype(np.int32)
+    g.set_z(z, 7)
+    g.rebuild_counts(); g.build_alias(); g.sync()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        g.sweep(captured)  # reads the one array of assignments and writes the other
+        g.rebuild_counts()
+    with torch.cuda.stream(stream):
+        graph.replay()
+    for m in others:  # an odd number: back into the one that the graph reads
+        g.build_alias(); g.sweep(m); g.rebuild_counts()
+    o.set_z(g.get_z(), 7)
+    o.rebuild_counts(); o.build_alias(); g.build_alias()
+    o.sweep(captured); o.rebuild_counts()
+    with torch.cuda.stream(stream):
+        graph.replay()
+    assert np.array_equal(g.get_nk(), o.get_nk())
+    for w in range(0, V, 411):
+        assert np.array_equal(g.get_nkw_row(w), o.get_nkw_row(w)), w
+    g.close(); o.close()
+
+
 def test_record_order_and_word_chains(lda_mod, oracle_mod):
     V, K = 12000, 1024
     doff, words = corpus_of(frequencies(V, K, 9), 9)
