@@ -164,9 +164,11 @@ struct DenseArgs {
     uint4* alias;
     uint32_t* cap;   // nullable
     uint4* metaA;    // nullable; word w at [2w]
-    // words whose tables are made from lists: how many (n_words is the most there can be), and these
+    // words whose tables are made from lists (n_words is the most there can be): the lengths of kMisfitLists
+    // lists of them, the lists, and the room of each
     const int32_t* n_dev;
     const int4* misfits;
+    int32_t misfit_words;
     const uint32_t* key;
     const uint64_t *sum0, *sum;  // sums of the weights, in the place of a list's running sums
     const uint32_t* qz;
@@ -198,21 +200,31 @@ __global__ __launch_bounds__(MAXB) void alias_dense_lds_kernel(DenseArgs a)
 
 // The same for the words whose sums did not fit the implied form, from their lists.  Only the device
 // knows how many there are, so the workgroups loop.
+static_assert(kMisfitLists == kWave, "a lane per list");
 template <int E, bool ONE, int MAXB>
 __global__ __launch_bounds__(MAXB, MAXB == 256 ? 8 : 1) void alias_dense_list_kernel(DenseArgs a)
 {
     extern __shared__ unsigned char smem_raw[];
     const int wv = ONE ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
     const int32_t step = ONE ? (int32_t)(gridDim.x * (blockDim.x >> 6)) : (int32_t)gridDim.x;
-    const int32_t n = *a.n_dev;
+    // the lists' words count through: those of list l end before `upto`
+    const int lane = threadIdx.x & (kWave - 1);
+    const int32_t mine = a.n_dev[lane * kMisfitStride];
+    const int32_t upto = (int32_t)wave_inclusive_scan_u32((uint32_t)mine);
+    const int32_t n = __builtin_amdgcn_readlane(upto, kWave - 1);
+    const int32_t base = lane * a.misfit_words - (upto - mine);  // of the list's words, less those before it
+    auto misfit = [&](int32_t j) {
+        const uint64_t after = __ballot(upto > j);  // (j < n: some list's)
+        return a.misfits[j + __builtin_amdgcn_readlane(base, __ffsll((unsigned long long)after) - 1)];
+    };
     int32_t i = ONE ? (int32_t)(blockIdx.x * (blockDim.x >> 6)) + wv : (int32_t)blockIdx.x;
     if (i >= n) return;
-    int4 next = a.misfits[i];
+    int4 next = misfit(i);
     for (; i < n; i += step) {
         const int32_t w = next.x;  // (word, list offset, entries)
         const size_t off = (uint32_t)next.y;
         const int32_t n_key = next.z;
-        next = a.misfits[i + step < n ? i + step : i];
+        next = misfit(i + step < n ? i + step : i);
         // a fresh K every time, or the compiler keeps what it derives from it in registers over the
         // loop (128 instead of 86 VGPRs at E = 12, and spills: twice the time)
         int32_t K = a.K;
@@ -587,7 +599,7 @@ int launch_dense_listed(lda_ctx* c)
     a.alias = c->d_alias; a.cap = c->d_cap;
     const int rc = launch_dense_lds(c, a);
     if (rc != LDA_OK) return rc;
-    a.misfits = c->d_misfits; a.n_words = c->n_implied; a.n_dev = c->d_n_misfits; a.key = c->d_im_key;
+    a.misfits = c->d_misfits; a.misfit_words = misfit_list_words(c->n_implied); a.n_words = c->n_implied; a.n_dev = c->d_n_misfits; a.key = c->d_im_key;
     a.sum0 = c->d_im_corr; a.sum = c->d_im_x; a.qz = c->d_im_qz;
     return launch_dense_lds(c, a);
 }

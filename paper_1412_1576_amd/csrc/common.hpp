@@ -164,7 +164,8 @@ struct lda_ctx {
     int32_t* d_fixed_words = nullptr;    // words with a dense table always
     int32_t n_fixed_words = 0;
     int4* d_misfits = nullptr;           // (word, list offset, entries) of the words whose sums do not fit the
-    int32_t* d_n_misfits = nullptr;      //   implied form, which have dense tables made from their lists; how many
+    int32_t* d_n_misfits = nullptr;      //   implied form, which have dense tables made from their lists; how many:
+                                         //   several lists of them (implied.hpp)
     int4* d_im_pieces = nullptr;         // pieces of the word pass, as d_gather_pieces
     int32_t n_im_pieces = 0;
     int4* d_bins_pieces = nullptr;       // d_gather_pieces where words with implied tables are drawn from bins too

@@ -27,7 +27,7 @@ __device__ __forceinline__ uint64_t quantise40(double a)
 
 // Shared by all words: q[k] = floor(beta / (n_k + betabar) * 2^40), saturated at 32 bits; pz[k] = sum of
 // max(1, q) below k; sum = (sum of the q, sum of max(1, q), largest max(1, q)).  One workgroup, a
-// run of consecutive topics per thread.  The list of misfits starts empty.
+// run of consecutive topics per thread.  The lists of misfits start empty.
 constexpr int kSumThreads = 1024;
 
 __global__ __launch_bounds__(kSumThreads) void implied_sums_kernel(const int32_t* __restrict__ nk, int32_t K,
@@ -88,8 +88,8 @@ __global__ __launch_bounds__(kSumThreads) void implied_sums_kernel(const int32_t
         sum[0] = q0_all;
         sum[1] = q_all;
         sum[2] = max_all;
-        *n_misfits = 0;
     }
+    if (t < kMisfitLists) n_misfits[t * kMisfitStride] = 0;
 }
 
 // A wave per word: its tokens' topics, ascending, with their counts.  The topics are marked in a
@@ -200,6 +200,8 @@ struct ImpliedArgs {
     uint64_t* __restrict__ x;
     int4* __restrict__ misfits;
     int32_t* __restrict__ n_misfits;
+    int32_t first;        // of these words among all, and the room of a list of misfits
+    int32_t misfit_words;
     const int32_t* __restrict__ stale;
     int32_t cap;  // keys of a wave in LDS
 };
@@ -274,7 +276,8 @@ __global__ __launch_bounds__(256) void implied_tables_kernel(ImpliedArgs a)
             a.head[w] = make_uint4(n | kImpliedDense, 0u, 0u, 0u);
             a.corr[off] = Q0;  // for the builder of its bins
             a.x[off] = Q;
-            a.misfits[atomicAdd(a.n_misfits, 1)] = make_int4(w, (int32_t)off, (int32_t)n, 0);
+            const int32_t list = (a.first + i) & (kMisfitLists - 1);
+            a.misfits[list * a.misfit_words + atomicAdd(a.n_misfits + list * kMisfitStride, 1)] = make_int4(w, (int32_t)off, (int32_t)n, 0);
         }
         return;
     }
@@ -415,8 +418,8 @@ int setup_implied(lda_ctx* c, const std::vector<int32_t>& woff)
     LDA_ALLOC(c, &c->d_im_pz, (size_t)K + 1, "implied tables");
     LDA_ALLOC(c, &c->d_im_sum, 3, "implied tables");
     LDA_ALLOC(c, &c->d_fixed_words, fixed.size(), "implied tables");
-    LDA_ALLOC(c, &c->d_misfits, all.size(), "implied tables");
-    LDA_ALLOC(c, &c->d_n_misfits, 1, "implied tables");
+    LDA_ALLOC(c, &c->d_misfits, (size_t)misfit_list_words((int32_t)n) * kMisfitLists, "implied tables");
+    LDA_ALLOC(c, &c->d_n_misfits, kMisfitLists * kMisfitStride, "implied tables");
     LDA_HIP(c, hipMemcpy(c->d_im_words, all.data(), sizeof(int32_t) * all.size(), hipMemcpyHostToDevice));
     LDA_HIP(c, hipMemcpy(c->d_im_off, off.data(), sizeof(uint32_t) * off.size(), hipMemcpyHostToDevice));
     if (!fixed.empty())
@@ -445,6 +448,7 @@ int launch_implied_tables(lda_ctx* c)
     a.qz = c->d_im_qz; a.sum = c->d_im_sum; a.off = c->d_im_off; a.head = c->d_im_head; a.key = c->d_im_key;
     a.corr = c->d_im_corr; a.x = c->d_im_x; a.misfits = c->d_misfits; a.n_misfits = c->d_n_misfits;
     a.words = c->d_im_words; a.n_list = c->d_im_n; a.stale = c->d_rows_stale;
+    a.misfit_words = misfit_list_words(c->n_implied);
     for (int i = 0; i < lda_ctx::kImpliedClasses; ++i) {
         a.n_words = c->n_im_class[i];
         a.cap = kImpliedClassCap[i];
@@ -453,6 +457,7 @@ int launch_implied_tables(lda_ctx* c)
                                sizeof(uint32_t) * 4 * (size_t)a.cap, c->stream, a);
         LDA_HIP(c, hipGetLastError());
         a.words += a.n_words;
+        a.first += a.n_words;
     }
     return LDA_OK;
 }
