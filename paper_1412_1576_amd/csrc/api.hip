@@ -123,7 +123,7 @@ void free_all(lda_ctx* c)
     dev_free(c, c->d_flag);
     dev_free(c, c->d_dense_alias_words);
     for (int i = 0; i < kMixClasses; ++i) dev_free(c, c->d_mix_class[i]);
-    dev_free(c, c->d_sparse_words); dev_free(c, c->d_row_words); dev_free(c, c->d_compact_words); dev_free(c, c->d_sp_off);
+    dev_free(c, c->d_sparse_words); dev_free(c, c->d_row_words); dev_free(c, c->d_list_rows); dev_free(c, c->d_compact_words); dev_free(c, c->d_sp_off);
     dev_free(c, c->d_sp_topic); dev_free(c, c->d_sp_count); dev_free(c, c->d_sp_nnz); dev_free(c, c->d_hs_off);
     dev_free(c, c->d_hs); dev_free(c, c->d_ma); dev_free(c, c->d_metaA); c->d_metaB = nullptr;
     dev_free(c, c->d_beta_alias); dev_free(c, c->d_beta_hdr);
@@ -228,7 +228,7 @@ int setup_hybrid(lda_ctx* c, const std::vector<int32_t>& woff)
     c->h_wkind.resize(V);
     c->h_sp_off.assign((size_t)V + 1, 0);
     c->h_hs_off.assign((size_t)V + 1, 0);
-    std::vector<int32_t> dense_alias, mix, sparse, compact, listed, row_words, mixc[kMixClasses];
+    std::vector<int32_t> dense_alias, mix, sparse, compact, listed, row_words, list_rows, mixc[kMixClasses];
     std::vector<uint4> meta(2 * (size_t)V, make_uint4(0u, 0u, 0u, 0u));
     const int32_t lds_max = max_lds_table_entries();
     const bool two_pass = c->opt.stream_block_tokens == 0 && c->opt.proposal_mode != 2 &&
@@ -273,6 +273,10 @@ int setup_hybrid(lda_ctx* c, const std::vector<int32_t>& woff)
                         kind |= (uint8_t)kKindListOnly;  // served from its list everywhere
                         c->h_wkind[w] = kind;
                         ++c->n_list_only;
+                        if (K > kMixRowTopics) {
+                            kind &= (uint8_t)~kKindListOnly;  // sweeps that look up rows have them
+                            if (cw > 0) list_rows.push_back(w);
+                        }
                     }
                 }
             } else {
@@ -306,6 +310,8 @@ int setup_hybrid(lda_ctx* c, const std::vector<int32_t>& woff)
     UP(d_sparse_words, sparse, "sparse-row words");
     UP(d_compact_words, compact, "compaction words");
     UP(d_row_words, row_words, "dense-row words");
+    UP(d_list_rows, list_rows, "list-only words");
+    c->n_list_rows = (int32_t)list_rows.size();
     for (int i = 0; i < kMixClasses; ++i) {
         c->n_mix_class[i] = (int32_t)mixc[i].size();
         UP(d_mix_class[i], mixc[i], "mixture class");
@@ -651,7 +657,7 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
         if (e - b <= limit) {
             const int32_t form = !list_from_rebuild(c, w) ? 0 : ((c->h_wkind[w] & kKindListOnly) ? 3 : 2);
             // rows of several topic ranges that also give a list have a kernel of their own
-            if (form == 3 && K > max_rebuild_topics()) continue;  // sorted with the sparse rows
+            if (form == 3 && K > kMixRowTopics) continue;  // sorted with the sparse rows
             if (form == 2 && K > max_rebuild_topics())
                 list_tiles.push_back(RebuildTile{w, b, e, form});
             else

@@ -243,6 +243,8 @@ struct lda_ctx {
     int32_t* d_row_words = nullptr;      // the other words: the log-likelihood sums over their rows
     int32_t n_row_words = 0;
     int32_t n_list_only = 0;             // words marked kKindListOnly
+    int32_t* d_list_rows = nullptr;      // those beyond kMixRowTopics topics: one-pass sweeps get their rows
+    int32_t n_list_rows = 0;
     int32_t* d_compact_words = nullptr;  // mixture words with a dense row (list made by compaction)
     int32_t n_compact = 0;
     uint32_t* d_sp_off = nullptr;        // [V+1] first list entry of word w (capacity min(c_w, K))
@@ -410,7 +412,9 @@ __host__ __device__ inline uint4 pack_mix_bin(uint32_t split, int32_t t_own, int
 // be the largest write of the rebuild (c3: 5.4 of 6.4 GB) for nobody to read, so the row is
 // left untouched (all zero since lda_init) and the word is marked with this bit; the rare
 // lookup outside the word pass (fused sweep) searches the word's mixture table, whose bins
-// are its non-zero topics in ascending order.
+// are its non-zero topics in ascending order.  In the larger K, where such words are the rare ones
+// and have most of the look-ups, a fused sweep puts the counts into the rows before it and
+// zeros back after it (list_rows_kernel), and the words' records on the device are not marked.
 constexpr uint32_t kKindListOnly = 4u;
 constexpr int32_t kMixRowTopics = 16384;   // largest K whose n_kw row a mixture item keeps in LDS
 constexpr int32_t kMixRowMinTokens = 128;
