@@ -112,10 +112,8 @@ void free_all(lda_ctx* c)
     c->side_stream = nullptr;
     dev_free(c, c->d_woff); dev_free(c, c->d_nkw); dev_free(c, c->d_nk);
     dev_free(c, c->d_doc_limit);
-    dev_free(c, c->d_im_words); dev_free(c, c->d_im_n); dev_free(c, c->d_rows_stale); dev_free(c, c->d_row_tiles);
-    dev_free(c, c->d_im_off); dev_free(c, c->d_im_head); dev_free(c, c->d_im_key);
-    dev_free(c, c->d_im_corr); dev_free(c, c->d_im_x); dev_free(c, c->d_im_qz); dev_free(c, c->d_im_pz);
-    dev_free(c, c->d_im_sum); dev_free(c, c->d_fixed_words); dev_free(c, c->d_misfits); dev_free(c, c->d_n_misfits); dev_free(c, c->d_im_pieces); dev_free(c, c->d_bins_pieces); dev_free(c, c->d_short_pieces);
+    free_implied(c);
+    dev_free(c, c->d_short_pieces);
     dev_free(c, c->d_alias); dev_free(c, c->d_cap); dev_free(c, c->d_chunk_doc); dev_free(c, c->d_chunk_tok); dev_free(c, c->d_tokdoc); dev_free(c, c->d_chunk_doc2); dev_free(c, c->d_chunk_tok2); dev_free(c, c->d_tokdoc2); dev_free(c, c->d_long_doc);
     dev_free(c, c->d_long_slot); dev_free(c, c->d_long_keys); dev_free(c, c->d_long_cnts); dev_free(c, c->d_long_first);
     dev_free(c, c->d_long_slices); dev_free(c, c->d_long_parts);
@@ -645,7 +643,6 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
         std::vector<uint32_t> limit;
         if (doc_limits(c->alphabar, limit)) TRY(upload(c, &c->d_doc_limit, limit, "document limits"));
     }
-    TRY(setup_implied(c, woff));
     TRY(setup_split_sweep(c, woff));
     TRY(dev_alloc(c, &c->d_alias, any_dense_alias ? VK : 1, "alias tables"));
     std::vector<RebuildTile> tiles, list_tiles;
@@ -668,23 +665,8 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
                 tiles.push_back(RebuildTile{w, p, std::min(e, p + limit), 1});
         }
     }
-    auto wide_first = [K](std::vector<RebuildTile>& v) {
-        const int32_t n = (int32_t)(std::stable_partition(v.begin(), v.end(), [K](const RebuildTile& t) {
-            return !is_wave_tile(K, t);
-        }) - v.begin());
-        // one launch where both would not fill the chip (10^5 tokens of 1000 words: 6.6 us in one, 8 in two)
-        return (int32_t)v.size() - n < kWaveTilesLeast ? (int32_t)v.size() : n;
-    };
     c->n_tiles = (int32_t)tiles.size();
-    c->n_wide_tiles = wide_first(tiles);
-    if (c->n_implied > 0) {
-        std::vector<RebuildTile> row_tiles;
-        for (const RebuildTile& t : tiles)
-            if (c->h_table_form[t.w] == 0) row_tiles.push_back(t);
-        c->n_row_tiles = (int32_t)row_tiles.size();
-        c->n_wide_row_tiles = wide_first(row_tiles);
-        TRY(upload(c, &c->d_row_tiles, row_tiles, "rebuild tiles"));
-    }
+    c->n_wide_tiles = wide_tiles_first(K, tiles);
     c->n_list_tiles = (int32_t)list_tiles.size();
     TRY(upload(c, &c->d_list_tiles, list_tiles, "rebuild tiles"));
     c->n_multi_words = (int32_t)multi.size();
@@ -695,6 +677,7 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
     if (!multi.empty())
         TRY_HIP(hipMemcpy(c->d_multi_words, multi.data(), sizeof(int32_t) * multi.size(),
                           hipMemcpyHostToDevice));
+    TRY(setup_implied(c, woff, tiles));
 
     TRY(hybrid ? launch_rebuild_hybrid(c) : launch_rebuild(c));
     TRY_HIP(hipStreamSynchronize(c->stream));
@@ -713,12 +696,19 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
     return LDA_OK;
 }
 
+// Before work is queued that a graph may replay
+static void note_capture(lda_ctx* c)
+{
+    if (c->n_implied > 0 && !c->implied_in_graph) c->implied_in_graph = stream_is_captured(c);
+}
+
 int lda_build_alias(lda_ctx* c)
 {
     if (!c) return LDA_ERR_ARG;
     if (c->state != COUNTS_VALID && c->state != ALIAS_VALID)
         return fail(c, LDA_ERR_STATE, "lda_build_alias: counts are stale (call lda_rebuild_counts)");
     int rc;
+    note_capture(c);
     c->implied_built = c->all_dense_built = false;
     c->state = COUNTS_VALID;  // a build that fails leaves no tables
     if (c->hybrid) {
@@ -740,6 +730,7 @@ int lda_sweep(lda_ctx* c, int32_t mh_steps)
         return fail(c, LDA_ERR_STATE, "lda_sweep: needs fresh alias tables (call lda_build_alias)");
     if (c->sweep_index == 0xFFFFFFFEu) return fail(c, LDA_ERR_STATE, "lda_sweep: sweep index exhausted");
     int rc;
+    note_capture(c);
     if (c->streamed) {
         rc = launch_sweep_streamed(c, mh_steps);
         c->pass_ev_recorded = false;
@@ -759,6 +750,8 @@ int lda_sweep(lda_ctx* c, int32_t mh_steps)
         const bool bins = !c->implied_built || (c->all_dense_built && c->bins_left > 0);
         if (c->n_implied > 0 && stream_is_captured(c)) (bins ? c->bins_captured : c->implied_captured) = true;
         rc = launch_sweep_split(c, mh_steps, bins);
+        if (rc == LDA_ERR_OOM && c->n_implied > 0 && give_up_implied(c) == LDA_OK)
+            rc = launch_sweep_split(c, mh_steps, true);
         if (rc == LDA_OK && c->bins_left > 0) --c->bins_left;
     } else {
         rc = c->hybrid ? LDA_OK : have_all_dense_tables(c);
@@ -792,6 +785,7 @@ int lda_sweep_pass_ms(lda_ctx* c, float* word_pass_ms, float* doc_pass_ms)
 int lda_rebuild_counts(lda_ctx* c)
 {
     if (!c) return LDA_ERR_ARG;
+    note_capture(c);
     const int rc = c->hybrid ? launch_rebuild_hybrid(c) : launch_rebuild(c);
     if (rc == LDA_OK) c->state = COUNTS_VALID;
     c->prev_valid = false;
@@ -809,6 +803,7 @@ int lda_update_counts(lda_ctx* c)
                     "rows are only made by lda_rebuild_counts)");
     if (c->state != SWEPT || !c->prev_valid)
         return fail(c, LDA_ERR_STATE, "lda_update_counts: needs the state left by lda_sweep");
+    note_capture(c);
     const int rc = launch_update_counts(c);
     c->prev_valid = false;
     if (rc == LDA_OK) c->state = COUNTS_VALID;

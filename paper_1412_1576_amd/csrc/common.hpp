@@ -168,8 +168,8 @@ struct lda_ctx {
                                          //   several lists of them (implied.hpp)
     int4* d_im_pieces = nullptr;         // pieces of the word pass, as d_gather_pieces
     int32_t n_im_pieces = 0;
-    int4* d_bins_pieces = nullptr;       // d_gather_pieces where words with implied tables are drawn from bins too
-    int32_t n_bins_pieces = 0;
+    int4* d_other_pieces = nullptr;      // d_gather_pieces without those words
+    int32_t n_other_pieces = 0;
     int4* d_short_pieces = nullptr;      // and of words of the mixture form with few tokens
     int32_t n_short_pieces = 0;
     // Which forms hold the tables of the current counts.  One-pass sweeps draw from bins, two-pass ones from
@@ -181,6 +181,7 @@ struct lda_ctx {
     // A sweep was captured into a graph that draws from these: lda_build_alias makes them from then on, as
     // the host does not see the replays.
     bool implied_captured = false, bins_captured = false;
+    bool implied_in_graph = false;  // a graph may use the arrays of the implied tables: never given back early
     // The counts of words with implied tables: in their lists alone after a recount, unless their rows
     // are wanted (by one-pass sweeps, or lda_update_counts lately).  What holds is kept on the device,
     // where captured work finds it too: *d_rows_stale = 1: the lists do, 0: the rows do.
@@ -362,7 +363,11 @@ int launch_alias_build_hybrid(lda_ctx* c);
 int launch_dense_listed(lda_ctx* c);                       // dense tables of d_fixed_words and d_misfits
 int launch_dense_table(lda_ctx* c, int32_t w);             // of one word (all-dense store)
 // implied tables (implied.hpp)
-int setup_implied(lda_ctx* c, const std::vector<int32_t>& woff);
+int setup_implied(lda_ctx* c, const std::vector<int32_t>& woff, const std::vector<RebuildTile>& tiles);
+void free_implied(lda_ctx* c);
+int give_up_implied(lda_ctx* c);                           // for their memory; the tables of the current counts are bins then
+void list_implied_pieces(const lda_ctx* c, const std::vector<int32_t>& woff, std::vector<int4>& implied,
+                         std::vector<int4>& others);       // word pass: their pieces, and those of the other words
 int launch_implied_tables(lda_ctx* c);
 int launch_implied_lists(lda_ctx* c);                      // their lists from the word-major z
 int launch_rows_from_lists(lda_ctx* c, int32_t w);         // rows of all such words (w < 0) or one, if stale
@@ -464,7 +469,7 @@ int launch_check_range(lda_ctx* c, const int32_t* d_vals, int64_t n, int32_t lo,
                        bool* ok);
 int max_alias_topics();    // largest K the dense alias kernel handles
 constexpr int32_t kWaveTilesLeast = 4096;
-bool is_wave_tile(int32_t K, const RebuildTile& t);
+int32_t wide_tiles_first(int32_t K, std::vector<RebuildTile>& tiles);  // returns how many these are
 int max_rebuild_topics();  // largest K the count-rebuild tiles handle
 // Tokens of a word whose row of several topic ranges gives its list too (nkw_list_rows_kernel)
 constexpr int32_t kListRowTokens = 8192;

@@ -372,7 +372,16 @@ __global__ __launch_bounds__(1024) void loglik_implied_kernel(const int32_t* __r
 // Classes by the tokens of a word, which bound its topics: the LDS of a wave's keys.
 static constexpr int32_t kImpliedClassCap[lda_ctx::kImpliedClasses] = {256, kImpliedTokens};
 
-int setup_implied(lda_ctx* c, const std::vector<int32_t>& woff)
+template <class T>
+static bool take(lda_ctx* c, T** p, size_t n)
+{
+    *p = static_cast<T*>(try_device_malloc(c, sizeof(T) * n));
+    return *p != nullptr;
+}
+
+// Without the memory for them (20 bytes per token of their words) every word has its bins; so the caller
+// allocates first what a sampler cannot do without.
+int setup_implied(lda_ctx* c, const std::vector<int32_t>& woff, const std::vector<RebuildTile>& tiles)
 {
     const int32_t V = c->V, K = c->K;
     const bool two_pass = c->opt.proposal_mode != 2 &&
@@ -405,35 +414,74 @@ int setup_implied(lda_ctx* c, const std::vector<int32_t>& woff)
     if (n * K < kImpliedLeastBins) return LDA_OK;
     std::vector<int32_t> all(words[0]);
     all.insert(all.end(), words[1].begin(), words[1].end());
+    c->h_table_form = std::move(form);
+    std::vector<int4> pieces, others;
+    list_implied_pieces(c, woff, pieces, others);
+    std::vector<RebuildTile> row_tiles;
+    for (const RebuildTile& t : tiles)
+        if (c->h_table_form[t.w] == 0) row_tiles.push_back(t);
+    c->n_wide_row_tiles = wide_tiles_first(K, row_tiles);
+    c->n_row_tiles = (int32_t)row_tiles.size();
     c->n_fixed_words = (int32_t)fixed.size();
-    LDA_ALLOC(c, &c->d_im_words, all.size(), "implied tables");
-    LDA_ALLOC(c, &c->d_im_n, (size_t)V, "implied tables");
-    LDA_ALLOC(c, &c->d_rows_stale, 1, "implied tables");
-    LDA_ALLOC(c, &c->d_im_off, off.size(), "implied tables");
-    LDA_ALLOC(c, &c->d_im_head, (size_t)V, "implied tables");
-    LDA_ALLOC(c, &c->d_im_key, entries, "implied tables");
-    LDA_ALLOC(c, &c->d_im_corr, entries, "implied tables");
-    LDA_ALLOC(c, &c->d_im_x, entries, "implied tables");
-    LDA_ALLOC(c, &c->d_im_qz, (size_t)K, "implied tables");
-    LDA_ALLOC(c, &c->d_im_pz, (size_t)K + 1, "implied tables");
-    LDA_ALLOC(c, &c->d_im_sum, 3, "implied tables");
-    LDA_ALLOC(c, &c->d_fixed_words, fixed.size(), "implied tables");
-    LDA_ALLOC(c, &c->d_misfits, (size_t)misfit_list_words((int32_t)n) * kMisfitLists, "implied tables");
-    LDA_ALLOC(c, &c->d_n_misfits, kMisfitLists * kMisfitStride, "implied tables");
-    LDA_HIP(c, hipMemcpy(c->d_im_words, all.data(), sizeof(int32_t) * all.size(), hipMemcpyHostToDevice));
-    LDA_HIP(c, hipMemcpy(c->d_im_off, off.data(), sizeof(uint32_t) * off.size(), hipMemcpyHostToDevice));
-    if (!fixed.empty())
-        LDA_HIP(c, hipMemcpy(c->d_fixed_words, fixed.data(), sizeof(int32_t) * fixed.size(), hipMemcpyHostToDevice));
+    c->n_im_pieces = (int32_t)pieces.size();
+    c->n_other_pieces = (int32_t)others.size();
+    for (int i = 0; i < lda_ctx::kImpliedClasses; ++i) c->n_im_class[i] = (int32_t)words[i].size();
+    const bool room =
+        take(c, &c->d_im_words, all.size()) && take(c, &c->d_im_n, (size_t)V) && take(c, &c->d_rows_stale, 1) &&
+        take(c, &c->d_im_off, off.size()) && take(c, &c->d_im_head, (size_t)V) && take(c, &c->d_im_key, entries) &&
+        take(c, &c->d_im_corr, entries) && take(c, &c->d_im_x, entries) && take(c, &c->d_im_qz, (size_t)K) &&
+        take(c, &c->d_im_pz, (size_t)K + 1) && take(c, &c->d_im_sum, 3) && take(c, &c->d_fixed_words, fixed.size()) &&
+        take(c, &c->d_misfits, (size_t)misfit_list_words((int32_t)n) * kMisfitLists) &&
+        take(c, &c->d_n_misfits, kMisfitLists * kMisfitStride) && take(c, &c->d_im_pieces, pieces.size()) &&
+        take(c, &c->d_other_pieces, others.size()) && take(c, &c->d_row_tiles, row_tiles.size());
+    if (!room) {
+        free_implied(c);
+        return LDA_OK;
+    }
+    auto upload = [](auto* to, const auto& from) {
+        return from.empty() ? hipSuccess : hipMemcpy(to, from.data(), sizeof(from[0]) * from.size(), hipMemcpyHostToDevice);
+    };
+    LDA_HIP(c, upload(c->d_im_words, all));
+    LDA_HIP(c, upload(c->d_im_off, off));
+    LDA_HIP(c, upload(c->d_fixed_words, fixed));
+    LDA_HIP(c, upload(c->d_im_pieces, pieces));
+    LDA_HIP(c, upload(c->d_other_pieces, others));
+    LDA_HIP(c, upload(c->d_row_tiles, row_tiles));
     // words without tokens
-    LDA_HIP(c, hipMemset(c->d_im_head, 0, sizeof(uint4) * (size_t)V));
-    LDA_HIP(c, hipMemset(c->d_im_n, 0, sizeof(int32_t) * (size_t)V));
-    LDA_HIP(c, hipMemset(c->d_rows_stale, 0, sizeof(int32_t)));
+    LDA_HIP(c, hipMemsetAsync(c->d_im_head, 0, sizeof(uint4) * (size_t)V, c->stream));
+    LDA_HIP(c, hipMemsetAsync(c->d_im_n, 0, sizeof(int32_t) * (size_t)V, c->stream));
+    LDA_HIP(c, hipMemsetAsync(c->d_rows_stale, 0, sizeof(int32_t), c->stream));
     // The recounts that make lists write no rows of words without tokens; the tables over all K bins are
     // built from those rows too.
     LDA_HIP(c, hipMemsetAsync(c->d_nkw, 0, sizeof(int32_t) * (size_t)V * (size_t)K, c->stream));
-    for (int i = 0; i < lda_ctx::kImpliedClasses; ++i) c->n_im_class[i] = (int32_t)words[i].size();
     c->n_implied = (int32_t)n;
-    c->h_table_form = std::move(form);
+    return LDA_OK;
+}
+
+void free_implied(lda_ctx* c)
+{
+    auto give = [c](auto*& p) {
+        device_free(c, p);
+        p = nullptr;
+    };
+    give(c->d_im_words); give(c->d_im_n); give(c->d_rows_stale); give(c->d_im_off); give(c->d_im_head);
+    give(c->d_im_key); give(c->d_im_corr); give(c->d_im_x); give(c->d_im_qz); give(c->d_im_pz); give(c->d_im_sum);
+    give(c->d_fixed_words); give(c->d_misfits); give(c->d_n_misfits); give(c->d_im_pieces); give(c->d_other_pieces);
+    give(c->d_row_tiles);
+    c->n_implied = 0;
+    c->h_table_form.clear();
+    c->implied_built = false;
+}
+
+// Where a sweep finds no room for its records: every word has its bins from now on, as in a sampler that
+// never had room for the lists.  Refused while a graph may use them.
+int give_up_implied(lda_ctx* c)
+{
+    if (c->implied_in_graph) return LDA_ERR_OOM;
+    const int rc = have_all_dense_tables(c);  // and the rows
+    if (rc != LDA_OK) return rc;
+    LDA_HIP(c, hipStreamSynchronize(c->stream));
+    free_implied(c);
     return LDA_OK;
 }
 

@@ -468,9 +468,18 @@ int max_rebuild_topics() { return 36 * 1024; }
 
 // Tiles that a wave counts by itself: a single tile of its word with at most kWaveTileTokens
 // tokens, in a row that 64 lanes clear and write in few steps.
-bool is_wave_tile(int32_t K, const RebuildTile& t)
+static bool is_wave_tile(int32_t K, const RebuildTile& t)
 {
     return t.multi != 1 && K <= kWaveTileTopics && t.p1 - t.p0 <= kWaveTileTokens;
+}
+
+int32_t wide_tiles_first(int32_t K, std::vector<RebuildTile>& tiles)
+{
+    const int32_t n = (int32_t)(std::stable_partition(tiles.begin(), tiles.end(), [K](const RebuildTile& t) {
+        return !is_wave_tile(K, t);
+    }) - tiles.begin());
+    // one launch where both would not fill the chip (10^5 tokens of 1000 words: 6.6 us in one, 8 in two)
+    return (int32_t)tiles.size() - n < kWaveTilesLeast ? (int32_t)tiles.size() : n;
 }
 
 namespace {

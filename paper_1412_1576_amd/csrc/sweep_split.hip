@@ -1825,13 +1825,20 @@ static int setup_long_docs(lda_ctx* c)
     return LDA_OK;
 }
 
-// Work lists of the word pass from the word segment offsets.
-int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
+// Work lists of the word pass from the word segment offsets: with `implied`, words with implied tables
+// (h_table_form) have pieces of their own.
+namespace {
+
+struct WordLists {
+    std::vector<int4> items, mix_items, pieces;
+    std::vector<int4> few_pieces;  // of words with few tokens: of implied tables, or (hybrid) of the mixture form
+};
+
+WordLists list_words(const lda_ctx* c, const std::vector<int32_t>& woff, bool implied)
 {
-    std::vector<int4> items, mix_items, pieces, im_pieces, short_pieces;
+    WordLists lists;
+    auto& [items, mix_items, pieces, few_pieces] = lists;
     const int32_t V = c->V;
-    // pieces of words with few tokens: of implied tables, or (hybrid) of the mixture form
-    std::vector<int4>& few_pieces = c->hybrid ? short_pieces : im_pieces;
     static_assert(kShortTokens == kImpliedTokens && kShortWords == kImpliedWords, "pieces of one size");
     int32_t im0 = -1;  // first word of the open piece
     auto close_implied = [&](int32_t w_end) {
@@ -1839,9 +1846,9 @@ int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
             few_pieces.push_back(make_int4(im0, w_end, woff[im0], woff[w_end] - woff[im0]));
         im0 = -1;
     };
-    bool use_short = true, use_implied = c->n_implied > 0;
+    bool use_short = true;
     auto few_tokens = [&](int32_t w, int32_t n) {
-        if (!c->hybrid) return use_implied && c->h_table_form[w] == 1;
+        if (!c->hybrid) return implied && c->h_table_form[w] == 1;
         return use_short && n > 0 && n <= kShortTokens && (c->h_wkind[w] & 2) == 0 &&
                !((c->h_wkind[w] & 1) && c->K <= kMixRowTopics && n >= kMixRowMinTokens && n > c->K / kShortShare);
     };
@@ -1869,67 +1876,65 @@ int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
     }
     const int32_t row_item = (int32_t)std::min<int64_t>(
         kRowItemTokens, std::max<int64_t>(std::max(kRowItemLeast, c->K), row_tokens / kRowItemsWanted));
-    auto list_words = [&]() {
-        for (int32_t w = 0; w < V; ++w) {
-            const int32_t b = woff[w], n = woff[w + 1] - b;
-            const bool dense_dense = dense_form(w);
-            if (few_tokens(w, n) || (n == 0 && im0 >= 0)) {
-                if (im0 >= 0 && (woff[w + 1] - woff[im0] > few_piece || w + 1 - im0 > kImpliedWords)) close_implied(w);
-                if (im0 < 0) {
-                    close_piece(w);
-                    im0 = w;
-                }
-                continue;
-            }
-            close_implied(w);
-            if (n >= kRowMinTokens && rows_fit && dense_dense) {
+    for (int32_t w = 0; w < V; ++w) {
+        const int32_t b = woff[w], n = woff[w + 1] - b;
+        const bool dense_dense = dense_form(w);
+        if (few_tokens(w, n) || (n == 0 && im0 >= 0)) {
+            if (im0 >= 0 && (woff[w + 1] - woff[im0] > few_piece || w + 1 - im0 > kImpliedWords)) close_implied(w);
+            if (im0 < 0) {
                 close_piece(w);
-                for (int32_t p = b; p < b + n; p += row_item)
-                    items.push_back(make_int4(w, p, std::min(row_item, b + n - p), 0));
-                continue;
+                im0 = w;
             }
-            // a mixture word with a dense row of at most kMixRowTopics topics and enough
-            // tokens to pay for clearing an LDS row
-            if (c->hybrid && (c->h_wkind[w] & 3) == 1 && c->K <= kMixRowTopics && n >= kMixRowMinTokens) {
-                close_piece(w);
-                for (int32_t p = b; p < b + n; p += kRowItemTokens)
-                    mix_items.push_back(make_int4(w, p, std::min(kRowItemTokens, b + n - p), 0));
-                continue;
-            }
-            if (n > kPieceTokens) {  // a long word that cannot be staged: pieces of its own
-                close_piece(w);
-                for (int32_t p = b; p < b + n; p += kPieceTokens)
-                    pieces.push_back(make_int4(w, w + 1, p, std::min(kPieceTokens, b + n - p)));
-                continue;
-            }
-            if (w0 >= 0 && (woff[w + 1] - woff[w0] > kPieceTokens || w + 1 - w0 > kPieceWords))
-                close_piece(w);
-            if (w0 < 0) w0 = w;
+            continue;
         }
-        close_piece(V);
-        close_implied(V);
-    };
-    if (use_implied) {  // first the pieces of all words without implied tables
-        use_implied = false;
-        list_words();
-        c->n_bins_pieces = (int32_t)pieces.size();
-        LDA_ALLOC(c, &c->d_bins_pieces, pieces.size(), "word-pass work list");
-        LDA_HIP(c, hipMemcpy(c->d_bins_pieces, pieces.data(), sizeof(int4) * pieces.size(), hipMemcpyHostToDevice));
-        items.clear();
-        pieces.clear();
-        use_implied = true;
+        close_implied(w);
+        if (n >= kRowMinTokens && rows_fit && dense_dense) {
+            close_piece(w);
+            for (int32_t p = b; p < b + n; p += row_item)
+                items.push_back(make_int4(w, p, std::min(row_item, b + n - p), 0));
+            continue;
+        }
+        // a mixture word with a dense row of at most kMixRowTopics topics and enough
+        // tokens to pay for clearing an LDS row
+        if (c->hybrid && (c->h_wkind[w] & 3) == 1 && c->K <= kMixRowTopics && n >= kMixRowMinTokens) {
+            close_piece(w);
+            for (int32_t p = b; p < b + n; p += kRowItemTokens)
+                mix_items.push_back(make_int4(w, p, std::min(kRowItemTokens, b + n - p), 0));
+            continue;
+        }
+        if (n > kPieceTokens) {  // a long word that cannot be staged: pieces of its own
+            close_piece(w);
+            for (int32_t p = b; p < b + n; p += kPieceTokens)
+                pieces.push_back(make_int4(w, w + 1, p, std::min(kPieceTokens, b + n - p)));
+            continue;
+        }
+        if (w0 >= 0 && (woff[w + 1] - woff[w0] > kPieceTokens || w + 1 - w0 > kPieceWords))
+            close_piece(w);
+        if (w0 < 0) w0 = w;
     }
-    list_words();
+    close_piece(V);
+    close_implied(V);
+    return lists;
+}
+
+}  // namespace
+
+void list_implied_pieces(const lda_ctx* c, const std::vector<int32_t>& woff, std::vector<int4>& implied,
+                         std::vector<int4>& others)
+{
+    WordLists lists = list_words(c, woff, true);
+    implied.swap(lists.few_pieces);
+    others.swap(lists.pieces);
+}
+
+int setup_split_sweep(lda_ctx* c, const std::vector<int32_t>& woff)
+{
+    const WordLists lists = list_words(c, woff, false);
+    const auto& [items, mix_items, pieces, short_pieces] = lists;
     c->n_short_pieces = (int32_t)short_pieces.size();
     if (!short_pieces.empty()) {
         LDA_ALLOC(c, &c->d_short_pieces, short_pieces.size(), "word-pass work list");
         LDA_HIP(c, hipMemcpy(c->d_short_pieces, short_pieces.data(), sizeof(int4) * short_pieces.size(),
-                             hipMemcpyHostToDevice));
-    }
-    c->n_im_pieces = (int32_t)im_pieces.size();
-    if (!im_pieces.empty()) {
-        LDA_ALLOC(c, &c->d_im_pieces, im_pieces.size(), "word-pass work list");
-        LDA_HIP(c, hipMemcpy(c->d_im_pieces, im_pieces.data(), sizeof(int4) * im_pieces.size(),
                              hipMemcpyHostToDevice));
     }
     c->n_row_items = (int32_t)items.size();
@@ -1977,10 +1982,9 @@ int launch_sweep_split(lda_ctx* c, int32_t mh_steps, bool bins)
     A.nkw = c->d_nkw; A.nk = c->d_nk; A.alias = c->d_alias; A.cap = c->d_cap;
     A.zt = c->d_zt; A.zt_pack16 = c->zt_pack16 ? 1 : 0; A.rec = c->d_rec; A.row_items = c->d_row_items; A.pieces = c->d_gather_pieces;
     A.n_chunks = c->n_chunks; A.n_row_items = c->n_row_items; A.n_pieces = c->n_gather_pieces;
-    A.im_pieces = c->d_im_pieces; A.n_im_pieces = c->n_im_pieces;
-    if (bins && c->n_implied > 0) {  // for every word
-        A.pieces = c->d_bins_pieces; A.n_pieces = c->n_bins_pieces;
-        A.n_im_pieces = 0;
+    if (!bins && c->n_implied > 0) {
+        A.pieces = c->d_other_pieces; A.n_pieces = c->n_other_pieces;
+        A.im_pieces = c->d_im_pieces; A.n_im_pieces = c->n_im_pieces;
     }
     A.row_run = xcd_run_length(c->n_row_items, kRowItemRun);
     A.mix_run = xcd_run_length(c->n_mix_items, kMixItemRun);

@@ -281,3 +281,91 @@ def test_a_failed_build_leaves_no_tables(lda_mod, oracle_mod, V):
         assert e.value.code == lda_mod.LDA_ERR_STATE
     step(g, o, 2, tables=(0, 3))
     g.close(); o.close()
+
+
+class Pool:
+    """A caller's allocator that refuses requests beyond a number of them, or of bytes held."""
+    def __init__(self, requests=1 << 60, most=1 << 60):
+        self.live, self.requests, self.left, self.most = {}, 0, requests, most
+
+    def held(self):
+        return sum(t.numel() for t in self.live.values())
+
+    def alloc(self, nbytes):
+        import torch
+        self.requests += 1
+        if self.requests > self.left or self.held() + nbytes > self.most:
+            return 0
+        t = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        self.live[t.data_ptr()] = t
+        return t.data_ptr()
+
+    def options(self):
+        return {"dev_alloc": self.alloc, "dev_free": lambda p: self.live.pop(p)}
+
+
+def test_without_room_for_the_lists(lda_mod, oracle_mod):
+    """An allocator that fails at the last, the last but one, ... request of lda_init: as long as what a
+    sampler cannot do without is there, every word has its bins."""
+    V, K = 12000, 1024
+    doff, words = corpus_of(frequencies(V, K, 5), 5)
+    all_of_it = Pool()
+    pair(lda_mod, oracle_mod, doff, words, V, K, beta=1e-4, **all_of_it.options())[0].close()
+    without = []
+    for left in range(all_of_it.requests - 1, 0, -1):
+        pool = Pool(requests=left)
+        try:
+            g, o = pair(lda_mod, oracle_mod, doff, words, V, K, beta=1e-4, **pool.options())
+        except lda_mod.LdaError as e:
+            assert e.code == lda_mod.LDA_ERR_OOM and not pool.live
+            break
+        without.append(pool.held())
+        pool.left = 1 << 60
+        if len(without) in (1, 9):
+            for i, m in enumerate((2, 9, 2, 4)):
+                step(g, o, m, update=i == 2, tables=(0, 5, 13, 1000))
+        g.close(); o.close()
+        assert not pool.live
+    assert len(without) > 9 and len(set(without)) == 1
+
+
+@pytest.mark.parametrize("captured", [False, True])
+def test_records_take_the_room_of_the_lists(lda_mod, oracle_mod, captured):
+    """A sweep that finds no room for its records beside the lists, and does without them; not where
+    a graph may replay work that uses the lists."""
+    import torch
+    V, K = 12000, 1024
+    doff, words = corpus_of(frequencies(V, K, 5), 5)
+    stream = torch.cuda.Stream()
+    pool = Pool()
+    g, o = pair(lda_mod, oracle_mod, doff, words, V, K, beta=1e-4, stream=stream.cuda_stream, **pool.options())
+    pool.left = pool.requests
+    lists, n = pool.held(), pool.requests
+    g.close()
+    pool = Pool(requests=n - 1)
+    g = lda_mod.Lda(doff, words, V, K, 0.1, 1e-4, seed=3, stream=stream.cuda_stream, **pool.options())
+    bins = pool.held()
+    g.close()
+    records = 16 * len(words)
+    assert lists - bins > 1 << 18
+    pool = Pool(most=bins + records + (1 << 16))
+    g = lda_mod.Lda(doff, words, V, K, 0.1, 1e-4, seed=3, stream=stream.cuda_stream, **pool.options())
+    assert pool.held() == lists
+    if captured:
+        g.sync()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            g.rebuild_counts()
+        g.build_alias()
+        with pytest.raises(lda_mod.LdaError) as e:
+            g.sweep(2)
+        assert e.value.code == lda_mod.LDA_ERR_OOM and pool.held() == lists
+        g.rebuild_counts()
+        pool.most = 1 << 60
+    for i, m in enumerate((2, 2, 9, 2)):
+        step(g, o, m, update=i == 1, tables=(0, 5, 13, 1000))
+    assert captured or pool.held() <= pool.most
+    pool.most = 1 << 60
+    step(g, o, 4, tables=(0, 5, 13, 1000))
+    g.close(); o.close()
+    assert not pool.live
