@@ -68,11 +68,7 @@ struct DenseListIo {
 #pragma clang fp contract(off)
         return quantise40(((double)count + beta) / ((double)nk[k] + betabar));
     }
-    __device__ __forceinline__ uint64_t mass(int32_t k) const
-    {
-        const uint32_t q = qz[k];
-        return q == 0xFFFFFFFFu ? weight(0, k) : q;  // (saturated)
-    }
+    __device__ __forceinline__ uint64_t mass(int32_t k) const { return qz[k]; }
     __device__ __forceinline__ void patch(uint64_t* m, int32_t t, int32_t threads) const
     {
         for (int32_t i = t; i < n_key; i += threads) {

@@ -17,6 +17,7 @@ namespace {
 // (Six iterations of 3.1 * 10^5 tokens, 7600 words, K = 544, 4 * 10^6 bins: 0.62 ms with bins, 0.75 implied;
 // of 1.8 * 10^6, 30 011 words, K = 333, 10^7 bins, five iterations: 1.12 and 0.94.)
 constexpr int64_t kImpliedLeastBins = (int64_t)1 << 23;
+static_assert(kImpliedLeastBins / kRegsMaxEntries >= 512, "beta / (V beta) * 2^40 is below 2^31");
 // A word's table is implied if it has at most K / kImpliedShare tokens (and kImpliedTokens).
 constexpr int32_t kImpliedShare = 2;
 
@@ -25,8 +26,8 @@ __device__ __forceinline__ uint64_t quantise40(double a)
     return (uint64_t)floor(a * 1099511627776.0);
 }
 
-// Shared by all words: q[k] = floor(beta / (n_k + betabar) * 2^40), saturated at 32 bits; pz[k] = sum of
-// max(1, q) below k; sum = (sum of the q, sum of max(1, q), largest max(1, q)).  One workgroup, a
+// Shared by all words: q[k] = floor(beta / (n_k + betabar) * 2^40), below 2^31 as betabar is beta times more than
+// 512 words; pz[k] = sum of max(1, q) below k; sum = (sum of the q, sum of max(1, q), largest max(1, q)).  One workgroup, a
 // run of consecutive topics per thread.  The lists of misfits start empty.
 constexpr int kSumThreads = 1024;
 
@@ -56,7 +57,7 @@ __global__ __launch_bounds__(kSumThreads) void implied_sums_kernel(const int32_t
             q[e] = v < 1 ? 1 : v;
             qs += q[e];
             most = q[e] > most ? q[e] : most;
-            qz[r0 + e] = v > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)v;
+            qz[r0 + e] = (uint32_t)v;
         }
     }
     const uint64_t inc = wave_inclusive_scan_u64(qs);
@@ -268,8 +269,7 @@ __global__ __launch_bounds__(256) void implied_tables_kernel(ImpliedArgs a)
     const uint64_t Q0 = a.sum[0] + wave_total_u64(dq0), Q = a.sum[1] + wave_total_u64(dq);
     const uint64_t C = (uint64_t)((double)(Q + (uint64_t)K - 1) / (double)K);  // as in alias_regs.hpp
     const uint64_t pad = (uint64_t)K * C - Q;
-    // (q saturates beyond 2^32, but then `most` does not pass)
-    const bool fits = most < (1ull << 31) && Q0 < ((uint64_t)K << 31) && most + 1 < C;
+    const bool fits = Q0 < ((uint64_t)K << 31) && most + 1 < C;
     if (!fits) {  // its bins are built, and until then drawn from; counts are looked up in the list
         for (uint32_t e = lane; e < n; e += kWave) a.key[off + e] = keys[e];
         if (lane == 0) {
