@@ -310,6 +310,8 @@ __global__ __launch_bounds__(256) void implied_tables_kernel(ImpliedArgs a)
 
 // Log-likelihood, word part, of all words of an all-dense store with implied tables: a wave per word,
 // over its list, or its row where that is kept (fixed: the words whose row always is).
+constexpr int32_t kRowPiece = 2048;
+
 __global__ __launch_bounds__(1024) void loglik_implied_kernel(const int32_t* __restrict__ fixed, int32_t n_fixed,
                                                              const int32_t* __restrict__ words, int32_t n_words,
                                                              int32_t K, const uint32_t* __restrict__ off,
@@ -331,7 +333,7 @@ __global__ __launch_bounds__(1024) void loglik_implied_kernel(const int32_t* __r
     for (int64_t i = (int64_t)blockIdx.x * 16 + wv; i < total; i += (int64_t)gridDim.x * 16) {
         if (i < row_pieces) {
             const int32_t r = (int32_t)(i / pieces), p = (int32_t)(i - (int64_t)r * pieces);
-            acc += row_terms(nkw + (size_t)fixed[r] * (size_t)K, p * kRowPiece,
+            acc += row_terms<false>(nkw + (size_t)fixed[r] * (size_t)K, p * kRowPiece,
                              K - p * kRowPiece < kRowPiece ? K : (p + 1) * kRowPiece, beta, lg_beta, terms);
             continue;
         }

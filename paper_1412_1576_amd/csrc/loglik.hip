@@ -176,6 +176,7 @@ __global__ __launch_bounds__(256) void loglik_nk_kernel(const int32_t* __restric
 // tokens even where there is a row too.  A group's list bounds are read together, and four lists at a time:
 // a wave per word waited for three loads in a row for each of its words, 39 us in all.  (54 000 words of 35 tokens, K = 500: 66 us over all rows, 9 more over the lists without a
 // row; so 19.)
+constexpr int32_t kRowPiece = 4096;
 constexpr int32_t kListGroup = 16;
 
 __global__ __launch_bounds__(256) void loglik_lists_kernel(const int32_t* __restrict__ rows, int32_t n_rows,
@@ -197,7 +198,7 @@ __global__ __launch_bounds__(256) void loglik_lists_kernel(const int32_t* __rest
     for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < total; i += (int64_t)gridDim.x * 4) {
         if (i < (int64_t)n_rows * pieces) {
             const int32_t r = (int32_t)(i / pieces), p = (int32_t)(i - (int64_t)r * pieces);
-            acc += row_terms(nkw + (size_t)rows[r] * (size_t)K, p * kRowPiece,
+            acc += row_terms<true>(nkw + (size_t)rows[r] * (size_t)K, p * kRowPiece,
                              K - p * kRowPiece < kRowPiece ? K : (p + 1) * kRowPiece, beta, lg_beta, terms);
         } else {
             const int32_t j0 = (int32_t)(i - (int64_t)n_rows * pieces) * kListGroup;
@@ -320,7 +321,14 @@ private:
 constexpr int kWordBlocks = 4096, kNkBlocks = 64;
 
 // Workgroups of the word part, whose sums the host adds: at most kWordBlocks, one for every 8192 tokens
-int word_blocks(const lda_ctx* c) { return (int)std::min<int64_t>(kWordBlocks, 256 + c->N / 8192); }
+// (lists) or counts of rows.  By tokens alone, a corpus of few tokens and many rows has too few in flight:
+// 10^6 tokens, 10^5 rows of 10 000 counts 1600 us, so 1270; 30 000 rows of 16 000 beside lists 1045, so 730.
+int word_blocks(const lda_ctx* c)
+{
+    const int64_t rows = c->n_implied > 0 ? c->n_fixed_words : (c->hybrid ? c->n_row_words : c->V);
+    const int64_t counts = rows * c->K / (c->n_implied > 0 ? 4 : 1);  // (that kernel's have four times the threads)
+    return (int)std::min<int64_t>(kWordBlocks, 256 + std::max(c->N, counts) / 8192);
+}
 
 // The log-likelihood with the partial sums in d_partial (device memory of cap doubles, at least
 // max(n_chunks, n_long, kWordBlocks)) and host staging in `h` (h_cap doubles).
