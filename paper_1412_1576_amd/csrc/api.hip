@@ -581,7 +581,7 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
     TRY(dev_alloc(c, &c->d_long_slot, (size_t)c->n_long + 1, "long document slots"));
     TRY(dev_alloc(c, &c->d_long_keys, (size_t)c->long_slots, "long document tables"));
     TRY(dev_alloc(c, &c->d_long_cnts, (size_t)c->long_slots, "long document tables"));
-    TRY(dev_alloc(c, &c->d_long_first, (size_t)c->long_slots, "long document tables"));
+    TRY(dev_alloc(c, &c->d_long_first, K > kLongDocTopics ? (size_t)c->long_slots : 0, "long document tables"));
     c->n_partial = (int32_t)loglik_partials(c);
     TRY(dev_alloc(c, &c->d_partial, (size_t)c->n_partial, "partial sums"));
     TRY(setup_loglik(c));

@@ -210,7 +210,7 @@ struct lda_ctx {
     int64_t* d_long_slot = nullptr;    // [n_long+1] first hash slot of each long document
     int32_t* d_long_keys = nullptr;    // [total slots]
     int32_t* d_long_cnts = nullptr;
-    int32_t* d_long_first = nullptr;   // [total slots] log-likelihood: first token of every topic
+    int32_t* d_long_first = nullptr;   // [total slots] log-likelihood beyond kLongDocTopics: first token of every topic
     int4* d_long_slices = nullptr;     // (first token, tokens, begin of the slice, its tokens): doc pass
     int4* d_long_parts = nullptr;      // the same for the doc proposals of the next sweep
     int32_t n_long_slices = 0, n_long_parts = 0;
