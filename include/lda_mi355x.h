@@ -17,8 +17,9 @@
  *     word-proposal for even j and a doc-proposal for odd j (Eq. 13).
  *   - Randomness is Philox4x32-10 with key = seed and counter
  *     (token id low, token id high, sweep index, step index), so results do not
- *     depend on launch geometry.  Acceptance ratios are evaluated in fp64 with
- *     separately rounded operations.
+ *     depend on launch geometry.  Every accept test has the outcome that its
+ *     products have in fp64, separately rounded (most are decided in fp32 with a
+ *     margin that no rounding crosses).
  *
  * Conventions
  *   - All pointers in the signatures are HOST pointers unless stated otherwise.
@@ -142,7 +143,9 @@ int lda_init(lda_ctx** out, int64_t D, int32_t V, int32_t K, const int64_t* doc_
  * over their non-zero topics, and all of them share one table over
  * beta/(n_k + V beta).  In the all-dense store the table of a word with few tokens may be held as
  * its topics with running sums, from which a draw computes the bin it hits; sweeps that run as one
- * kernel and lda_get_alias_row make such words' bins when they need them.
+ * kernel and lda_get_alias_row make such words' bins when they need them.  This takes 20 bytes per token
+ * of these words from lda_init on; where that finds no room, or a sweep later finds none for its
+ * records beside it, every word has its bins.
  * COUNTS_VALID -> ALIAS_VALID.
  */
 int lda_build_alias(lda_ctx* ctx);

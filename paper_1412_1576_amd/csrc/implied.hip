@@ -1,5 +1,6 @@
-// Implied tables (implied.hpp): which words get one, the sums they share, and their build from the
-// dense n_kw rows.  All-dense store.
+// Implied tables (implied.hpp): which words get one, the sums they share, the words' lists out of the
+// word-major assignment, and the tables out of the lists or, where those are kept, the n_kw rows.
+// All-dense store.
 #include <algorithm>
 #include <cmath>
 
@@ -393,8 +394,9 @@ int setup_implied(lda_ctx* c, const std::vector<int32_t>& woff, const std::vecto
     // A word fits the form if its capacity, some (tokens + K beta) / K of a bin's share, exceeds every
     // mass of a topic without tokens.  With topics as even as a random assignment leaves them, four
     // standard deviations, words with fewer tokens than this do not, and get their bins from the rows as
-    // other words do; sizes that drift apart are allowed for with a factor of 2.5.  (4.3 * 10^5 tokens, 22 500 words, K = 1734, half of the words of up to four tokens:
-    // five iterations 1.75 ms with bins, 2.14 with all words tried.)
+    // other words do; sizes that drift apart are allowed for with a factor of 2.5.  (4.3 * 10^5 tokens, 22 500
+    // words, K = 1734, half of the words of up to four tokens: five iterations 1.75 ms with bins, 2.14 with all
+    // words tried.)
     const double topic = (double)c->N / (double)K, spread = 4.0 * std::sqrt(topic);
     const double least = 2.5 * (double)K * c->beta * spread / std::max(topic - spread + c->betabar, 1e-300);
     std::vector<int32_t> words[lda_ctx::kImpliedClasses], fixed;
