@@ -54,9 +54,9 @@ def doc_pass_bytes_per_token(mh_steps: int) -> float:
 # dense_alias_min_count as passed to the library).  None where not measured.
 MEASURED_TRAFFIC_BYTES = {
     ("c3", 2, 10000): {"doc_pass_tiles_kernel": 48.70e9},
-    ("c2", 2, 1000): {"doc_pass_tiles_kernel": 6.59e9},
-    ("c4", 2, None): {"doc_pass_tiles_kernel": 75.05e9, "word_pass_gather_kernel": 50.33e9},
-    ("c5", 2, None): {"doc_pass_tiles_kernel": 92.44e9, "word_pass_gather_kernel": 147.41e9},
+    ("c2", 2, 1000): {"doc_pass_tiles_kernel": 6.64e9},
+    ("c4", 2, None): {"doc_pass_tiles_kernel": 74.64e9, "word_pass_gather_kernel": 42.71e9},
+    ("c5", 2, None): {"doc_pass_tiles_kernel": 89.73e9, "word_pass_gather_kernel": 144.75e9},
 }
 
 
