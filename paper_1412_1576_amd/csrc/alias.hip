@@ -25,7 +25,7 @@ __device__ __forceinline__ uint64_t quantise40(double a)
 // dense form: entry k is topic k.  A bin also carries the word-topic counts of its two outcomes,
 // so the sweep's accept test needs no second gather.
 struct DenseIo {
-    static constexpr bool kListed = false;
+    static constexpr bool kListed = false, kMassesFirst = true;
     const int32_t* __restrict__ row;
     const int32_t* __restrict__ nk;
     double beta, betabar;
@@ -50,7 +50,7 @@ struct DenseIo {
 // The same table from the word's list (implied.hpp) and the masses of topics without tokens; the row
 // only exists in LDS.
 struct DenseListIo {
-    static constexpr bool kListed = true;
+    static constexpr bool kListed = true, kMassesFirst = false;
     const uint32_t* __restrict__ key;
     int32_t n_key;
     const uint64_t *__restrict__ sum0, *__restrict__ sum;
@@ -101,7 +101,7 @@ struct DenseListIo {
 // sparse term of the mixture: entry i is the word's i-th non-zero topic (ascending); its bin
 // carries the topics and counts of both outcomes
 struct MixIo {
-    static constexpr bool kListed = false;
+    static constexpr bool kListed = false, kMassesFirst = false;
     const int32_t* __restrict__ topic;
     const int32_t* __restrict__ count;
     const int32_t* __restrict__ nk;
@@ -129,7 +129,7 @@ struct MixIo {
 
 // shared beta term of the mixture: entry k is topic k
 struct BetaIo {
-    static constexpr bool kListed = false;
+    static constexpr bool kListed = false, kMassesFirst = false;
     const int32_t* __restrict__ nk;
     double beta, betabar;
     uint2* __restrict__ out;

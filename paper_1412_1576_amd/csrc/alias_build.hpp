@@ -22,6 +22,7 @@
 // entry k's weight if it is not in the list, patch(weights, thread, threads) writes those in it, Q0()
 // and Q() are the sums known beforehand; load() reads an array of n ints in LDS, made by
 // clear(array, n, thread, threads) and fill(array, thread, threads), and is called late.
+// kMassesFirst: see alias_regs.hpp, build_table_workgroup.
 #pragma once
 
 #include "common.hpp"
